@@ -207,6 +207,120 @@ def run(s):
     return dict(pair=s["pair"], delta=s["delta"])
 
 
+# ---- the same pass in 64 bits ---------------------------------------------------------------------------------
+
+
+def _matmul(x, w):
+    """x w^T in 64 bits, a slice of the weight's rows at a time."""
+    return torch.cat([x @ r.double().t() for r in w.split(32768)], dim=1)
+
+
+def _norm64(u):
+    return u * torch.rsqrt(u.pow(2).mean(1, keepdim=True) + 1e-6)
+
+
+def _layer64(c, u, layer, plen):
+    """One decoder layer of the transformer body on u [M][d]."""
+    (wqkv, wo, wgu, wdown, kc, vc), B, L, P, nh, nkv = layer, c["B"], c["L"], c["P"], c["nh"], c["nkv"]
+    qkv = _matmul(_norm64(u), wqkv).view(B, L, nh + 2 * nkv, 128)
+    pos = plen.double().view(B, 1) + torch.arange(L, device="cuda", dtype=torch.float64)
+    ang = (pos.unsqueeze(2) * 1.0e6 ** (-torch.arange(64, device="cuda", dtype=torch.float64) / 64)).unsqueeze(2)
+    x0, x1 = qkv[..., :64], qkv[..., 64:]
+    rot = torch.cat([x0 * ang.cos() - x1 * ang.sin(), x1 * ang.cos() + x0 * ang.sin()], dim=3)
+    q, k, v = rot[:, :, :nh], rot[:, :, nh:nh + nkv], qkv[:, :, nh + nkv:]
+    seen = torch.cat([torch.arange(P, device="cuda") < plen.view(B, 1), torch.ones(B, L, dtype=torch.bool, device="cuda")], 1)
+    keys = torch.cat([kc.double(), k], 1).permute(0, 2, 1, 3).contiguous()
+    vals = torch.cat([vc.double(), v], 1).permute(0, 2, 1, 3).contiguous()
+    q = q.reshape(B, L, nkv, nh // nkv, 128).permute(0, 2, 3, 1, 4).reshape(B, nkv, -1, 128)
+    w = (q @ keys.transpose(2, 3).contiguous()) / math.sqrt(128.0)
+    w = torch.softmax(w.masked_fill(~seen.view(B, 1, 1, -1), -math.inf), -1)
+    o = (w @ vals).view(B, nkv, nh // nkv, L, 128).permute(0, 3, 1, 2, 4).reshape(B * L, nh * 128)
+    a = u + _matmul(o, wo)
+    gate, up = _matmul(_norm64(a), wgu).chunk(2, dim=1)
+    return a + _matmul(gate * torch.sigmoid(gate) * up, wdown)
+
+
+def _chain64(c, g):
+    d, V, B, L, K = c["d"], c["V"], c["B"], c["L"], c["K"]
+    M, tau, tau_r = B * L, c["tau"], c.get("tau_remask", -1.0)
+    E, W = _normal(g, V, d, std=0.02), _normal(g, V, d, std=0.02)
+    h, z = _normal(g, M, d).double(), _logits(g, M, V)
+    if c["kind"] == "chain":
+        heads = [(_normal(g, d, 2 * d, std=0.02), _normal(g, d, d, std=0.02)) for _ in range(K)]
+    else:
+        w1 = _normal(g, d, 2 * d, std=0.02)
+        o = c["nh"] * 128
+        layers = [tuple(_normal(g, r, k, std=0.02) for r, k in (((c["nh"] + 2 * c["nkv"]) * 128, d), (d, o), (2 * c["ff"], d), (d, c["ff"])))
+                  + (_normal(g, B, c["P"], c["nkv"], 128), _normal(g, B, c["P"], c["nkv"], 128)) for _ in range(c["D"])]
+        plen = torch.randint(c["P"] + 1, (B,), device="cuda", generator=g, dtype=torch.int32)
+        plen[0], plen[-1] = 0, c["P"]
+    z = z.double()
+    rows = torch.arange(B, device="cuda")
+    masked = torch.ones(B, L, dtype=torch.bool, device="cuda")
+    at = torch.full((B, L), -1, device="cuda")
+    cond, prot, confs, lses = None, None, [], []
+    for k in range(K + 1):
+        if k:
+            x = torch.cat([h, E[cond].double().repeat_interleave(L, 0)], 1)
+            if c["kind"] == "chain":
+                a = _matmul(x, heads[k - 1][0])
+                u = _matmul(a * torch.sigmoid(a), heads[k - 1][1])
+            else:
+                u = _matmul(x, w1)
+                for layer in layers:
+                    u = _layer64(c, u, layer, plen)
+            h = h + u
+            z += _matmul(_norm64(u).bfloat16().double(), W)      # the LM head takes its operand in bf16
+        lse = torch.logsumexp(z, 1)
+        top, tok = z.max(1)
+        conf, tok = torch.exp(top - lse).view(B, L), tok.view(B, L)
+        confs.append(conf.reshape(M))
+        lses.append(lse)
+        left, best = masked.any(1), torch.where(masked, conf, -1.0).argmax(1)
+        new = masked & (conf > tau)
+        new[rows, best] |= left                    # at least one reveal for each sequence with a masked row
+        cond = tok[rows, best] if k == 0 else torch.where(left, tok[rows, best], cond)
+        prot = best if k == 0 else prot
+        masked, at = masked & ~new, torch.where(new, k, at)
+        if k and tau_r >= 0:
+            again = (at >= 0) & (at < k) & (torch.arange(L, device="cuda") != prot.unsqueeze(1)) & (conf < tau_r)
+            masked, at = masked | again, torch.where(again, -1, at)
+    return dict(z=z, h_run=h, conf=torch.stack(confs), lse=torch.stack(lses))
+
+
+def exact(case, seed):
+    """The computed numbers of one pass; None for the decisions (tokens, positions, flags)."""
+    c, g = dict(case), torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    if c["kind"] in ("chain", "tf"):
+        out = _chain64(c, g)
+        none = ["tok", "masked", "revealed_at", "cond_tok", "draft_pos", "draft_tok", "remasked", "x_tok"]
+        return dict(out, **{n: None for n in none + (["x_out", "n_masked"] if c.get("commit") else [])})
+    if c["kind"] == "kl":
+        V, M = c["V"], c["M"]
+        t = _logits(g, M, V)
+        s = (t + _normal(g, M, V, std=0.5, dtype=torch.float32)).double()
+        t = t.double()
+        on = torch.ones(M, 1, device="cuda") if c["share"] >= 1 else (torch.rand(M, device="cuda", generator=g) < c["share"]).view(M, 1)
+        p, q = torch.log_softmax(t, 1), torch.log_softmax(s, 1)
+        out = dict(loss=((p.exp() * (p - q)).sum(1, keepdim=True) * on / M).view(M))
+        return dict(out, grad=(q.exp() - p.exp()) * on / M) if c["grad"] else out
+    if c["kind"] == "rms":
+        n, S, N = c["n"], c["S"], c["N"]
+        pair = torch.zeros(n, S, S, dtype=torch.float64, device="cuda")
+        for i in range(n):
+            w = _normal(g, S, N, std=0.4, dtype=torch.float32)
+            w[0] *= 5.0
+            x = torch.cumsum(w, 0).to(torch.bfloat16 if c["bf16"] else torch.float32).double()
+            for t in range(S):
+                pair[i, t, t] = x[t].pow(2).mean().sqrt()
+                pair[i, t, t + 1:] = (x[t + 1:] - x[t]).pow(2).mean(1).sqrt()
+        delta = [pair[:, torch.arange(1, S), torch.arange(1, S)].mean()]
+        delta += [torch.diagonal(pair, r, 1, 2).mean() for r in range(1, S)]
+        return dict(pair=pair, delta=torch.stack(delta))
+    return None
+
+
 # ---- what a pass cannot do without, and how close another correct one comes -----------------------------------
 
 
