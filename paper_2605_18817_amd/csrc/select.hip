@@ -371,30 +371,64 @@ __global__ __launch_bounds__(256) void verify_argmax_kernel(int L, int V, int K,
     }
 }
 
+// Accept test of one sequence, one wavefront each.  What bounds it is latency: the nC partials of a draft are
+// contiguous, so the lanes fetch them (and those of VB drafts) in one round trip and merge them across lanes; equal
+// maxima keep the lower index, as in a walk over the chunks.  One thread per sequence, walking drafts and chunks
+// serially, took 15.6 us for 128 sequences x 3 drafts x 19 chunks; this form takes 4.
+constexpr int VB = 4;   // drafts fetched together
 __global__ __launch_bounds__(256) void verify_accept_kernel(int B, int K, int nC, const float *__restrict__ wm,
                                                             const int *__restrict__ wi,
                                                             const int32_t *__restrict__ draft_tok, int draft_stride,
                                                             uint8_t *__restrict__ match, int32_t *__restrict__ accept_len,
                                                             int32_t *__restrict__ correction_tok) {
-    const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b >= B) return;
+    const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (b >= B) return;   // (uniform over the wave)
+    const int tok = lane < K ? draft_tok[(size_t)b * draft_stride + lane] : 0;   // (K <= 16)
     int alen = 0, corr = -1;
     bool open = true;
-    for (int j = 0; j < K; ++j) {
-        const size_t base = ((size_t)b * K + j) * nC;
-        float m = wm[base];
-        int vj = wi[base];
-        for (int c = 1; c < nC; ++c)
-            if (wm[base + c] > m) { m = wm[base + c]; vj = wi[base + c]; }
-        const bool ok = vj >= 0 && vj == draft_tok[(size_t)b * draft_stride + j];
-        match[(size_t)b * K + j] = ok ? 1 : 0;
-        if (open) {
-            if (ok) ++alen;
-            else { open = false; corr = vj; }
+    for (int j0 = 0; j0 < K; j0 += VB) {
+        float m[VB];
+        int v[VB];
+#pragma unroll
+        for (int u = 0; u < VB; ++u) { m[u] = -INFINITY; v[u] = 0x7fffffff; }
+        for (int c = lane; c < nC; c += 64) {
+            float mc[VB];
+            int vc[VB];
+#pragma unroll
+            for (int u = 0; u < VB; ++u) {   // (a draft past the last one repeats it and is not used)
+                const size_t o = ((size_t)b * K + (j0 + u < K ? j0 + u : K - 1)) * nC + c;
+                mc[u] = wm[o];
+                vc[u] = wi[o];
+            }
+#pragma unroll
+            for (int u = 0; u < VB; ++u)
+                if (mc[u] > m[u] || (mc[u] == m[u] && vc[u] < v[u])) { m[u] = mc[u]; v[u] = vc[u]; }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+            for (int u = 0; u < VB; ++u) {
+                const float mo = __shfl_xor(m[u], off);
+                const int vo = __shfl_xor(v[u], off);
+                if (mo > m[u] || (mo == m[u] && vo < v[u])) { m[u] = mo; v[u] = vo; }
+            }
+#pragma unroll
+        for (int u = 0; u < VB; ++u) {
+            const int j = j0 + u;
+            if (j < K) {
+                const bool ok = v[u] >= 0 && v[u] == __shfl(tok, j);
+                if (lane == 0) match[(size_t)b * K + j] = ok ? 1 : 0;
+                if (open) {
+                    if (ok) ++alen;
+                    else { open = false; corr = v[u]; }
+                }
+            }
         }
     }
-    accept_len[b] = alen;
-    correction_tok[b] = corr;
+    if (lane == 0) {
+        accept_len[b] = alen;
+        correction_tok[b] = corr;
+    }
 }
 
 // Candidate blocks of the joint verification (paper Figure 1 (d)): candidate k of a sequence is its
@@ -478,7 +512,7 @@ hipError_t launch_verify(int B, int L, int V, int K, int joint, const float *ver
                            draft_pos, draft_stride, nC, wm, wi, err_flag);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(verify_accept_kernel, dim3((B + 255) / 256), dim3(256), 0, st, B, K, nC, wm, wi,
+    hipLaunchKernelGGL(verify_accept_kernel, dim3((B + 3) / 4), dim3(256), 0, st, B, K, nC, wm, wi,
                        draft_tok, draft_stride, match, accept_len, correction_tok);
     return hipGetLastError();
 }

@@ -50,6 +50,22 @@ def test_verify_accept_patterns(V):
     ctx.close()
 
 
+@pytest.mark.parametrize("V,K", [(8192 * 64 + 8, 5), (8192 * 2, 9)])   # more chunks than lanes; drafts in two and three rounds
+def test_verify_accept_many_chunks_and_drafts(V, K):
+    B, L = 5, max(K, 5)
+    ctx = mrp.MrpContext(128, V, B * L, L)
+    verify = RNG.normal(0, 2, (B, L, V)).astype(np.float32)
+    pos = np.stack([RNG.permutation(L)[:K] for _ in range(B)]).astype(np.int32)
+    tok = np.stack([verify[b, pos[b]].argmax(-1) for b in range(B)]).astype(np.int32)
+    for b in range(1, B):                                 # sequence b rejects a draft of its own, sequence 0 none
+        tok[b, (2 * b) % K] = (tok[b, (2 * b) % K] + 1) % V
+    # an exact tie between two chunks: the lowest index is the verifier's token
+    r = verify[0, pos[0, K - 1]]; r[V - 2] = r[8200] = float(r.max()) + 1.0; tok[0, K - 1] = 8200
+    a = _verify_case(ctx, B, L, V, K, verify, pos, tok)
+    assert a[0] == K
+    ctx.close()
+
+
 def test_remask_entry_point():
     B, L = 37, 16
     M = B * L
