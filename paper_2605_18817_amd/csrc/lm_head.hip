@@ -39,7 +39,8 @@ static_assert(LM_RING == 2 || LM_RING == 3, "ring depth");
 // memory time)
 // KS: 16-wide k blocks per activation stage and weight ring slot (8; 4 in the 256-row form, whose 128
 // accumulators leave room for half the ring)
-template <int LM_IT, int KS>
+// RAG: V is not a multiple of 4, rows of z start on any 4-byte boundary
+template <int LM_IT, int KS, bool RAG>
 __device__ __forceinline__ void lm_persist_body(const LmPersistArgs &a) {
     constexpr int LM_ROWS = 32 * LM_IT;
     constexpr int LM_STAGE = KS * LM_IT * 64;      // u32x4 per activation stage (32 KiB)
@@ -115,7 +116,7 @@ __device__ __forceinline__ void lm_persist_body(const LmPersistArgs &a) {
     }
 
     f32x16 acc[LM_IT];
-    auto zload = [&](int p) __attribute__((always_inline)) {
+    auto zload_pieces = [&](int p) __attribute__((always_inline)) {
         bool act;
         const int rb = pass_rb(p, act);
 #pragma unroll
@@ -131,7 +132,7 @@ __device__ __forceinline__ void lm_persist_body(const LmPersistArgs &a) {
             }
         }
     };
-    auto epilogue = [&](int p) __attribute__((always_inline)) {
+    auto epilogue_pieces = [&](int p) __attribute__((always_inline)) {
         bool act;
         const int rb = pass_rb(p, act);
         float *red_m = red_base + (p & 1) * RED_SET;
@@ -174,6 +175,103 @@ __device__ __forceinline__ void lm_persist_body(const LmPersistArgs &a) {
                 red_i[wave * LM_ROWS + it * 32 + ln] = pt.i;
             }
         }
+    };
+    // The same where V is not a multiple of 4 (RAG): only the block that holds the end of a row (one wave of the
+    // launch) goes entry by entry; everywhere else a lane moves 16 bytes at a time, whatever the row's alignment.
+    // (A form of its own: as the only one it costs the 128-row kernel 2.4 % at V = 151936.)
+    auto zload_any = [&](int p) __attribute__((always_inline)) {
+        bool act;
+        const int rb = pass_rb(p, act);
+        const int v0 = rb * 32 + 4 * lh;
+        if (!act || rb * 32 + 32 <= a.V) {      // (uniform over the wave)
+#pragma unroll
+            for (int it = 0; it < LM_IT; ++it) {
+                const int i = it * 32 + ln;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (act && i < a.M) x = load4(a.z + (size_t)i * a.V + v0 + 8 * q);
+                    acc[it][4 * q + 0] = x.x; acc[it][4 * q + 1] = x.y;
+                    acc[it][4 * q + 2] = x.z; acc[it][4 * q + 3] = x.w;
+                }
+            }
+        } else {
+#pragma unroll
+            for (int it = 0; it < LM_IT; ++it) {
+                const int i = it * 32 + ln;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int v = v0 + 8 * (r >> 2) + (r & 3);
+                    acc[it][r] = 0.f;
+                    if (i < a.M && v < a.V) acc[it][r] = a.z[(size_t)i * a.V + v];
+                }
+            }
+        }
+    };
+    auto epilogue_any = [&](int p) __attribute__((always_inline)) {
+        bool act;
+        const int rb = pass_rb(p, act);
+        const int v0 = rb * 32 + 4 * lh;
+        float *red_m = red_base + (p & 1) * RED_SET;
+        float *red_s = red_m + LM_WAVES * LM_ROWS;
+        int *red_i = reinterpret_cast<int *>(red_s + LM_WAVES * LM_ROWS);
+        const bool whole = act && rb * 32 + 32 <= a.V;      // (uniform over the wave)
+        if (whole) {
+#pragma unroll
+            for (int it = 0; it < LM_IT; ++it) {
+                const int i = it * 32 + ln;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (i < a.M)
+                        store4(a.z + (size_t)i * a.V + v0 + 8 * q,
+                               make_float4(acc[it][4 * q], acc[it][4 * q + 1], acc[it][4 * q + 2], acc[it][4 * q + 3]));
+            }
+        } else {                                            // entries past V (or a wave without a block): no part of the row
+#pragma unroll
+            for (int it = 0; it < LM_IT; ++it) {
+                const int i = it * 32 + ln;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int v = v0 + 8 * (r >> 2) + (r & 3);
+                    const bool ok = act && v < a.V;
+                    if (ok && i < a.M) a.z[(size_t)i * a.V + v] = acc[it][r];
+                    if (!ok) acc[it][r] = -INFINITY;
+                }
+            }
+        }
+#pragma unroll
+        for (int it = 0; it < LM_IT; ++it) {
+            Part pt = part_identity();
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float x = acc[it][r];
+                if (x > pt.m) { pt.m = x; pt.i = v0 + 8 * (r >> 2) + (r & 3); }
+            }
+            float s = 0.f;
+            if (pt.m > -INFINITY) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s += __expf(acc[it][r] - pt.m);
+            }
+            pt.s = s;
+            Part other;
+            other.m = __shfl_xor(pt.m, 32);
+            other.s = __shfl_xor(pt.s, 32);
+            other.i = __shfl_xor(pt.i, 32);
+            pt = part_merge(pt, other);
+            if (lh == 0) {
+                red_m[wave * LM_ROWS + it * 32 + ln] = pt.m;
+                red_s[wave * LM_ROWS + it * 32 + ln] = pt.s;
+                red_i[wave * LM_ROWS + it * 32 + ln] = pt.i;
+            }
+        }
+    };
+    auto zload = [&](int p) __attribute__((always_inline)) {
+        if constexpr (RAG) zload_any(p);
+        else zload_pieces(p);
+    };
+    auto epilogue = [&](int p) __attribute__((always_inline)) {
+        if constexpr (RAG) epilogue_any(p);
+        else epilogue_pieces(p);
     };
     // after a barrier: merge the 8 waves' partials of pass p into the running partial
     auto write_partials = [&](int p) __attribute__((always_inline)) {
@@ -263,21 +361,32 @@ __device__ __forceinline__ void lm_persist_body(const LmPersistArgs &a) {
 #undef LM_YLOAD
 }
 
+template <bool RAG>
 __global__ __launch_bounds__(LM_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lm_persist_kernel(
     const LmPersistArgs a) {
-    lm_persist_body<4, 8>(a);
+    lm_persist_body<4, 8, RAG>(a);
 }
+template <bool RAG>
 __global__ __launch_bounds__(LM_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lm_persist_kernel_256rows(
     const LmPersistArgs a) {
-    lm_persist_body<8, 4>(a);
+    lm_persist_body<8, 4, RAG>(a);
 }
+template <bool RAG>
 __global__ __launch_bounds__(LM_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lm_persist_kernel_64rows(
     const LmPersistArgs a) {
-    lm_persist_body<2, 8>(a);
+    lm_persist_body<2, 8, RAG>(a);
 }
+template <bool RAG>
 __global__ __launch_bounds__(LM_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void lm_persist_kernel_32rows(
     const LmPersistArgs a) {
-    lm_persist_body<1, 8>(a);
+    lm_persist_body<1, 8, RAG>(a);
+}
+
+template <bool RAG>
+auto kernel_for(int M) -> void (*)(const LmPersistArgs) {
+    return M <= 32 ? lm_persist_kernel_32rows<RAG>
+                   : (M <= 64 ? lm_persist_kernel_64rows<RAG>
+                              : (M <= 128 ? lm_persist_kernel<RAG> : lm_persist_kernel_256rows<RAG>));
 }
 
 }  // namespace
@@ -289,19 +398,16 @@ size_t lm_persist_lds_bytes() { return (size_t)2 * 32768 + (size_t)2 * LM_WAVES 
 // Once per device (mrp_create): the kernels need more than the default 64 KiB of dynamic LDS.
 hipError_t lm_persist_configure() {
     hipError_t e = hipSuccess;
-    for (const void *k : {reinterpret_cast<const void *>(lm_persist_kernel),
-                          reinterpret_cast<const void *>(lm_persist_kernel_256rows),
-                          reinterpret_cast<const void *>(lm_persist_kernel_64rows),
-                          reinterpret_cast<const void *>(lm_persist_kernel_32rows)})
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lm_persist_lds_bytes());
+    for (int M : {32, 64, 128, 256})
+        for (const void *k : {reinterpret_cast<const void *>(kernel_for<false>(M)), reinterpret_cast<const void *>(kernel_for<true>(M))})
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lm_persist_lds_bytes());
     return e;
 }
 
 hipError_t launch_lm_persist(const LmPersistArgs &a, hipStream_t st) {
     if (a.M > 256) return hipErrorInvalidValue;
-    auto k = a.M <= 32 ? lm_persist_kernel_32rows
-                       : (a.M <= 64 ? lm_persist_kernel_64rows : (a.M <= 128 ? lm_persist_kernel : lm_persist_kernel_256rows));
+    auto k = a.V % 4 ? kernel_for<true>(a.M) : kernel_for<false>(a.M);
     hipLaunchKernelGGL(k, dim3(a.nWG), dim3(LM_THREADS), lm_persist_lds_bytes(), st, a);
     return hipGetLastError();
 }

@@ -20,8 +20,6 @@ struct mrp_ctx {
     int nT_max;         // partial tiles per row
     size_t part_rows;   // capacity of the k-split partial buffer, in rows of d floats
     int maxB;
-    bool use_tiled;     // 256 x 256 tiled GEMMs for M >= 768
-    bool lm_persist;    // the persistent LM-head kernel for M <= 512 (launches of at most 256 rows)
     int nCU;            // compute units of the device (workgroups of the persistent LM-head kernel)
     char *ws;
     size_t ws_bytes;
@@ -157,7 +155,7 @@ int small_tile_blocks(int R, int nrt, int nCU) { return (R % 64 == 0 && (R / 32)
 // of k splits written (1 for the tiled kernel) or -1 after a launch error (*err set).
 int gemm_partial(mrp_ctx *c, hipStream_t st, const void *Wp, int R, int Kc, const uint4 *act, long plane_stride,
                  int nplanes, int M, float *out, size_t out_floats, hipError_t *err) {
-    if (c->use_tiled && body_on_tiles(M, Kc) && R % 256 == 0) {
+    if (body_on_tiles(M, Kc) && R % 256 == 0) {
         TiledGemmArgs tg;
         memset(&tg, 0, sizeof(tg));
         tg.Wp = static_cast<const uint4 *>(Wp);
@@ -208,7 +206,7 @@ int gemm_partial(mrp_ctx *c, hipStream_t st, const void *Wp, int R, int Kc, cons
     g.nVt = R / WG_ROWS; g.nMg = ((M + 31) / 32 + IT - 1) / IT; g.G = Kc / (16 * KSTEP);
     g.nKs = pick_ksplit(g.nVt, g.nMg, g.G, out_floats / (size_t)R, M);
     g.out = out;
-    *err = launch_stream_gemm(g, EPI_PARTIAL, st);
+    *err = launch_stream_gemm(g, st);
     return *err == hipSuccess ? g.nKs : -1;
 }
 
@@ -234,8 +232,6 @@ int mrp_create(mrp_ctx **out, const mrp_dims *dims) {
     c->ev_used = 0;
     c->tb_on = false;
     c->tb_ws = nullptr;
-    c->lm_persist = true;
-    c->use_tiled = true;
     if (hipGetDevice(&c->device) != hipSuccess ||
         hipDeviceGetAttribute(&c->nCU, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || c->nCU < 1) {
         delete c;
@@ -499,10 +495,10 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
         StreamGemmArgs g;
         // The LM head has V / 256 tiles per 256 rows and takes the tile kernel beyond 512 rows (measured at
         // d = 4096, V = 151936: 931 / 955 / 1031 / 1074 us at 272 / 512 / 752 / 768 rows); below, the persistent
-        // kernel in launches of at most 256 rows is ahead (see there).  The streaming kernel is left with
-        // vocabularies that are not a multiple of 4.
-        const bool tiled = c->use_tiled && body_on_tiles(M, d);
-        const bool tiled_lm = c->use_tiled && M > 512;
+        // kernel in launches of at most 256 rows is ahead (see there).  Both take rows at any 4-byte offset, so a
+        // vocabulary that is not a multiple of 4 goes the same way (192 rows, d = 2048, V = 50257: 138 us on the
+        // streaming kernel that served it before, 90 us on the persistent one).
+        const bool tiled = body_on_tiles(M, d);
         int nks1 = 1, nks2 = 1;
         bool silu_done = false;   // the first GEMM's epilogue already wrote s = SiLU(a) as activation planes
         const float *resid = nullptr;   // transformer body: residual stream added to the last projection
@@ -550,7 +546,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             g.nKs = pick_ksplit(g.nVt, nMg, g.G, c->part_rows, M);
             g.out = c->PART;
             nks1 = g.nKs;
-            HIP_TRY(c, launch_stream_gemm(g, EPI_PARTIAL, st));
+            HIP_TRY(c, launch_stream_gemm(g, st));
         }
         if (layers) {
             const mrp_tbody_dims &tb = c->tb;
@@ -614,7 +610,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             g.nKs = pick_ksplit(g.nVt, nMg, g.G, c->part_rows, M);
             g.out = c->PART;
             nks2 = g.nKs;
-            HIP_TRY(c, launch_stream_gemm(g, EPI_PARTIAL, st));
+            HIP_TRY(c, launch_stream_gemm(g, st));
         }
         }
         }
@@ -627,7 +623,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
         if (prof) HIP_TRY(c, hipEventRecord(c->ev[2 * c->ev_used], st));
         int nT_lm = 0;
         bool lm_rowmajor = false;  // partial layout [M][nT] (persistent kernel) or [nT][M]
-        if (c->lm_persist && M <= 512 && V % 4 == 0) {
+        if (M <= 512) {
             // up to 256 rows per launch; a second launch for the rows beyond streams W_lm again, which up to
             // 512 rows is still cheaper than the tile kernel (measured at d = 4096: 392 us for 256 rows,
             // 281 us for 128, against 931-955 us for the tile kernel at 272-512 rows)
@@ -650,7 +646,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             }
             nT_lm = c->nCU;
             lm_rowmajor = true;
-        } else if (tiled_lm && V % 4 == 0) {
+        } else {
             TiledGemmArgs tg;
             memset(&tg, 0, sizeof(tg));
             tg.Wp = static_cast<const uint4 *>(W_lm_packed);
@@ -662,16 +658,6 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             tg.z = z; tg.pm = c->pm; tg.ps = c->ps; tg.pi = c->pi;
             HIP_TRY(c, launch_tiled_gemm(tg, EPI_LM, st));
             nT_lm = tg.nVt;
-        } else {
-            memset(&g, 0, sizeof(g));
-            g.Wp = static_cast<const uint4 *>(W_lm_packed);
-            g.KBw = d / 16; g.n_rb = (V + 31) / 32; g.nIb = c->nIb; g.M = M; g.R = V;
-            g.seg[0] = ActSeg{c->Y, 0, nkr_d, 1};
-            g.nseg = 1;
-            g.nVt = (g.n_rb + WG_WAVES - 1) / WG_WAVES; g.nMg = nMg; g.nKs = 1; g.G = nkr_d;
-            g.z = z; g.pm = c->pm; g.ps = c->ps; g.pi = c->pi;
-            HIP_TRY(c, launch_stream_gemm(g, EPI_LM, st));
-            nT_lm = g.nVt;
         }
         if (prof) {
             HIP_TRY(c, hipEventRecord(c->ev[2 * c->ev_used + 1], st));

@@ -48,15 +48,10 @@ struct StreamGemmArgs {
     int nseg;
     int nVt, nMg, nKs; // grid decomposition: weight tiles, row groups, k splits
     int G;             // total k ranges = KBw / KSTEP
-    // EPI_PARTIAL: out[ks][M][R] fp32
-    float *out;
-    // EPI_LM: z [M][R] fp32 in/out; partials [nVt][M]
-    float *z;
-    float *pm, *ps;
-    int *pi;
+    float *out;        // out[ks][M][R] fp32
 };
 
-// Persistent LM-head kernel (at most 128 activation rows, V % 4 == 0)
+// Persistent LM-head kernel (at most 256 activation rows)
 struct LmPersistArgs {
     const uint4 *Wp;   // packed W_lm [n_rb][KB][64]
     const uint4 *Y;    // packed bf16 activation plane [KB][nIb][64]
@@ -112,6 +107,30 @@ struct HeadFusedArgs {
     int nf;                    // weight row blocks per tile (1 or 2)
     int nct, nrt;              // feature tiles d / (32 nf), row tiles ceil(M / 32)
 };
+
+// Four consecutive floats at any 4-byte address (one 16-byte request: the rows of a logit matrix whose vocabulary is
+// not a multiple of 4 start on any of the four offsets)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4(const float *p) {
+    const f32x4_any v = *reinterpret_cast<const f32x4_any *>(p);
+    return make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void store4(float *p, const float4 &x) {
+    const f32x4_any v = {x.x, x.y, x.z, x.w};
+    *reinterpret_cast<f32x4_any *>(p) = v;
+}
+// The four entries v .. v + 3 of a row of V floats, `fill` past its end
+__device__ __forceinline__ float4 load4_row(const float *row, int v, int V, float fill) {
+    float4 x = make_float4(fill, fill, fill, fill);
+    if (v + 4 <= V) {
+        x = load4(row + v);
+    } else if (v < V) {
+        x.x = row[v];
+        if (v + 1 < V) x.y = row[v + 1];
+        if (v + 2 < V) x.z = row[v + 2];
+    }
+    return x;
+}
 
 // row-reduction partial: running max, sum of exp(x - max), index of the max
 struct Part {
@@ -235,7 +254,7 @@ __device__ __forceinline__ void sum_partials(const float *__restrict__ part, siz
 }
 
 // ---- host-side launchers (defined in the .hip files) ----
-hipError_t launch_stream_gemm(const StreamGemmArgs &a, int epi, hipStream_t st);
+hipError_t launch_stream_gemm(const StreamGemmArgs &a, hipStream_t st);
 size_t stream_gemm_lds_bytes(int it);
 hipError_t stream_gemm_configure();   // once per device
 int stream_gemm_it(int M);   // activation row blocks per workgroup for M rows

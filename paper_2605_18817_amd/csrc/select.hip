@@ -45,7 +45,6 @@ __device__ __forceinline__ Part block_merge(Part p, float *sm, float *ss, int *s
     return p;
 }
 
-template <bool VEC4>
 __global__ __launch_bounds__(256) void reduce_rows_kernel(const float *__restrict__ z, int M, int V,
                                                           float *__restrict__ pm, float *__restrict__ ps,
                                                           int *__restrict__ pi) {
@@ -55,25 +54,15 @@ __global__ __launch_bounds__(256) void reduce_rows_kernel(const float *__restric
     const float *row = z + (size_t)i * V;
     const int v0 = t * RT;
     float x[32];
-    if constexpr (VEC4) {
 #pragma unroll
-        for (int n = 0; n < 8; ++n) {
-            const int v = v0 + 4 * (threadIdx.x + 256 * n);
-            float4 q = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-            if (v < V) q = *reinterpret_cast<const float4 *>(row + v);
-            x[4 * n] = q.x; x[4 * n + 1] = q.y; x[4 * n + 2] = q.z; x[4 * n + 3] = q.w;
-        }
-    } else {
-#pragma unroll
-        for (int n = 0; n < 32; ++n) {
-            const int v = v0 + threadIdx.x + 256 * n;
-            x[n] = (v < V) ? row[v] : -INFINITY;
-        }
+    for (int n = 0; n < 8; ++n) {
+        const float4 q = load4_row(row, v0 + 4 * (threadIdx.x + 256 * n), V, -INFINITY);
+        x[4 * n] = q.x; x[4 * n + 1] = q.y; x[4 * n + 2] = q.z; x[4 * n + 3] = q.w;
     }
     Part p = part_identity();
 #pragma unroll
     for (int n = 0; n < 32; ++n) {
-        const int v = VEC4 ? v0 + 4 * (threadIdx.x + 256 * (n >> 2)) + (n & 3) : v0 + threadIdx.x + 256 * n;
+        const int v = v0 + 4 * (threadIdx.x + 256 * (n >> 2)) + (n & 3);
         if (x[n] > p.m) { p.m = x[n]; p.i = v; }
     }
     float s = 0.f;
@@ -319,7 +308,6 @@ __global__ __launch_bounds__(64) void remask_kernel(int B, int L, int state, con
 }
 
 // argmax partial of one RT-wide chunk of the verifier row of draft (b, j)
-template <bool VEC4>
 __global__ __launch_bounds__(256) void verify_argmax_kernel(int L, int V, int K, int joint,
                                                             const float *__restrict__ verify,
                                                             const int32_t *__restrict__ draft_pos, int draft_stride,
@@ -340,28 +328,16 @@ __global__ __launch_bounds__(256) void verify_argmax_kernel(int L, int V, int K,
         const size_t blk = joint ? (size_t)b * (K + 1) + j : (size_t)b;
         const float *row = verify + (blk * L + pos) * V;
         const int v0 = c * RT;
-        if constexpr (VEC4) {
-            float4 q[8];
+        float4 q[8];
 #pragma unroll
-            for (int n = 0; n < 8; ++n) {
-                const int v = v0 + 4 * (threadIdx.x + 256 * n);
-                q[n] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-                if (v < V) q[n] = *reinterpret_cast<const float4 *>(row + v);
-            }
+        for (int n = 0; n < 8; ++n) q[n] = load4_row(row, v0 + 4 * (threadIdx.x + 256 * n), V, -INFINITY);
 #pragma unroll
-            for (int n = 0; n < 8; ++n) {
-                const int v = v0 + 4 * (threadIdx.x + 256 * n);
-                if (q[n].x > p.m) { p.m = q[n].x; p.i = v; }
-                if (q[n].y > p.m) { p.m = q[n].y; p.i = v + 1; }
-                if (q[n].z > p.m) { p.m = q[n].z; p.i = v + 2; }
-                if (q[n].w > p.m) { p.m = q[n].w; p.i = v + 3; }
-            }
-        } else {
-            for (int n = 0; n < 32; ++n) {
-                const int v = v0 + threadIdx.x + 256 * n;
-                const float x = (v < V) ? row[v] : -INFINITY;
-                if (x > p.m) { p.m = x; p.i = v; }
-            }
+        for (int n = 0; n < 8; ++n) {
+            const int v = v0 + 4 * (threadIdx.x + 256 * n);
+            if (q[n].x > p.m) { p.m = q[n].x; p.i = v; }
+            if (q[n].y > p.m) { p.m = q[n].y; p.i = v + 1; }
+            if (q[n].z > p.m) { p.m = q[n].z; p.i = v + 2; }
+            if (q[n].w > p.m) { p.m = q[n].w; p.i = v + 3; }
         }
     }
     p = block_merge(p, sm, ss, si);
@@ -474,10 +450,7 @@ hipError_t launch_reduce_rows(const float *z, int M, int V, float *pm, float *ps
                               hipStream_t st) {
     const int nT = reduce_rows_tiles(V);
     *nT_out = nT;
-    if (V % 4 == 0)
-        hipLaunchKernelGGL(reduce_rows_kernel<true>, dim3(nT, M), dim3(256), 0, st, z, M, V, pm, ps, pi);
-    else
-        hipLaunchKernelGGL(reduce_rows_kernel<false>, dim3(nT, M), dim3(256), 0, st, z, M, V, pm, ps, pi);
+    hipLaunchKernelGGL(reduce_rows_kernel, dim3(nT, M), dim3(256), 0, st, z, M, V, pm, ps, pi);
     return hipGetLastError();
 }
 
@@ -504,12 +477,8 @@ hipError_t launch_verify(int B, int L, int V, int K, int joint, const float *ver
                          const int32_t *draft_tok, int draft_stride, float *wm, int *wi, uint8_t *match,
                          int32_t *accept_len, int32_t *correction_tok, int *err_flag, hipStream_t st) {
     const int nC = verify_chunks(V);
-    if (V % 4 == 0)
-        hipLaunchKernelGGL(verify_argmax_kernel<true>, dim3(nC, B * K), dim3(256), 0, st, L, V, K, joint, verify,
-                           draft_pos, draft_stride, nC, wm, wi, err_flag);
-    else
-        hipLaunchKernelGGL(verify_argmax_kernel<false>, dim3(nC, B * K), dim3(256), 0, st, L, V, K, joint, verify,
-                           draft_pos, draft_stride, nC, wm, wi, err_flag);
+    hipLaunchKernelGGL(verify_argmax_kernel, dim3(nC, B * K), dim3(256), 0, st, L, V, K, joint, verify, draft_pos,
+                       draft_stride, nC, wm, wi, err_flag);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(verify_accept_kernel, dim3((B + 3) / 4), dim3(256), 0, st, B, K, nC, wm, wi,

@@ -1,4 +1,4 @@
-// Weight-streaming MFMA GEMM for gfx950 (bf16 operands for the LM head, fp16 for the head body):  out[i][r] (+)= sum_k W[r][k] * X[i][k].
+// Weight-streaming MFMA GEMM for gfx950 (fp16 operands):  out[i][r] (+)= sum_k W[r][k] * X[i][k].
 //
 // W is a packed weight matrix (32x16 fragment blocks, contiguous along k for a
 // 32-row block), X a packed activation operand made of one or more 16-bit planes.
@@ -7,17 +7,9 @@
 // the activation slice of the current k range is shared by the four waves of a
 // workgroup through LDS.  The MFMA's "A" operand is the weight fragment, its
 // "B" operand the activation fragment, so a lane's 16 accumulators of a 32x32
-// tile are 16 outputs of ONE activation row: a row reduction over the outputs
-// (the vocabulary, for the LM head) is done in registers plus one cross-lane
-// exchange.
+// tile are 16 outputs of ONE activation row.
 //
-// Epilogues:
-//   EPI_PARTIAL  store the fp32 tile to out[ks][i][r] (k-split partial sums)
-//   EPI_LM       LM head of the MRP chain (paper Section 3.2: the head reuses
-//                the backbone's LM head; Algorithm 2: l <- l + delta): the
-//                accumulators start from the logit state z, the updated z is
-//                stored back, and the tile's per-row (max, sum-exp, argmax)
-//                partial is written for the split-vocabulary softmax reduction.
+// Epilogue: the fp32 tile goes to out[ks][i][r] (k-split partial sums).
 #include "mrp_kernels.h"
 
 #include <type_traits>
@@ -28,23 +20,17 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));  // native vector: stays in registers
 
-// One 32x32x16 matrix multiply-accumulate on 16-byte operand fragments: the partial-sum GEMMs of the
-// head body take fp16 operands (weights converted at pack time, activations as fp16 planes), the LM
-// head bf16 ones.
-template <int EPI>
+// One 32x32x16 matrix multiply-accumulate on 16-byte operand fragments (fp16: weights converted at pack
+// time, activations as fp16 planes).
 __device__ __forceinline__ f32x16 mma_frag(const u32x4 &w, const u32x4 &x, const f32x16 &c) {
-    if constexpr (EPI == EPI_PARTIAL)
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, w), __builtin_bit_cast(f16x8, x), c, 0, 0, 0);
-    else
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, w), __builtin_bit_cast(f16x8, x), c, 0, 0, 0);
 }
 
-template <int IT, int EPI, bool VEC4>
+template <int IT>
 __device__ __forceinline__ void stream_gemm_body(const StreamGemmArgs &a) {
     extern __shared__ u32x4 smem[];
     constexpr int STAGE = KSTEP * IT * 64;  // uint4 per activation stage
     constexpr int NLD = STAGE / 256;        // uint4 each thread moves per stage
-    constexpr int ROWS = IT * 32;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ln = lane & 31, lh = lane >> 5;
@@ -108,35 +94,10 @@ __device__ __forceinline__ void stream_gemm_body(const StreamGemmArgs &a) {
     }
 
     f32x16 acc[IT];
-    if constexpr (EPI == EPI_LM) {
 #pragma unroll
-        for (int it = 0; it < IT; ++it) {
-            const int i = (ib0 + it) * 32 + ln;
+    for (int it = 0; it < IT; ++it)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int v = rb * 32 + 8 * q + 4 * lh;
-                float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (rb_ok && i < a.M) {
-                    const float *zp = a.z + (size_t)i * a.R + v;
-                    if constexpr (VEC4) {
-                        if (v < a.R) x = *reinterpret_cast<const float4 *>(zp);
-                    } else {
-                        if (v + 0 < a.R) x.x = zp[0];
-                        if (v + 1 < a.R) x.y = zp[1];
-                        if (v + 2 < a.R) x.z = zp[2];
-                        if (v + 3 < a.R) x.w = zp[3];
-                    }
-                }
-                acc[it][4 * q + 0] = x.x; acc[it][4 * q + 1] = x.y;
-                acc[it][4 * q + 2] = x.z; acc[it][4 * q + 3] = x.w;
-            }
-        }
-    } else {
-#pragma unroll
-        for (int it = 0; it < IT; ++it)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[it][r] = 0.f;
-    }
+        for (int r = 0; r < 16; ++r) acc[it][r] = 0.f;
     __syncthreads();
 
     // ---- main loop over (k range, plane) stages ----
@@ -163,7 +124,7 @@ __device__ __forceinline__ void stream_gemm_body(const StreamGemmArgs &a) {
 #pragma unroll
                 for (int it = 0; it < IT; ++it) bfr[it] = cur[(j * IT + it) * 64 + lane];
 #pragma unroll
-                for (int it = 0; it < IT; ++it) acc[it] = mma_frag<EPI>(wreg[PAR * KSTEP + j], bfr[it], acc[it]);
+                for (int it = 0; it < IT; ++it) acc[it] = mma_frag(wreg[PAR * KSTEP + j], bfr[it], acc[it]);
             }
             if (p == np - 1 && g + 2 < g_end) {
 #pragma unroll
@@ -185,85 +146,19 @@ __device__ __forceinline__ void stream_gemm_body(const StreamGemmArgs &a) {
 
 #undef MRP_LOAD_STAGE
     // ---- epilogue ----
-    if constexpr (EPI == EPI_PARTIAL) {
-        if (rb_ok) {
-#pragma unroll
-            for (int it = 0; it < IT; ++it) {
-                const int i = (ib0 + it) * 32 + ln;
-                if (i < a.M) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int r = rb * 32 + 8 * q + 4 * lh;
-                        if (r < a.R)
-                            *reinterpret_cast<float4 *>(a.out + ((size_t)ks * a.M + i) * a.R + r) =
-                                make_float4(acc[it][4 * q], acc[it][4 * q + 1], acc[it][4 * q + 2],
-                                            acc[it][4 * q + 3]);
-                    }
-                }
-            }
-        }
-    } else {
-        float *red_m = reinterpret_cast<float *>(smem + 2 * STAGE);
-        float *red_s = red_m + WG_WAVES * ROWS;
-        int *red_i = reinterpret_cast<int *>(red_s + WG_WAVES * ROWS);
+    if (rb_ok) {
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
             const int i = (ib0 + it) * 32 + ln;
-            const bool row_ok = rb_ok && i < a.M;
-            Part pt = part_identity();
-            // store the updated logits and find this lane's maximum (ascending v)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int v = rb * 32 + 8 * q + 4 * lh;
-                if (row_ok) {
-                    float *zp = a.z + (size_t)i * a.R + v;
-                    if constexpr (VEC4) {
-                        if (v < a.R)
-                            *reinterpret_cast<float4 *>(zp) = make_float4(
-                                acc[it][4 * q], acc[it][4 * q + 1], acc[it][4 * q + 2], acc[it][4 * q + 3]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (v + e < a.R) zp[e] = acc[it][4 * q + e];
-                    }
-                }
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float x = acc[it][4 * q + e];
-                    if (rb_ok && v + e < a.R && x > pt.m) { pt.m = x; pt.i = v + e; }
-                }
-            }
-            float s = 0.f;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int v = rb * 32 + 8 * q + 4 * lh + e;
-                    if (rb_ok && v < a.R) s += __expf(acc[it][4 * q + e] - pt.m);
-                }
-            pt.s = s;
-            Part other;
-            other.m = __shfl_xor(pt.m, 32);
-            other.s = __shfl_xor(pt.s, 32);
-            other.i = __shfl_xor(pt.i, 32);
-            pt = part_merge(pt, other);
-            if (lh == 0) {
-                red_m[wave * ROWS + it * 32 + ln] = pt.m;
-                red_s[wave * ROWS + it * 32 + ln] = pt.s;
-                red_i[wave * ROWS + it * 32 + ln] = pt.i;
-            }
-        }
-        __syncthreads();
-        if (tid < ROWS) {
-            Part pt = {red_m[tid], red_s[tid], red_i[tid]};
-#pragma unroll
-            for (int wv = 1; wv < WG_WAVES; ++wv)
-                pt = part_merge(pt, Part{red_m[wv * ROWS + tid], red_s[wv * ROWS + tid], red_i[wv * ROWS + tid]});
-            const int i = ib0 * 32 + tid;
             if (i < a.M) {
-                a.pm[(size_t)vt * a.M + i] = pt.m;
-                a.ps[(size_t)vt * a.M + i] = pt.s;
-                a.pi[(size_t)vt * a.M + i] = pt.i;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int r = rb * 32 + 8 * q + 4 * lh;
+                    if (r < a.R)
+                        *reinterpret_cast<float4 *>(a.out + ((size_t)ks * a.M + i) * a.R + r) =
+                            make_float4(acc[it][4 * q], acc[it][4 * q + 1], acc[it][4 * q + 2],
+                                        acc[it][4 * q + 3]);
+                }
             }
         }
     }
@@ -271,38 +166,36 @@ __device__ __forceinline__ void stream_gemm_body(const StreamGemmArgs &a) {
 
 // IT = 4 (up to 128 activation rows per workgroup): two workgroups per CU, so the
 // register budget is capped at 256 per lane.  IT = 8: one workgroup per CU.
-template <int EPI, bool VEC4>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void stream_gemm_kernel4(
     const StreamGemmArgs a) {
-    stream_gemm_body<4, EPI, VEC4>(a);
+    stream_gemm_body<4>(a);
 }
-template <int EPI, bool VEC4>
 __global__ __launch_bounds__(256) void stream_gemm_kernel8(const StreamGemmArgs a) {
-    stream_gemm_body<8, EPI, VEC4>(a);
+    stream_gemm_body<8>(a);
 }
 
 template <int IT>
 constexpr size_t lds_bytes() {
-    return (size_t)2 * KSTEP * IT * 64 * 16 + (size_t)WG_WAVES * IT * 32 * 12;
+    return (size_t)2 * KSTEP * IT * 64 * 16;
 }
 
-template <int IT, int EPI, bool VEC4>
+template <int IT>
 auto kernel_of() -> void (*)(const StreamGemmArgs) {
-    if constexpr (IT == 4) return stream_gemm_kernel4<EPI, VEC4>;
-    else return stream_gemm_kernel8<EPI, VEC4>;
+    if constexpr (IT == 4) return stream_gemm_kernel4;
+    else return stream_gemm_kernel8;
 }
 
-template <int IT, int EPI, bool VEC4>
+template <int IT>
 hipError_t configure_inst() {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel_of<IT, EPI, VEC4>()),
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel_of<IT>()),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes<IT>());
 }
 
-template <int IT, int EPI, bool VEC4>
+template <int IT>
 hipError_t launch_inst(const StreamGemmArgs &a, hipStream_t st) {
     const int nWG = a.nVt * a.nMg * a.nKs;
     const int per = (nWG + 7) / 8;
-    hipLaunchKernelGGL((kernel_of<IT, EPI, VEC4>()), dim3(per * 8), dim3(256), lds_bytes<IT>(), st, a);
+    hipLaunchKernelGGL((kernel_of<IT>()), dim3(per * 8), dim3(256), lds_bytes<IT>(), st, a);
     return hipGetLastError();
 }
 
@@ -310,12 +203,8 @@ hipError_t launch_inst(const StreamGemmArgs &a, hipStream_t st) {
 
 // Once per device (mrp_create): the kernels need more than the default 64 KiB of dynamic LDS.
 hipError_t stream_gemm_configure() {
-    hipError_t e = configure_inst<4, EPI_PARTIAL, true>();
-    if (e == hipSuccess) e = configure_inst<8, EPI_PARTIAL, true>();
-    if (e == hipSuccess) e = configure_inst<4, EPI_LM, true>();
-    if (e == hipSuccess) e = configure_inst<4, EPI_LM, false>();
-    if (e == hipSuccess) e = configure_inst<8, EPI_LM, true>();
-    if (e == hipSuccess) e = configure_inst<8, EPI_LM, false>();
+    hipError_t e = configure_inst<4>();
+    if (e == hipSuccess) e = configure_inst<8>();
     return e;
 }
 
@@ -323,15 +212,8 @@ int stream_gemm_it(int M) { return M > 128 ? 8 : 4; }
 
 size_t stream_gemm_lds_bytes(int it) { return it == 8 ? lds_bytes<8>() : lds_bytes<4>(); }
 
-hipError_t launch_stream_gemm(const StreamGemmArgs &a, int epi, hipStream_t st) {
-    const int it = stream_gemm_it(a.M);
-    const bool vec4 = (a.R % 4) == 0;
-    if (epi == EPI_PARTIAL) {
-        return it == 8 ? launch_inst<8, EPI_PARTIAL, true>(a, st) : launch_inst<4, EPI_PARTIAL, true>(a, st);
-    }
-    if (it == 8)
-        return vec4 ? launch_inst<8, EPI_LM, true>(a, st) : launch_inst<8, EPI_LM, false>(a, st);
-    return vec4 ? launch_inst<4, EPI_LM, true>(a, st) : launch_inst<4, EPI_LM, false>(a, st);
+hipError_t launch_stream_gemm(const StreamGemmArgs &a, hipStream_t st) {
+    return stream_gemm_it(a.M) == 8 ? launch_inst<8>(a, st) : launch_inst<4>(a, st);
 }
 
 }  // namespace mrp

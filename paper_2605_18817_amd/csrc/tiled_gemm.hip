@@ -63,7 +63,9 @@ typedef __attribute__((address_space(3))) void *las_ptr;
 __device__ __forceinline__ void tg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // REM = 2 + (k steps - 2) % 3: the k steps left for the straight-line tail after the unrolled loop
-template <int EPI, int REM>
+// RAG: R is not a multiple of 4 (EPI_LM), so a row of the logit state starts on any 4-byte boundary and ends inside a
+// 16-byte piece
+template <int EPI, int REM, bool RAG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void tiled_gemm_kernel(
     const TiledGemmArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -180,14 +182,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // the matrix; what lies outside is never used), so the number of requests per step is fixed.
     // The first two slices are requested during the last two k steps, in place of the operand
     // requests those steps no longer need (more would not fit the registers next to the k loop's).
-    constexpr int ZD = 6;                       // slice buffers: five slices in flight ahead of the one added
+    constexpr int ZD = RAG ? 2 : 6;             // slice buffers: five (one) slices in flight ahead of the one added
     f32x4 zc[ZD][8];
     const int zv_lane = (rb0 + wave * 2) * 32 + 4 * lh;     // + 32 v2 + 8 q
+    // last start of a piece of row i inside the matrix (RAG: a piece that crosses the end of its row takes in the
+    // start of the next one, never used; where that would pass the end of the matrix the piece starts early instead
+    // and is shifted where it is added)
+    auto zlast = [&](int i) __attribute__((always_inline)) -> int {
+        const int to_end = a.M - i < 4 ? (a.M - i) * a.R - 4 : a.R;
+        return to_end < a.R - 1 ? to_end : a.R - 1;
+    };
     auto zpiece = [&](int ib, int pc) __attribute__((always_inline)) -> f32x4 {
         int i = (ib0 + ib) * 32 + ln;
         int v = zv_lane + 32 * (pc >> 2) + 8 * (pc & 3);
         i = i < a.M ? i : a.M - 1;
-        v = v < a.R - 4 ? v : a.R - 4;          // (R % 4 == 0 on this path)
+        if constexpr (RAG) {
+            const int v_max = zlast(i);
+            v = v < v_max ? v : v_max;
+            const float4 x = load4(a.z + ((long)i * a.R + v));
+            return f32x4{x.x, x.y, x.z, x.w};
+        }
+        v = v < a.R - 4 ? v : a.R - 4;
         return *reinterpret_cast<const f32x4 *>(a.z + (size_t)i * a.R + v);
     };
 
@@ -343,9 +358,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
             for (int pc = 0; pc < 8; ++pc) dst[pc] = zpiece(ib, pc);
         };
-        zfetch(2, zc[2]);
-        zfetch(3, zc[3]);
-        zfetch(4, zc[4]);
+#pragma unroll
+        for (int n = 2; n < ZD - 1; ++n) zfetch(n, zc[n]);
 #pragma unroll
         for (int ib = 0; ib < 8; ++ib) {
             if (ib + ZD - 1 < 8) zfetch(ib + ZD - 1, zc[(ib + ZD - 1) % ZD]);
@@ -358,11 +372,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 for (int q = 0; q < 4; ++q) {
                     const int v = (rb0 + wave * 2 + v2) * 32 + 8 * q + 4 * lh;
                     f32x4 &x4 = xs[v2 * 4 + q];
+                    if constexpr (RAG) {
+                        const int sh = (i < a.M && v < a.R) ? v - zlast(i) : 0;
+                        if (sh > 0) {       // (at most the end of the matrix's last rows)
+                            if (sh == 1) x4 = f32x4{x4[1], x4[2], x4[3], 0.f};
+                            else if (sh == 2) x4 = f32x4{x4[2], x4[3], 0.f, 0.f};
+                            else x4 = f32x4{x4[3], 0.f, 0.f, 0.f};
+                        }
+                    }
                     x4[0] += acc[v2][ib][4 * q + 0];
                     x4[1] += acc[v2][ib][4 * q + 1];
                     x4[2] += acc[v2][ib][4 * q + 2];
                     x4[3] += acc[v2][ib][4 * q + 3];
-                    if (i < a.M && v < a.R) *reinterpret_cast<f32x4 *>(a.z + (size_t)i * a.R + v) = x4;
+                    if constexpr (RAG) {
+                        if (v + 4 <= a.R) {
+                            if (i < a.M) store4(a.z + (size_t)i * a.R + v, make_float4(x4[0], x4[1], x4[2], x4[3]));
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                if (i < a.M && v + e < a.R) a.z[(size_t)i * a.R + v + e] = x4[e];
+                                if (v + e >= a.R) x4[e] = -INFINITY;      // no part of the row
+                            }
+                        }
+                    } else if (i < a.M && v < a.R) {
+                        *reinterpret_cast<f32x4 *>(a.z + (size_t)i * a.R + v) = x4;
+                    }
                     if (v < a.R) {
                         if (x4[0] > pt.m) { pt.m = x4[0]; pt.i = v; }
                         if (x4[1] > pt.m) { pt.m = x4[1]; pt.i = v + 1; }
@@ -407,26 +441,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 }
 
-template <int EPI, int REM>
+template <int EPI, int REM, bool RAG>
 hipError_t launch_inst(const TiledGemmArgs &a, hipStream_t st) {
     const int nMgrp = (a.nMt + 3) / 4, nVch = (a.nVt + 7) / 8;
     const int nsb = nMgrp * nVch * a.nKs;
     const int per_xcd = (nsb + 7) / 8;          // super-blocks per XCD
     const int grid = per_xcd * 32 * 8;
-    hipLaunchKernelGGL((tiled_gemm_kernel<EPI, REM>), dim3(grid), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((tiled_gemm_kernel<EPI, REM, RAG>), dim3(grid), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
-template <int EPI>
+template <int EPI, bool RAG>
 hipError_t launch_epi(const TiledGemmArgs &a, hipStream_t st) {
     int nsteps = 0;
     for (int sg = 0; sg < a.nseg; ++sg) nsteps += a.seg[sg].nkq * a.seg[sg].nplanes;
     if (a.nKs < 1 || nsteps % a.nKs != 0 || nsteps / a.nKs < 2 || (EPI != EPI_PARTIAL && a.nKs != 1)) return hipErrorInvalidValue;
     nsteps /= a.nKs;
     const int rem = 2 + (nsteps - 2) % 3;       // (at least two k steps per part)
-    if (rem == 2) return launch_inst<EPI, 2>(a, st);
-    if (rem == 3) return launch_inst<EPI, 3>(a, st);
-    return launch_inst<EPI, 4>(a, st);
+    if (rem == 2) return launch_inst<EPI, 2, RAG>(a, st);
+    if (rem == 3) return launch_inst<EPI, 3, RAG>(a, st);
+    return launch_inst<EPI, 4, RAG>(a, st);
 }
 
 }  // namespace
@@ -446,8 +480,11 @@ int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M) {
 }
 
 hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st) {
-    if (epi == EPI_SILU) return launch_epi<EPI_SILU>(a, st);
-    return epi == EPI_LM ? launch_epi<EPI_LM>(a, st) : launch_epi<EPI_PARTIAL>(a, st);
+    if (epi == EPI_SILU) return launch_epi<EPI_SILU, false>(a, st);
+    if (epi == EPI_PARTIAL) return launch_epi<EPI_PARTIAL, false>(a, st);
+    // (a row that is no whole number of pieces has its own form: the handling of its end costs registers, and with
+    //  them four of the five logit slices in flight)
+    return a.R % 4 ? launch_epi<EPI_LM, true>(a, st) : launch_epi<EPI_LM, false>(a, st);
 }
 
 }  // namespace mrp

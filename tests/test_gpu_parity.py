@@ -1,6 +1,6 @@
 """GPU parity: the HIP path (through the C ABI) against the CPU oracle, element by
 element at sizes the oracle finishes in seconds (several tiles, ragged tails,
-both activation-tile variants, the scalar vocabulary path)."""
+both activation-tile variants, vocabularies that are not a multiple of 4)."""
 import numpy as np
 import pytest
 import torch
@@ -263,4 +263,29 @@ def test_row_counts_where_the_kernels_change(d, B, L, K):
     V = 1028 if d > 256 else 4096 + 36
     cfg = mi.straddling(mi.config(0, d=d, V=V, B=B, L=L, K=K))
     prob, g, o, stats = _free_run(cfg, mrp.RevealCfg(tau=0.9, tau_remask=0.5), seqs=list(range(0, B, max(1, B // 5))))
+    prob.close()
+
+
+@pytest.mark.parametrize("B,L,V", [(1, 3, 1001),      # one row block; the last 32-block of the vocabulary holds 9 entries
+                                   (9, 16, 4099),     # 144 rows: the 256-row form
+                                   (20, 16, 2049),    # 320 rows: two launches, the last block holds one entry
+                                   (33, 16, 1002),    # 528 rows on the tile kernel, rows on 8-byte boundaries
+                                   (130, 5, 1031),    # 650 rows, a row ends 3 entries into a piece
+                                   (600, 1, 6)])      # a row shorter than two pieces
+def test_vocabulary_not_a_multiple_of_four(B, L, V):
+    """Rows of the logit state start on any 4-byte boundary: every LM-head form, and nothing written past the end."""
+    cfg = mi.straddling(mi.config(0, d=128, V=V, B=B, L=L, K=2))
+    prob = Problem(cfg)
+    rcfg = mrp.RevealCfg(tau=0.9, tau_remask=0.5)
+    z0, h = mi.logits0(cfg), mi.hidden(cfg)
+    flat = torch.full((cfg.M * V + 64,), 7.0, device="cuda")
+    z_d = flat[:cfg.M * V].view(cfg.M, V)
+    z_d.copy_(torch.from_numpy(z0))
+    io, hrun_d = gpu_chain(prob, B, cfg.K, z_d, h, rcfg)
+    o = oracle_chain(prob, z0, mi.bf16_bits_to_f64(h), rcfg, cfg.K)
+    # All sequences are compared, so some decisions may fall between two confidences that agree to 1e-3 (relative): two
+    # of L = 5 .. 16 confidences spread over a decade or more do so in about one of 200 states, 3 states each
+    compare_chain(io_to_host(io), z_d.cpu().numpy(), hrun_d.cpu().numpy(), o, list(range(B)), L, cfg.K, rcfg,
+                  max_exempt=(3 * B + 99) // 100)
+    assert bool((flat[cfg.M * V:] == 7.0).all())
     prob.close()
