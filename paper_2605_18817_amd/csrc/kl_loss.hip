@@ -4,14 +4,13 @@
 //     dL_i / ds[i][v] = softmax(s[i])[v] - softmax(l_{t-1}[i])[v],
 // with teacher T = l_{t-1} and student S = l_t + delta_t given as fp32 [M][V].
 //
-// Like the chain's reductions it is a pure HBM stream.  Forward: one pass over both
-// tensors; every (row, 8192-wide vocabulary tile) keeps the online partial
+// Both passes are memory streams.  Every (row, 8192-wide vocabulary tile) keeps the online partial
 //     (m_T, s_T = sum e^{T - m_T}, a_T = sum e^{T - m_T} (T - S),  m_S, s_S = sum e^{S - m_S})
-// and a second tiny kernel merges a row's partials in a fixed order:
+// of the forward pass, and a row's partials merge to
 //     L_i = a_T / s_T - (m_T + log s_T) + (m_S + log s_S).
-// No softmax is written.  Backward: one more pass that reads both tensors and writes the
-// gradient from the two row log-sum-exps.  Algorithmic bytes: 8 M V forward,
-// 8 M V + 4 M V backward.
+// No softmax is written.  The gradient reads both tensors once more and writes the difference of the two
+// softmaxes.  Algorithmic bytes: 8 M V forward, 4 M V for the gradient; its second read of the tensors comes
+// from the last-level cache where the rows are taken in groups (see launch_kl_loss).
 #include "mrp_kernels.h"
 
 namespace mrp {
@@ -45,150 +44,177 @@ __device__ __forceinline__ KlPart kl_shfl_xor(const KlPart &p, int off) {
             __shfl_xor(p.sS, off)};
 }
 
-// partial of one KT-wide tile of one row; partial (t, i) of array a lives at a[i * nT + t]
-template <bool VEC4>
-__global__ __launch_bounds__(256) void kl_partial_kernel(const float *__restrict__ T, const float *__restrict__ S,
-                                                         const uint8_t *__restrict__ mask, int V,
-                                                         float *__restrict__ part, size_t stride) {
-    __shared__ KlPart sw[4];
-    const int t = blockIdx.x, i = blockIdx.y;
-    if (mask && !mask[i]) return;   // (uniform over the workgroup)
-    const float *tr = T + (size_t)i * V, *sr = S + (size_t)i * V;
-    const int v0 = t * KT;
-    float xt[32], xs[32];
-    if constexpr (VEC4) {
+__device__ __forceinline__ KlPart kl_wave_merge(KlPart p) {
 #pragma unroll
-        for (int n = 0; n < 8; ++n) {
-            const int v = v0 + 4 * (threadIdx.x + 256 * n);
-            float4 a = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY), b = a;
-            if (v < V) {
-                a = *reinterpret_cast<const float4 *>(tr + v);
-                b = *reinterpret_cast<const float4 *>(sr + v);
-            }
-            xt[4 * n] = a.x; xt[4 * n + 1] = a.y; xt[4 * n + 2] = a.z; xt[4 * n + 3] = a.w;
-            xs[4 * n] = b.x; xs[4 * n + 1] = b.y; xs[4 * n + 2] = b.z; xs[4 * n + 3] = b.w;
-        }
-    } else {
-#pragma unroll
-        for (int n = 0; n < 32; ++n) {
-            const int v = v0 + threadIdx.x + 256 * n;
-            xt[n] = (v < V) ? tr[v] : -INFINITY;
-            xs[n] = (v < V) ? sr[v] : -INFINITY;
-        }
+    for (int off = 32; off > 0; off >>= 1) p = kl_merge(p, kl_shfl_xor(p, off));
+    return p;
+}
+
+// Partials of row i, all its nT tiles: lane l merges tiles l, l + 64, ...; the result is in every lane.
+// Partial (t, i) of array a lives at a[i * nT + t].
+__device__ __forceinline__ KlPart kl_row(const float *__restrict__ part, size_t stride, int nT, int i) {
+    KlPart p = kl_identity();
+    for (int t = threadIdx.x & 63; t < nT; t += 64) {
+        const size_t o = (size_t)i * nT + t;
+        p = kl_merge(p, KlPart{part[o], part[stride + o], part[2 * stride + o], part[3 * stride + o], part[4 * stride + o]});
     }
+    return kl_wave_merge(p);
+}
+
+struct KlArgs {
+    const float *T, *S;
+    const uint8_t *mask;
+    int V, nT;
+    float scale;
+    float *part;
+    size_t stride;
+    float *loss, *grad;
+    int p0, nP;      // rows p0 .. p0 + nP - 1: partials
+    int g0, nG;      // rows g0 .. g0 + nG - 1: loss and gradient (their partials are complete)
+};
+
+// The 32 entries of a tensor's row that a thread handles in tile t: eight 16-byte pieces, -inf past the row's end
+__device__ __forceinline__ void kl_fetch(const float *row, int v0, int V, float4 (&x)[8]) {
+#pragma unroll
+    for (int n = 0; n < 8; ++n) x[n] = load4_row(row, v0 + 4 * (threadIdx.x + 256 * n), V, -INFINITY);
+}
+__device__ __forceinline__ float kl_at(const float4 (&x)[8], int n) {
+    const float4 &q = x[n >> 2];
+    return (n & 3) == 0 ? q.x : ((n & 3) == 1 ? q.y : ((n & 3) == 2 ? q.z : q.w));
+}
+
+// partial of one KT-wide tile of one row
+__device__ __forceinline__ void kl_partial(const KlArgs &a, int t, int i, KlPart *sw) {
+    if (a.mask && !a.mask[i]) return;   // (uniform over the workgroup)
+    float4 xt[8], xs[8];
+    kl_fetch(a.T + (size_t)i * a.V, t * KT, a.V, xt);
+    kl_fetch(a.S + (size_t)i * a.V, t * KT, a.V, xs);
     KlPart p = kl_identity();
 #pragma unroll
-    for (int n = 0; n < 32; ++n) { p.mT = fmaxf(p.mT, xt[n]); p.mS = fmaxf(p.mS, xs[n]); }
+    for (int n = 0; n < 32; ++n) { p.mT = fmaxf(p.mT, kl_at(xt, n)); p.mS = fmaxf(p.mS, kl_at(xs, n)); }
     if (p.mT > -INFINITY) {
 #pragma unroll
         for (int n = 0; n < 32; ++n) {
-            if (xt[n] > -INFINITY) {   // (padding past V is -inf in both tensors: skip, T - S would be NaN)
-                const float e = __expf(xt[n] - p.mT);
+            const float vt = kl_at(xt, n), vs = kl_at(xs, n);
+            if (vt > -INFINITY) {   // (padding past V is -inf in both tensors: skip, T - S would be NaN)
+                const float e = __expf(vt - p.mT);
                 p.sT += e;
-                p.aT += e * (xt[n] - xs[n]);
-                p.sS += __expf(xs[n] - p.mS);
+                p.aT += e * (vt - vs);
+                p.sS += __expf(vs - p.mS);
             }
         }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) p = kl_merge(p, kl_shfl_xor(p, off));
+    p = kl_wave_merge(p);
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) sw[wave] = p;
     __syncthreads();
     if (threadIdx.x == 0) {
         p = sw[0];
         for (int w = 1; w < 4; ++w) p = kl_merge(p, sw[w]);
-        const size_t o = (size_t)i * gridDim.x + t;
-        part[o] = p.mT; part[stride + o] = p.sT; part[2 * stride + o] = p.aT;
-        part[3 * stride + o] = p.mS; part[4 * stride + o] = p.sS;
+        const size_t o = (size_t)i * a.nT + t;
+        a.part[o] = p.mT; a.part[a.stride + o] = p.sT; a.part[2 * a.stride + o] = p.aT;
+        a.part[3 * a.stride + o] = p.mS; a.part[4 * a.stride + o] = p.sS;
     }
 }
 
-// one thread per row: merge the row's partials in tile order
-__global__ __launch_bounds__(256) void kl_finish_kernel(const float *__restrict__ part, size_t stride, int nT, int M,
-                                                        const uint8_t *__restrict__ mask, float scale,
-                                                        float *__restrict__ loss_rows, float *__restrict__ lse) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= M) return;
-    if (mask && !mask[i]) {
-        loss_rows[i] = 0.f;
-        lse[i] = 0.f; lse[M + i] = 0.f;
-        return;
-    }
-    KlPart p = kl_identity();
-    for (int t = 0; t < nT; ++t) {
-        const size_t o = (size_t)i * nT + t;
-        p = kl_merge(p, KlPart{part[o], part[stride + o], part[2 * stride + o], part[3 * stride + o],
-                               part[4 * stride + o]});
-    }
-    const float lseT = p.mT + logf(p.sT), lseS = p.mS + logf(p.sS);
-    loss_rows[i] = scale * (p.aT / p.sT - lseT + lseS);
-    lse[i] = lseT; lse[M + i] = lseS;
-}
-
-template <bool VEC4>
-__global__ __launch_bounds__(256) void kl_grad_kernel(const float *__restrict__ T, const float *__restrict__ S,
-                                                      const uint8_t *__restrict__ mask, int V, int M,
-                                                      const float *__restrict__ lse, float scale,
-                                                      float *__restrict__ grad) {
-    const int t = blockIdx.x, i = blockIdx.y;
-    const bool on = !mask || mask[i];
-    const float lT = lse[i], lS = lse[M + i];
-    const size_t ro = (size_t)i * V;
+// gradient of one KT-wide tile of one row; tile 0 also writes the row's loss
+__device__ __forceinline__ void kl_gradient(const KlArgs &a, int t, int i) {
+    const bool on = !a.mask || a.mask[i];     // (uniform over the workgroup)
+    float *gr = a.grad + (size_t)i * a.V;
     const int v0 = t * KT;
-    if constexpr (VEC4) {
+    float4 xt[8], xs[8];
+    float lT = 0.f, lS = 0.f;
+    if (on) {
+        kl_fetch(a.T + (size_t)i * a.V, v0, a.V, xt);     // in flight while the row's partials are merged
+        kl_fetch(a.S + (size_t)i * a.V, v0, a.V, xs);
+        const KlPart p = kl_row(a.part, a.stride, a.nT, i);
+        lT = p.mT + logf(p.sT);
+        lS = p.mS + logf(p.sS);
+        if (t == 0 && threadIdx.x == 0) a.loss[i] = a.scale * (p.aT / p.sT - lT + lS);
+    } else if (t == 0 && threadIdx.x == 0) {
+        a.loss[i] = 0.f;
+    }
 #pragma unroll
-        for (int n = 0; n < 8; ++n) {
-            const int v = v0 + 4 * (threadIdx.x + 256 * n);
-            if (v < V) {
-                float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (on) {
-                    const float4 a = *reinterpret_cast<const float4 *>(T + ro + v);
-                    const float4 b = *reinterpret_cast<const float4 *>(S + ro + v);
-                    g.x = scale * (__expf(b.x - lS) - __expf(a.x - lT));
-                    g.y = scale * (__expf(b.y - lS) - __expf(a.y - lT));
-                    g.z = scale * (__expf(b.z - lS) - __expf(a.z - lT));
-                    g.w = scale * (__expf(b.w - lS) - __expf(a.w - lT));
-                }
-                *reinterpret_cast<float4 *>(grad + ro + v) = g;
-            }
+    for (int n = 0; n < 8; ++n) {
+        const int v = v0 + 4 * (threadIdx.x + 256 * n);
+        float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (on) {
+            g.x = a.scale * (__expf(xs[n].x - lS) - __expf(xt[n].x - lT));
+            g.y = a.scale * (__expf(xs[n].y - lS) - __expf(xt[n].y - lT));
+            g.z = a.scale * (__expf(xs[n].z - lS) - __expf(xt[n].z - lT));
+            g.w = a.scale * (__expf(xs[n].w - lS) - __expf(xt[n].w - lT));
         }
-    } else {
-#pragma unroll 4
-        for (int n = 0; n < 32; ++n) {
-            const int v = v0 + threadIdx.x + 256 * n;
-            if (v < V) grad[ro + v] = on ? scale * (__expf(S[ro + v] - lS) - __expf(T[ro + v] - lT)) : 0.f;
+        if (v + 4 <= a.V) {
+            // (not kept in the last-level cache, which the rows still to be read again need)
+            const f32x4_any gv = {g.x, g.y, g.z, g.w};
+            __builtin_nontemporal_store(gv, reinterpret_cast<f32x4_any *>(gr + v));
+        } else if (v < a.V) {
+            gr[v] = g.x;
+            if (v + 1 < a.V) gr[v + 1] = g.y;
+            if (v + 2 < a.V) gr[v + 2] = g.z;
         }
     }
 }
+
+// One launch takes the partials of one group of rows and the gradient of the group before it, alternating while
+// both have rows left, so that the reads of the one run beside the writes of the other.
+__global__ __launch_bounds__(256) void kl_kernel(const KlArgs a) {
+    __shared__ KlPart sw[4];
+    const int t = blockIdx.x, y = blockIdx.y, both = 2 * (a.nP < a.nG ? a.nP : a.nG);
+    const bool part = y < both ? (y & 1) == 0 : a.nP > a.nG;
+    const int r = y < both ? y >> 1 : y - both / 2;
+    if (part) kl_partial(a, t, a.p0 + r, sw);
+    else kl_gradient(a, t, a.g0 + r);
+}
+
+// loss alone: one wavefront per row
+__global__ __launch_bounds__(256) void kl_finish_kernel(const KlArgs a, int M) {
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= M) return;
+    float loss = 0.f;
+    if (!a.mask || a.mask[i]) {
+        const KlPart p = kl_row(a.part, a.stride, a.nT, i);
+        loss = a.scale * (p.aT / p.sT - (p.mT + logf(p.sT)) + (p.mS + logf(p.sS)));
+    }
+    if ((threadIdx.x & 63) == 0) a.loss[i] = loss;
+}
+
+// Rows taken together when there is a gradient: a group's teacher and student rows are read for the partials and
+// once more, one launch later, for the gradient.  What is live in between, two tensors of two groups, has to fit the
+// 256 MB last-level cache; smaller groups only add launches.  Measured at 1024 rows, V = 151936: 503 us with groups of
+// 52 MB per tensor, 523 of 40, 542 of 30, 612 of 20, 601 of 80, 558 in one group (579 with a launch per pass and the
+// scalar merge between them); at 64 rows one group, 34 us.
+constexpr size_t GROUP_BYTES = (size_t)52 << 20;
 
 }  // namespace
 
 int kl_tiles(int V) { return (V + KT - 1) / KT; }
 
 hipError_t launch_kl_loss(int M, int V, const float *teacher, const float *student, const uint8_t *mask, float scale,
-                          float *part, size_t part_stride, float *lse, float *loss_rows, float *grad,
-                          hipStream_t st) {
-    const int nT = kl_tiles(V);
-    if (V % 4 == 0)
-        hipLaunchKernelGGL(kl_partial_kernel<true>, dim3(nT, M), dim3(256), 0, st, teacher, student, mask, V, part,
-                           part_stride);
-    else
-        hipLaunchKernelGGL(kl_partial_kernel<false>, dim3(nT, M), dim3(256), 0, st, teacher, student, mask, V, part,
-                           part_stride);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kl_finish_kernel, dim3((M + 255) / 256), dim3(256), 0, st, part, part_stride, nT, M, mask,
-                       scale, loss_rows, lse);
-    e = hipGetLastError();
-    if (e != hipSuccess || !grad) return e;
-    if (V % 4 == 0)
-        hipLaunchKernelGGL(kl_grad_kernel<true>, dim3(nT, M), dim3(256), 0, st, teacher, student, mask, V, M, lse,
-                           scale, grad);
-    else
-        hipLaunchKernelGGL(kl_grad_kernel<false>, dim3(nT, M), dim3(256), 0, st, teacher, student, mask, V, M, lse,
-                           scale, grad);
-    return hipGetLastError();
+                          float *part, size_t part_stride, float *loss_rows, float *grad, hipStream_t st) {
+    KlArgs a = {teacher, student, mask, V, kl_tiles(V), scale, part, part_stride, loss_rows, grad, 0, M, 0, 0};
+    if (!grad) {
+        hipLaunchKernelGGL(kl_kernel, dim3(a.nT, M), dim3(256), 0, st, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kl_finish_kernel, dim3((M + 3) / 4), dim3(256), 0, st, a, M);
+        return hipGetLastError();
+    }
+    const size_t bytes = (size_t)M * V * sizeof(float);
+    int groups = (int)((bytes + GROUP_BYTES / 2) / GROUP_BYTES);
+    groups = groups < 1 ? 1 : (groups > M ? M : groups);
+    int rows = (M + groups - 1) / groups;
+    if (groups > 1 && rows > 32767) rows = 32767;    // (grid limit: two groups in one launch)
+    for (int r0 = 0; r0 < M + rows; r0 += rows) {
+        a.g0 = a.p0; a.nG = r0 ? a.nP : 0;
+        a.p0 = r0;
+        a.nP = r0 >= M ? 0 : (M - r0 < rows ? M - r0 : rows);
+        if (a.nP + a.nG == 0) break;
+        hipLaunchKernelGGL(kl_kernel, dim3(a.nT, a.nP + a.nG), dim3(256), 0, st, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace mrp

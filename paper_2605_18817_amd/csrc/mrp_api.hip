@@ -28,7 +28,7 @@ struct mrp_ctx {
     int *pi;
     float *vwm;
     int *vwi;
-    float *kl_part, *kl_lse;   // KL loss: 5 partial arrays [max_rows * tiles], row log-sum-exps [2][max_rows]
+    float *kl_part;            // KL loss: 5 partial arrays [max_rows * tiles]
     size_t kl_stride;
     double *rms_part;          // residual magnitudes: per-workgroup sums of squares
     int *err_flag;             // device error word (MRP_FLAG_* bits), read and cleared by mrp_poll_error
@@ -61,7 +61,7 @@ struct Layout {
     int nT_max;
     size_t part_rows;
     int maxB;
-    size_t off_XH, off_XE, off_S, off_Y, off_PART, off_pm, off_ps, off_pi, off_vwm, off_vwi, off_klp, off_kll, off_rms, off_err, total;
+    size_t off_XH, off_XE, off_S, off_Y, off_PART, off_pm, off_ps, off_pi, off_vwm, off_vwi, off_klp, off_rms, off_err, total;
     size_t kl_stride;
 };
 
@@ -99,7 +99,6 @@ Layout make_layout(const mrp_dims *dm, int nCU) {
     l.off_vwi = take(vw * 4);
     l.kl_stride = (size_t)dm->max_rows * kl_tiles(dm->V);
     l.off_klp = take(5 * l.kl_stride * 4);
-    l.off_kll = take((size_t)2 * dm->max_rows * 4);
     l.off_rms = take(residual_rms_part_bytes());
     l.off_err = take(256);
     l.total = o;
@@ -263,7 +262,6 @@ int mrp_create(mrp_ctx **out, const mrp_dims *dims) {
     c->vwm = reinterpret_cast<float *>(c->ws + l.off_vwm);
     c->vwi = reinterpret_cast<int *>(c->ws + l.off_vwi);
     c->kl_part = reinterpret_cast<float *>(c->ws + l.off_klp);
-    c->kl_lse = reinterpret_cast<float *>(c->ws + l.off_kll);
     c->kl_stride = l.kl_stride;
     c->rms_part = reinterpret_cast<double *>(c->ws + l.off_rms);
     c->err_flag = reinterpret_cast<int *>(c->ws + l.off_err);
@@ -312,7 +310,7 @@ int mrp_kl_loss(mrp_ctx *c, void *stream, int M, const float *teacher, const flo
     if (c->dims.V % 4 == 0 && (!aligned16(teacher) || !aligned16(student) || (grad && !aligned16(grad))))
         return fail(c, MRP_ERR_ALIGN, "mrp_kl_loss: tensors must be 16-byte aligned");
     if (M == 0) return MRP_OK;
-    HIP_TRY(c, launch_kl_loss(M, c->dims.V, teacher, student, row_mask, scale, c->kl_part, c->kl_stride, c->kl_lse,
+    HIP_TRY(c, launch_kl_loss(M, c->dims.V, teacher, student, row_mask, scale, c->kl_part, c->kl_stride,
                               loss_rows, grad, static_cast<hipStream_t>(stream)));
     return MRP_OK;
 }

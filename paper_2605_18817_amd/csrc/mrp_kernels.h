@@ -381,7 +381,6 @@ hipError_t launch_residual_rms(int n_blocks, int S, long N, const void *X, bool 
 
 int kl_tiles(int V);
 hipError_t launch_kl_loss(int M, int V, const float *teacher, const float *student, const uint8_t *mask, float scale,
-                          float *part, size_t part_stride, float *lse, float *loss_rows, float *grad,
-                          hipStream_t st);
+                          float *part, size_t part_stride, float *loss_rows, float *grad, hipStream_t st);
 
 }  // namespace mrp

@@ -134,3 +134,26 @@ def test_kl_loss_full_size_sampled_rows():
         assert torch.all(grad[torch.from_numpy(~on).cuda()] == 0)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("V,M", [(151936, 391), (50257, 403), (50257, 259)])   # several groups of rows, uneven; one group
+def test_kl_loss_over_groups_of_rows(V, M):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V + M)
+    t = torch.empty(M, V, device="cuda").normal_(0, 2, generator=g)
+    s = t + torch.empty(M, V, device="cuda").normal_(0, 0.5, generator=g)
+    mask = (torch.arange(M, device="cuda") % 5 != 2).to(torch.uint8)
+    loss, loss1 = torch.full((M,), 9.0, device="cuda"), torch.full((M,), 9.0, device="cuda")
+    grad = torch.full((M + 1, V), 9.0, device="cuda")
+    ctx = mrp.MrpContext(128, V, M, 1)
+    ctx.kl_loss(M, t, s, mask, 0.5, loss, grad[:M])
+    ctx.kl_loss(M, t, s, mask, 0.5, loss1)
+    on = mask.double().unsqueeze(1)
+    p, q = torch.log_softmax(t.double(), 1), torch.log_softmax(s.double(), 1)
+    want = 0.5 * ((p.exp() * (p - q)).sum(1) * on[:, 0])
+    for got in (loss, loss1):
+        assert bool(((got - want).abs() <= 0.5 * 1e-4 + 1e-4 * want).all())
+    bound = 0.5 * (2e-5 * (p.exp() + q.exp()) + 1e-12) * on       # as above; rows that are off: exactly zero
+    assert bool(((grad[:M] - 0.5 * (q.exp() - p.exp()) * on).abs() <= bound).all())
+    assert bool((grad[M] == 9.0).all())
+    ctx.close()
