@@ -185,19 +185,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     constexpr int ZD = RAG ? 2 : 6;             // slice buffers: five (one) slices in flight ahead of the one added
     f32x4 zc[ZD][8];
     const int zv_lane = (rb0 + wave * 2) * 32 + 4 * lh;     // + 32 v2 + 8 q
-    // last start of a piece of row i inside the matrix (RAG: a piece that crosses the end of its row takes in the
-    // start of the next one, never used; where that would pass the end of the matrix the piece starts early instead
-    // and is shifted where it is added)
-    auto zlast = [&](int i) __attribute__((always_inline)) -> int {
-        const int to_end = a.M - i < 4 ? (a.M - i) * a.R - 4 : a.R;
-        return to_end < a.R - 1 ? to_end : a.R - 1;
-    };
     auto zpiece = [&](int ib, int pc) __attribute__((always_inline)) -> f32x4 {
         int i = (ib0 + ib) * 32 + ln;
         int v = zv_lane + 32 * (pc >> 2) + 8 * (pc & 3);
         i = i < a.M ? i : a.M - 1;
         if constexpr (RAG) {
-            const int v_max = zlast(i);
+            // (a piece that crosses the end of its row takes in the start of the next one, or starts early where that
+            //  would pass the end of the matrix: the epilogue does not use it)
+            const int to_end = a.M - i < 4 ? (a.M - i) * a.R - 4 : a.R, v_max = to_end < a.R - 1 ? to_end : a.R - 1;
             v = v < v_max ? v : v_max;
             const float4 x = load4(a.z + ((long)i * a.R + v));
             return f32x4{x.x, x.y, x.z, x.w};
@@ -373,11 +368,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                     const int v = (rb0 + wave * 2 + v2) * 32 + 8 * q + 4 * lh;
                     f32x4 &x4 = xs[v2 * 4 + q];
                     if constexpr (RAG) {
-                        const int sh = (i < a.M && v < a.R) ? v - zlast(i) : 0;
-                        if (sh > 0) {       // (at most the end of the matrix's last rows)
-                            if (sh == 1) x4 = f32x4{x4[1], x4[2], x4[3], 0.f};
-                            else if (sh == 2) x4 = f32x4{x4[2], x4[3], 0.f, 0.f};
-                            else x4 = f32x4{x4[3], 0.f, 0.f, 0.f};
+                        if (v + 4 > a.R) {      // the piece with the end of the row (or past it): entry by entry
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                x4[e] = 0.f;
+                                if (i < a.M && v + e < a.R) x4[e] = a.z[(size_t)i * a.R + v + e];
+                            }
                         }
                     }
                     x4[0] += acc[v2][ib][4 * q + 0];
