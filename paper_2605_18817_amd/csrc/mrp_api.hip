@@ -161,7 +161,7 @@ int gemm_partial(mrp_ctx *c, hipStream_t st, const void *Wp, int R, int Kc, cons
         tg.KBw = Kc / 16; tg.n_rb = R / 32; tg.nIb = c->nIb; tg.M = M; tg.R = R;
         tg.seg[0] = TiledSeg{act, plane_stride, Kc / 64, nplanes};
         tg.nseg = 1;
-        tg.nMt = (M + 255) / 256; tg.nVt = R / 256;
+        tg.nMt = tiled_row_tiles(M); tg.nVt = R / 256;
         tg.nKs = tiled_ksplit(tg.nMt * tg.nVt, (Kc / 64) * nplanes, c->nCU, out_floats / (size_t)R, M);
         tg.out = out;
         *err = launch_tiled_gemm(tg, EPI_PARTIAL, st);
@@ -525,7 +525,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             tg.seg[0] = TiledSeg{c->XH, c->plane, d / 64, np_h};
             tg.seg[1] = TiledSeg{c->XE, 0, d / 64, 1};
             tg.nseg = 2;
-            tg.nMt = (M + 255) / 256; tg.nVt = (d + 255) / 256;
+            tg.nMt = tiled_row_tiles(M); tg.nVt = (d + 255) / 256;
             tg.nKs = tiled_ksplit(tg.nMt * tg.nVt, (d / 64) * (np_h + 1), c->nCU, c->part_rows, M);
             nks1 = tg.nKs;
             tg.out = c->PART;
@@ -593,7 +593,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             tg.KBw = d / 16; tg.n_rb = d / 32; tg.nIb = c->nIb; tg.M = M; tg.R = d;
             tg.seg[0] = TiledSeg{c->S, c->plane, d / 64, NSPLIT};
             tg.nseg = 1;
-            tg.nMt = (M + 255) / 256; tg.nVt = (d + 255) / 256;
+            tg.nMt = tiled_row_tiles(M); tg.nVt = (d + 255) / 256;
             tg.nKs = tiled_ksplit(tg.nMt * tg.nVt, (d / 64) * NSPLIT, c->nCU, c->part_rows, M);
             nks2 = tg.nKs;
             tg.out = c->PART;
@@ -651,7 +651,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             tg.KBw = d / 16; tg.n_rb = (V + 31) / 32; tg.nIb = c->nIb; tg.M = M; tg.R = V;
             tg.seg[0] = TiledSeg{c->Y, 0, d / 64, 1};
             tg.nseg = 1;
-            tg.nMt = (M + 255) / 256; tg.nVt = (V + 255) / 256;
+            tg.nMt = tiled_row_tiles(M); tg.nVt = (V + 255) / 256;
             tg.nKs = 1;
             tg.z = z; tg.pm = c->pm; tg.ps = c->ps; tg.pi = c->pi;
             HIP_TRY(c, launch_tiled_gemm(tg, EPI_LM, st));

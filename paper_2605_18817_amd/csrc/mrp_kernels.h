@@ -76,7 +76,7 @@ struct TiledGemmArgs {
     int KBw, n_rb, nIb, M, R;
     TiledSeg seg[2];
     int nseg;
-    int nMt, nVt;        // tiles along activation rows / weight rows
+    int nMt, nVt;        // tiles along activation rows (tiled_row_tiles(M)) / weight rows
     int nKs;             // k parts (EPI_PARTIAL only: part ks writes out[ks][M][R]; 1 for EPI_LM)
     float *out;          // EPI_PARTIAL: [nKs][M][R]
     uint4 *planes;       // EPI_SILU: the NSPLIT fp16 planes [R / 16][nIb][64] of SiLU(X W^T), plane_stride apart
@@ -260,6 +260,8 @@ hipError_t stream_gemm_configure();   // once per device
 int stream_gemm_it(int M);   // activation row blocks per workgroup for M rows
 
 hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st);
+int tiled_row_blocks(int M);   // 32-row blocks of activation rows per tile for M rows
+inline int tiled_row_tiles(int M) { return (M + 32 * tiled_row_blocks(M) - 1) / (32 * tiled_row_blocks(M)); }
 // k parts for a partial-sum tile GEMM with `tiles` output tiles and `nsteps` k steps, writing at most `cap_rows` rows
 int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M);
 hipError_t launch_lm_persist(const LmPersistArgs &a, hipStream_t st);

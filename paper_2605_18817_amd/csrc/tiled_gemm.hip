@@ -1,8 +1,9 @@
 // Tiled MFMA GEMM (bf16 operands for the LM head, fp16 for the head body) for many activation rows (the MFMA-bound regime of the MRP
 // chain):  out[i][r] (+)= sum_k W[r][k] * X[i][k]  with 256 x 256 output tiles.
 //
-// A workgroup of four wavefronts computes a tile of 256 weight rows x 256 activation rows;
-// each wave owns 64 weight rows x all 256 activation rows as 2 x 8 MFMA 32x32x16 tiles (256
+// A workgroup of four wavefronts computes a tile of 256 weight rows x 256 activation rows (192 or 224
+// where M rows fall into as many tiles of that height);
+// each wave owns 64 weight rows x all activation rows as 2 x 8 (6, 7) MFMA 32x32x16 tiles (256
 // fp32 accumulators).  The weight fragments go from the packed layout straight into MFMA
 // operand registers (one contiguous 1 KiB read per 32 rows x 16 k); no two waves load the
 // same fragment.  The activation operand arrives in LDS by LDS-direct loads (three 32 KiB
@@ -44,9 +45,8 @@ __device__ __forceinline__ f32x16 mma_frag(const u32x4 &w, const u32x4 &x, const
 }
 
 constexpr int TG_KB = 4;                    // 16-wide k blocks per step (64 k)
-constexpr int TG_B = TG_KB * 8 * 64;        // u32x4 of an activation stage (256 rows x 64 k)
+constexpr int TG_B = TG_KB * 8 * 64;        // u32x4 of an activation stage (up to 256 rows x 64 k)
 constexpr int TG_STAGE = TG_B;              // 32 KiB
-constexpr int TG_NLD = TG_B / 256;          // 1 KiB chunks per wave per step (8)
 constexpr int TG_DEPTH = 3;                 // operand sets: steps s, s + 1, s + 2
 
 // One array per activation stage: the stage arrives by LDS-direct loads, and with separate
@@ -65,7 +65,8 @@ __device__ __forceinline__ void tg_barrier() { asm volatile("s_waitcnt lgkmcnt(0
 // REM = 2 + (k steps - 2) % 3: the k steps left for the straight-line tail after the unrolled loop
 // RAG: R is not a multiple of 4 (EPI_LM), so a row of the logit state starts on any 4-byte boundary and ends inside a
 // 16-byte piece
-template <int EPI, int REM, bool RAG>
+// NB: 32-row blocks of activation rows per tile (5 to 8)
+template <int EPI, int REM, bool RAG, int NB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void tiled_gemm_kernel(
     const TiledGemmArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -73,19 +74,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int ln = lane & 31, lh = lane >> 5;
 
     // ---- workgroup -> tile (XCD-aware) ----
-    // (with a k split every (tile block, k part) pair is a block of its own, so that few tiles still spread
-    //  over all XCDs)
-    const int x = blockIdx.x & 7, s = blockIdx.x >> 3;
-    const int sbk = (s >> 5) * 8 + x, t = s & 31;
-    const int nMgrp = (a.nMt + 3) >> 2;
-    const int nsb = nMgrp * ((a.nVt + 7) >> 3);
-    const int sb = sbk % nsb, ks = sbk / nsb;
-    if (ks >= a.nKs) return;
-    const int mgrp = sb % nMgrp, vchunk = sb / nMgrp;
-    const int mt = mgrp * 4 + (t & 3), vt = vchunk * 8 + (t >> 2);
-    if (mt >= a.nMt || vt >= a.nVt) return;
+    // The tiles in an order where 32 consecutive ones are a block of up to 4 (activation) x 8 (weight) tiles go to
+    // the XCDs 32 at a time in turn; what is left after the last whole turn of all eight is dealt out evenly.  (The
+    // k parts of a split follow each other, so that few tiles still spread over all XCDs.)
+    const int x = blockIdx.x & 7, s = blockIdx.x >> 3, T = a.nMt * a.nVt, total = T * a.nKs;
+    const int turns = total >> 8, left = total & 255, per = (left + 7) >> 3, s_left = s - 32 * turns;
+    if (s_left >= 0 && (s_left >= per || x * per + s_left >= left)) return;
+    const int id = s_left < 0 ? ((s >> 5) * 8 + x) * 32 + (s & 31) : 256 * turns + x * per + s_left;
+    const int ks = id / T, tl = id - ks * T;
+    const int vchunk = tl / (8 * a.nMt), in_chunk = tl - vchunk * 8 * a.nMt;
+    const int v_cnt = a.nVt - 8 * vchunk < 8 ? a.nVt - 8 * vchunk : 8;
+    const int mgrp = in_chunk / (4 * v_cnt), in_grp = in_chunk - mgrp * 4 * v_cnt;
+    const int m_cnt = a.nMt - 4 * mgrp < 4 ? a.nMt - 4 * mgrp : 4;
+    const int vt = vchunk * 8 + in_grp / m_cnt, mt = mgrp * 4 + in_grp % m_cnt;
 
-    const int rb0 = vt * 8, ib0 = mt * 8;
+    const int rb0 = vt * 8, ib0 = mt * NB;
     const u32x4 *Wp = reinterpret_cast<const u32x4 *>(a.Wp);
 
     // this wave's two weight row blocks (rows past the padded matrix re-read the last block)
@@ -136,8 +139,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         }
     };
 
-    // Operands are requested two steps ahead.  Per step and wave: 8 LDS-direct loads (this wave's
-    // quarter of the 32 KiB activation stage) and 8 weight-fragment loads into the register set
+    // Operands are requested two steps ahead.  Per step and wave: NB LDS-direct loads (this wave's
+    // quarter of the activation stage, [k block][row block]) and 8 weight-fragment loads into the register set
     // of that step; requests complete in issue order.
     u32x4 areg[TG_DEPTH][2][TG_KB];   // [step % 3][row block][k block]
 #define TG_LOAD(st, set, stage)                                                            \
@@ -146,10 +149,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         const u32x4 *bp_;                                                                  \
         cursor_get(kbw_, bp_);                                                             \
         cursor_next();                                                                     \
-        _Pragma("unroll") for (int n = 0; n < TG_NLD; ++n) {                               \
-            const int c = wave + 4 * n;            /* chunk: k block c / 8, row block c % 8 */ \
+        _Pragma("unroll") for (int n = 0; n < NB; ++n) {                                   \
+            const int c = wave + 4 * n;            /* chunk: k block c / NB, row block c % NB */ \
             __builtin_amdgcn_global_load_lds(                                              \
-                (gas_ptr)(bp_ + ((size_t)(c >> 3) * a.nIb + (c & 7)) * 64 + lane),         \
+                (gas_ptr)(bp_ + ((size_t)(c / NB) * a.nIb + (c % NB)) * 64 + lane),        \
                 (las_ptr)((stage) + c * 64), 16, 0, 0);                                    \
         }                                                                                  \
         __builtin_amdgcn_sched_barrier(0);                                                 \
@@ -157,17 +160,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             _Pragma("unroll") for (int kb = 0; kb < TG_KB; ++kb)                           \
                 areg[set][v2][kb] = asrc[v2][(size_t)(kbw_ + kb) * 64];                    \
     }
-    // the group requested one step ago is complete when at most the youngest group (16) is pending
-#define TG_WAIT_PREV() __builtin_amdgcn_s_waitcnt(0x4F70)   /* vmcnt(16) */
+    // the group requested one step ago is complete when at most the youngest group (NB + 8) is pending
+    constexpr int NREQ = NB + 8;
+#define TG_WAIT_PREV() __builtin_amdgcn_s_waitcnt(0x0F70 | (NREQ & 15) | (NREQ >> 4 << 14))   /* vmcnt(NREQ) */
 
     TG_LOAD(0, 0, tg_stage0)
     TG_LOAD(1, 1, tg_stage1)
 
-    f32x16 acc[2][8];
+    f32x16 acc[2][NB];
 #pragma unroll
     for (int v2 = 0; v2 < 2; ++v2)
 #pragma unroll
-        for (int ib = 0; ib < 8; ++ib)
+        for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[v2][ib][r] = 0.f;
     TG_WAIT_PREV();
@@ -175,7 +179,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
     // activation fragments are double-buffered: the LDS reads of the next k block are issued
     // among the MFMAs of the current one (one wave per SIMD: nothing else hides them)
-    u32x4 bf[2][8];
+    u32x4 bf[2][NB];
 
     // Logit tile of the epilogue (EPI_LM): 8 slices of 32 activation rows x this wave's 64 vocabulary
     // entries, 8 16-byte pieces per lane each.  A piece is always fetched (addresses clamped into
@@ -202,8 +206,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     };
 
     // One k step.  A wave issues in order, and a memory request that finds the request queue full
-    // holds up the MFMAs behind it, so the step's 16 requests are spread between its 64 MFMAs
-    // (one ahead of every group of four but the first) instead of being issued in a burst.
+    // holds up the MFMAs behind it, so the step's NB + 8 requests are spread between its 8 NB MFMAs
+    // (one ahead of every sixteenth of them but the first) instead of being issued in a burst.
     int kbw_n;
     const u32x4 *bp_n;
     auto step = [&](auto par_c, auto role_c, const u32x4 *cur, u32x4 *after) __attribute__((always_inline)) {
@@ -217,7 +221,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         constexpr bool live = true;
         {
 #pragma unroll
-            for (int ib = 0; ib < 8; ++ib) bf[0][ib] = cur[ib * 64 + lane];
+            for (int ib = 0; ib < NB; ++ib) bf[0][ib] = cur[ib * 64 + lane];
         }
 #pragma unroll
         for (int kb = 0; kb < TG_KB; ++kb) {
@@ -230,10 +234,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                         if (rq & 1) {
                             const int wl = rq >> 1;        // weight fragment 0..6 (7 below)
                             areg[NS][wl >> 2][wl & 3] = asrc[wl >> 2][(size_t)(kbw_n + (wl & 3)) * 64];
-                        } else {
-                            const int ch = wave + 4 * (rq >> 1);   // chunk: k block ch / 8, row block ch % 8
+                        } else if (rq >> 1 < NB) {
+                            const int ch = wave + 4 * (rq >> 1);   // chunk: k block ch / NB, row block ch % NB
                             __builtin_amdgcn_global_load_lds(
-                                (gas_ptr)(bp_n + ((size_t)(ch >> 3) * a.nIb + (ch & 7)) * 64 + lane),
+                                (gas_ptr)(bp_n + ((size_t)(ch / NB) * a.nIb + (ch % NB)) * 64 + lane),
                                 (las_ptr)(after + ch * 64), 16, 0, 0);
                         }
                         if (c == 15) areg[NS][1][3] = asrc[1][(size_t)(kbw_n + 3) * 64];
@@ -245,15 +249,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                     }
                 }
                 if (live) {
-                    if (kb + 1 < TG_KB) {
-                        bf[(kb + 1) & 1][2 * g4] = cur[((kb + 1) * 8 + 2 * g4) * 64 + lane];
-                        bf[(kb + 1) & 1][2 * g4 + 1] = cur[((kb + 1) * 8 + 2 * g4 + 1) * 64 + lane];
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    const int v2 = g4 >> 1, i0 = (g4 & 1) * 4;
 #pragma unroll
-                    for (int it = 0; it < 4; ++it)
-                        acc[v2][i0 + it] = mma_frag<EPI>(areg[PAR][v2][kb], bf[kb & 1][i0 + it], acc[v2][i0 + it]);
+                    for (int ib = 2 * g4; ib < 2 * g4 + 2; ++ib)
+                        if (kb + 1 < TG_KB && ib < NB) bf[(kb + 1) & 1][ib] = cur[((kb + 1) * NB + ib) * 64 + lane];
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int m = g4 * 2 * NB / 4; m < (g4 + 1) * 2 * NB / 4; ++m)      // this group's share of the 2 x NB
+                        acc[m / NB][m % NB] = mma_frag<EPI>(areg[PAR][m / NB][kb], bf[kb & 1][m % NB], acc[m / NB][m % NB]);
                 }
                 if (c == 0 && role == 0) {   // behind the first MFMAs: where the operands of the step after next are
                     cursor_get(kbw_n, bp_n);
@@ -305,7 +307,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int v2 = 0; v2 < 2; ++v2)
 #pragma unroll
-            for (int ib = 0; ib < 8; ++ib) {
+            for (int ib = 0; ib < NB; ++ib) {
                 const int i = (ib0 + ib) * 32 + lne;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -323,7 +325,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int v2 = 0; v2 < 2; ++v2)
 #pragma unroll
-            for (int ib = 0; ib < 8; ++ib) {
+            for (int ib = 0; ib < NB; ++ib) {
                 const int i = (ib0 + ib) * 32 + lne;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
@@ -356,8 +358,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int n = 2; n < ZD - 1; ++n) zfetch(n, zc[n]);
 #pragma unroll
-        for (int ib = 0; ib < 8; ++ib) {
-            if (ib + ZD - 1 < 8) zfetch(ib + ZD - 1, zc[(ib + ZD - 1) % ZD]);
+        for (int ib = 0; ib < NB; ++ib) {
+            if (ib + ZD - 1 < NB) zfetch(ib + ZD - 1, zc[(ib + ZD - 1) % ZD]);
             const int i = (ib0 + ib) * 32 + lne;
             f32x4(&xs)[8] = zc[ib % ZD];
             Part pt = part_identity();
@@ -423,7 +425,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             }
         }
         __syncthreads();
-        {
+        if (tid < 32 * NB) {
             Part pt = {red_m[tid], red_s[tid], red_i[tid]};
 #pragma unroll
             for (int w = 1; w < 4; ++w) pt = part_merge(pt, Part{red_m[w * 256 + tid], red_s[w * 256 + tid], red_i[w * 256 + tid]});
@@ -437,29 +439,47 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 }
 
-template <int EPI, int REM, bool RAG>
+template <int EPI, int REM, bool RAG, int NB>
 hipError_t launch_inst(const TiledGemmArgs &a, hipStream_t st) {
-    const int nMgrp = (a.nMt + 3) / 4, nVch = (a.nVt + 7) / 8;
-    const int nsb = nMgrp * nVch * a.nKs;
-    const int per_xcd = (nsb + 7) / 8;          // super-blocks per XCD
-    const int grid = per_xcd * 32 * 8;
-    hipLaunchKernelGGL((tiled_gemm_kernel<EPI, REM, RAG>), dim3(grid), dim3(256), 0, st, a);
+    const int total = a.nMt * a.nVt * a.nKs;
+    const int grid = 8 * (total / 256 * 32 + (total % 256 + 7) / 8);
+    hipLaunchKernelGGL((tiled_gemm_kernel<EPI, REM, RAG, NB>), dim3(grid), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
-template <int EPI, bool RAG>
+template <int EPI, bool RAG, int NB>
 hipError_t launch_epi(const TiledGemmArgs &a, hipStream_t st) {
     int nsteps = 0;
     for (int sg = 0; sg < a.nseg; ++sg) nsteps += a.seg[sg].nkq * a.seg[sg].nplanes;
     if (a.nKs < 1 || nsteps % a.nKs != 0 || nsteps / a.nKs < 2 || (EPI != EPI_PARTIAL && a.nKs != 1)) return hipErrorInvalidValue;
     nsteps /= a.nKs;
     const int rem = 2 + (nsteps - 2) % 3;       // (at least two k steps per part)
-    if (rem == 2) return launch_inst<EPI, 2, RAG>(a, st);
-    if (rem == 3) return launch_inst<EPI, 3, RAG>(a, st);
-    return launch_inst<EPI, 4, RAG>(a, st);
+    if (rem == 2) return launch_inst<EPI, 2, RAG, NB>(a, st);
+    if (rem == 3) return launch_inst<EPI, 3, RAG, NB>(a, st);
+    return launch_inst<EPI, 4, RAG, NB>(a, st);
+}
+
+template <int NB>
+hipError_t launch_nb(const TiledGemmArgs &a, int epi, hipStream_t st) {
+    if (epi == EPI_SILU) {      // (needs an unsplit k: many tiles, so 768 rows and more)
+        if constexpr (NB >= 7) return launch_epi<EPI_SILU, false, NB>(a, st);
+        else return hipErrorInvalidValue;
+    }
+    if (epi == EPI_PARTIAL) return launch_epi<EPI_PARTIAL, false, NB>(a, st);
+    // (a row that is no whole number of pieces has its own form: the handling of its end costs registers, and with
+    //  them four of the five logit slices in flight)
+    return a.R % 4 ? launch_epi<EPI_LM, true, NB>(a, st) : launch_epi<EPI_LM, false, NB>(a, st);
 }
 
 }  // namespace
+
+// Activation rows per tile: M rows in the fewest tiles of at most 256, each of as few 32-row blocks as that needs.
+// A block that no row falls into costs what a full one does (time per tile goes with the blocks: 592 rows in three
+// tiles are 21 blocks instead of 24).
+int tiled_row_blocks(int M) {
+    const int ib = (M + 31) / 32, nMt = (ib + 7) / 8, nb = (ib + nMt - 1) / nMt;
+    return nb < 5 ? 5 : nb;
+}
 
 // Few output tiles (the head body's GEMMs at 1024 or 2048 rows have 64 or 128) leave most CUs idle: split k
 // into up to 16 parts so that tiles x parts comes near the CU count; every part must have an equal number of at
@@ -476,11 +496,12 @@ int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M) {
 }
 
 hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st) {
-    if (epi == EPI_SILU) return launch_epi<EPI_SILU, false>(a, st);
-    if (epi == EPI_PARTIAL) return launch_epi<EPI_PARTIAL, false>(a, st);
-    // (a row that is no whole number of pieces has its own form: the handling of its end costs registers, and with
-    //  them four of the five logit slices in flight)
-    return a.R % 4 ? launch_epi<EPI_LM, true>(a, st) : launch_epi<EPI_LM, false>(a, st);
+    const int nb = tiled_row_blocks(a.M);
+    if (a.nMt != (a.M + 32 * nb - 1) / (32 * nb) || a.nMt * nb > a.nIb) return hipErrorInvalidValue;
+    if (nb == 5) return launch_nb<5>(a, epi, st);
+    if (nb == 6) return launch_nb<6>(a, epi, st);
+    if (nb == 7) return launch_nb<7>(a, epi, st);
+    return launch_nb<8>(a, epi, st);
 }
 
 }  // namespace mrp
