@@ -88,7 +88,12 @@ __device__ __forceinline__ bool more_confident(const float *conf, int a, int b) 
     return a < b;
 }
 
-__global__ __launch_bounds__(256) void merge_select_kernel(const SelectArgs a) {
+// One workgroup per sequence.  What bounds it is latency (partials, decision and gather follow each other), so the
+// workgroup is wide enough that the merge is one round of loads: 1024 threads, or 256 where four wavefronts already
+// hold a row each.
+template <int NT>
+__global__ __launch_bounds__(NT) void merge_select_kernel(const SelectArgs a) {
+    constexpr int NW = NT / 64;
     __shared__ float s_conf[MAX_L], s_lse[MAX_L];
     __shared__ int s_tok[MAX_L], s_xtok[MAX_L];
     __shared__ uint8_t s_mk[MAX_L];
@@ -113,12 +118,11 @@ __global__ __launch_bounds__(256) void merge_select_kernel(const SelectArgs a) {
         // Layout [tile][row] (the GEMM kernels that own whole row tiles write it): the sequence's L
         // rows of one tile are contiguous.  Thread (row p, group grp) merges tiles grp, grp + NG, ...
         // in order, so a load instruction fetches whole 4 L-byte runs; the groups' results are then
-        // merged per row in group order.
-        __shared__ float g_m[256], g_s[256];
-        __shared__ int g_i[256];
+        // merged per row, first inside each wavefront, then over the wavefronts in order.
+        __shared__ Part g_part[NW][MAX_L];
         int Lp = 1;
         while (Lp < L) Lp <<= 1;
-        const int NG = 256 / Lp, p = threadIdx.x % Lp, grp = threadIdx.x / Lp;
+        const int NG = NT / Lp, p = threadIdx.x % Lp, grp = threadIdx.x / Lp;
         Part pt = part_identity();
         if (p < L) {
             const size_t i = (size_t)b * L + p;
@@ -138,12 +142,20 @@ __global__ __launch_bounds__(256) void merge_select_kernel(const SelectArgs a) {
                 for (int u = 0; u < 8; ++u) pt = part_merge(pt, Part{m[u], sx[u], ix[u]});
             }
         }
-        g_m[threadIdx.x] = pt.m; g_s[threadIdx.x] = pt.s; g_i[threadIdx.x] = pt.i;
+        for (int o = Lp; o < 64; o <<= 1) {      // (lanes o apart hold the same row)
+            Part other;
+            other.m = __shfl_xor(pt.m, o);
+            other.s = __shfl_xor(pt.s, o);
+            other.i = __shfl_xor(pt.i, o);
+            pt = part_merge(pt, other);
+        }
+        if (lane < Lp) g_part[wave][p] = pt;
         __syncthreads();
         if (threadIdx.x < L) {
             const int q = threadIdx.x;
             Part r = part_identity();
-            for (int gq = 0; gq < NG; ++gq) r = part_merge(r, Part{g_m[gq * Lp + q], g_s[gq * Lp + q], g_i[gq * Lp + q]});
+#pragma unroll
+            for (int w = 0; w < NW; ++w) r = part_merge(r, g_part[w][q]);
             const int i = b * L + q;
             const float conf = 1.0f / r.s;
             const float lse = r.m + logf(r.s);
@@ -152,7 +164,7 @@ __global__ __launch_bounds__(256) void merge_select_kernel(const SelectArgs a) {
         }
     } else {
     // one wavefront per row: merge the row's nT partials in a fixed order
-    for (int p = wave; p < L; p += 4) {
+    for (int p = wave; p < L; p += NW) {
         const int i = b * L + p;
         Part pt = part_identity();
         for (int t0 = 0; t0 < a.nT; t0 += 64 * MERGE_BATCH) {
@@ -262,9 +274,9 @@ __global__ __launch_bounds__(256) void merge_select_kernel(const SelectArgs a) {
         if ((tokc < 0 || tokc >= a.V) && threadIdx.x == 0 && a.err_flag) atomicOr(a.err_flag, ERR_COND_TOK);
         tokc = tokc < 0 ? 0 : (tokc >= a.V ? a.V - 1 : tokc);
         const uint4 *erow = reinterpret_cast<const uint4 *>(a.E + (size_t)tokc * a.d);
-        for (int c8 = threadIdx.x; c8 < C8; c8 += 256) {
-            const uint4 v = bf16x8_to_f16x8(erow[c8]);   // the head body's operands are fp16
-            for (int p = 0; p < L; ++p) a.xe[act_chunk_index(b * L + p, c8, a.nIb)] = v;
+        for (int n = threadIdx.x; n < C8 * L; n += NT) {   // a plane's rows of one chunk are contiguous
+            const int c8 = n / L, p = n - c8 * L;
+            a.xe[act_chunk_index(b * L + p, c8, a.nIb)] = bf16x8_to_f16x8(erow[c8]);   // the head body's operands are fp16
         }
     }
 }
@@ -455,7 +467,8 @@ hipError_t launch_reduce_rows(const float *z, int M, int V, float *pm, float *ps
 }
 
 hipError_t launch_merge_select(const SelectArgs &a, hipStream_t st) {
-    hipLaunchKernelGGL(merge_select_kernel, dim3(a.B), dim3(256), 0, st, a);
+    if (a.L <= 4 && a.slot_stride == 1) hipLaunchKernelGGL(merge_select_kernel<256>, dim3(a.B), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(merge_select_kernel<1024>, dim3(a.B), dim3(1024), 0, st, a);
     return hipGetLastError();
 }
 
