@@ -143,6 +143,19 @@ int pick_ksplit(int nVt, int nMg, int G, size_t part_rows, int M) {
 bool body_on_tiles(int M, int Kc) { return M >= 768 || (Kc > 2048 && M > 512); }
 bool small_rows_kernel(int M, int Kc) { return !body_on_tiles(M, Kc); }
 
+// LM head of M rows on the tile kernel?  The persistent kernel streams W_lm once through all CUs and is bound by that
+// stream up to 128 rows; its 256-row form pays for 256 rows whatever M is, and rows beyond would stream W_lm a second
+// time.  The tile kernel pays for the 32-row blocks it needs but leaves CUs idle where the vocabulary has fewer 256-entry
+// tiles than there are CUs.  Measured (us, persistent / tile kernel): d = 4096, V = 151936: 396 / 323 at 144 rows, 387 /
+// 341 at 192, 406 / 399 at 256, 622 / 439 at 272 (two launches), 816 / 624 at 512; d = 2048: 205 / 186, 216 / 207, 239 /
+// 242, 367 / 269, 496 / 395; V = 50257, d = 2048: 75 / 52, 79 / 59, 86 / 75, 122 / 99, 181 / 159; d = 1024, V = 151936:
+// 124 / 122, 135 / 139, 152 / 168, 234 / 180; d = 4096, V = 32000: 96 / 92, 97 / 98, 102 / 110, 158 / 98; d = 2048, V =
+// 8192: 49 / 41, 49 / 46, 50 / 58, 67 / 42.
+bool lm_on_tiles(int M, int d, int V, int nCU) {
+    if (M <= 128 || M > 256) return M > 256;
+    return M <= 160 || (d >= 2048 && (V + 255) / 256 * 4 >= 3 * nCU);
+}
+
 // Weight row blocks per tile of the small-row GEMM kernels: two (64 features), so that a workgroup's
 // activation fragments serve twice the weights, once there are more 32-feature tiles than CUs and at least
 // six row tiles (measured per head: d = 4096 at 384 rows 209 us against 227, d = 2048 at 256 rows 63 us
@@ -491,11 +504,6 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
     for (int k = 1; k <= K; ++k) {
         const mrp_head &hd = heads[k - 1];
         StreamGemmArgs g;
-        // The LM head has V / 256 tiles per 256 rows and takes the tile kernel beyond 512 rows (measured at
-        // d = 4096, V = 151936: 931 / 955 / 1031 / 1074 us at 272 / 512 / 752 / 768 rows); below, the persistent
-        // kernel in launches of at most 256 rows is ahead (see there).  Both take rows at any 4-byte offset, so a
-        // vocabulary that is not a multiple of 4 goes the same way (192 rows, d = 2048, V = 50257: 138 us on the
-        // streaming kernel that served it before, 90 us on the persistent one).
         const bool tiled = body_on_tiles(M, d);
         int nks1 = 1, nks2 = 1;
         bool silu_done = false;   // the first GEMM's epilogue already wrote s = SiLU(a) as activation planes
@@ -621,27 +629,20 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
         if (prof) HIP_TRY(c, hipEventRecord(c->ev[2 * c->ev_used], st));
         int nT_lm = 0;
         bool lm_rowmajor = false;  // partial layout [M][nT] (persistent kernel) or [nT][M]
-        if (M <= 512) {
-            // up to 256 rows per launch; a second launch for the rows beyond streams W_lm again, which up to
-            // 512 rows is still cheaper than the tile kernel (measured at d = 4096: 392 us for 256 rows,
-            // 281 us for 128, against 931-955 us for the tile kernel at 272-512 rows)
-            int chunk = 0;
-            for (int row0 = 0; row0 < M; row0 += 256, ++chunk) {
-                LmPersistArgs la;
-                memset(&la, 0, sizeof(la));
-                la.Wp = static_cast<const uint4 *>(W_lm_packed);
-                la.Y = c->Y + (size_t)(row0 / 32) * 64;      // (planes are [k block][row block][lane])
-                la.KB = d / 16; la.n_rb = (V + 31) / 32; la.nIb = c->nIb;
-                la.M = M - row0 < 256 ? M - row0 : 256; la.V = V;
-                la.nWG = c->nCU;
-                // consecutive launches walk the vocabulary in opposite directions: what the previous one
-                // touched last (W_lm is shared by all heads) is still in the L2s when this one starts
-                la.reverse = (off + k + chunk) & 1;
-                la.z = z + (size_t)row0 * V;
-                la.pm = c->pm + (size_t)row0 * la.nWG; la.ps = c->ps + (size_t)row0 * la.nWG;
-                la.pi = c->pi + (size_t)row0 * la.nWG;
-                HIP_TRY(c, launch_lm_persist(la, st));
-            }
+        if (!lm_on_tiles(M, d, V, c->nCU)) {
+            LmPersistArgs la;
+            memset(&la, 0, sizeof(la));
+            la.Wp = static_cast<const uint4 *>(W_lm_packed);
+            la.Y = c->Y;
+            la.KB = d / 16; la.n_rb = (V + 31) / 32; la.nIb = c->nIb;
+            la.M = M; la.V = V;
+            la.nWG = c->nCU;
+            // consecutive launches walk the vocabulary in opposite directions: what the previous one
+            // touched last (W_lm is shared by all heads) is still in the L2s when this one starts
+            la.reverse = (off + k) & 1;
+            la.z = z;
+            la.pm = c->pm; la.ps = c->ps; la.pi = c->pi;
+            HIP_TRY(c, launch_lm_persist(la, st));
             nT_lm = c->nCU;
             lm_rowmajor = true;
         } else {
