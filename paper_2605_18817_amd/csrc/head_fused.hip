@@ -8,7 +8,8 @@
 //
 // A workgroup of 8 wavefronts owns one output tile of 32 activation rows x 32
 // features (64 features when there are more 32-feature tiles than CUs: a
-// workgroup's activation fragments then serve two weight row blocks); wave w
+// workgroup's activation fragments then serve two weight row blocks; 16 while
+// twice the 32-feature tiles still find a CU each); wave w
 // takes the 16-wide k blocks kb = w, w + 8, ... of the tile's weight rows, which
 // it streams from HBM fragment by fragment (1 KiB each, used once), together
 // with the matching activation fragments from L2.  The grid is
@@ -291,19 +292,178 @@ __global__ __launch_bounds__(HF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     small_gemm_body<2>(a);
 }
 
+// ---- 16-feature tiles --------------------------------------------------------------------------------------
+// Few row tiles and a narrow output (one sequence: d / 32 = 64 workgroups at d = 2048) leave most CUs idle while
+// each of the others pulls in 256 KB of weights.  Half tiles (a.nf = 0: 16 features, v_mfma_f32_16x16x32_f16) are twice
+// the workgroups with half the weights each, and where at most 16 rows are left (HR = 1) half the activation
+// fragments, too.  A fragment of 16 rows x 32 k is four runs of 256 bytes of two packed blocks.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// acc[hr] += the sum over this wave's pairs of 16-wide k blocks (pair wave + 8 j of `npair`) of W x, then, with
+// EMBED, the same over the conditioning half (weights w + w2, activations the embedding row e).  w, x, e: this lane's
+// chunk of pair 0; xp: plane stride; xs: pair stride of the planes; hs: u32x4 between the two row halves.
+template <int HR, int NP, bool EMBED>
+__device__ __forceinline__ void half_tile_gemm(f32x4 (&acc)[HR], const u32x4 *w, size_t w2, const u32x4 *x, long xp,
+                                               size_t xs, const uint4 *const (&e)[HR], int npair, int wave) {
+    const int nj = (npair - wave + HF_WAVES - 1) / HF_WAVES;     // pairs of this wave
+    if (nj <= 0) return;                                         // (uniform over the wave)
+    const int nch = (nj + HF_CH - 1) / HF_CH, tot = EMBED ? 2 * nch : nch;
+    u32x4 wr[2][HF_CH], xr[2][HF_CH][NP][HR];
+    auto fetch = [&](int buf, int q) __attribute__((always_inline)) {
+        q = q < tot ? q : tot - 1;
+        const bool emb = EMBED && q >= nch;
+        const int j0 = (emb ? q - nch : q) * HF_CH;
+#pragma unroll
+        for (int u = 0; u < HF_CH; ++u) {
+            const int j = j0 + u < nj ? j0 + u : nj - 1;
+            const size_t kp = wave + HF_WAVES * j;
+            wr[buf][u] = w[(emb ? w2 : 0) + kp * 128];
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int hr = 0; hr < HR; ++hr) {
+                    const u32x4 *src = x + p * xp + hr * 16 + kp * xs;
+                    if constexpr (EMBED) src = emb ? reinterpret_cast<const u32x4 *>(e[hr]) + kp * 4 : src;
+                    xr[buf][u][p][hr] = *src;
+                }
+        }
+    };
+    auto compute = [&](int buf, int q) __attribute__((always_inline)) {
+        const bool emb = EMBED && q >= nch;
+        const int j0 = (emb ? q - nch : q) * HF_CH;
+#pragma unroll
+        for (int u = 0; u < HF_CH; ++u)
+            if (j0 + u < nj) {
+                const f16x8 wf = __builtin_bit_cast(f16x8, wr[buf][u]);
+                if (emb) {
+#pragma unroll
+                    for (int hr = 0; hr < HR; ++hr) {
+                        const uint4 fx = bf16x8_to_f16x8(__builtin_bit_cast(uint4, xr[buf][u][0][hr]));
+                        acc[hr] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf, __builtin_bit_cast(f16x8, fx), acc[hr], 0, 0, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int p = 0; p < NP; ++p)
+#pragma unroll
+                        for (int hr = 0; hr < HR; ++hr)
+                            acc[hr] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf, __builtin_bit_cast(f16x8, xr[buf][u][p][hr]),
+                                                                             acc[hr], 0, 0, 0);
+                }
+            }
+    };
+    fetch(0, 0);
+    for (int q = 0; q < tot; q += 2) {     // (fetches without a condition, as above)
+        fetch(1, q + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(0, q);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(0, q + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        if (q + 1 < tot) compute(1, q + 1);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+constexpr int HT_LD = 16 + HF_PAD;
+
+template <int HR>
+__device__ __forceinline__ void spill_half(float (*t)[HT_LD], const f32x4 (&acc)[HR], int lane) {
+#pragma unroll
+    for (int hr = 0; hr < HR; ++hr)      // lane: row lane % 16, features 4 (lane / 16) ..
+        *reinterpret_cast<float4 *>(&t[hr * 16 + (lane & 15)][4 * (lane >> 4)]) =
+            make_float4(acc[hr][0], acc[hr][1], acc[hr][2], acc[hr][3]);
+}
+
+template <int HR>
+__global__ __launch_bounds__(HF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void head_gemm1_kernel_16(
+    const HeadFusedArgs a) {
+    __shared__ float tile[HF_WAVES][32][HT_LD];
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, cq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int rt, ct;
+    if (!tile_of(a.nct, a.nrt, rt, ct)) return;
+    const int KBd = a.d >> 4;
+    f32x4 acc[HR];
+    const uint4 *e[HR];
+#pragma unroll
+    for (int hr = 0; hr < HR; ++hr) {
+        acc[hr] = f32x4{0.f, 0.f, 0.f, 0.f};
+        int i = rt * 32 + hr * 16 + l16;
+        i = i < a.M ? i : a.M - 1;
+        int tok = a.cond_tok[i / a.L];
+        if ((tok < 0 || tok >= a.V) && ct == 0 && a.err_flag) atomicOr(a.err_flag, ERR_COND_TOK);
+        tok = tok < 0 ? 0 : (tok >= a.V ? a.V - 1 : tok);
+        e[hr] = reinterpret_cast<const uint4 *>(a.E + (size_t)tok * a.d) + cq;
+    }
+    const u32x4 *w = reinterpret_cast<const u32x4 *>(a.W1p) + ((size_t)(ct >> 1) * 2 * KBd + (cq >> 1)) * 64 + 16 * (ct & 1) + l16 + 32 * (cq & 1);
+    const u32x4 *x = reinterpret_cast<const u32x4 *>(a.XH) + ((size_t)(cq >> 1) * a.nIb + rt) * 64 + l16 + 32 * (cq & 1);
+    const size_t xs = (size_t)2 * a.nIb * 64;
+    if (a.np_h == 2) half_tile_gemm<HR, 2, true>(acc, w, (size_t)KBd * 64, x, a.plane, xs, e, KBd >> 1, wave);
+    else half_tile_gemm<HR, 1, true>(acc, w, (size_t)KBd * 64, x, a.plane, xs, e, KBd >> 1, wave);
+    spill_half<HR>(tile[wave], acc, lane);
+    __syncthreads();
+    if (tid < 32 * HR) {
+        const int row = tid % (16 * HR), c = tid / (16 * HR), i = rt * 32 + row;
+        float v[8];
+        reduce_chunk<HT_LD>(tile, row, c, v);
+        if (i < a.M) {
+#pragma unroll
+            for (int n = 0; n < 8; ++n) v[n] = v[n] / (1.0f + expf(-v[n]));
+            split_store(v, a.S, act_chunk_index(i, ct * 2 + c, a.nIb), a.plane);
+        }
+    }
+}
+
+template <int HR>
+__global__ __launch_bounds__(HF_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void small_gemm_kernel_16(
+    const SmallGemmArgs a) {
+    __shared__ float tile[HF_WAVES][32][HT_LD];
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, cq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int rt, ct;
+    if (!tile_of(a.nct, a.nrt, rt, ct)) return;
+    const int KB = a.Kc >> 4;
+    f32x4 acc[HR];
+    const uint4 *e[HR];
+#pragma unroll
+    for (int hr = 0; hr < HR; ++hr) { acc[hr] = f32x4{0.f, 0.f, 0.f, 0.f}; e[hr] = nullptr; }
+    const u32x4 *w = reinterpret_cast<const u32x4 *>(a.Wp) + ((size_t)(ct >> 1) * KB + (cq >> 1)) * 64 + 16 * (ct & 1) + l16 + 32 * (cq & 1);
+    const u32x4 *x = reinterpret_cast<const u32x4 *>(a.X) + ((size_t)(cq >> 1) * a.nIb + rt) * 64 + l16 + 32 * (cq & 1);
+    const size_t xs = (size_t)2 * a.nIb * 64;
+    if (a.nplanes == 2) half_tile_gemm<HR, 2, false>(acc, w, 0, x, a.plane, xs, e, KB >> 1, wave);
+    else half_tile_gemm<HR, 1, false>(acc, w, 0, x, a.plane, xs, e, KB >> 1, wave);
+    spill_half<HR>(tile[wave], acc, lane);
+    __syncthreads();
+    if (tid < 32 * HR) {
+        const int row = tid % (16 * HR), c = tid / (16 * HR), i = rt * 32 + row;
+        float v[8];
+        reduce_chunk<HT_LD>(tile, row, c, v);
+        if (i < a.M) {
+            float4 *up = reinterpret_cast<float4 *>(a.out + (size_t)i * a.R + 16 * ct + 8 * c);
+            up[0] = make_float4(v[0], v[1], v[2], v[3]);
+            up[1] = make_float4(v[4], v[5], v[6], v[7]);
+        }
+    }
+}
+
 }  // namespace
 
-// 64-feature tiles (a.nf = 2) once there are more 32-feature tiles than CUs; a.nct counts tiles of 32 a.nf features
+// 64-feature tiles (a.nf = 2) once there are more 32-feature tiles than CUs, 16-feature tiles (a.nf = 0) while twice
+// the 32-feature tiles still find a CU each; a.nct counts the tiles
 hipError_t launch_small_gemm(const SmallGemmArgs &a, hipStream_t st) {
     const int per = (a.nct * a.nrt + 7) / 8;
-    if (a.nf == 2) hipLaunchKernelGGL(small_gemm_kernel_64, dim3(per * 8), dim3(HF_THREADS), 0, st, a);
+    if (a.nf == 0 && a.M <= 16) hipLaunchKernelGGL(small_gemm_kernel_16<1>, dim3(per * 8), dim3(HF_THREADS), 0, st, a);
+    else if (a.nf == 0) hipLaunchKernelGGL(small_gemm_kernel_16<2>, dim3(per * 8), dim3(HF_THREADS), 0, st, a);
+    else if (a.nf == 2) hipLaunchKernelGGL(small_gemm_kernel_64, dim3(per * 8), dim3(HF_THREADS), 0, st, a);
     else hipLaunchKernelGGL(small_gemm_kernel, dim3(per * 8), dim3(HF_THREADS), 0, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_head_fused(const HeadFusedArgs &a, hipStream_t st) {
     const int per = (a.nct * a.nrt + 7) / 8;
-    if (a.nf == 2) hipLaunchKernelGGL(head_gemm1_kernel_64, dim3(per * 8), dim3(HF_THREADS), 0, st, a);
+    if (a.nf == 0 && a.M <= 16) hipLaunchKernelGGL(head_gemm1_kernel_16<1>, dim3(per * 8), dim3(HF_THREADS), 0, st, a);
+    else if (a.nf == 0) hipLaunchKernelGGL(head_gemm1_kernel_16<2>, dim3(per * 8), dim3(HF_THREADS), 0, st, a);
+    else if (a.nf == 2) hipLaunchKernelGGL(head_gemm1_kernel_64, dim3(per * 8), dim3(HF_THREADS), 0, st, a);
     else hipLaunchKernelGGL(head_gemm1_kernel, dim3(per * 8), dim3(HF_THREADS), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -161,7 +161,16 @@ bool lm_on_tiles(int M, int d, int V, int nCU) {
 // six row tiles (measured per head: d = 4096 at 384 rows 209 us against 227, d = 2048 at 256 rows 63 us
 // against 70; but at 128 rows, d = 4096, 110 us against 100: with four row tiles the 512 smaller workgroups,
 // two per CU, keep more requests in flight)
-int small_tile_blocks(int R, int nrt, int nCU) { return (R % 64 == 0 && (R / 32) * nrt > nCU && nrt >= 6) ? 2 : 1; }
+// Zero stands for 16-feature tiles, while twice the 32-feature tiles still find a CU each and a wave has k pairs enough
+// to fetch ahead.  Measured per step of three heads with a small LM head (V = 4096), 32- / 16-feature tiles: d = 2048 177 /
+// 136 us at 16 rows, 180 / 152 at 32, 190 / 168 at 64; d = 4096 240 / 203 at 4, 285 / 246 at 32; d = 1024 105 / 99.5 at 4,
+// 108.5 / 114 at 32; d = 256 81 / 85 at 4.
+int small_tile_blocks(int R, int Kc, int M, int nCU) {
+    const int nrt = (M + 31) / 32;
+    if ((Kc >= 2048 || (Kc >= 1024 && M <= 16)) && 2 * (R / 32) * nrt <= nCU) return 0;
+    return (R % 64 == 0 && (R / 32) * nrt > nCU && nrt >= 6) ? 2 : 1;
+}
+int small_tile_features(int nf) { return nf == 0 ? 16 : 32 * nf; }
 
 // out[ks][M][R] = partial sums of W [R][Kc] (packed) times the activation planes; returns the number
 // of k splits written (1 for the tiled kernel) or -1 after a launch error (*err set).
@@ -203,8 +212,8 @@ int gemm_partial(mrp_ctx *c, hipStream_t st, const void *Wp, int R, int Kc, cons
         sg.Wp = static_cast<const uint4 *>(Wp); sg.X = act; sg.plane = plane_stride; sg.nplanes = nplanes;
         sg.out = out; sg.nIb = c->nIb; sg.M = M; sg.R = R; sg.Kc = Kc;
         sg.nrt = (M + 31) / 32;
-        sg.nf = small_tile_blocks(R, sg.nrt, c->nCU);
-        sg.nct = R / (32 * sg.nf);
+        sg.nf = small_tile_blocks(R, Kc, M, c->nCU);
+        sg.nct = R / small_tile_features(sg.nf);
         *err = launch_small_gemm(sg, st);
         return *err == hipSuccess ? 1 : -1;
     }
@@ -520,8 +529,8 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             fa.nIb = c->nIb; fa.M = M; fa.d = d;
             fa.err_flag = c->err_flag;
             fa.nrt = (M + 31) / 32;
-            fa.nf = small_tile_blocks(d, fa.nrt, c->nCU);
-            fa.nct = d / (32 * fa.nf);
+            fa.nf = small_tile_blocks(d, d, M, c->nCU);
+            fa.nct = d / small_tile_features(fa.nf);
             HIP_TRY(c, launch_head_fused(fa, st));
         } else {
         // a = W1 [h_run ; e]

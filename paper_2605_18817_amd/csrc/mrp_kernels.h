@@ -104,8 +104,8 @@ struct HeadFusedArgs {
     float *U;                  // [M][d] fp32 u = W2 s
     int nIb, M, d;
     int *err_flag;
-    int nf;                    // weight row blocks per tile (1 or 2)
-    int nct, nrt;              // feature tiles d / (32 nf), row tiles ceil(M / 32)
+    int nf;                    // weight row blocks per tile (1 or 2; 0: half a block, 16 features)
+    int nct, nrt;              // feature tiles, row tiles ceil(M / 32)
 };
 
 // Four consecutive floats at any 4-byte address (one 16-byte request: the rows of a logit matrix whose vocabulary is
@@ -366,8 +366,8 @@ struct SmallGemmArgs {
     int nplanes;               // 1 or 2
     float *out;                // [M][R]
     int nIb, M, R, Kc;
-    int nf;                    // weight row blocks per tile (1 or 2; R % (32 nf) == 0)
-    int nct, nrt;              // feature tiles R / (32 nf), row tiles ceil(M / 32)
+    int nf;                    // weight row blocks per tile (1 or 2; 0: half a block; R % (32 nf) == 0)
+    int nct, nrt;              // feature tiles, row tiles ceil(M / 32)
 };
 hipError_t launch_small_gemm(const SmallGemmArgs &a, hipStream_t st);
 hipError_t launch_head_fused(const HeadFusedArgs &a, hipStream_t st);   // both GEMMs: S and U written
