@@ -7,8 +7,9 @@
 // the mean over blocks and offsets t for every r.
 //
 // All S (S + 1) / 2 sums come out of ONE pass over the states: a workgroup stages a 512-entry
-// tile of all S states in LDS (HBM traffic = every state once), every lane turns its entries of
-// the S states to fp64 in registers, and the four waves split the jobs (job p goes to wave p mod
+// tile of all S states in LDS (HBM traffic = every state once), turned to fp64 on the way in (once
+// per entry; with the tile in fp32 each of the four waves converted all of it: 352 us against 337
+// for 8 blocks of 17 x 2430976), and the four waves split the jobs (job p goes to wave p mod
 // 4), so a wave carries at most 39 fp64 accumulators.  Workgroup partials are summed in
 // workgroup order by a second kernel: the result does not depend on timing.
 #include "mrp_kernels.h"
@@ -46,7 +47,7 @@ template <int S, bool BF16, bool VEC>
 __global__ __launch_bounds__(256) void rms_partial_kernel(const void *__restrict__ X, long N, int nwg,
                                                           double *__restrict__ part) {
     constexpr int J = S * (S + 1) / 2, JA = (J + 3) / 4;
-    __shared__ float tile[S][RT];
+    __shared__ double tile[S][RT];
     const int blk = blockIdx.y, wg = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const size_t base = (size_t)blk * S * N;
     double acc[JA];
@@ -99,13 +100,17 @@ __global__ __launch_bounds__(256) void rms_partial_kernel(const void *__restrict
 #pragma unroll
             for (int n = 0; n < NV; ++n) {
                 const int idx = tid + 256 * n;
-                if (idx < S * (RT / 4)) *reinterpret_cast<float4 *>(&tile[idx / (RT / 4)][4 * (idx % (RT / 4))]) = rv[n];
+                if (idx < S * (RT / 4)) {
+                    double2 *o = reinterpret_cast<double2 *>(&tile[idx / (RT / 4)][4 * (idx % (RT / 4))]);
+                    o[0] = make_double2((double)rv[n].x, (double)rv[n].y);
+                    o[1] = make_double2((double)rv[n].z, (double)rv[n].w);
+                }
             }
         } else {
 #pragma unroll
             for (int n = 0; n < NV; ++n) {
                 const int idx = tid + 256 * n;
-                if (idx < S * RT) tile[idx / RT][idx % RT] = rs[n];
+                if (idx < S * RT) tile[idx / RT][idx % RT] = (double)rs[n];
             }
         }
     };
@@ -120,9 +125,9 @@ __global__ __launch_bounds__(256) void rms_partial_kernel(const void *__restrict
             double x[S][2];
 #pragma unroll
             for (int s = 0; s < S; ++s) {
-                const float2 v = *reinterpret_cast<const float2 *>(&tile[s][c2]);
-                x[s][0] = (double)v.x;
-                x[s][1] = (double)v.y;
+                const double2 v = *reinterpret_cast<const double2 *>(&tile[s][c2]);
+                x[s][0] = v.x;
+                x[s][1] = v.y;
             }
             // entries past N were staged as zeros in every state: they add nothing to any job
             switch (wave) {   // (uniform over the wave)
@@ -227,7 +232,11 @@ bool residual_rms_supported(int S) { return S == 3 || S == 5 || S == 9 || S == 1
 hipError_t launch_residual_rms(int n_blocks, int S, long N, const void *X, bool bf16, double *part,
                                double *rms_pair, double *rms_delta, hipStream_t st) {
     const long ntiles = (N + RT - 1) / RT;
-    long nwg = RMS_MAX_PART / n_blocks;
+    // Workgroups per block: two per CU in all (as many as are resident), so that each pays for its start and its lane
+    // reduction once over many tiles; with more than 64 blocks that division leaves CUs idle, so several rounds of
+    // smaller workgroups.  Measured with 512 / 1024 / 4096 workgroups, S = 17: 1 block of 804112 entries 29 / 35 / 43
+    // us, 64 of 65536 91 / 92 / 111 us, 300 of 32768 302 / 232 / 228 us, 8 of 2430976 the same.
+    long nwg = (n_blocks <= 64 ? 512 : RMS_MAX_PART) / n_blocks;
     if (nwg > ntiles) nwg = ntiles;
     if (nwg < 1) nwg = 1;
     const uintptr_t a = reinterpret_cast<uintptr_t>(X);
