@@ -513,7 +513,11 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
     for (int k = 1; k <= K; ++k) {
         const mrp_head &hd = heads[k - 1];
         StreamGemmArgs g;
-        const bool tiled = body_on_tiles(M, d);
+        // (The fuse projection of the transformer body has no small-row kernel: the tile kernel with its k split is
+        // ahead of the streaming kernel from there on.  Measured per head of one layer, streaming / tile: d = 4096 213 /
+        // 208 us at 4 rows, 327 / 323 at 128, 598 / 566 at 384; d = 2048 156 / 157 at 128, 193 / 192 at 192, 273 / 253 at
+        // 384; d = 1024 117 / 120 at 128, 168 / 171 at 512.)
+        const bool tiled = body_on_tiles(M, d) || (layers && (M > 128 ? d >= 2048 : d > 2048));
         int nks1 = 1, nks2 = 1;
         bool silu_done = false;   // the first GEMM's epilogue already wrote s = SiLU(a) as activation planes
         const float *resid = nullptr;   // transformer body: residual stream added to the last projection
