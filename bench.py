@@ -91,7 +91,7 @@ def bench_kl_loss(args, np, torch, mi, mrp) -> dict:
     ach = byt / (ev / args.steps) / 1e9
     roof = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
             "traffic": traffic_from_profile(None, "kl_loss_pmc.txt") if (M, V) == (1024, 151936) else None,
-            "kernel": "kl_partial_kernel + kl_finish_kernel + kl_grad_kernel",
+            "kernel": "kl_kernel (partials of a group of rows, gradient of the one before)",
             "kernel_ms": 1e3 * ev / args.steps}
     cpu = None
     if not args.skip_cpu_baseline:
@@ -369,11 +369,10 @@ def run_chain_config(cfg, args, np, torch, mi, mrp) -> dict:
     roof["traffic_source"] = (f"profiles/lm_head_cfg{cfg.cid}_pmc.txt: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of an earlier "
                               "run of this command, scaled by what the counters read for a 1 GiB copy; not measured in this run"
                               if roof["traffic"] is not None else None)
+    persist = M <= 128 or (160 < M <= 256 and (cfg.d < 2048 or (V + 255) // 256 * 4 < 3 * 256))
     roof["kernel"] = (("lm_persist_kernel_32rows" if M <= 32 else "lm_persist_kernel_64rows" if M <= 64 else
-                       "lm_persist_kernel" if M <= 128 else "lm_persist_kernel_256rows")
-                      if M <= 256 and V % 4 == 0 else
-                      "lm_persist_kernel_256rows (+ a second launch for the rows beyond 256)" if M <= 512 and V % 4 == 0 else
-                      "tiled_gemm_kernel<EPI_LM>" if V % 4 == 0 else "stream_gemm_kernel<EPI_LM>")
+                       "lm_persist_kernel" if M <= 128 else "lm_persist_kernel_256rows") if persist else
+                      "tiled_gemm_kernel<EPI_LM>")
     roof["kernel_ms"] = lm_avg_ms
     roof["launches"] = len(lm_ms)
     roof["algorithmic_bytes_per_launch"] = lm_bytes
