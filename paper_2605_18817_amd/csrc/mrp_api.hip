@@ -144,16 +144,21 @@ bool body_on_tiles(int M, int Kc) { return M >= 768 || (Kc > 2048 && M > 512); }
 bool small_rows_kernel(int M, int Kc) { return !body_on_tiles(M, Kc); }
 
 // LM head of M rows on the tile kernel?  The persistent kernel streams W_lm once through all CUs and is bound by that
-// stream up to 128 rows; its 256-row form pays for 256 rows whatever M is, and rows beyond would stream W_lm a second
-// time.  The tile kernel pays for the 32-row blocks it needs but leaves CUs idle where the vocabulary has fewer 256-entry
-// tiles than there are CUs.  Measured (us, persistent / tile kernel): d = 4096, V = 151936: 396 / 323 at 144 rows, 387 /
-// 341 at 192, 406 / 399 at 256, 622 / 439 at 272 (two launches), 816 / 624 at 512; d = 2048: 205 / 186, 216 / 207, 239 /
-// 242, 367 / 269, 496 / 395; V = 50257, d = 2048: 75 / 52, 79 / 59, 86 / 75, 122 / 99, 181 / 159; d = 1024, V = 151936:
-// 124 / 122, 135 / 139, 152 / 168, 234 / 180; d = 4096, V = 32000: 96 / 92, 97 / 98, 102 / 110, 158 / 98; d = 2048, V =
-// 8192: 49 / 41, 49 / 46, 50 / 58, 67 / 42.
+// stream up to 128 rows; its 256-row form pays for 256 rows whatever M is, and rows beyond stream W_lm a second time.
+// The tile kernel pays for the 32-row blocks it needs, in whole rounds of one tile per CU.  Measured (us, persistent / tile
+// kernel): d = 4096, V = 151936: 396 / 323 at 144 rows, 387 / 341 at 192, 406 / 399 at 256, 622 / 439 at 272 (two
+// launches), 816 / 624 at 512; d = 2048: 205 / 186, 216 / 207, 239 / 242, 367 / 269, 496 / 395; V = 50257, d = 2048: 75 /
+// 52, 79 / 59, 86 / 75, 122 / 99, 181 / 159; d = 1024, V = 151936: 124 / 122, 135 / 139, 152 / 168, 234 / 180; d = 256:
+// 68 / 61, -, 87 / 88, 107 / 100, 189 / 189; d = 4096, V = 32000: 96 / 92, 97 / 98, 102 / 110, 158 / 98; d = 2048, V =
+// 8192: 49 / 41, 49 / 46, 50 / 58, 67 / 42.  Those fill three quarters of their rounds or have one round only; the
+// tile kernel's time goes with the rounds and the persistent kernel's with V, so where a round is emptier than that the
+// margins above are used up (narrow operands, whose margins are smaller: seven eighths).
 bool lm_on_tiles(int M, int d, int V, int nCU) {
-    if (M <= 128 || M > 256) return M > 256;
-    return M <= 160 || (d >= 2048 && (V + 255) / 256 * 4 >= 3 * nCU);
+    if (M <= 128 || M > 512) return M > 512;
+    const long tiles = (long)tiled_row_tiles(M) * ((V + 255) / 256), slots = (tiles + nCU - 1) / nCU * nCU;
+    const bool full = d < 1024 && M > 256 ? 8 * tiles >= 7 * slots : 4 * tiles >= 3 * slots;
+    if (M > 160 && M <= 256) return d >= 2048 && full;
+    return tiles <= nCU || full;
 }
 
 // Weight row blocks per tile of the small-row GEMM kernels: two (64 features), so that a workgroup's
@@ -643,19 +648,24 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
         int nT_lm = 0;
         bool lm_rowmajor = false;  // partial layout [M][nT] (persistent kernel) or [nT][M]
         if (!lm_on_tiles(M, d, V, c->nCU)) {
-            LmPersistArgs la;
-            memset(&la, 0, sizeof(la));
-            la.Wp = static_cast<const uint4 *>(W_lm_packed);
-            la.Y = c->Y;
-            la.KB = d / 16; la.n_rb = (V + 31) / 32; la.nIb = c->nIb;
-            la.M = M; la.V = V;
-            la.nWG = c->nCU;
-            // consecutive launches walk the vocabulary in opposite directions: what the previous one
-            // touched last (W_lm is shared by all heads) is still in the L2s when this one starts
-            la.reverse = (off + k) & 1;
-            la.z = z;
-            la.pm = c->pm; la.ps = c->ps; la.pi = c->pi;
-            HIP_TRY(c, launch_lm_persist(la, st));
+            // up to 256 rows per launch; a second launch for the rows beyond streams W_lm again
+            int chunk = 0;
+            for (int row0 = 0; row0 < M; row0 += 256, ++chunk) {
+                LmPersistArgs la;
+                memset(&la, 0, sizeof(la));
+                la.Wp = static_cast<const uint4 *>(W_lm_packed);
+                la.Y = c->Y + (size_t)(row0 / 32) * 64;      // (planes are [k block][row block][lane])
+                la.KB = d / 16; la.n_rb = (V + 31) / 32; la.nIb = c->nIb;
+                la.M = M - row0 < 256 ? M - row0 : 256; la.V = V;
+                la.nWG = c->nCU;
+                // consecutive launches walk the vocabulary in opposite directions: what the previous one
+                // touched last (W_lm is shared by all heads) is still in the L2s when this one starts
+                la.reverse = (off + k + chunk) & 1;
+                la.z = z + (size_t)row0 * V;
+                la.pm = c->pm + (size_t)row0 * la.nWG; la.ps = c->ps + (size_t)row0 * la.nWG;
+                la.pi = c->pi + (size_t)row0 * la.nWG;
+                HIP_TRY(c, launch_lm_persist(la, st));
+            }
             nT_lm = c->nCU;
             lm_rowmajor = true;
         } else {

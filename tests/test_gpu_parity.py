@@ -267,8 +267,9 @@ def test_row_counts_where_the_kernels_change(d, B, L, K):
 
 
 @pytest.mark.parametrize("B,L,V", [(1, 3, 1001),      # one row block; the last 32-block of the vocabulary holds 9 entries
-                                   (9, 16, 4099),     # 144 rows: the 256-row form
+                                   (9, 16, 4099),     # 144 rows: one 160-row tile
                                    (20, 16, 2049),    # 320 rows: 160-row tiles, the last one holds one entry
+                                   (25, 16, 35073),   # 400 rows on the persistent kernel: 276 tiles leave a round half empty
                                    (33, 16, 1002),    # 528 rows on the tile kernel, rows on 8-byte boundaries
                                    (33, 16, 1025),    # ... on 4-byte boundaries, one entry in the last piece
                                    (130, 5, 1031),    # 650 rows, a row ends 3 entries into a piece
