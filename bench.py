@@ -369,9 +369,9 @@ def run_chain_config(cfg, args, np, torch, mi, mrp) -> dict:
     roof["traffic_source"] = (f"profiles/lm_head_cfg{cfg.cid}_pmc.txt: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE of an earlier "
                               "run of this command, scaled by what the counters read for a 1 GiB copy; not measured in this run"
                               if roof["traffic"] is not None else None)
-    persist = M <= 128 or (160 < M <= 256 and (cfg.d < 2048 or (V + 255) // 256 * 4 < 3 * 256))
+    persist = M <= 128      # (129 to 512 rows: the benchmark's vocabularies fill their rounds of tiles)
     roof["kernel"] = (("lm_persist_kernel_32rows" if M <= 32 else "lm_persist_kernel_64rows" if M <= 64 else
-                       "lm_persist_kernel" if M <= 128 else "lm_persist_kernel_256rows") if persist else
+                       "lm_persist_kernel") if persist else
                       "tiled_gemm_kernel<EPI_LM>")
     roof["kernel_ms"] = lm_avg_ms
     roof["launches"] = len(lm_ms)
