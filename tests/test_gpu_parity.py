@@ -291,3 +291,32 @@ def test_vocabulary_not_a_multiple_of_four(B, L, V):
                   max_exempt=(3 * B + 99) // 100)
     assert bool((flat[cfg.M * V:] == 7.0).all())
     prob.close()
+
+
+@pytest.mark.parametrize("d,L,B,B_big", [(2048, 4, 4, 32), (2048, 16, 4, 8), (1024, 4, 4, 8)])
+def test_16_feature_tiles_are_no_further_from_64_bits(d, L, B, B_big):
+    """The head GEMMs on 16-feature tiles (16 and 64 rows) and, in a larger batch, on 32-feature tiles, for the same rows:
+    both sum the same exact products in fp32, so the half tiles' error of h_run - h against fp64 may not be the larger one
+    (a root mean square over at least 16 x 1024 sums, of which each kernel's rounding is a fixed property)."""
+    K, V = 2, 4096
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d + B)
+    normal = lambda *s, std=0.02: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0, std, generator=gen)
+    E, W = normal(V, d), normal(V, d)
+    w = [(normal(d, 2 * d), normal(d, d)) for _ in range(K)]
+    h, z = normal(B_big * L, d, std=1.0), torch.empty(B_big * L, V, device="cuda").normal_(0, 2, generator=gen)
+    gamma = torch.ones(d, dtype=torch.bfloat16, device="cuda")
+    heads = [mrp.Head(mrp.pack_weight(a, body=True), mrp.pack_weight(b, body=True), gamma) for a, b in w]
+    Wp, err = mrp.pack_weight(W), []
+    for nb in (B, B_big):
+        ctx, io = mrp.MrpContext(d, V, nb * L, L), mrp.StepIO(nb, L, K)
+        hrun = torch.zeros(nb * L, d, device="cuda")
+        ctx.chain_step(nb, K, h[:nb * L], hrun, E, Wp, heads, z[:nb * L].clone(), mrp.RevealCfg(tau=2.0), io)
+        x = h[:B * L].double()
+        tok = io.draft_tok.view(nb, K + 1)[:B].long()          # (tau above 1: one reveal per state, the draft)
+        for k, (w1, w2) in enumerate(w):
+            a = torch.cat([x, E[tok[:, k]].double().repeat_interleave(L, 0)], 1) @ w1.double().t()
+            x = x + (a * torch.sigmoid(a)) @ w2.double().t()
+        err.append(float((hrun[:B * L].double() - x).norm() / (x - h[:B * L].double()).norm()))
+        ctx.close()
+    assert err[0] <= err[1] < 1e-6, err
