@@ -331,7 +331,9 @@ __device__ __forceinline__ void half_tile_gemm(f32x4 (&acc)[HR], const u32x4 *w,
                 for (int hr = 0; hr < HR; ++hr) {
                     const u32x4 *src = x + p * xp + hr * 16 + kp * xs;
                     if constexpr (EMBED) src = emb ? reinterpret_cast<const u32x4 *>(e[hr]) + kp * 4 : src;
-                    xr[buf][u][p][hr] = *src;
+                    // (the embedding has one plane; the branch is uniform: 4096 wide, 32 rows, V = 4096, three heads 247 ->
+                    //  244 us against fetching its chunk once per plane, the same at 4 to 16 rows)
+                    if (!(EMBED && p > 0 && emb)) xr[buf][u][p][hr] = *src;
                 }
         }
     };
@@ -360,7 +362,7 @@ __device__ __forceinline__ void half_tile_gemm(f32x4 (&acc)[HR], const u32x4 *w,
             }
     };
     fetch(0, 0);
-    for (int q = 0; q < tot; q += 2) {     // (fetches without a condition, as above)
+    for (int q = 0; q < tot; q += 2) {     // (fetches without a condition on the loop's end, as above)
         fetch(1, q + 1);
         __builtin_amdgcn_sched_barrier(0);
         compute(0, q);
