@@ -238,6 +238,30 @@ int gemm_partial(mrp_ctx *c, hipStream_t st, const void *Wp, int R, int Kc, cons
 
 }  // namespace
 
+// The fuse projection of the transformer body (W1 [h_run ; e] of M rows, `nplanes` planes of h_run) has no small-row
+// kernel.  The tile kernel with its k split is ahead of the streaming kernel for d > 2048, and at d = 2048 beyond 128 rows
+// (measured per head of one layer, streaming / tile: d = 4096 213 / 208 us at 4 rows, 327 / 323 at 128, 598 / 566 at 384;
+// d = 2048 156 / 157 at 128, 193 / 192 at 192; d = 1024 117 / 120 at 128, 168 / 171 at 512), as long as it splits k into as
+// many parts: longer sums round more.  With the parts that fill one round of CUs u_0 was 3.1e-7 of its norm from 64 bits at
+// d = 5120, 384 rows (streaming kernel: 2.4e-7); with twice as many in two rounds 2.2e-7, a step of three heads of one layer
+// 1439 -> 1503 us (streaming: 1752); d = 2048, 384 rows 1.47e-7 -> 1.32e-7 (1.39e-7), 748 -> 765 us.  The parts are
+// powers of two that divide the k steps; where those end below the streaming kernel's (widths that are no multiple of 1024)
+// CUs would idle, too (d = 2176, 4 rows: 108 us per head against 85).
+// Returns the tile kernel's parts, whose partial sums take at most `cap_rows` rows; 0: streaming kernel, whose partial
+// sums take at most `part_rows`.
+int mrp::fuse_tile_parts(int M, int d, int nplanes, int nCU, size_t part_rows, size_t cap_rows) {
+    if (M > 128 ? d < 2048 : d <= 2048) return 0;
+    const int IT = stream_gemm_it(M);
+    const int streamed = pick_ksplit(d / WG_ROWS, ((M + 31) / 32 + IT - 1) / IT, 2 * d / (16 * KSTEP), part_rows, M);
+    const int tiles = tiled_row_tiles(M) * ((d + 255) / 256), nsteps = (d / 64) * (nplanes + 1);
+    int parts = tiled_ksplit(tiles, nsteps, nCU, part_rows, M);      // (what fills one round)
+    while (parts < streamed) {
+        parts *= 2;
+        if (nsteps % parts != 0 || nsteps / parts < MRP_TILED_MIN_STEPS || (size_t)parts * M > cap_rows) return 0;
+    }
+    return parts;
+}
+
 extern "C" {
 
 size_t mrp_workspace_bytes(const mrp_dims *dims) {
@@ -518,11 +542,11 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
     for (int k = 1; k <= K; ++k) {
         const mrp_head &hd = heads[k - 1];
         StreamGemmArgs g;
-        // (The fuse projection of the transformer body has no small-row kernel: the tile kernel with its k split is
-        // ahead of the streaming kernel from there on.  Measured per head of one layer, streaming / tile: d = 4096 213 /
-        // 208 us at 4 rows, 327 / 323 at 128, 598 / 566 at 384; d = 2048 156 / 157 at 128, 193 / 192 at 192, 273 / 253 at
-        // 384; d = 1024 117 / 120 at 128, 168 / 171 at 512.)
-        const bool tiled = body_on_tiles(M, d) || (layers && (M > 128 ? d >= 2048 : d > 2048));
+        // (transformer body: the fuse projection's partial sums on tiles go to the layers' buffer, which is the larger)
+        const int fuse_parts = layers && !body_on_tiles(M, d)
+            ? fuse_tile_parts(M, d, np_h, c->nCU, c->part_rows, c->tb_part_floats / (size_t)d) : 0;
+        float *const fused_u = fuse_parts ? c->tb_part : c->PART;
+        const bool tiled = body_on_tiles(M, d) || fuse_parts;
         int nks1 = 1, nks2 = 1;
         bool silu_done = false;   // the first GEMM's epilogue already wrote s = SiLU(a) as activation planes
         const float *resid = nullptr;   // transformer body: residual stream added to the last projection
@@ -552,9 +576,10 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             tg.seg[1] = TiledSeg{c->XE, 0, d / 64, 1};
             tg.nseg = 2;
             tg.nMt = tiled_row_tiles(M); tg.nVt = (d + 255) / 256;
-            tg.nKs = tiled_ksplit(tg.nMt * tg.nVt, (d / 64) * (np_h + 1), c->nCU, c->part_rows, M);
+            tg.nKs = fuse_parts ? fuse_parts
+                                : tiled_ksplit(tg.nMt * tg.nVt, (d / 64) * (np_h + 1), c->nCU, c->part_rows, M);
             nks1 = tg.nKs;
-            tg.out = c->PART;
+            tg.out = fused_u;
             // a single k part of the MLP body: SiLU and the fp16 split sit in the tile epilogue
             silu_done = !layers && tg.nKs == 1;
             tg.planes = c->S; tg.plane_stride = c->plane;
@@ -584,7 +609,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             int nks = nks1;
             for (int l = 0; l < tb.D; ++l) {
                 const mrp_tlayer &ly = layers[(size_t)(k - 1) * tb.D + l];
-                HIP_TRY(c, launch_resid_norm_split(c->PART, nks, l == 0 ? nullptr : c->tb_U, c->tb_U,
+                HIP_TRY(c, launch_resid_norm_split(l == 0 ? fused_u : c->PART, nks, l == 0 ? nullptr : c->tb_U, c->tb_U,
                                                    static_cast<const uint16_t *>(ly.g1), c->dims.rms_eps, c->tb_P,
                                                    c->tb_plane, c->nIb, M, d, st));
                 nks = gemm_partial(c, st, ly.Wqkv_packed, qkvd, d, c->tb_P, c->tb_plane, NSPLIT, M, c->tb_part,

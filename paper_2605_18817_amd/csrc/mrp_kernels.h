@@ -262,8 +262,13 @@ int stream_gemm_it(int M);   // activation row blocks per workgroup for M rows
 hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st);
 int tiled_row_blocks(int M);   // 32-row blocks of activation rows per tile for M rows
 inline int tiled_row_tiles(int M) { return (M + 32 * tiled_row_blocks(M) - 1) / (32 * tiled_row_blocks(M)); }
+#ifndef MRP_TILED_MIN_STEPS
+#define MRP_TILED_MIN_STEPS 4     // fewest k steps of a part
+#endif
 // k parts for a partial-sum tile GEMM with `tiles` output tiles and `nsteps` k steps, writing at most `cap_rows` rows
 int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M);
+// k parts of the transformer body's fuse projection of M rows on the tile kernel; 0: it is the streaming kernel's
+int fuse_tile_parts(int M, int d, int nplanes, int nCU, size_t part_rows, size_t cap_rows);
 hipError_t launch_lm_persist(const LmPersistArgs &a, hipStream_t st);
 size_t lm_persist_lds_bytes();
 hipError_t lm_persist_configure();    // once per device

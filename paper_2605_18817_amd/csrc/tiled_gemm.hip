@@ -484,9 +484,6 @@ int tiled_row_blocks(int M) {
 // Few output tiles (the head body's GEMMs at 1024 or 2048 rows have 64 or 128) leave most CUs idle: split k
 // into up to 16 parts so that tiles x parts comes near the CU count; every part must have an equal number of at
 // least MRP_TILED_MIN_STEPS k steps and its partial sums must fit the buffer.
-#ifndef MRP_TILED_MIN_STEPS
-#define MRP_TILED_MIN_STEPS 4
-#endif
 int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M) {
     int ks = 1;
     while (ks < 16 && tiles * ks * 2 <= nCU && nsteps % (ks * 2) == 0 && nsteps / (ks * 2) >= MRP_TILED_MIN_STEPS &&

@@ -160,6 +160,19 @@ def test_config1_shape_three_layers():
     _run(cfg, td, mrp.RevealCfg(tau=cfg.tau), seqs=[0, 31], gain="ones")
 
 
+@pytest.mark.parametrize("d,B,L,K", [(2048, 9, 16, 1),     # 144 rows: 8 tiles x 16 k parts
+                                     (2048, 24, 16, 1),    # 384 rows: 16 parts, more rows than the head body's buffer takes
+                                     (4096, 2, 4, 2),      # 8 rows in a tile of 160; the second head's two planes
+                                     (2560, 2, 4, 2),      # first head 16 parts of 5 k steps, second on the streaming kernel
+                                     (2176, 2, 4, 1),      # a width whose k steps do not split: streaming kernel
+                                     (5120, 9, 16, 1)])    # 20 tiles x 16 parts: more than one round of CUs
+def test_fuse_projection_kernels(d, B, L, K):
+    """The fuse projection's forms below the row counts of the tile kernel proper, first and last sequence compared."""
+    cfg = mi.straddling(mi.config(0, d=d, V=1028, B=B, L=L, K=K))
+    td = mi.TBodyDims(D=1, n_heads=2, n_kv_heads=1, head_dim=128, d_ff=1024, P_max=20)
+    _run(cfg, td, mrp.RevealCfg(tau=0.9), seqs=[0, B - 1])
+
+
 def test_tbody_argument_errors():
     cfg = mi.config(0)
     ctx = mrp.MrpContext(cfg.d, cfg.V, cfg.M, cfg.L)
