@@ -461,9 +461,9 @@ hipError_t launch_epi(const TiledGemmArgs &a, hipStream_t st) {
 
 template <int NB>
 hipError_t launch_nb(const TiledGemmArgs &a, int epi, hipStream_t st) {
-    if (epi == EPI_SILU) {      // (needs an unsplit k: many tiles, so 768 rows and more)
+    if (epi == EPI_SILU) {
         if constexpr (NB >= 7) return launch_epi<EPI_SILU, false, NB>(a, st);
-        else return hipErrorInvalidValue;
+        else return hipErrorInvalidValue;      // (launch_tiled_gemm rounds up to 7)
     }
     if (epi == EPI_PARTIAL) return launch_epi<EPI_PARTIAL, false, NB>(a, st);
     // (a row that is no whole number of pieces has its own form: the handling of its end costs registers, and with
@@ -493,7 +493,11 @@ int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M) {
 }
 
 hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st) {
-    const int nb = tiled_row_blocks(a.M);
+    int nb = tiled_row_blocks(a.M);
+    // EPI_SILU has instances of 7 and 8 row blocks only: on 256 CUs an unsplit k comes with 768 rows and more, which make
+    // no shorter tiles.  With fewer CUs (a partition of the device) it comes with fewer rows, too; those are as many
+    // tiles of 7 blocks, which fit the workspace (at most 8 blocks for each tile's 256 rows).
+    if (epi == EPI_SILU && nb < 7) nb = 7;
     if (a.nMt != (a.M + 32 * nb - 1) / (32 * nb) || a.nMt * nb > a.nIb) return hipErrorInvalidValue;
     if (nb == 5) return launch_nb<5>(a, epi, st);
     if (nb == 6) return launch_nb<6>(a, epi, st);

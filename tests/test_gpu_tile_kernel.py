@@ -1,0 +1,67 @@
+"""The tile kernel's SiLU epilogue through its own launcher: with all the CUs of a whole device the library splits k at
+the row counts whose tiles are shorter than seven row blocks, so no chain step reaches this epilogue there; on a partition
+of the device, with fewer CUs, it does."""
+import ctypes as C
+
+import pytest
+import torch
+
+import paper_2605_18817_amd as mrp
+
+pytestmark = pytest.mark.gpu
+
+EPI_SILU = 2
+
+
+class _Seg(C.Structure):
+    _fields_ = [("base", C.c_void_p), ("plane_stride", C.c_long), ("nkq", C.c_int), ("nplanes", C.c_int)]
+
+
+class _Args(C.Structure):
+    _fields_ = ([("Wp", C.c_void_p)] + [(n, C.c_int) for n in ("KBw", "n_rb", "nIb", "M", "R")] + [("seg", _Seg * 2)]
+                + [(n, C.c_int) for n in ("nseg", "nMt", "nVt", "nKs")]
+                + [("out", C.c_void_p), ("planes", C.c_void_p), ("plane_stride", C.c_long)]
+                + [(n, C.c_void_p) for n in ("z", "pm", "ps", "pi")])
+
+
+def _plane_index(rows, cols, nIb):
+    """Position of entry (row, col) in an activation plane [k block][row block][lane][8]."""
+    r, c = torch.arange(rows, device="cuda").unsqueeze(1), torch.arange(cols, device="cuda").unsqueeze(0)
+    return (((c >> 4) * nIb + (r >> 5)) * 64 + (r & 31) + 32 * ((c >> 3) & 1)) * 8 + (c & 7)
+
+
+@pytest.mark.parametrize("M", [1, 300, 513, 576, 577, 768])     # 5, 5, 6, 6, 7 and 8 row blocks fit the rows
+def test_silu_epilogue_at_every_tile_height(M):
+    lib = mrp.load_library()
+    row_blocks = getattr(lib, "_ZN3mrp16tiled_row_blocksEi")(M)
+    launch = getattr(lib, "_ZN3mrp17launch_tiled_gemmERKNS_13TiledGemmArgsEiP12ihipStream_t")
+    R, K, nIb = 256, 256, -(-M // 256) * 8
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M)
+    x = torch.empty(M, K, device="cuda").normal_(0, 1, generator=gen)
+    w = torch.empty(R, K, dtype=torch.bfloat16, device="cuda").normal_(0, 0.05, generator=gen)
+    planes = torch.zeros(2, K // 16 * nIb * 512, dtype=torch.float16, device="cuda")
+    idx = _plane_index(M, K, nIb)
+    hi = x.half()
+    planes[0, idx], planes[1, idx] = hi, (x - hi.float()).half()
+    out = torch.full((2, R // 16 * nIb * 512), 7.0, dtype=torch.float16, device="cuda")
+    Wp = mrp.pack_weight(w, body=True)
+    a = _Args()
+    a.Wp, a.KBw, a.n_rb, a.nIb, a.M, a.R = Wp.data_ptr(), K // 16, R // 32, nIb, M, R
+    a.seg[0] = _Seg(planes.data_ptr(), planes.shape[1] // 8, K // 64, 2)
+    a.nseg, a.nMt, a.nVt, a.nKs = 1, -(-M // (32 * row_blocks)), 1, 1
+    a.planes, a.plane_stride = out.data_ptr(), out.shape[1] // 8
+    assert launch(C.byref(a), EPI_SILU, C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    torch.cuda.synchronize()
+    xe, we = planes[0, idx].double() + planes[1, idx].double(), w.half().double()
+    s = xe @ we.t()
+    ref = s * torch.sigmoid(s)
+    idx_o = _plane_index(M, R, nIb)
+    got = out[0, idx_o].double() + out[1, idx_o].double()
+    # fp32 sums: two planes of K / 16 MFMAs of 16 products, each addition within 2^-24 of what was summed so far; SiLU's
+    # slope is below 1.1 and its own evaluation a few ulp; hi + lo holds 2^-22 of the value, 2^-25 where lo is subnormal
+    bound = 1.1 * (2 * K // 16 + 16) * 2.0 ** -24 * (xe.abs() @ we.abs().t()) + 2.0 ** -20 * ref.abs() + 2.0 ** -24
+    assert bool(((got - ref).abs() <= bound).all()), float(((got - ref).abs() / bound).max())
+    rest = torch.ones_like(out[0], dtype=torch.bool)
+    rest[idx_o] = False
+    assert bool((out[:, rest] == 7.0).all())                      # rows past M are not written
