@@ -382,7 +382,7 @@ int mrp_residual_rms(mrp_ctx *c, void *stream, int n_blocks, int S, long N, cons
         return fail(c, MRP_ERR_ALIGN, "mrp_residual_rms: pointers must be aligned to their element size");
     if (n_blocks == 0) return MRP_OK;
     HIP_TRY(c, launch_residual_rms(n_blocks, S, N, X, dtype == MRP_DTYPE_BF16, c->rms_part, rms_pair, rms_delta,
-                                   static_cast<hipStream_t>(stream)));
+                                   c->nCU, static_cast<hipStream_t>(stream)));
     return MRP_OK;
 }
 

@@ -384,7 +384,9 @@ size_t residual_rms_part_bytes();
 int residual_rms_max_blocks();
 bool residual_rms_supported(int S);
 hipError_t launch_residual_rms(int n_blocks, int S, long N, const void *X, bool bf16, double *part,
-                               double *rms_pair, double *rms_delta, hipStream_t st);
+                               double *rms_pair, double *rms_delta, int nCU, hipStream_t st);
+// workgroups per block of `ntiles` 512-entry tiles
+int residual_rms_workgroups(int n_blocks, int S, long ntiles, int nCU);
 
 int kl_tiles(int V);
 hipError_t launch_kl_loss(int M, int V, const float *teacher, const float *student, const uint8_t *mask, float scale,

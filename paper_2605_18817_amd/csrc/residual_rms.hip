@@ -7,12 +7,13 @@
 // the mean over blocks and offsets t for every r.
 //
 // All S (S + 1) / 2 sums come out of ONE pass over the states: a workgroup stages a 512-entry
-// tile of all S states in LDS (HBM traffic = every state once), turned to fp64 on the way in (once
-// per entry; with the tile in fp32 each of the four waves converted all of it: 352 us against 337
-// for 8 blocks of 17 x 2430976), and the four waves split the jobs (job p goes to wave p mod
-// 4), so a wave carries at most 39 fp64 accumulators.  Workgroup partials are summed in
+// tile of all S states in LDS (HBM traffic = every state once; 17 states turned to fp64 on the way
+// in, once per entry instead of once per wave), and the four waves split the jobs (job p goes to
+// wave p mod 4), so a wave carries at most 39 fp64 accumulators.  Workgroup partials are summed in
 // workgroup order by a second kernel: the result does not depend on timing.
 #include "mrp_kernels.h"
+
+#include <type_traits>
 
 namespace mrp {
 
@@ -20,6 +21,12 @@ namespace {
 
 constexpr int RT = 512;            // entries of one state per tile
 constexpr int RMS_MAX_PART = 4096; // workgroup partials the context's buffer holds (all blocks together)
+
+// Entry of a staged tile: fp64 (converted once, on the way into LDS) for 17 states, where the arithmetic decides; for
+// fewer states the stream does, and the wider tile only costs LDS bandwidth (5 states, 43 blocks of 607744 bf16 entries
+// with 4096 workgroups: 77 us in fp32, 85 in fp64; 9 states, 57 of 402056: 206 against 209)
+template <int S>
+using TileT = std::conditional_t<S == 17, double, float>;
 
 // job (r, t): r = 0 is the plain magnitude of state t, r > 0 the pair (t, t + r)
 __host__ __device__ constexpr int job_index(int S, int r, int t) { return r * S - r * (r - 1) / 2 + t; }
@@ -47,7 +54,7 @@ template <int S, bool BF16, bool VEC>
 __global__ __launch_bounds__(256) void rms_partial_kernel(const void *__restrict__ X, long N, int nwg,
                                                           double *__restrict__ part) {
     constexpr int J = S * (S + 1) / 2, JA = (J + 3) / 4;
-    __shared__ double tile[S][RT];
+    __shared__ TileT<S> tile[S][RT];
     const int blk = blockIdx.y, wg = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const size_t base = (size_t)blk * S * N;
     double acc[JA];
@@ -101,16 +108,20 @@ __global__ __launch_bounds__(256) void rms_partial_kernel(const void *__restrict
             for (int n = 0; n < NV; ++n) {
                 const int idx = tid + 256 * n;
                 if (idx < S * (RT / 4)) {
-                    double2 *o = reinterpret_cast<double2 *>(&tile[idx / (RT / 4)][4 * (idx % (RT / 4))]);
-                    o[0] = make_double2((double)rv[n].x, (double)rv[n].y);
-                    o[1] = make_double2((double)rv[n].z, (double)rv[n].w);
+                    TileT<S> *o = &tile[idx / (RT / 4)][4 * (idx % (RT / 4))];
+                    if constexpr (S == 17) {
+                        reinterpret_cast<double2 *>(o)[0] = make_double2((double)rv[n].x, (double)rv[n].y);
+                        reinterpret_cast<double2 *>(o)[1] = make_double2((double)rv[n].z, (double)rv[n].w);
+                    } else {
+                        *reinterpret_cast<float4 *>(o) = rv[n];
+                    }
                 }
             }
         } else {
 #pragma unroll
             for (int n = 0; n < NV; ++n) {
                 const int idx = tid + 256 * n;
-                if (idx < S * RT) tile[idx / RT][idx % RT] = (double)rs[n];
+                if (idx < S * RT) tile[idx / RT][idx % RT] = (TileT<S>)rs[n];
             }
         }
     };
@@ -125,9 +136,10 @@ __global__ __launch_bounds__(256) void rms_partial_kernel(const void *__restrict
             double x[S][2];
 #pragma unroll
             for (int s = 0; s < S; ++s) {
-                const double2 v = *reinterpret_cast<const double2 *>(&tile[s][c2]);
-                x[s][0] = v.x;
-                x[s][1] = v.y;
+                using Pair = std::conditional_t<S == 17, double2, float2>;
+                const Pair v = *reinterpret_cast<const Pair *>(&tile[s][c2]);
+                x[s][0] = (double)v.x;
+                x[s][1] = (double)v.y;
             }
             // entries past N were staged as zeros in every state: they add nothing to any job
             switch (wave) {   // (uniform over the wave)
@@ -229,16 +241,35 @@ size_t residual_rms_part_bytes() { return (size_t)RMS_MAX_PART * (17 * 18 / 2) *
 int residual_rms_max_blocks() { return RMS_MAX_PART; }
 bool residual_rms_supported(int S) { return S == 3 || S == 5 || S == 9 || S == 17; }
 
+// Workgroups per block.  Each pays for its start and its lane reduction (about half a tile's time) and holds a slot: with
+// 17 states two are resident per CU (69 KB of LDS, 218 registers), with 9 states four (104 registers).  Those come in
+// whole rounds of resident workgroups: as many rounds as cost the fewest tile times, counting the tiles of a block that
+// its workgroups do not share evenly.  Fewer states are bound by the stream alone and short of requests in flight, so
+// they take all the partials there is room for.  Measured, us, 4096 workgroups / rule (17 states with the tile in fp32 in
+// the first figure): 17 states, fp32: 1 block of 804112 entries 38 / 28, 8 of 2430976 358 / 347, 43 of 262144 226 / 212,
+// 57 of 262144 287 / 271, 100 of 65536 152 / 132, 300 of 32768 220 / 203; 9 states: 1 of 1215488 25 / 20, 8 of 1215488 in
+// bf16 84 / 77, 57 of 402056 165 / 163.  Two workgroups per CU in all for fewer states: 5 states, 43 blocks of 607744 in
+// bf16 197 against 79 with 4096.
+int residual_rms_workgroups(int n_blocks, int S, long ntiles, int nCU) {
+    long best = RMS_MAX_PART / n_blocks, least = -1;
+    if (S >= 9) {
+        const long resident = (long)nCU * (S == 17 ? 2 : 4);
+        for (long k = 1; k * resident <= RMS_MAX_PART; ++k) {
+            long w = k * resident / n_blocks;
+            if (w > ntiles) w = ntiles;
+            if (w < 1) continue;
+            const long cost = k * (2 * ((ntiles + w - 1) / w) + 1);
+            if (least < 0 || cost < least) { least = cost; best = w; }
+        }
+    }
+    if (best > ntiles) best = ntiles;
+    return best < 1 ? 1 : (int)best;
+}
+
 hipError_t launch_residual_rms(int n_blocks, int S, long N, const void *X, bool bf16, double *part,
-                               double *rms_pair, double *rms_delta, hipStream_t st) {
+                               double *rms_pair, double *rms_delta, int nCU, hipStream_t st) {
     const long ntiles = (N + RT - 1) / RT;
-    // Workgroups per block: two per CU in all (as many as are resident), so that each pays for its start and its lane
-    // reduction once over many tiles; with more than 64 blocks that division leaves CUs idle, so several rounds of
-    // smaller workgroups.  Measured with 512 / 1024 / 4096 workgroups, S = 17: 1 block of 804112 entries 29 / 35 / 43
-    // us, 64 of 65536 91 / 92 / 111 us, 300 of 32768 302 / 232 / 228 us, 8 of 2430976 the same.
-    long nwg = (n_blocks <= 64 ? 512 : RMS_MAX_PART) / n_blocks;
-    if (nwg > ntiles) nwg = ntiles;
-    if (nwg < 1) nwg = 1;
+    const long nwg = residual_rms_workgroups(n_blocks, S, ntiles, nCU);
     const uintptr_t a = reinterpret_cast<uintptr_t>(X);
     const bool vec = (N % 4 == 0) && (a % (bf16 ? 8 : 16) == 0);
     hipError_t e;

@@ -40,3 +40,21 @@ def test_fuse_projection_keeps_its_k_parts_on_tiles(nCU, wide):
     if nCU == 256 and wide == 6:                     # the sizes it was measured at, on either side
         assert {(4, 4096), (128, 4096), (384, 4096), (512, 4096), (256, 2048), (384, 2048), (384, 5120)} <= taken
         assert not {(128, 2048), (128, 1024), (512, 1024), (4, 2176), (128, 2176)} & taken
+
+
+@pytest.mark.parametrize("S,resident", [(3, 8), (5, 8), (9, 4), (17, 2)])      # workgroups that a CU holds (LDS, registers)
+def test_residual_workgroups_fill_the_device(S, resident):
+    workgroups = _fn("_ZN3mrp23residual_rms_workgroupsEiili", C.c_int, C.c_int, C.c_int, C.c_long, C.c_int)
+    nCU, room = 256, 4096                            # partials the context's buffer holds
+    for n in [*range(1, 130), 200, 300, 400, 1000, 4095, 4096]:
+        for ntiles in (1, 2, 31, 32, 33, 128, 512, 786, 1571, 2374, 4749):
+            w = workgroups(n, S, ntiles, nCU)
+            assert 1 <= w <= ntiles and n * w <= room
+            if S < 9:
+                assert w == min(ntiles, room // n)   # requests in flight: every partial there is room for
+                continue
+            # tile times until the last workgroup is done, in whole rounds of what is resident: no more than with all
+            # the partials' room (a start and a reduction, half a tile each time, included)
+            rounds = lambda v: -(-n * v // (resident * nCU))
+            cost = lambda v: rounds(v) * (2 * -(-ntiles // v) + 1)
+            assert cost(w) <= cost(min(ntiles, room // n)), (n, ntiles, w)

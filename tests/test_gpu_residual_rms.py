@@ -55,6 +55,16 @@ def test_residual_rms_matches_oracle(ctx, S, N, nb, bf16):
     assert np.all(pair_g[:, np.tri(S, k=-1, dtype=bool)] == 0.0)
 
 
+@pytest.mark.parametrize("S,N,nb", [(17, 16000, 43), (17, 600, 300), (9, 9001, 57), (5, 700, 64)])
+def test_residual_rms_many_blocks(ctx, S, N, nb):
+    """Block counts that share the device's workgroups unevenly: several rounds, and a last tile that few entries are in."""
+    X = _states(nb, S, N, False)
+    pair_g, delta_g = _run(ctx, X, False)
+    pair_o, delta_o = _oracle(X, False)
+    np.testing.assert_allclose(pair_g, pair_o, rtol=RTOL, atol=0)
+    np.testing.assert_allclose(delta_g, delta_o, rtol=RTOL, atol=0)
+
+
 def test_residual_rms_is_deterministic_and_sees_sub_ulp_differences(ctx):
     X = _states(2, 17, 40000, False)
     a = _run(ctx, X, False)
