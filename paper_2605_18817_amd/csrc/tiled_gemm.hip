@@ -1,10 +1,10 @@
 // Tiled MFMA GEMM (bf16 operands for the LM head, fp16 for the head body) for many activation rows (the MFMA-bound regime of the MRP
-// chain):  out[i][r] (+)= sum_k W[r][k] * X[i][k]  with 256 x 256 output tiles.
+// chain):  out[i][r] (+)= sum_k W[r][k] * X[i][k]  with output tiles of up to 256 x 256.
 //
-// A workgroup of four wavefronts computes a tile of 256 weight rows x 256 activation rows (192 or 224
-// where M rows fall into as many tiles of that height);
-// each wave owns 64 weight rows x all activation rows as 2 x 8 (6, 7) MFMA 32x32x16 tiles (256
-// fp32 accumulators).  The weight fragments go from the packed layout straight into MFMA
+// A workgroup of four wavefronts computes a tile of 256 weight rows x 256 activation rows (160, 192 or
+// 224 where M rows fall into as many tiles of that height);
+// each wave owns 64 weight rows x all activation rows as 2 x 8 (5, 6, 7) MFMA 32x32x16 tiles (up to
+// 256 fp32 accumulators).  The weight fragments go from the packed layout straight into MFMA
 // operand registers (one contiguous 1 KiB read per 32 rows x 16 k); no two waves load the
 // same fragment.  The activation operand arrives in LDS by LDS-direct loads (three 32 KiB
 // stages) and every wave reads all of it.  What limits this kernel is how many memory
@@ -181,12 +181,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // among the MFMAs of the current one (one wave per SIMD: nothing else hides them)
     u32x4 bf[2][NB];
 
-    // Logit tile of the epilogue (EPI_LM): 8 slices of 32 activation rows x this wave's 64 vocabulary
+    // Logit tile of the epilogue (EPI_LM): NB slices of 32 activation rows x this wave's 64 vocabulary
     // entries, 8 16-byte pieces per lane each.  A piece is always fetched (addresses clamped into
     // the matrix; what lies outside is never used), so the number of requests per step is fixed.
     // The first two slices are requested during the last two k steps, in place of the operand
-    // requests those steps no longer need (more would not fit the registers next to the k loop's).
+    // requests those steps no longer need (more would not fit the registers next to the k loop's; RAG with eight row
+    // blocks has room for the first only: with the second it spills ten registers, 108 -> 111 us at 512 rows, d = 1024,
+    // V = 50257).
     constexpr int ZD = RAG ? 2 : 6;             // slice buffers: five (one) slices in flight ahead of the one added
+    constexpr int ZE = RAG && NB == 8 ? 1 : 2;  // slices requested in the k loop
     f32x4 zc[ZD][8];
     const int zv_lane = (rb0 + wave * 2) * 32 + 4 * lh;     // + 32 v2 + 8 q
     auto zpiece = [&](int ib, int pc) __attribute__((always_inline)) -> f32x4 {
@@ -244,7 +247,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                     } else if constexpr (EPI == EPI_LM) {
                         if (rq < 8) {                      // second to last step: slice 0; last step: slice 1
                             if constexpr (role == 1) zc[0][rq] = zpiece(0, rq);
-                            else zc[1][rq] = zpiece(1, rq);
+                            else if constexpr (ZE == 2) zc[1][rq] = zpiece(1, rq);
                         }
                     }
                 }
@@ -264,8 +267,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        // the next step's operands (requested one step ago) are there once at most this step's 16
-        // requests are pending; the second to last step requests 8 logit pieces (none in the partial-sum kernel)
+        // the next step's operands (requested one step ago) are there once at most this step's
+        // NB + 8 requests are pending; the second to last step requests 8 logit pieces (none in the partial-sum kernel)
         if constexpr (role == 1) __builtin_amdgcn_s_waitcnt(EPI == EPI_LM ? 0x0F78 : 0x0F70);   // vmcnt(8) / vmcnt(0)
         else if constexpr (role == 0) TG_WAIT_PREV();
         tg_barrier();
@@ -344,22 +347,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 }
             }
     } else {
-        // per wave: 256 activation rows x 64 vocabulary entries.  The logit tile is added here, one
+        // per wave: 32 NB activation rows x 64 vocabulary entries.  The logit tile is added here, one
         // 32-row slice (32 registers) at a time; the row reduction over v runs in registers.
         float *red_m = reinterpret_cast<float *>(tg_stage0);       // [4 waves][256 rows] (the stages are dead)
         float *red_s = red_m + 1024;
         int *red_i = reinterpret_cast<int *>(red_s + 1024);
-        // Slices 0 and 1 were requested during the last two k steps; five slices are kept in flight
+        // The first ZE slices were requested during the last two k steps; ZD - 1 slices are kept in flight
         // ahead of the one being added; the sum is formed in place in the fetched registers.
         auto zfetch = [&](int ib, f32x4 (&dst)[8]) __attribute__((always_inline)) {
 #pragma unroll
             for (int pc = 0; pc < 8; ++pc) dst[pc] = zpiece(ib, pc);
         };
 #pragma unroll
-        for (int n = 2; n < ZD - 1; ++n) zfetch(n, zc[n]);
+        for (int n = ZE; n < ZD - 1; ++n) zfetch(n, zc[n]);
 #pragma unroll
         for (int ib = 0; ib < NB; ++ib) {
-            if (ib + ZD - 1 < NB) zfetch(ib + ZD - 1, zc[(ib + ZD - 1) % ZD]);
+            if (ib + ZD - 1 >= ZE && ib + ZD - 1 < NB) zfetch(ib + ZD - 1, zc[(ib + ZD - 1) % ZD]);
             const int i = (ib0 + ib) * 32 + lne;
             f32x4(&xs)[8] = zc[ib % ZD];
             Part pt = part_identity();
