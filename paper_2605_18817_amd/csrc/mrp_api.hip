@@ -143,6 +143,8 @@ int pick_ksplit(int nVt, int nMg, int G, size_t part_rows, int M) {
 bool body_on_tiles(int M, int Kc) { return M >= 768 || (Kc > 2048 && M > 512); }
 bool small_rows_kernel(int M, int Kc) { return !body_on_tiles(M, Kc); }
 
+}  // namespace
+
 // LM head of M rows on the tile kernel?  The persistent kernel streams W_lm once through all CUs and is bound by that
 // stream up to 128 rows; its 256-row form pays for 256 rows whatever M is, and rows beyond stream W_lm a second time.
 // The tile kernel pays for the 32-row blocks it needs, in whole rounds of one tile per CU.  Measured (us, persistent / tile
@@ -153,7 +155,7 @@ bool small_rows_kernel(int M, int Kc) { return !body_on_tiles(M, Kc); }
 // 8192: 49 / 41, 49 / 46, 50 / 58, 67 / 42.  Those fill three quarters of their rounds or have one round only; the
 // tile kernel's time goes with the rounds and the persistent kernel's with V, so where a round is emptier than that the
 // margins above are used up (narrow operands, whose margins are smaller: seven eighths).
-bool lm_on_tiles(int M, int d, int V, int nCU) {
+bool mrp::lm_on_tiles(int M, int d, int V, int nCU) {
     if (M <= 128 || M > 512) return M > 512;
     const long tiles = (long)tiled_row_tiles(M) * ((V + 255) / 256), slots = (tiles + nCU - 1) / nCU * nCU;
     const bool full = d < 1024 && M > 256 ? 8 * tiles >= 7 * slots : 4 * tiles >= 3 * slots;
@@ -170,11 +172,14 @@ bool lm_on_tiles(int M, int d, int V, int nCU) {
 // to fetch ahead.  Measured per step of three heads with a small LM head (V = 4096), 32- / 16-feature tiles: d = 2048 177 /
 // 136 us at 16 rows, 180 / 152 at 32, 190 / 168 at 64; d = 4096 240 / 203 at 4, 285 / 246 at 32; d = 1024 105 / 99.5 at 4,
 // 108.5 / 114 at 32; d = 256 81 / 85 at 4.
-int small_tile_blocks(int R, int Kc, int M, int nCU) {
+int mrp::small_tile_blocks(int R, int Kc, int M, int nCU) {
     const int nrt = (M + 31) / 32;
     if ((Kc >= 2048 || (Kc >= 1024 && M <= 16)) && 2 * (R / 32) * nrt <= nCU) return 0;
     return (R % 64 == 0 && (R / 32) * nrt > nCU && nrt >= 6) ? 2 : 1;
 }
+
+namespace {
+
 int small_tile_features(int nf) { return nf == 0 ? 16 : 32 * nf; }
 
 // out[ks][M][R] = partial sums of W [R][Kc] (packed) times the activation planes; returns the number

@@ -267,6 +267,11 @@ inline int tiled_row_tiles(int M) { return (M + 32 * tiled_row_blocks(M) - 1) / 
 #endif
 // k parts for a partial-sum tile GEMM with `tiles` output tiles and `nsteps` k steps, writing at most `cap_rows` rows
 int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M);
+// ---- which kernel (mrp_api.hip) ----
+// Is the LM head of M rows on the tile kernel (or the persistent one)?
+bool lm_on_tiles(int M, int d, int V, int nCU);
+// Weight row blocks per tile of the small-row GEMM kernels for R outputs of Kc inputs (1 or 2; 0: 16 features)
+int small_tile_blocks(int R, int Kc, int M, int nCU);
 // k parts of the transformer body's fuse projection of M rows on the tile kernel; 0: it is the streaming kernel's
 int fuse_tile_parts(int M, int d, int nplanes, int nCU, size_t part_rows, size_t cap_rows);
 hipError_t launch_lm_persist(const LmPersistArgs &a, hipStream_t st);

@@ -19,6 +19,7 @@ parity rule:
 """
 from __future__ import annotations
 
+import ctypes
 from dataclasses import dataclass, field
 from types import SimpleNamespace
 from typing import List, Optional, Sequence
@@ -168,6 +169,25 @@ def oracle_chain(prob: Problem, z0_rows: np.ndarray, hrun_rows: np.ndarray, rcfg
                           draft_tok=dtok, masked=o.masked, revealed_at=o.revealed_at, cond_tok=o.cond_tok,
                           protect_pos=o.protect_pos, x_tok=o.x_tok, ptok=ptok)
     return OracleRun(out, snaps, pre0)
+
+
+def library_rule(mangled: str, restype, *argtypes):
+    """One of the library's host functions that choose between kernels by size (C++ linkage, not part of the C ABI)."""
+    f = getattr(mrp.load_library(), mangled)
+    f.restype, f.argtypes = restype, list(argtypes)
+    return f
+
+
+def lm_head_on_tiles(M: int, d: int, V: int) -> bool:
+    """Which kernel the LM head takes on this device: the tile kernel, or the persistent one."""
+    rule = library_rule("_ZN3mrp11lm_on_tilesEiiii", ctypes.c_bool, *[ctypes.c_int] * 4)
+    return rule(M, d, V, torch.cuda.get_device_properties(0).multi_processor_count)
+
+
+def small_tile_features(R: int, Kc: int, M: int) -> int:
+    """Features per tile of the small-row GEMM kernels on this device."""
+    rule = library_rule("_ZN3mrp17small_tile_blocksEiiii", ctypes.c_int, *[ctypes.c_int] * 4)
+    return {0: 16, 1: 32, 2: 64}[rule(R, Kc, M, torch.cuda.get_device_properties(0).multi_processor_count)]
 
 
 def head_view(run: OracleRun, k: int) -> OracleRun:

@@ -4,13 +4,7 @@ import ctypes as C
 
 import pytest
 
-import paper_2605_18817_amd as mrp
-
-
-def _fn(mangled, restype, *argtypes):
-    f = getattr(mrp.load_library(), mangled)
-    f.restype, f.argtypes = restype, list(argtypes)
-    return f
+from harness import library_rule
 
 
 def _stream_parts(M, d, part_rows):
@@ -24,7 +18,7 @@ def _stream_parts(M, d, part_rows):
 @pytest.mark.parametrize("nCU", [32, 256])
 @pytest.mark.parametrize("wide", [1, 6])             # the layers' partial-sum buffer holds that many times as many rows
 def test_fuse_projection_keeps_its_k_parts_on_tiles(nCU, wide):
-    fuse_parts = _fn("_ZN3mrp15fuse_tile_partsEiiiimm", C.c_int, *[C.c_int] * 4, C.c_size_t, C.c_size_t)
+    fuse_parts = library_rule("_ZN3mrp15fuse_tile_partsEiiiimm", C.c_int, *[C.c_int] * 4, C.c_size_t, C.c_size_t)
     taken = set()
     for M in [*range(1, 20), *range(20, 768, 7), 128, 129, 192, 256, 257, 384, 512, 513]:
         part_rows = 16 * M if M <= 128 else 4096
@@ -44,7 +38,7 @@ def test_fuse_projection_keeps_its_k_parts_on_tiles(nCU, wide):
 
 @pytest.mark.parametrize("S,resident", [(3, 8), (5, 8), (9, 4), (17, 2)])      # workgroups that a CU holds (LDS, registers)
 def test_residual_workgroups_fill_the_device(S, resident):
-    workgroups = _fn("_ZN3mrp23residual_rms_workgroupsEiili", C.c_int, C.c_int, C.c_int, C.c_long, C.c_int)
+    workgroups = library_rule("_ZN3mrp23residual_rms_workgroupsEiili", C.c_int, C.c_int, C.c_int, C.c_long, C.c_int)
     nCU, room = 256, 4096                            # partials the context's buffer holds
     for n in [*range(1, 130), 200, 300, 400, 1000, 4095, 4096]:
         for ntiles in (1, 2, 31, 32, 33, 128, 512, 786, 1571, 2374, 4749):

@@ -7,7 +7,8 @@ import torch
 
 import mrp_inputs as mi
 import paper_2605_18817_amd as mrp
-from harness import (Problem, compare_chain, dev_bits, gpu_chain, io_to_host, oracle_chain)
+from harness import (Problem, compare_chain, dev_bits, gpu_chain, io_to_host, lm_head_on_tiles, oracle_chain,
+                     small_tile_features)
 
 pytestmark = pytest.mark.gpu
 
@@ -113,7 +114,7 @@ def test_tile_major_partials_with_odd_and_long_blocks(B, L):
 
 
 def test_many_rows_wide_tile_static_top2():
-    # M = 336 > 128 selects the 256-row activation tile (two row groups, the second ragged)
+    # M = 336: the LM head in two row tiles of 192 rows, the second ragged
     cfg = mi.straddling(mi.config(0, d=256, V=2048 + 64, B=21, L=16))
     rcfg = mrp.RevealCfg(tau=1.0, r_min=2)           # static decoding: the two most confident per state
     prob, g, o, stats = _free_run(cfg, rcfg)
@@ -122,12 +123,12 @@ def test_many_rows_wide_tile_static_top2():
 
 
 def test_tiled_path_ragged_tiles():
-    # M = 800 >= 768 selects the 256 x 256 tiled kernels: 4 row tiles (the last with 32 rows),
+    # M = 800 >= 768 selects the tile kernel throughout: 4 row tiles of 224 rows (the last with 128),
     # V = 1000 -> 4 vocabulary tiles (the last with 232 entries, 8 of them in a partial 32-block)
     cfg = mi.straddling(mi.config(0, d=128, V=1000, B=50, L=16))
     prob, g, o, stats = _free_run(cfg, mrp.RevealCfg(tau=0.5, tau_remask=0.3))
     prob.close()
-    # same row count with a vocabulary that is not a multiple of 4: tiled head GEMMs, scalar LM-head path
+    # 768 rows (three whole tiles) and a vocabulary that is not a multiple of 4: rows on 8-byte boundaries
     cfg = mi.straddling(mi.config(0, d=256, V=1030, B=48, L=16, K=2))
     prob, g, o, stats = _free_run(cfg, mrp.RevealCfg(tau=0.5))
     prob.close()
@@ -248,21 +249,59 @@ def test_empty_batch_and_errors():
 
 
 @pytest.mark.parametrize("d,B,L,K", [
-    (256, 129, 1, 2),    # one row past the 128-row LM-head form: its 256-row form, small-row head GEMMs (5 row tiles)
-    (256, 16, 16, 2),    # 256 rows: the 256-row form filled exactly
-    (256, 257, 1, 1),    # two LM-head launches (256 + 1 rows), 9 row tiles: 64-feature tiles
-    (256, 32, 16, 1),    # 512 rows: two full LM-head launches
-    (256, 513, 1, 1),    # one row past: the tile kernel for the LM head, small-row kernels for the body
+    (256, 129, 1, 2),    # one row past the persistent kernel's 128-row form: the tile kernel (160-row tiles), five row tiles of the body
+    (256, 16, 16, 2),    # 256 rows: the persistent kernel's 256-row form filled exactly
+    (256, 257, 1, 1),    # the tile kernel again (two 160-row tiles); nine row tiles of the body: 64-feature tiles
+    (256, 32, 16, 1),    # 512 rows: two tiles of 256
+    (256, 513, 1, 1),    # one row past: three tiles of 192
     (256, 59, 13, 1),    # 767 rows, the last row count of the small-row head body at this width
-    (4096, 25, 8, 2),    # wide model, 200 rows: 64-feature tiles, 7 row tiles, the last ragged
+    (4096, 25, 8, 2),    # wide model, 200 rows: persistent kernel (17 tiles leave their round empty); 64-feature tiles, 7 row tiles
     (4096, 37, 16, 1),   # wide model, 592 rows: tile kernel with k split for the head body (48 tiles x 4 parts)
 ])
 def test_row_counts_where_the_kernels_change(d, B, L, K):
-    """Row counts on both sides of every switch between kernel families (LM head: 128 / 256 / 512 rows;
-    head body: 768 rows, 512 for d > 2048; 32- against 64-feature tiles), each against the oracle."""
+    """Row counts on both sides of the switches by rows alone (LM head: 128 / 512 rows; head body: 768 rows, 512 for
+    d > 2048; 32- against 64-feature tiles), each against the oracle.  The switches that go by width or vocabulary, too:
+    the tests below."""
     V = 1028 if d > 256 else 4096 + 36
     cfg = mi.straddling(mi.config(0, d=d, V=V, B=B, L=L, K=K))
     prob, g, o, stats = _free_run(cfg, mrp.RevealCfg(tau=0.9, tau_remask=0.5), seqs=list(range(0, B, max(1, B // 5))))
+    prob.close()
+
+
+# Vocabularies are chosen by how full they leave the rounds of one tile per CU on 256 CUs
+@pytest.mark.parametrize("d,B,L,V,tiles", [
+    (256, 160, 1, 1028, True),          # up to 160 rows any vocabulary of one round
+    (256, 161, 1, 1028, False),         # from 161 narrow operands stay on the persistent kernel ...
+    (128, 257, 1, 35072, False),        # ... and past 256 where 274 tiles leave the second round empty: 256 + 1 rows
+    (128, 32, 16, 35072, False),        # 512 rows: two full launches
+    (256, 17, 16, 57344, True),         # 272 rows, 448 tiles of 512 slots: seven eighths (d < 1024)
+    (256, 17, 16, 57088, False),        # 446
+    (1024, 17, 16, 49152, True),        # 384 tiles: three quarters
+    (1024, 17, 16, 48896, False),       # 382; two launches
+    (2048, 11, 16, 49152, True),        # 176 rows, d = 2048: 192 tiles of 256
+    (2048, 11, 16, 48896, False),       # 191
+])
+def test_lm_head_kernel_by_width_and_vocabulary(d, B, L, V, tiles):
+    """129 to 512 rows: both sides of every switch between the tile kernel and the persistent kernel (in one launch up to
+    256 rows, in two beyond); first and last sequence compared (first and last row group)."""
+    assert lm_head_on_tiles(B * L, d, V) == tiles
+    cfg = mi.straddling(mi.config(0, d=d, V=V, B=B, L=L, K=1))
+    prob, g, o, stats = _free_run(cfg, mrp.RevealCfg(tau=2.0), seqs=[0, B - 1])
+    prob.close()
+
+
+@pytest.mark.parametrize("d,B,L,features", [
+    (1024, 4, 4, 16), (1024, 17, 1, 32),                       # 16 rows | 17
+    (2048, 4, 4, 16), (2048, 17, 1, 16), (2048, 4, 16, 16),    # one half tile of rows; two, the second with one row; 64 rows
+    (2048, 13, 5, 32),                                         # 65 rows: three row tiles of 64 would pass the CU count
+    (4096, 8, 4, 16), (4096, 11, 3, 32),                       # 32 rows | 33
+])
+def test_head_tiles_of_16_features(d, B, L, features):
+    """Both sides of the switch between 16- and 32-feature tiles of the head GEMMs, two heads (the second takes both planes
+    of the running hidden state), every sequence compared."""
+    assert small_tile_features(d, d, B * L) == features
+    cfg = mi.straddling(mi.config(0, d=d, V=1028, B=B, L=L, K=2))
+    prob, g, o, stats = _free_run(cfg, mrp.RevealCfg(tau=2.0))
     prob.close()
 
 
@@ -278,7 +317,8 @@ def test_row_counts_where_the_kernels_change(d, B, L, K):
                                    (130, 5, 1031),    # 650 rows, a row ends 3 entries into a piece
                                    (600, 1, 6)])      # a row shorter than two pieces
 def test_vocabulary_not_a_multiple_of_four(B, L, V):
-    """Rows of the logit state start on any 4-byte boundary: every LM-head form, and nothing written past the end."""
+    """Rows of the logit state start on any 4-byte boundary: the persistent kernel's forms and the tile kernel at two k steps
+    (more of them, and its tallest tiles: below), and nothing written past the end."""
     cfg = mi.straddling(mi.config(0, d=128, V=V, B=B, L=L, K=2))
     prob = Problem(cfg)
     rcfg = mrp.RevealCfg(tau=0.9, tau_remask=0.5)
