@@ -27,7 +27,7 @@ def _verify_case(ctx, B, L, V, K, verify, pos, tok):
     return a_o
 
 
-@pytest.mark.parametrize("V", [16, 8192 + 4, 20000 + 3])     # one chunk, ragged chunks, scalar path
+@pytest.mark.parametrize("V", [16, 8192 + 4, 20000 + 3])     # one chunk, ragged chunks, rows that end inside a 16-byte piece
 def test_verify_accept_patterns(V):
     L, K = 8, 3
     pats = list(itertools.product([0, 1], repeat=K))
