@@ -3,16 +3,23 @@
 //
 // A workgroup of four wavefronts computes a tile of 256 weight rows x 256 activation rows (160, 192 or
 // 224 where M rows fall into as many tiles of that height);
-// each wave owns 64 weight rows x all activation rows as 2 x 8 (5, 6, 7) MFMA 32x32x16 tiles (up to
+// each wave owns 64 weight rows x all activation rows as 4 x 16 (10, 12, 14) MFMA 16x16x32 tiles (up to
 // 256 fp32 accumulators).  The weight fragments go from the packed layout straight into MFMA
-// operand registers (one contiguous 1 KiB read per 32 rows x 16 k); no two waves load the
-// same fragment.  The activation operand arrives in LDS by LDS-direct loads (three 32 KiB
-// stages) and every wave reads all of it.  What limits this kernel is how many memory
-// requests the CU's address unit takes per k step next to the MFMAs of four single-wave
-// SIMDs, so the layout is the one with the fewest request bytes (64 KiB per step), operands
-// are requested two steps ahead, and the requests are spread between the MFMAs.  As in the
-// streaming kernels the weight fragment is the MFMA "A" operand, so a lane's accumulators of
-// a sub-tile are 16 outputs of one activation row.
+// operand registers (the same 1 KiB blocks of 32 rows x 16 k, a fragment of 16 rows x 32 k being four 256-byte
+// runs of two of them); no two waves load the same fragment.  The activation operand arrives in LDS by LDS-direct
+// loads (three 32 KiB stages) and every wave reads all of it.  As in the streaming kernels the weight fragment is
+// the MFMA "A" operand, so a lane's accumulators of a sub-tile are 4 consecutive outputs of one activation row.
+//
+// What limits this kernel: the chip's power and the memory requests of a k step.  With zero weights the LM head of
+// 4096 rows (d = 4096, V = 151936) takes 3.71 ms, with random ones 4.28 ms: the clock falls under the load.  So it
+// takes the MFMA that costs the least per product: a loop of LDS fragment reads and MFMAs reaches 1.73 PFLOP/s on random
+// data with 32x32x16 (which passes its accumulators through the core twice as often) and 1.93 with 16x16x32 (2.45 both
+// on zeros).  Without its epilogue that LM head takes 3.64 ms (1.4 PFLOP/s; without the k loop's memory requests
+// 2.84 ms, without its LDS reads as well 2.55 ms): the layout is the one with the fewest request bytes (64 KiB per
+// step), operands are requested two steps ahead, and the requests are spread between the MFMAs.
+// Per head, 32x32x16 / now: 4.66 / 4.27 ms at 4096 rows, 1.22 / 1.12 at 1024, 0.78 / 0.72 at 592, 0.50 / 0.475 at 384
+// (d = 4096); of that the MFMA shape 4 %, one wait for the LDS reads per phase 1.5 %, the place of the barrier 1.5 %, the order of
+// the MFMAs 0.7 %.
 //
 // Workgroups are ordered so that the 32 CUs of one XCD work at the same time on a
 // block of 4 (activation) x 8 (weight) tiles and share its operand slices in that
@@ -33,15 +40,18 @@ namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));   // native vector: arrays of it stay in registers
-// One 32x32x16 matrix multiply-accumulate on 16-byte operand fragments: the partial-sum GEMMs of the
+// One 16x16x32 matrix multiply-accumulate on 16-byte operand fragments: the partial-sum GEMMs of the
 // head body take fp16 operands (weights converted at pack time, activations as fp16 planes), the LM
-// head bf16 ones.
+// head bf16 ones.  The accumulator stays where it is (with the builtin the compiler gives sources and result
+// different registers and moves accumulators about), and volatile statements keep their order against the memory
+// requests.  Nothing here waits: operands must come from loads, and accumulators may be read after
+// acc_ready() only.
 template <int EPI>
-__device__ __forceinline__ f32x16 mma_frag(const u32x4 &w, const u32x4 &x, const f32x16 &c) {
+__device__ __forceinline__ void mma_frag(f32x4 &c, const u32x4 &w, const u32x4 &x) {
     if constexpr (EPI != EPI_LM)
-        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, w), __builtin_bit_cast(f16x8, x), c, 0, 0, 0);
+        asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
     else
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x), c, 0, 0, 0);
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
 }
 
 constexpr int TG_KB = 4;                    // 16-wide k blocks per step (64 k)
@@ -62,6 +72,25 @@ typedef __attribute__((address_space(3))) void *las_ptr;
 // flight for later steps are not drained.
 __device__ __forceinline__ void tg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// A value's other copies lie in lane ^ 16, lane ^ 32 and lane ^ 48 (the four lanes of a row of a 16 x 16 tile):
+// the exchanges swap every other 16 lanes / the two halves of two registers, here of two copies of the same one.
+template <class F>
+__device__ __forceinline__ int row_combine(int x, F f) {
+    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = f(a[0], a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return f(b[0], b[1]);
+}
+__device__ __forceinline__ float row_max(float x) {
+    return __int_as_float(row_combine(__float_as_int(x), [](int p, int q) { return __float_as_int(fmaxf(__int_as_float(p), __int_as_float(q))); }));
+}
+__device__ __forceinline__ float row_sum(float x) {
+    return __int_as_float(row_combine(__float_as_int(x), [](int p, int q) { return __float_as_int(__int_as_float(p) + __int_as_float(q)); }));
+}
+__device__ __forceinline__ int row_min(int x) {
+    return row_combine(x, [](int p, int q) { return p < q ? p : q; });
+}
+
 // REM = 2 + (k steps - 2) % 3: the k steps left for the straight-line tail after the unrolled loop
 // RAG: R is not a multiple of 4 (EPI_LM), so a row of the logit state starts on any 4-byte boundary and ends inside a
 // 16-byte piece
@@ -71,7 +100,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const TiledGemmArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ln = lane & 31, lh = lane >> 5;
+    const int ln = lane & 15, lq = lane >> 4;
 
     // ---- workgroup -> tile (XCD-aware) ----
     // The tiles in an order where 32 consecutive ones are a block of up to 4 (activation) x 8 (weight) tiles go to
@@ -91,13 +120,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int rb0 = vt * 8, ib0 = mt * NB;
     const u32x4 *Wp = reinterpret_cast<const u32x4 *>(a.Wp);
 
+    // A fragment of 16 rows x 32 k is four runs of 16 chunks (256 bytes) of two packed blocks: the lane's chunk in it
+    // (for activations, whose next k block lies NB blocks on, frag_x)
+    const int frag_w = ln + 32 * (lq & 1) + 64 * (lq >> 1), frag_x = ln + 32 * (lq & 1) + 64 * NB * (lq >> 1);
+
     // this wave's two weight row blocks (rows past the padded matrix re-read the last block)
     const u32x4 *asrc[2];
 #pragma unroll
     for (int v2 = 0; v2 < 2; ++v2) {
         int rb = rb0 + wave * 2 + v2;
         rb = rb < a.n_rb ? rb : a.n_rb - 1;
-        asrc[v2] = Wp + (size_t)rb * a.KBw * 64 + lane;
+        asrc[v2] = Wp + (size_t)rb * a.KBw * 64 + frag_w;
     }
 
     // k-step sequence: segments x (k quads) x planes
@@ -142,7 +175,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // Operands are requested two steps ahead.  Per step and wave: NB LDS-direct loads (this wave's
     // quarter of the activation stage, [k block][row block]) and 8 weight-fragment loads into the register set
     // of that step; requests complete in issue order.
-    u32x4 areg[TG_DEPTH][2][TG_KB];   // [step % 3][row block][k block]
+    u32x4 areg[TG_DEPTH][2][4];       // [step % 3][32 k][16 weight rows]
 #define TG_LOAD(st, set, stage)                                                            \
     {                                                                                      \
         int kbw_;                                                                          \
@@ -156,9 +189,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 (las_ptr)((stage) + c * 64), 16, 0, 0);                                    \
         }                                                                                  \
         __builtin_amdgcn_sched_barrier(0);                                                 \
-        _Pragma("unroll") for (int v2 = 0; v2 < 2; ++v2)                                   \
-            _Pragma("unroll") for (int kb = 0; kb < TG_KB; ++kb)                           \
-                areg[set][v2][kb] = asrc[v2][(size_t)(kbw_ + kb) * 64];                    \
+        _Pragma("unroll") for (int kp = 0; kp < 2; ++kp)                                   \
+            _Pragma("unroll") for (int q = 0; q < 4; ++q)                                  \
+                areg[set][kp][q] = asrc[q >> 1][(size_t)(kbw_ + 2 * kp) * 64 + 16 * (q & 1)]; \
     }
     // the group requested one step ago is complete when at most the youngest group (NB + 8) is pending
     constexpr int NREQ = NB + 8;
@@ -167,19 +200,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     TG_LOAD(0, 0, tg_stage0)
     TG_LOAD(1, 1, tg_stage1)
 
-    f32x16 acc[2][NB];
+    f32x4 acc[4][NB][2];              // [16 weight rows][32-row block][its 16 rows]
 #pragma unroll
-    for (int v2 = 0; v2 < 2; ++v2)
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[v2][ib][r] = 0.f;
+            for (int hi = 0; hi < 2; ++hi) acc[q][ib][hi] = f32x4{0.f, 0.f, 0.f, 0.f};
     TG_WAIT_PREV();
     tg_barrier();
 
-    // activation fragments are double-buffered: the LDS reads of the next k block are issued
-    // among the MFMAs of the current one (one wave per SIMD: nothing else hides them)
+    // activation fragments are double-buffered: the LDS reads of the next phase (half the rows of every row block,
+    // 32 k) are issued among the MFMAs of the current one (one wave per SIMD: nothing else hides them)
     u32x4 bf[2][NB];
+#pragma unroll
+    for (int ib = 0; ib < NB; ++ib) bf[0][ib] = tg_stage0[ib * 64 + frag_x];
+    constexpr int NBQ = (NB + 2) / 3;           // LDS reads in each of a phase's first three quarters
 
     // Logit tile of the epilogue (EPI_LM): NB slices of 32 activation rows x this wave's 64 vocabulary
     // entries, 8 16-byte pieces per lane each.  A piece is always fetched (addresses clamped into
@@ -191,10 +227,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     constexpr int ZD = RAG ? 2 : 6;             // slice buffers: five (one) slices in flight ahead of the one added
     constexpr int ZE = RAG && NB == 8 ? 1 : 2;  // slices requested in the k loop
     f32x4 zc[ZD][8];
-    const int zv_lane = (rb0 + wave * 2) * 32 + 4 * lh;     // + 32 v2 + 8 q
-    auto zpiece = [&](int ib, int pc) __attribute__((always_inline)) -> f32x4 {
-        int i = (ib0 + ib) * 32 + ln;
-        int v = zv_lane + 32 * (pc >> 2) + 8 * (pc & 3);
+    const int zv_lane = (rb0 + wave * 2) * 32 + 4 * lq;     // + 16 q
+    auto zpiece = [&](int ib, int pc) __attribute__((always_inline)) -> f32x4 {   // pc: 4 hi + q
+        int i = (ib0 + ib) * 32 + 16 * (pc >> 2) + ln;
+        int v = zv_lane + 16 * (pc & 3);
         i = i < a.M ? i : a.M - 1;
         if constexpr (RAG) {
             // (a piece that crosses the end of its row takes in the start of the next one, or starts early where that
@@ -209,41 +245,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     };
 
     // One k step.  A wave issues in order, and a memory request that finds the request queue full
-    // holds up the MFMAs behind it, so the step's NB + 8 requests are spread between its 8 NB MFMAs
+    // holds up the MFMAs behind it, so the step's NB + 8 requests are spread between its 16 NB MFMAs
     // (one ahead of every sixteenth of them but the first) instead of being issued in a burst.
     int kbw_n;
     const u32x4 *bp_n;
-    auto step = [&](auto par_c, auto role_c, const u32x4 *cur, u32x4 *after) __attribute__((always_inline)) {
+    // The workgroup meets three quarters into the step: the next step's operands (requested a step ago) are there by
+    // then, every wave has read its last fragments of this step, and the last quarter reads the next step's first ones
+    // behind its MFMAs (meeting at the end of a step, these reads are in nobody's shadow: four waves fetch 8 KiB each).
+    auto step = [&](auto par_c, auto role_c, const u32x4 *cur, const u32x4 *next, u32x4 *after) __attribute__((always_inline)) {
         constexpr int PAR = decltype(par_c)::value;   // st % 3: activation stage and weight register set
         constexpr int NS = (PAR + 2) % TG_DEPTH;      // set and stage (`after`) of step st + 2
         // 0: the operands of the step after next are still to request, 1: second to last step,
         // 2: last step
         constexpr int role = decltype(role_c)::value;
-        // (`after` was last read one step ago and every wave has passed the barrier since;
+        // (`after` was last read one step ago and every wave has met the others since;
         //  past the end the last step is re-fetched, never used)
-        constexpr bool live = true;
-        {
 #pragma unroll
-            for (int ib = 0; ib < NB; ++ib) bf[0][ib] = cur[ib * 64 + lane];
-        }
-#pragma unroll
-        for (int kb = 0; kb < TG_KB; ++kb) {
+        for (int ph = 0; ph < 4; ++ph) {               // phase: 32 k (ph / 2), rows 16 (ph % 2) .. of every row block
+            // (all of this phase's fragments are there, the last of them requested a quarter of a phase ago; without this
+            //  wait the compiler waits for every LDS read, the youngest among them, ahead of each use)
+            __builtin_amdgcn_s_waitcnt(0xC07F);        // lgkmcnt(0)
+            if (ph == 3) {
+                // the next step's operands are there once at most the requests of this step's groups 1..11 are pending
+                // (8 logit pieces in the second to last step, none there in the partial-sum kernel)
+                constexpr int NP = role == 0 ? 5 + (NB < 6 ? NB : 6) : (EPI == EPI_LM ? 8 : 0);
+                if constexpr (role < 2) __builtin_amdgcn_s_waitcnt(0x0F70 | NP);       // vmcnt(NP)
+                tg_barrier();
+            }
 #pragma unroll
             for (int g4 = 0; g4 < 4; ++g4) {
-                const int c = kb * 4 + g4;             // group 0..15
+                const int c = ph * 4 + g4;             // group 0..15
                 if (c >= 1) {                          // requests 0..14 (15 goes with group 15, too)
                     const int rq = c - 1;
                     if constexpr (role == 0) {
                         if (rq & 1) {
                             const int wl = rq >> 1;        // weight fragment 0..6 (7 below)
-                            areg[NS][wl >> 2][wl & 3] = asrc[wl >> 2][(size_t)(kbw_n + (wl & 3)) * 64];
+                            areg[NS][wl >> 2][wl & 3] = asrc[(wl >> 1) & 1][(size_t)(kbw_n + 2 * (wl >> 2)) * 64 + 16 * (wl & 1)];
                         } else if (rq >> 1 < NB) {
                             const int ch = wave + 4 * (rq >> 1);   // chunk: k block ch / NB, row block ch % NB
                             __builtin_amdgcn_global_load_lds(
                                 (gas_ptr)(bp_n + ((size_t)(ch / NB) * a.nIb + (ch % NB)) * 64 + lane),
                                 (las_ptr)(after + ch * 64), 16, 0, 0);
                         }
-                        if (c == 15) areg[NS][1][3] = asrc[1][(size_t)(kbw_n + 3) * 64];
+                        if (c == 15) areg[NS][1][3] = asrc[1][(size_t)(kbw_n + 2) * 64 + 16];
                     } else if constexpr (EPI == EPI_LM) {
                         if (rq < 8) {                      // second to last step: slice 0; last step: slice 1
                             if constexpr (role == 1) zc[0][rq] = zpiece(0, rq);
@@ -251,14 +295,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                         }
                     }
                 }
-                if (live) {
 #pragma unroll
-                    for (int ib = 2 * g4; ib < 2 * g4 + 2; ++ib)
-                        if (kb + 1 < TG_KB && ib < NB) bf[(kb + 1) & 1][ib] = cur[((kb + 1) * NB + ib) * 64 + lane];
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int ib = NBQ * g4; ib < NBQ * (g4 + 1); ++ib)
+                    if (ib < NB) {
+                        if (ph < 3) bf[(ph + 1) & 1][ib] = cur[(((ph + 1) >> 1) * 2 * NB + ib) * 64 + 16 * ((ph + 1) & 1) + frag_x];
+                        else if (role < 2) bf[0][ib] = next[ib * 64 + frag_x];
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+                // this group's share of the phase's 4 NB, in an order in which successive ones share an operand (the
+                // matrix cores run against the power limit: 1.90 PFLOP/s in a loop of LDS reads and MFMAs, 1.86 with the
+                // weight fragments in the same order every time)
 #pragma unroll
-                    for (int m = g4 * 2 * NB / 4; m < (g4 + 1) * 2 * NB / 4; ++m)      // this group's share of the 2 x NB
-                        acc[m / NB][m % NB] = mma_frag<EPI>(areg[PAR][m / NB][kb], bf[kb & 1][m % NB], acc[m / NB][m % NB]);
+                for (int m = g4 * NB; m < (g4 + 1) * NB; ++m) {
+                    const int ib = m >> 2, q = ib & 1 ? 3 - (m & 3) : m & 3;
+                    mma_frag<EPI>(acc[q][ib][ph & 1], areg[PAR][ph >> 1][q], bf[ph & 1][ib]);
                 }
                 if (c == 0 && role == 0) {   // behind the first MFMAs: where the operands of the step after next are
                     cursor_get(kbw_n, bp_n);
@@ -267,40 +317,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        // the next step's operands (requested one step ago) are there once at most this step's
-        // NB + 8 requests are pending; the second to last step requests 8 logit pieces (none in the partial-sum kernel)
-        if constexpr (role == 1) __builtin_amdgcn_s_waitcnt(EPI == EPI_LM ? 0x0F78 : 0x0F70);   // vmcnt(8) / vmcnt(0)
-        else if constexpr (role == 0) TG_WAIT_PREV();
-        tg_barrier();
     };
     {
         using P0 = std::integral_constant<int, 0>;
         using P1 = std::integral_constant<int, 1>;
         using P2 = std::integral_constant<int, 2>;
         for (int st = 0; st + TG_DEPTH <= nsteps - 2; st += TG_DEPTH) {
-            step(P0{}, P0{}, tg_stage0, tg_stage2);
-            step(P1{}, P0{}, tg_stage1, tg_stage0);
-            step(P2{}, P0{}, tg_stage2, tg_stage1);
+            step(P0{}, P0{}, tg_stage0, tg_stage1, tg_stage2);
+            step(P1{}, P0{}, tg_stage1, tg_stage2, tg_stage0);
+            step(P2{}, P0{}, tg_stage2, tg_stage0, tg_stage1);
         }
         // the last REM steps (second template argument: 0 ordinary, 1 second to last, 2 last)
         if constexpr (REM == 2) {
-            step(P0{}, P1{}, tg_stage0, tg_stage2);
-            step(P1{}, P2{}, tg_stage1, tg_stage0);
+            step(P0{}, P1{}, tg_stage0, tg_stage1, tg_stage2);
+            step(P1{}, P2{}, tg_stage1, tg_stage2, tg_stage0);
         } else if constexpr (REM == 3) {
-            step(P0{}, P0{}, tg_stage0, tg_stage2);
-            step(P1{}, P1{}, tg_stage1, tg_stage0);
-            step(P2{}, P2{}, tg_stage2, tg_stage1);
+            step(P0{}, P0{}, tg_stage0, tg_stage1, tg_stage2);
+            step(P1{}, P1{}, tg_stage1, tg_stage2, tg_stage0);
+            step(P2{}, P2{}, tg_stage2, tg_stage0, tg_stage1);
         } else {
-            step(P0{}, P0{}, tg_stage0, tg_stage2);
-            step(P1{}, P0{}, tg_stage1, tg_stage0);
-            step(P2{}, P1{}, tg_stage2, tg_stage1);
-            step(P0{}, P2{}, tg_stage0, tg_stage2);
+            step(P0{}, P0{}, tg_stage0, tg_stage1, tg_stage2);
+            step(P1{}, P0{}, tg_stage1, tg_stage2, tg_stage0);
+            step(P2{}, P1{}, tg_stage2, tg_stage0, tg_stage1);
+            step(P0{}, P2{}, tg_stage0, tg_stage1, tg_stage2);
         }
     }
 #undef TG_LOAD
 #undef TG_WAIT_PREV
 
     // ---- epilogue ----
+    // (an MFMA's result may be read 18 cycles after it was issued at the earliest; the compiler does not see the MFMAs)
+    asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+            for (int hi = 0; hi < 2; ++hi) asm volatile("" : "+a"(acc[q][ib][hi]));
     // (an opaque zero keeps the compiler from sharing the prologue's 64 tile addresses with
     // the epilogue, which would hold them in registers across the whole k loop)
     int opq = 0;
@@ -308,39 +361,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int lne = ln + opq;
     if constexpr (EPI == EPI_PARTIAL) {
 #pragma unroll
-        for (int v2 = 0; v2 < 2; ++v2)
+        for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
-            for (int ib = 0; ib < NB; ++ib) {
-                const int i = (ib0 + ib) * 32 + lne;
+            for (int hi = 0; hi < 2; ++hi) {
+                const int i = (ib0 + ib) * 32 + 16 * hi + lne;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int r = (rb0 + wave * 2 + v2) * 32 + 8 * q + 4 * lh;
+                    const int r = (rb0 + wave * 2) * 32 + 16 * q + 4 * lq;
                     if (i < a.M && r < a.R)
-                        *reinterpret_cast<float4 *>(a.out + ((size_t)ks * a.M + i) * a.R + r) = make_float4(
-                            acc[v2][ib][4 * q], acc[v2][ib][4 * q + 1], acc[v2][ib][4 * q + 2], acc[v2][ib][4 * q + 3]);
+                        *reinterpret_cast<f32x4 *>(a.out + ((size_t)ks * a.M + i) * a.R + r) = acc[q][ib][hi];
                 }
             }
     } else if constexpr (EPI == EPI_SILU) {
         // s = SiLU(tile) written as the two fp16 planes of the next GEMM's activation: a lane holds 4 of the
-        // 8 features of a 16-byte chunk (the lane ^ 32 holds the other 4), so it stores 8 bytes per plane;
-        // the 64 lanes' pieces of one (v2, ib, q) are 512 contiguous bytes
+        // 8 features of a 16-byte chunk (the lane ^ 16 holds the other 4), so it stores 8 bytes per plane;
+        // the 64 lanes' pieces of one (q, ib, hi) are two runs of 256 contiguous bytes
         uint2 *planes = reinterpret_cast<uint2 *>(a.planes);
 #pragma unroll
-        for (int v2 = 0; v2 < 2; ++v2)
+        for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
-            for (int ib = 0; ib < NB; ++ib) {
-                const int i = (ib0 + ib) * 32 + lne;
+            for (int hi = 0; hi < 2; ++hi) {
+                const int i = (ib0 + ib) * 32 + 16 * hi + lne;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int c8 = (rb0 + wave * 2 + v2) * 4 + q;
+                    const int c8 = (rb0 + wave * 2) * 4 + 2 * q + (lq >> 1);
                     if (i < a.M && c8 * 8 < a.R) {
                         uint16_t h[4], l[4];
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const float x = acc[v2][ib][4 * q + e];
+                            const float x = acc[q][ib][hi][e];
                             split2(x / (1.0f + expf(-x)), h[e], l[e]);
                         }
-                        const size_t o = 2 * act_chunk_index(i, c8, a.nIb) + lh;
+                        const size_t o = 2 * act_chunk_index(i, c8, a.nIb) + (lq & 1);
                         planes[o] = make_uint2(pack2(h[0], h[1]), pack2(h[2], h[3]));
                         planes[o + 2 * a.plane_stride] = make_uint2(pack2(l[0], l[1]), pack2(l[2], l[3]));
                     }
@@ -348,7 +400,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             }
     } else {
         // per wave: 32 NB activation rows x 64 vocabulary entries.  The logit tile is added here, one
-        // 32-row slice (32 registers) at a time; the row reduction over v runs in registers.
+        // 32-row slice (32 registers) at a time; the row reduction over v runs in registers: the maximum of a row's 64
+        // entries first (they lie in four lanes), then the sum of exponentials against it.
         float *red_m = reinterpret_cast<float *>(tg_stage0);       // [4 waves][256 rows] (the stages are dead)
         float *red_s = red_m + 1024;
         int *red_i = reinterpret_cast<int *>(red_s + 1024);
@@ -363,15 +416,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int ib = 0; ib < NB; ++ib) {
             if (ib + ZD - 1 >= ZE && ib + ZD - 1 < NB) zfetch(ib + ZD - 1, zc[(ib + ZD - 1) % ZD]);
-            const int i = (ib0 + ib) * 32 + lne;
             f32x4(&xs)[8] = zc[ib % ZD];
-            Part pt = part_identity();
 #pragma unroll
-            for (int v2 = 0; v2 < 2; ++v2)
+            for (int hi = 0; hi < 2; ++hi) {
+                const int i = (ib0 + ib) * 32 + 16 * hi + lne;
+                float m = -INFINITY;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int v = (rb0 + wave * 2 + v2) * 32 + 8 * q + 4 * lh;
-                    f32x4 &x4 = xs[v2 * 4 + q];
+                    const int v = (rb0 + wave * 2) * 32 + 16 * q + 4 * lq;
+                    f32x4 &x4 = xs[4 * hi + q];
                     if constexpr (RAG) {
                         if (v + 4 > a.R) {      // the piece with the end of the row (or past it): entry by entry
 #pragma unroll
@@ -381,10 +434,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                             }
                         }
                     }
-                    x4[0] += acc[v2][ib][4 * q + 0];
-                    x4[1] += acc[v2][ib][4 * q + 1];
-                    x4[2] += acc[v2][ib][4 * q + 2];
-                    x4[3] += acc[v2][ib][4 * q + 3];
+                    x4 += acc[q][ib][hi];
                     if constexpr (RAG) {
                         if (v + 4 <= a.R) {
                             if (i < a.M) store4(a.z + (size_t)i * a.R + v, make_float4(x4[0], x4[1], x4[2], x4[3]));
@@ -395,36 +445,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                                 if (v + e >= a.R) x4[e] = -INFINITY;      // no part of the row
                             }
                         }
-                    } else if (i < a.M && v < a.R) {
-                        *reinterpret_cast<f32x4 *>(a.z + (size_t)i * a.R + v) = x4;
+                    } else {
+                        if (i < a.M && v < a.R) *reinterpret_cast<f32x4 *>(a.z + (size_t)i * a.R + v) = x4;
+                        if (v >= a.R) x4 = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
                     }
-                    if (v < a.R) {
-                        if (x4[0] > pt.m) { pt.m = x4[0]; pt.i = v; }
-                        if (x4[1] > pt.m) { pt.m = x4[1]; pt.i = v + 1; }
-                        if (x4[2] > pt.m) { pt.m = x4[2]; pt.i = v + 2; }
-                        if (x4[3] > pt.m) { pt.m = x4[3]; pt.i = v + 3; }
-                    }
+                    m = fmaxf(fmaxf(m, fmaxf(x4[0], x4[1])), fmaxf(x4[2], x4[3]));
                 }
-            float sum = 0.f;
+                m = row_max(m);
+                int at = 0x7fffffff;
+                float sum = 0.f;
 #pragma unroll
-            for (int v2 = 0; v2 < 2; ++v2)
+                for (int q = 3; q >= 0; --q) {
+                    const int v = (rb0 + wave * 2) * 32 + 16 * q + 4 * lq;
+                    const f32x4 x4 = xs[4 * hi + q];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const bool ok = (rb0 + wave * 2 + v2) * 32 + 8 * q + 4 * lh < a.R;
-                    const f32x4 x4 = xs[v2 * 4 + q];
-                    if (ok) sum += (__expf(x4[0] - pt.m) + __expf(x4[1] - pt.m)) + (__expf(x4[2] - pt.m) + __expf(x4[3] - pt.m));
+                    for (int e = 3; e >= 0; --e) at = x4[e] == m ? v + e : at;      // (the lowest index of equal entries)
+                    sum += (__expf(x4[0] - m) + __expf(x4[1] - m)) + (__expf(x4[2] - m) + __expf(x4[3] - m));
                 }
-            pt.s = sum;
-            Part other;
-            other.m = __shfl_xor(pt.m, 32);
-            other.s = __shfl_xor(pt.s, 32);
-            other.i = __shfl_xor(pt.i, 32);
-            pt = part_merge(pt, other);
-            if (lh == 0) {
-                const int row = ib * 32 + lne;
-                red_m[wave * 256 + row] = pt.m;
-                red_s[wave * 256 + row] = pt.s;
-                red_i[wave * 256 + row] = pt.i;
+                at = row_min(m > -INFINITY ? at : 0x7fffffff);
+                sum = row_sum(sum);
+                if (lq == 0) {
+                    const int row = 32 * ib + 16 * hi + lne;
+                    red_m[wave * 256 + row] = m;
+                    red_s[wave * 256 + row] = sum;
+                    red_i[wave * 256 + row] = at;
+                }
             }
         }
         __syncthreads();
