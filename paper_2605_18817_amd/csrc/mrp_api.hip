@@ -132,14 +132,10 @@ int pick_ksplit(int nVt, int nMg, int G, size_t part_rows, int M) {
     return want < 1 ? 1 : want;
 }
 
-// Which GEMM kernel the head body (and the transformer body's projections) take for M rows and operands of
-// width Kc.  The 256 x 256 tile kernel (with its k split when the tiles are few) from 768 rows, for wide
+// Which GEMM kernel the transformer body's projections take for M rows and operands of width Kc (below; the MLP body:
+// mlp_on_tiles).  The 256 x 256 tile kernel (with its k split when the tiles are few) from 768 rows, for wide
 // operands from 513; below, the kernels that reduce their k split inside the workgroup (no partial sums in
-// memory).  Measured per head of the MLP body, small-row kernels against the tile kernel: d = 4096 153 / 156 /
-// 208 / 254 / 294 us at 192 / 256 / 384 / 512 / 640 rows against 248 / 272 / 240 / 258 / 226 us; d = 2048 63 /
-// 103 / 128 us at 256 / 512 / 640 rows against 119 / 120 / 145 us.  (The streaming kernel with its partial
-// sums is behind both: d = 2048 102 / 133 / 160 us at 256 / 512 / 640 rows, d = 4096 202 / 268 / 329 us at
-// 256 / 512 / 752 rows.)
+// memory) or the wide ones.
 bool body_on_tiles(int M, int Kc) { return M >= 768 || (Kc > 2048 && M > 512); }
 bool small_rows_kernel(int M, int Kc) { return !body_on_tiles(M, Kc); }
 
@@ -178,6 +174,42 @@ int mrp::small_tile_blocks(int R, int Kc, int M, int nCU) {
     return (R % 64 == 0 && (R / 32) * nrt > nCU && nrt >= 6) ? 2 : 1;
 }
 
+// The MLP head body's GEMMs on the tile kernel: from 768 rows, for d > 2048 from 513, and there from 129 where the
+// first GEMM's tiles and k parts find three quarters of the CUs (d = 4096, but not 2560, whose 40 k steps of a plane split
+// into 8 parts).  Measured per step of three heads with V = 4096, small-row kernels / tile kernel: d = 4096 485 / 426 us at
+// 144 rows, 549 / 491 at 192, 552 / 521 at 256, 608 / 485 at 320, 658 / 531 at 384, 832 / 638 at 512; d = 2560 285 / 354 at 192,
+// 346 / 370 at 384; d = 2048 284 / 298 at 288, 306 / 326 at 384, 346 / 377 at 512, 394 / 391 at 640; d = 1024 237 / 284 at 640.
+// (Error of u against 64 bits at 384 rows, d = 4096: 3.46e-7 / 3.08e-7 of its norm.)
+bool mrp::mlp_on_tiles(int M, int d, int nCU, size_t part_rows) {
+    if (M >= 768 || d <= 2048) return M >= 768;
+    const int tiles = tiled_row_tiles(M) * ((d + 255) / 256);
+    return M > 512 || (M > 128 && 4 * tiles * tiled_ksplit(tiles, (d / 64) * (NSPLIT + 1), nCU, part_rows, M) >= 3 * nCU);
+}
+
+// Form of the tile kernel for [M][R] partial sums of two activation planes over Kc columns: weight rows per tile, row
+// blocks and k parts, the fastest by what the forms were measured to take: a round of tiles about 6 us and, per k step,
+// 0.15 us and 10.1 ns for each of its 4 nv nb MFMAs per wave; a part's sums 2 x 4 bytes per entry at 4 TB/s.  Forms that
+// follow from it (two-plane products, us): 24576 x 4096 at 384 rows as 256 tiles of 192 x 192 114 (256 x 192: 132, three
+// quarters of a round); 4096 x 4096 at 592 rows as 64 tiles of 256 x 160 x 4 parts 37 (256 x 224: 46), at 1024 rows 128 tiles of
+// 256 x 128 x 2 parts 53 (256 x 256 x 4 parts: 59).
+TileForm mrp::two_plane_form(int M, int R, int Kc, int nCU, size_t cap_rows) {
+    const int ib = (M + 31) / 32, nIb = (ib + 7) / 8 * 8, nsteps = Kc / 32;
+    TileForm best = {8, 4, 1};
+    double best_cost = 1e300;
+    for (int nv = 4; nv >= 3; --nv)
+        for (int nb = 4; nb <= 8; ++nb) {
+            const int nMt = (ib + nb - 1) / nb, tiles = nMt * ((R + 64 * nv - 1) / (64 * nv));
+            if (nMt * nb > nIb) continue;      // (row blocks that the planes have)
+            for (int ks = 1; ks <= 16; ks *= 2) {
+                if (nsteps % ks != 0 || nsteps / ks < MRP_TILED_MIN_STEPS || (size_t)ks * M > cap_rows) break;
+                const double rounds = (tiles * ks + nCU - 1) / nCU;
+                const double cost = rounds * (nsteps / ks * (0.15 + 0.0404 * nv * nb) + 6.0) + (ks - 1) * (double)M * R * 2e-6;
+                if (cost < best_cost) { best_cost = cost; best = TileForm{nb, nv, ks}; }
+            }
+        }
+    return best;
+}
+
 namespace {
 
 int small_tile_features(int nf) { return nf == 0 ? 16 : 32 * nf; }
@@ -186,17 +218,22 @@ int small_tile_features(int nf) { return nf == 0 ? 16 : 32 * nf; }
 // of k splits written (1 for the tiled kernel) or -1 after a launch error (*err set).
 int gemm_partial(mrp_ctx *c, hipStream_t st, const void *Wp, int R, int Kc, const uint4 *act, long plane_stride,
                  int nplanes, int M, float *out, size_t out_floats, hipError_t *err) {
-    if (body_on_tiles(M, Kc) && R % 256 == 0) {
+    // On the tile kernel where the body is, and from 65 rows for weights of 20 M entries and more (measured at 96 to 512
+    // rows, wide / tile kernel with what the consumer takes longer to add up the parts: 25 M entries 23 to 55 us / 21 to 39,
+    // 101 M 64 to 204 / 54 to 158; but 17 M 18 to 37 / 19 to 37, 8 M 11 to 23 / 13 to 23).
+    if (nplanes == 2 && R % 32 == 0 && Kc % 64 == 0 &&
+        ((body_on_tiles(M, Kc) && R % 256 == 0) || (M > 64 && (size_t)R * Kc >= 20000000))) {
+        const TileForm f = two_plane_form(M, R, Kc, c->nCU, out_floats / (size_t)R);
         TiledGemmArgs tg;
         memset(&tg, 0, sizeof(tg));
         tg.Wp = static_cast<const uint4 *>(Wp);
         tg.KBw = Kc / 16; tg.n_rb = R / 32; tg.nIb = c->nIb; tg.M = M; tg.R = R;
         tg.seg[0] = TiledSeg{act, plane_stride, Kc / 64, nplanes};
         tg.nseg = 1;
-        tg.nMt = tiled_row_tiles(M); tg.nVt = R / 256;
-        tg.nKs = tiled_ksplit(tg.nMt * tg.nVt, (Kc / 64) * nplanes, c->nCU, out_floats / (size_t)R, M);
+        tg.nKs = f.ks;
+        tg.nMt = (M + 32 * f.nb - 1) / (32 * f.nb); tg.nVt = (R + 64 * f.nv - 1) / (64 * f.nv);
         tg.out = out;
-        *err = launch_tiled_gemm(tg, EPI_PARTIAL, st);
+        *err = launch_tiled_two_planes(tg, f.nb, f.nv, st);
         return *err == hipSuccess ? tg.nKs : -1;
     }
     if (small_rows_kernel(M, Kc) && M > 64 && R % 64 == 0 && nplanes <= 2) {
@@ -508,7 +545,8 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
     const int off = cfg->state_offset;
     // MLP body at small row counts: the first GEMM also reads the conditioning embeddings from the table
     // itself (no gathered copy is made) and applies the SiLU
-    const bool fused = !layers && d % 128 == 0 && small_rows_kernel(M, d);
+    const bool mlp_tiles = !layers && mlp_on_tiles(M, d, c->nCU, c->part_rows);
+    const bool fused = !layers && !mlp_tiles;
 
     SelectArgs sa;
     memset(&sa, 0, sizeof(sa));
@@ -551,7 +589,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
         const int fuse_parts = layers && !body_on_tiles(M, d)
             ? fuse_tile_parts(M, d, np_h, c->nCU, c->part_rows, c->tb_part_floats / (size_t)d) : 0;
         float *const fused_u = fuse_parts ? c->tb_part : c->PART;
-        const bool tiled = body_on_tiles(M, d) || fuse_parts;
+        const bool tiled = layers ? body_on_tiles(M, d) || fuse_parts : mlp_tiles;
         int nks1 = 1, nks2 = 1;
         bool silu_done = false;   // the first GEMM's epilogue already wrote s = SiLU(a) as activation planes
         const float *resid = nullptr;   // transformer body: residual stream added to the last projection
@@ -642,30 +680,17 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
         } else {
         if (!silu_done) HIP_TRY(c, launch_silu_split(c->PART, nks1, c->S, c->plane, c->nIb, M, d, st));
         // u = W2 s
-        if (tiled) {
-            TiledGemmArgs tg;
-            memset(&tg, 0, sizeof(tg));
-            tg.Wp = static_cast<const uint4 *>(hd.W2_packed);
-            tg.KBw = d / 16; tg.n_rb = d / 32; tg.nIb = c->nIb; tg.M = M; tg.R = d;
-            tg.seg[0] = TiledSeg{c->S, c->plane, d / 64, NSPLIT};
-            tg.nseg = 1;
-            tg.nMt = tiled_row_tiles(M); tg.nVt = (d + 255) / 256;
-            tg.nKs = tiled_ksplit(tg.nMt * tg.nVt, (d / 64) * NSPLIT, c->nCU, c->part_rows, M);
-            nks2 = tg.nKs;
-            tg.out = c->PART;
-            HIP_TRY(c, launch_tiled_gemm(tg, EPI_PARTIAL, st));
-        } else {
-            memset(&g, 0, sizeof(g));
-            g.Wp = static_cast<const uint4 *>(hd.W2_packed);
-            g.KBw = d / 16; g.n_rb = d / 32; g.nIb = c->nIb; g.M = M; g.R = d;
-            g.seg[0] = ActSeg{c->S, c->plane, nkr_d, NSPLIT};
-            g.nseg = 1;
-            g.nVt = d / WG_ROWS; g.nMg = nMg; g.G = nkr_d;
-            g.nKs = pick_ksplit(g.nVt, nMg, g.G, c->part_rows, M);
-            g.out = c->PART;
-            nks2 = g.nKs;
-            HIP_TRY(c, launch_stream_gemm(g, st));
-        }
+        TiledGemmArgs tg;
+        memset(&tg, 0, sizeof(tg));
+        const TileForm f = two_plane_form(M, d, d, c->nCU, c->part_rows);
+        tg.Wp = static_cast<const uint4 *>(hd.W2_packed);
+        tg.KBw = d / 16; tg.n_rb = d / 32; tg.nIb = c->nIb; tg.M = M; tg.R = d;
+        tg.seg[0] = TiledSeg{c->S, c->plane, d / 64, NSPLIT};
+        tg.nseg = 1;
+        tg.nKs = nks2 = f.ks;
+        tg.nMt = (M + 32 * f.nb - 1) / (32 * f.nb); tg.nVt = (d + 64 * f.nv - 1) / (64 * f.nv);
+        tg.out = c->PART;
+        HIP_TRY(c, launch_tiled_two_planes(tg, f.nb, f.nv, st));
         }
         }
         // h_run += u ; y = bf16(RMSNorm(u) * gamma)

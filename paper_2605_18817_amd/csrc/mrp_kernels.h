@@ -260,6 +260,9 @@ hipError_t stream_gemm_configure();   // once per device
 int stream_gemm_it(int M);   // activation row blocks per workgroup for M rows
 
 hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st);
+// EPI_PARTIAL of one segment of two planes on tiles of 64 nv weight rows (nv: 3 or 4) and nb 32-row blocks (4 to 8) of
+// activation rows
+hipError_t launch_tiled_two_planes(const TiledGemmArgs &a, int nb, int nv, hipStream_t st);
 int tiled_row_blocks(int M);   // 32-row blocks of activation rows per tile for M rows
 inline int tiled_row_tiles(int M) { return (M + 32 * tiled_row_blocks(M) - 1) / (32 * tiled_row_blocks(M)); }
 #ifndef MRP_TILED_MIN_STEPS
@@ -268,6 +271,11 @@ inline int tiled_row_tiles(int M) { return (M + 32 * tiled_row_blocks(M) - 1) / 
 // k parts for a partial-sum tile GEMM with `tiles` output tiles and `nsteps` k steps, writing at most `cap_rows` rows
 int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M);
 // ---- which kernel (mrp_api.hip) ----
+// Tile kernel for the partial sums of two planes: 32-row blocks per tile, weight rows per tile / 64, k parts
+struct TileForm { int nb, nv, ks; };
+TileForm two_plane_form(int M, int R, int Kc, int nCU, size_t cap_rows);
+// Are the MLP head body's GEMMs of M rows on the tile kernel (or on the small-row kernels)?
+bool mlp_on_tiles(int M, int d, int nCU, size_t part_rows);
 // Is the LM head of M rows on the tile kernel (or the persistent one)?
 bool lm_on_tiles(int M, int d, int V, int nCU);
 // Weight row blocks per tile of the small-row GEMM kernels for R outputs of Kc inputs (1 or 2; 0: 16 features)

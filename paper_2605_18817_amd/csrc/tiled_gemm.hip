@@ -21,6 +21,12 @@
 // (d = 4096); of that the MFMA shape 4 %, one wait for the LDS reads per phase 1.5 %, the place of the barrier 1.5 %, the order of
 // the MFMAs 0.7 %.
 //
+// The head body's activations are two fp16 planes.  Where all of an operand is (P2), a k step is 32 k of both planes,
+// so that a weight fragment is requested once for both (48 KiB of requests per step instead of 64), and the tiles
+// come in more sizes (192 or 256 weight rows, 128 to 256 activation rows): with few tiles what counts is how many CUs
+// they leave idle.  At 384 rows, d = 4096 (us, the wide GEMM kernel / 256 x 192 tiles with the planes one after the other /
+// now): 24576 x 4096 187 / 146 / 114 - 123, 6144 x 4096 52 / 45 / 36 - 40, 4096 x 12288 78 / 62 / 60 - 63.
+//
 // Workgroups are ordered so that the 32 CUs of one XCD work at the same time on a
 // block of 4 (activation) x 8 (weight) tiles and share its operand slices in that
 // XCD's L2.
@@ -46,9 +52,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));   // native vector: arr
 // different registers and moves accumulators about), and volatile statements keep their order against the memory
 // requests.  Nothing here waits: operands must come from loads, and accumulators may be read after
 // acc_ready() only.
-template <int EPI>
+template <int EPI, bool VREG = false>      // VREG: the accumulator is among the ordinary registers
 __device__ __forceinline__ void mma_frag(f32x4 &c, const u32x4 &w, const u32x4 &x) {
-    if constexpr (EPI != EPI_LM)
+    if constexpr (VREG)
+        asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(c) : "v"(w), "v"(x));
+    else if constexpr (EPI != EPI_LM)
         asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
     else
         asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(w), "v"(x));
@@ -91,11 +99,14 @@ __device__ __forceinline__ int row_min(int x) {
     return row_combine(x, [](int p, int q) { return p < q ? p : q; });
 }
 
-// REM = 2 + (k steps - 2) % 3: the k steps left for the straight-line tail after the unrolled loop
+// REM = 2 + (k steps - 2) % 3: the k steps left for the straight-line tail after the unrolled loop (one form each: where
+// the tails of one form meet again, accumulators are moved about)
 // RAG: R is not a multiple of 4 (EPI_LM), so a row of the logit state starts on any 4-byte boundary and ends inside a
 // 16-byte piece
-// NB: 32-row blocks of activation rows per tile (5 to 8)
-template <int EPI, int REM, bool RAG, int NB>
+// NB: 32-row blocks of activation rows per tile (4 to 8)
+// NV: 16-row blocks of weight rows per wave (3 or 4: tiles of 192 or 256 weight rows)
+// P2: the activation is one segment of two planes; a step is 32 k of both, whose weight fragments are fetched once
+template <int EPI, int REM, bool RAG, int NB, int NV, bool P2>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void tiled_gemm_kernel(
     const TiledGemmArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
@@ -117,21 +128,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int m_cnt = a.nMt - 4 * mgrp < 4 ? a.nMt - 4 * mgrp : 4;
     const int vt = vchunk * 8 + in_grp / m_cnt, mt = mgrp * 4 + in_grp % m_cnt;
 
-    const int rb0 = vt * 8, ib0 = mt * NB;
+    const int rw0 = (vt * 4 + wave) * 16 * NV, ib0 = mt * NB;      // this wave's first weight row, the tile's first row block
     const u32x4 *Wp = reinterpret_cast<const u32x4 *>(a.Wp);
 
     // A fragment of 16 rows x 32 k is four runs of 16 chunks (256 bytes) of two packed blocks: the lane's chunk in it
     // (for activations, whose next k block lies NB blocks on, frag_x)
     const int frag_w = ln + 32 * (lq & 1) + 64 * (lq >> 1), frag_x = ln + 32 * (lq & 1) + 64 * NB * (lq >> 1);
 
-    // this wave's two weight row blocks (rows past the padded matrix re-read the last block)
-    const u32x4 *asrc[2];
+    // this wave's NV blocks of 16 weight rows, two of which share a packed block (rows past the padded matrix re-read
+    // the last one)
+    constexpr int NPTR = NV % 2 ? NV : NV / 2;
+    const u32x4 *asrc[NPTR];
 #pragma unroll
-    for (int v2 = 0; v2 < 2; ++v2) {
-        int rb = rb0 + wave * 2 + v2;
-        rb = rb < a.n_rb ? rb : a.n_rb - 1;
-        asrc[v2] = Wp + (size_t)rb * a.KBw * 64 + frag_w;
+    for (int n = 0; n < NPTR; ++n) {
+        const int r16 = rw0 / 16 + n * (NV / NPTR);
+        const int rb = r16 / 2 < a.n_rb ? r16 / 2 : a.n_rb - 1;
+        asrc[n] = Wp + (size_t)rb * a.KBw * 64 + 16 * (r16 & 1) + frag_w;
     }
+    auto wfrag = [&](int q, int kb) __attribute__((always_inline)) -> u32x4 {      // rows 16 q .., k blocks kb and kb + 1
+        return NV % 2 ? asrc[q % NPTR][(size_t)kb * 64] : asrc[q / 2 % NPTR][(size_t)kb * 64 + 16 * (q & 1)];
+    };
 
     // k-step sequence: segments x (k quads) x planes
     const int seg0_steps = a.seg[0].nkq * a.seg[0].nplanes;
@@ -157,6 +173,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         cu_p = sl % np;
     }
     auto cursor_get = [&](int &kbw, const u32x4 *&bptr) __attribute__((always_inline)) {
+        if constexpr (P2) {
+            kbw = 2 * cu_st;
+            bptr = reinterpret_cast<const u32x4 *>(seg_base0) + ((long)kbw * a.nIb + ib0) * 64;
+            return;
+        }
         kbw = ((cu_seg ? seg_nkq0 : 0) + cu_kq) * TG_KB;
         const long base = cu_seg ? seg_base1 : seg_base0;
         const long ps = cu_seg ? seg_ps1 : seg_ps0;
@@ -165,49 +186,72 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     auto cursor_next = [&]() __attribute__((always_inline)) {
         if (cu_st + 1 < st_end) {
             ++cu_st;
-            if (++cu_p == (cu_seg ? seg_np1 : seg_np0)) {
-                cu_p = 0;
-                if (++cu_kq == seg_nkq0 && cu_seg == 0) { cu_kq = 0; cu_seg = 1; }
+            if constexpr (!P2) {
+                if (++cu_p == (cu_seg ? seg_np1 : seg_np0)) {
+                    cu_p = 0;
+                    if (++cu_kq == seg_nkq0 && cu_seg == 0) { cu_kq = 0; cu_seg = 1; }
+                }
             }
         }
     };
+    // activation chunk c of a step (c = 0 .. 4 NB - 1: row block c % NB of k block c / NB; P2: of plane c / (2 NB))
+    const long chunk_hi = P2 ? seg_ps0 : 2 * (long)a.nIb * 64;
+    auto chunk_at = [&](const u32x4 *b, int c) __attribute__((always_inline)) -> const u32x4 * {
+        return b + ((c / NB >> 1) * chunk_hi + ((long)(c / NB & 1) * a.nIb + c % NB) * 64 + lane);
+    };
 
     // Operands are requested two steps ahead.  Per step and wave: NB LDS-direct loads (this wave's
-    // quarter of the activation stage, [k block][row block]) and 8 weight-fragment loads into the register set
-    // of that step; requests complete in issue order.
-    u32x4 areg[TG_DEPTH][2][4];       // [step % 3][32 k][16 weight rows]
-#define TG_LOAD(st, set, stage)                                                            \
-    {                                                                                      \
-        int kbw_;                                                                          \
-        const u32x4 *bp_;                                                                  \
-        cursor_get(kbw_, bp_);                                                             \
-        cursor_next();                                                                     \
-        _Pragma("unroll") for (int n = 0; n < NB; ++n) {                                   \
-            const int c = wave + 4 * n;            /* chunk: k block c / NB, row block c % NB */ \
-            __builtin_amdgcn_global_load_lds(                                              \
-                (gas_ptr)(bp_ + ((size_t)(c / NB) * a.nIb + (c % NB)) * 64 + lane),        \
-                (las_ptr)((stage) + c * 64), 16, 0, 0);                                    \
-        }                                                                                  \
-        __builtin_amdgcn_sched_barrier(0);                                                 \
-        _Pragma("unroll") for (int kp = 0; kp < 2; ++kp)                                   \
-            _Pragma("unroll") for (int q = 0; q < 4; ++q)                                  \
-                areg[set][kp][q] = asrc[q >> 1][(size_t)(kbw_ + 2 * kp) * 64 + 16 * (q & 1)]; \
-    }
-    // the group requested one step ago is complete when at most the youngest group (NB + 8) is pending
-    constexpr int NREQ = NB + 8;
-#define TG_WAIT_PREV() __builtin_amdgcn_s_waitcnt(0x0F70 | (NREQ & 15) | (NREQ >> 4 << 14))   /* vmcnt(NREQ) */
-
-    TG_LOAD(0, 0, tg_stage0)
-    TG_LOAD(1, 1, tg_stage1)
-
-    f32x4 acc[4][NB][2];              // [16 weight rows][32-row block][its 16 rows]
+    // quarter of the activation stage, [k block][row block]) and NWL weight-fragment loads into the register set
+    // of that step, in turn; requests complete in issue order.
+    constexpr int NWK = P2 ? 1 : 2, NWL = NWK * NV, NREQ = NB + NWL;
+    u32x4 areg[TG_DEPTH][NWK][NV];    // [step % 3][32 k][16 weight rows]
+    auto request = [&](u32x4 (&set)[NWK][NV], u32x4 *stage, int kbw, const u32x4 *bp, int r) __attribute__((always_inline)) {
+        const int wl = r * NWL / NREQ;
+        if ((r + 1) * NWL / NREQ > wl) {
+            set[wl / NV][wl % NV] = wfrag(wl % NV, kbw + 2 * (wl / NV));
+        } else {
+            const int c = wave + 4 * (r - wl);
+            __builtin_amdgcn_global_load_lds((gas_ptr)chunk_at(bp, c), (las_ptr)(stage + c * 64), 16, 0, 0);
+        }
+    };
+    int kbw_n;
+    const u32x4 *bp_n;
+    auto request_step = [&](u32x4 (&set)[NWK][NV], u32x4 *stage) __attribute__((always_inline)) {
+        cursor_get(kbw_n, bp_n);
+        cursor_next();
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+        for (int r = 0; r < NREQ; ++r) request(set, stage, kbw_n, bp_n, r);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    request_step(areg[0], tg_stage0);
+    request_step(areg[1], tg_stage1);
+
+    f32x4 acc[NV][NB][2];             // [16 weight rows][32-row block][its 16 rows]
+#pragma unroll
+    for (int q = 0; q < NV; ++q)
 #pragma unroll
         for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
-            for (int hi = 0; hi < 2; ++hi) acc[q][ib][hi] = f32x4{0.f, 0.f, 0.f, 0.f};
-    TG_WAIT_PREV();
+            for (int hi = 0; hi < 2; ++hi) {
+                acc[q][ib][hi] = f32x4{0.f, 0.f, 0.f, 0.f};
+                asm volatile("" : "+a"(acc[q][ib][hi]));      // (opaque: zeros made anew on two paths end in copies where they meet)
+            }
+    // Two planes on short tiles leave registers for a sum of its own for the low plane: its products (2^-11 of the high
+    // plane's) would round the high plane's sum as often again.
+    constexpr bool LO = P2 && NV * NB <= 18;
+    f32x4 low[LO ? NV : 1][LO ? NB : 1][2];
+    if constexpr (LO) {
+#pragma unroll
+        for (int q = 0; q < NV; ++q)
+#pragma unroll
+            for (int ib = 0; ib < NB; ++ib)
+#pragma unroll
+                for (int hi = 0; hi < 2; ++hi) {
+                    low[q][ib][hi] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    asm volatile("" : "+v"(low[q][ib][hi]));
+                }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (NREQ & 15) | (NREQ >> 4 << 14));   // vmcnt(NREQ): the first step's operands
     tg_barrier();
 
     // activation fragments are double-buffered: the LDS reads of the next phase (half the rows of every row block,
@@ -227,7 +271,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     constexpr int ZD = RAG ? 2 : 6;             // slice buffers: five (one) slices in flight ahead of the one added
     constexpr int ZE = RAG && NB == 8 ? 1 : 2;  // slices requested in the k loop
     f32x4 zc[ZD][8];
-    const int zv_lane = (rb0 + wave * 2) * 32 + 4 * lq;     // + 16 q
+    const int zv_lane = rw0 + 4 * lq;           // + 16 q
     auto zpiece = [&](int ib, int pc) __attribute__((always_inline)) -> f32x4 {   // pc: 4 hi + q
         int i = (ib0 + ib) * 32 + 16 * (pc >> 2) + ln;
         int v = zv_lane + 16 * (pc & 3);
@@ -245,10 +289,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     };
 
     // One k step.  A wave issues in order, and a memory request that finds the request queue full
-    // holds up the MFMAs behind it, so the step's NB + 8 requests are spread between its 16 NB MFMAs
-    // (one ahead of every sixteenth of them but the first) instead of being issued in a burst.
-    int kbw_n;
-    const u32x4 *bp_n;
+    // holds up the MFMAs behind it, so the step's NREQ requests are spread between its 4 NV NB MFMAs
+    // (ahead of every sixteenth of them but the first) instead of being issued in a burst.
+    constexpr auto group_of = [](int r) { return 1 + r * 15 / NREQ; };
+    constexpr int NEARLY = [] { int n = 0; for (int r = 0; r < NREQ; ++r) n += 1 + r * 15 / NREQ < 12; return n; }();
     // The workgroup meets three quarters into the step: the next step's operands (requested a step ago) are there by
     // then, every wave has read its last fragments of this step, and the last quarter reads the next step's first ones
     // behind its MFMAs (meeting at the end of a step, these reads are in nobody's shadow: four waves fetch 8 KiB each).
@@ -268,31 +312,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             if (ph == 3) {
                 // the next step's operands are there once at most the requests of this step's groups 1..11 are pending
                 // (8 logit pieces in the second to last step, none there in the partial-sum kernel)
-                constexpr int NP = role == 0 ? 5 + (NB < 6 ? NB : 6) : (EPI == EPI_LM ? 8 : 0);
+                constexpr int NP = role == 0 ? NEARLY : (EPI == EPI_LM ? 8 : 0);
+                static_assert(NP < 16);
                 if constexpr (role < 2) __builtin_amdgcn_s_waitcnt(0x0F70 | NP);       // vmcnt(NP)
                 tg_barrier();
             }
 #pragma unroll
             for (int g4 = 0; g4 < 4; ++g4) {
                 const int c = ph * 4 + g4;             // group 0..15
-                if (c >= 1) {                          // requests 0..14 (15 goes with group 15, too)
-                    const int rq = c - 1;
-                    if constexpr (role == 0) {
-                        if (rq & 1) {
-                            const int wl = rq >> 1;        // weight fragment 0..6 (7 below)
-                            areg[NS][wl >> 2][wl & 3] = asrc[(wl >> 1) & 1][(size_t)(kbw_n + 2 * (wl >> 2)) * 64 + 16 * (wl & 1)];
-                        } else if (rq >> 1 < NB) {
-                            const int ch = wave + 4 * (rq >> 1);   // chunk: k block ch / NB, row block ch % NB
-                            __builtin_amdgcn_global_load_lds(
-                                (gas_ptr)(bp_n + ((size_t)(ch / NB) * a.nIb + (ch % NB)) * 64 + lane),
-                                (las_ptr)(after + ch * 64), 16, 0, 0);
-                        }
-                        if (c == 15) areg[NS][1][3] = asrc[1][(size_t)(kbw_n + 2) * 64 + 16];
-                    } else if constexpr (EPI == EPI_LM) {
-                        if (rq < 8) {                      // second to last step: slice 0; last step: slice 1
-                            if constexpr (role == 1) zc[0][rq] = zpiece(0, rq);
-                            else if constexpr (ZE == 2) zc[1][rq] = zpiece(1, rq);
-                        }
+                if constexpr (role == 0) {
+#pragma unroll
+                    for (int r = 0; r < NREQ; ++r)
+                        if (group_of(r) == c) request(areg[NS], after, kbw_n, bp_n, r);
+                } else if constexpr (EPI == EPI_LM) {
+                    if (c >= 1 && c <= 8) {            // second to last step: slice 0; last step: slice 1
+                        if constexpr (role == 1) zc[0][c - 1] = zpiece(0, c - 1);
+                        else if constexpr (ZE == 2) zc[1][c - 1] = zpiece(1, c - 1);
                     }
                 }
 #pragma unroll
@@ -302,13 +337,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                         else if (role < 2) bf[0][ib] = next[ib * 64 + frag_x];
                     }
                 __builtin_amdgcn_sched_barrier(0);
-                // this group's share of the phase's 4 NB, in an order in which successive ones share an operand (the
+                // this group's share of the phase's NV NB, in an order in which successive ones share an operand (the
                 // matrix cores run against the power limit: 1.90 PFLOP/s in a loop of LDS reads and MFMAs, 1.86 with the
                 // weight fragments in the same order every time)
 #pragma unroll
-                for (int m = g4 * NB; m < (g4 + 1) * NB; ++m) {
-                    const int ib = m >> 2, q = ib & 1 ? 3 - (m & 3) : m & 3;
-                    mma_frag<EPI>(acc[q][ib][ph & 1], areg[PAR][ph >> 1][q], bf[ph & 1][ib]);
+                for (int m = g4 * NV * NB / 4; m < (g4 + 1) * NV * NB / 4; ++m) {
+                    const int ib = m / NV, q = ib & 1 ? NV - 1 - m % NV : m % NV;
+                    if constexpr (LO) {
+                        if (ph >= 2) mma_frag<EPI, true>(low[q][ib][ph & 1], areg[PAR][0][q], bf[ph & 1][ib]);
+                        else mma_frag<EPI>(acc[q][ib][ph & 1], areg[PAR][0][q], bf[ph & 1][ib]);
+                    } else {
+                        mma_frag<EPI>(acc[q][ib][ph & 1], areg[PAR][P2 ? 0 : ph >> 1][q], bf[ph & 1][ib]);
+                    }
                 }
                 if (c == 0 && role == 0) {   // behind the first MFMAs: where the operands of the step after next are
                     cursor_get(kbw_n, bp_n);
@@ -321,39 +361,43 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     {
         using P0 = std::integral_constant<int, 0>;
         using P1 = std::integral_constant<int, 1>;
-        using P2 = std::integral_constant<int, 2>;
-        for (int st = 0; st + TG_DEPTH <= nsteps - 2; st += TG_DEPTH) {
+        using P2_ = std::integral_constant<int, 2>;
+        for (int left = nsteps; left >= TG_DEPTH + 2; left -= TG_DEPTH) {
             step(P0{}, P0{}, tg_stage0, tg_stage1, tg_stage2);
             step(P1{}, P0{}, tg_stage1, tg_stage2, tg_stage0);
-            step(P2{}, P0{}, tg_stage2, tg_stage0, tg_stage1);
+            step(P2_{}, P0{}, tg_stage2, tg_stage0, tg_stage1);
         }
-        // the last REM steps (second template argument: 0 ordinary, 1 second to last, 2 last)
+        // the last REM steps (second argument: 0 ordinary, 1 second to last, 2 last)
         if constexpr (REM == 2) {
             step(P0{}, P1{}, tg_stage0, tg_stage1, tg_stage2);
-            step(P1{}, P2{}, tg_stage1, tg_stage2, tg_stage0);
+            step(P1{}, P2_{}, tg_stage1, tg_stage2, tg_stage0);
         } else if constexpr (REM == 3) {
             step(P0{}, P0{}, tg_stage0, tg_stage1, tg_stage2);
             step(P1{}, P1{}, tg_stage1, tg_stage2, tg_stage0);
-            step(P2{}, P2{}, tg_stage2, tg_stage0, tg_stage1);
+            step(P2_{}, P2_{}, tg_stage2, tg_stage0, tg_stage1);
         } else {
             step(P0{}, P0{}, tg_stage0, tg_stage1, tg_stage2);
             step(P1{}, P0{}, tg_stage1, tg_stage2, tg_stage0);
-            step(P2{}, P1{}, tg_stage2, tg_stage0, tg_stage1);
-            step(P0{}, P2{}, tg_stage0, tg_stage1, tg_stage2);
+            step(P2_{}, P1{}, tg_stage2, tg_stage0, tg_stage1);
+            step(P0{}, P2_{}, tg_stage0, tg_stage1, tg_stage2);
         }
     }
-#undef TG_LOAD
-#undef TG_WAIT_PREV
 
     // ---- epilogue ----
     // (an MFMA's result may be read 18 cycles after it was issued at the earliest; the compiler does not see the MFMAs)
     asm volatile("s_nop 15\n\ts_nop 15");
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < NV; ++q)
 #pragma unroll
         for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
-            for (int hi = 0; hi < 2; ++hi) asm volatile("" : "+a"(acc[q][ib][hi]));
+            for (int hi = 0; hi < 2; ++hi) {
+                asm volatile("" : "+a"(acc[q][ib][hi]));
+                if constexpr (LO) {
+                    asm volatile("" : "+v"(low[q][ib][hi]));
+                    acc[q][ib][hi] += low[q][ib][hi];
+                }
+            }
     // (an opaque zero keeps the compiler from sharing the prologue's 64 tile addresses with
     // the epilogue, which would hold them in registers across the whole k loop)
     int opq = 0;
@@ -366,8 +410,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             for (int hi = 0; hi < 2; ++hi) {
                 const int i = (ib0 + ib) * 32 + 16 * hi + lne;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int r = (rb0 + wave * 2) * 32 + 16 * q + 4 * lq;
+                for (int q = 0; q < NV; ++q) {
+                    const int r = rw0 + 16 * q + 4 * lq;
                     if (i < a.M && r < a.R)
                         *reinterpret_cast<f32x4 *>(a.out + ((size_t)ks * a.M + i) * a.R + r) = acc[q][ib][hi];
                 }
@@ -383,8 +427,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             for (int hi = 0; hi < 2; ++hi) {
                 const int i = (ib0 + ib) * 32 + 16 * hi + lne;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int c8 = (rb0 + wave * 2) * 4 + 2 * q + (lq >> 1);
+                for (int q = 0; q < NV; ++q) {
+                    const int c8 = rw0 / 8 + 2 * q + (lq >> 1);
                     if (i < a.M && c8 * 8 < a.R) {
                         uint16_t h[4], l[4];
 #pragma unroll
@@ -423,7 +467,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 float m = -INFINITY;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int v = (rb0 + wave * 2) * 32 + 16 * q + 4 * lq;
+                    const int v = rw0 + 16 * q + 4 * lq;
                     f32x4 &x4 = xs[4 * hi + q];
                     if constexpr (RAG) {
                         if (v + 4 > a.R) {      // the piece with the end of the row (or past it): entry by entry
@@ -456,7 +500,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 float sum = 0.f;
 #pragma unroll
                 for (int q = 3; q >= 0; --q) {
-                    const int v = (rb0 + wave * 2) * 32 + 16 * q + 4 * lq;
+                    const int v = rw0 + 16 * q + 4 * lq;
                     const f32x4 x4 = xs[4 * hi + q];
 #pragma unroll
                     for (int e = 3; e >= 0; --e) at = x4[e] == m ? v + e : at;      // (the lowest index of equal entries)
@@ -487,36 +531,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
 }
 
-template <int EPI, int REM, bool RAG, int NB>
-hipError_t launch_inst(const TiledGemmArgs &a, hipStream_t st) {
+template <int EPI, bool RAG, int NB, int NV, bool P2>
+hipError_t launch_inst(const TiledGemmArgs &a, int rem, hipStream_t st) {
     const int total = a.nMt * a.nVt * a.nKs;
-    const int grid = 8 * (total / 256 * 32 + (total % 256 + 7) / 8);
-    hipLaunchKernelGGL((tiled_gemm_kernel<EPI, REM, RAG, NB>), dim3(grid), dim3(256), 0, st, a);
+    const dim3 grid(8 * (total / 256 * 32 + (total % 256 + 7) / 8)), block(256);
+    if (rem == 2) hipLaunchKernelGGL((tiled_gemm_kernel<EPI, 2, RAG, NB, NV, P2>), grid, block, 0, st, a);
+    else if (rem == 3) hipLaunchKernelGGL((tiled_gemm_kernel<EPI, 3, RAG, NB, NV, P2>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((tiled_gemm_kernel<EPI, 4, RAG, NB, NV, P2>), grid, block, 0, st, a);
     return hipGetLastError();
 }
 
-template <int EPI, bool RAG, int NB>
-hipError_t launch_epi(const TiledGemmArgs &a, hipStream_t st) {
-    int nsteps = 0;
-    for (int sg = 0; sg < a.nseg; ++sg) nsteps += a.seg[sg].nkq * a.seg[sg].nplanes;
-    if (a.nKs < 1 || nsteps % a.nKs != 0 || nsteps / a.nKs < 2 || (EPI != EPI_PARTIAL && a.nKs != 1)) return hipErrorInvalidValue;
-    nsteps /= a.nKs;
-    const int rem = 2 + (nsteps - 2) % 3;       // (at least two k steps per part)
-    if (rem == 2) return launch_inst<EPI, 2, RAG, NB>(a, st);
-    if (rem == 3) return launch_inst<EPI, 3, RAG, NB>(a, st);
-    return launch_inst<EPI, 4, RAG, NB>(a, st);
+template <int NB>
+hipError_t launch_nb(const TiledGemmArgs &a, int epi, int rem, hipStream_t st) {
+    if (epi == EPI_SILU) {
+        if constexpr (NB >= 7) return launch_inst<EPI_SILU, false, NB, 4, false>(a, rem, st);
+        else return hipErrorInvalidValue;      // (launch_tiled_gemm rounds up to 7)
+    }
+    if (epi == EPI_PARTIAL) return launch_inst<EPI_PARTIAL, false, NB, 4, false>(a, rem, st);
+    // (a row that is no whole number of pieces has its own form: the handling of its end costs registers, and with
+    //  them four of the five logit slices in flight)
+    return a.R % 4 ? launch_inst<EPI_LM, true, NB, 4, false>(a, rem, st) : launch_inst<EPI_LM, false, NB, 4, false>(a, rem, st);
 }
 
 template <int NB>
-hipError_t launch_nb(const TiledGemmArgs &a, int epi, hipStream_t st) {
-    if (epi == EPI_SILU) {
-        if constexpr (NB >= 7) return launch_epi<EPI_SILU, false, NB>(a, st);
-        else return hipErrorInvalidValue;      // (launch_tiled_gemm rounds up to 7)
-    }
-    if (epi == EPI_PARTIAL) return launch_epi<EPI_PARTIAL, false, NB>(a, st);
-    // (a row that is no whole number of pieces has its own form: the handling of its end costs registers, and with
-    //  them four of the five logit slices in flight)
-    return a.R % 4 ? launch_epi<EPI_LM, true, NB>(a, st) : launch_epi<EPI_LM, false, NB>(a, st);
+hipError_t launch_two_planes(const TiledGemmArgs &a, int nv, int rem, hipStream_t st) {
+    return nv == 3 ? launch_inst<EPI_PARTIAL, false, NB, 3, true>(a, rem, st) : launch_inst<EPI_PARTIAL, false, NB, 4, true>(a, rem, st);
+}
+
+// k steps of a part (0: the arguments do not fit)
+int part_steps(const TiledGemmArgs &a, bool split) {
+    int nsteps = 0;
+    for (int sg = 0; sg < a.nseg; ++sg) nsteps += a.seg[sg].nkq * a.seg[sg].nplanes;
+    if (a.nKs < 1 || nsteps % a.nKs != 0 || nsteps / a.nKs < 2 || (!split && a.nKs != 1)) return 0;
+    return nsteps / a.nKs;       // (at least two)
 }
 
 }  // namespace
@@ -541,16 +588,30 @@ int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M) {
 }
 
 hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st) {
+    const int nsteps = part_steps(a, epi == EPI_PARTIAL), rem = 2 + (nsteps - 2) % 3;
+    if (nsteps == 0) return hipErrorInvalidValue;
     int nb = tiled_row_blocks(a.M);
     // EPI_SILU has instances of 7 and 8 row blocks only: on 256 CUs an unsplit k comes with 768 rows and more, which make
     // no shorter tiles.  With fewer CUs (a partition of the device) it comes with fewer rows, too; those are as many
     // tiles of 7 blocks, which fit the workspace (at most 8 blocks for each tile's 256 rows).
     if (epi == EPI_SILU && nb < 7) nb = 7;
     if (a.nMt != (a.M + 32 * nb - 1) / (32 * nb) || a.nMt * nb > a.nIb) return hipErrorInvalidValue;
-    if (nb == 5) return launch_nb<5>(a, epi, st);
-    if (nb == 6) return launch_nb<6>(a, epi, st);
-    if (nb == 7) return launch_nb<7>(a, epi, st);
-    return launch_nb<8>(a, epi, st);
+    if (nb == 5) return launch_nb<5>(a, epi, rem, st);
+    if (nb == 6) return launch_nb<6>(a, epi, rem, st);
+    if (nb == 7) return launch_nb<7>(a, epi, rem, st);
+    return launch_nb<8>(a, epi, rem, st);
+}
+
+hipError_t launch_tiled_two_planes(const TiledGemmArgs &a, int nb, int nv, hipStream_t st) {
+    const int nsteps = part_steps(a, true), rem = 2 + (nsteps - 2) % 3;
+    if (nsteps == 0 || a.nseg != 1 || a.seg[0].nplanes != 2 || nv < 3 || nv > 4 || nb < 4 || nb > 8 || a.R % 4 != 0 ||
+        a.nMt != (a.M + 32 * nb - 1) / (32 * nb) || a.nMt * nb > a.nIb || a.nVt != (a.R + 64 * nv - 1) / (64 * nv))
+        return hipErrorInvalidValue;
+    if (nb == 4) return launch_two_planes<4>(a, nv, rem, st);
+    if (nb == 5) return launch_two_planes<5>(a, nv, rem, st);
+    if (nb == 6) return launch_two_planes<6>(a, nv, rem, st);
+    if (nb == 7) return launch_two_planes<7>(a, nv, rem, st);
+    return launch_two_planes<8>(a, nv, rem, st);
 }
 
 }  // namespace mrp

@@ -52,3 +52,38 @@ def test_residual_workgroups_fill_the_device(S, resident):
             rounds = lambda v: -(-n * v // (resident * nCU))
             cost = lambda v: rounds(v) * (2 * -(-ntiles // v) + 1)
             assert cost(w) <= cost(min(ntiles, room // n)), (n, ntiles, w)
+
+
+class _TileForm(C.Structure):
+    _fields_ = [("nb", C.c_int), ("nv", C.c_int), ("ks", C.c_int)]
+
+
+@pytest.mark.parametrize("nCU", [32, 256])
+def test_two_plane_forms_fit(nCU):
+    form = library_rule("_ZN3mrp14two_plane_formEiiiim", _TileForm, *[C.c_int] * 4, C.c_size_t)
+    for M in [*range(1, 70), 96, 128, 129, 160, 192, 193, 250, 384, 400, 512, 513, 592, 767, 768, 1000, 1024, 4096, 65535]:
+        for R, K in [(32, 64), (32, 128), (128, 128), (4096, 4096), (6144, 4096), (24576, 4096), (4096, 12288), (12288, 2048),
+                     (2176, 2176), (131072, 128), (2304, 8192)]:
+            for cap in (M, 4 * M, 16 * M, max(M, 4096)):
+                f = form(M, R, K, nCU, cap)
+                tiles = -(-M // (32 * f.nb))
+                assert 4 <= f.nb <= 8 and f.nv in (3, 4) and 1 <= f.ks <= 16 and f.ks * M <= cap
+                assert tiles * f.nb <= -(-M // 256) * 8 and tiles * f.nb * 32 >= M      # row blocks that the planes hold
+                assert K // 32 % f.ks == 0 and K // 32 // f.ks >= min(4, K // 32)       # whole parts of four k steps at least
+    if nCU == 256:                                   # the sizes it was measured at
+        assert [(f.nb, f.nv, f.ks) for f in (form(384, 24576, 4096, 256, 1 << 20), form(592, 4096, 4096, 256, 4096),
+                                             form(1024, 4096, 4096, 256, 4096), form(4096, 4096, 4096, 256, 4096))] \
+            == [(6, 3, 1), (5, 4, 4), (4, 4, 2), (8, 4, 1)]
+
+
+def test_mlp_body_kernel_by_rows_and_width():
+    on_tiles = library_rule("_ZN3mrp12mlp_on_tilesEiiim", C.c_bool, *[C.c_int] * 3, C.c_size_t)
+    rows = lambda M: 16 * M if M <= 128 else 4096
+    for M in range(1, 800):
+        for d in range(128, 8193, 128):
+            if M >= 768 or (d > 2048 and M > 512):
+                assert on_tiles(M, d, 256, rows(M))
+            elif M <= 128 or d <= 2048:
+                assert not on_tiles(M, d, 256, rows(M))
+    assert all(on_tiles(M, 4096, 256, 4096) for M in (129, 144, 160, 256, 257, 512))
+    assert not any(on_tiles(M, 2560, 256, 4096) for M in (129, 192, 384))

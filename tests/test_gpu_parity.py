@@ -268,6 +268,22 @@ def test_row_counts_where_the_kernels_change(d, B, L, K):
     prob.close()
 
 
+@pytest.mark.parametrize("d,B,L,K", [
+    (4096, 8, 16, 1),    # 128 rows: small-row kernels
+    (4096, 43, 3, 2),    # 129 rows: the tile kernel, 16 tiles of 160 rows x 16 parts; the second head's two planes
+    (4096, 16, 16, 1),   # 256 rows: one row of 256-row tiles
+    (4096, 24, 16, 1),   # 384 rows
+    (2560, 12, 16, 1),   # 192 rows, a width whose parts leave the tile kernel's round empty: small-row kernels
+    (2048, 64, 16, 1),   # 1024 rows: second GEMM on 128-row tiles
+    (384, 48, 16, 2),    # 768 rows, a width that ends inside a tile
+])
+def test_head_body_on_tiles(d, B, L, K):
+    """The MLP head body on both sides of the switch to the tile kernel below 768 rows, and its second GEMM's forms."""
+    cfg = mi.straddling(mi.config(0, d=d, V=1028, B=B, L=L, K=K))
+    prob, g, o, stats = _free_run(cfg, mrp.RevealCfg(tau=2.0), seqs=[0, B // 2, B - 1])
+    prob.close()
+
+
 # Vocabularies are chosen by how full they leave the rounds of one tile per CU on 256 CUs
 @pytest.mark.parametrize("d,B,L,V,tiles", [
     (256, 160, 1, 1028, True),          # up to 160 rows any vocabulary of one round

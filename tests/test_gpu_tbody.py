@@ -173,6 +173,14 @@ def test_fuse_projection_kernels(d, B, L, K):
     _run(cfg, td, mrp.RevealCfg(tau=0.9), seqs=[0, B - 1])
 
 
+@pytest.mark.parametrize("B,L", [(16, 4), (13, 5), (12, 16)])      # 64 rows | 65, 192
+def test_large_projections_on_tiles(B, L):
+    """Weights of 21 M entries (gate/up 10240 x 2048): from 65 rows on the tile kernel with two planes per k step."""
+    cfg = mi.straddling(mi.config(0, d=2048, V=1028, B=B, L=L, K=1))
+    td = mi.TBodyDims(D=1, n_heads=4, n_kv_heads=2, head_dim=128, d_ff=5120, P_max=20)
+    _run(cfg, td, mrp.RevealCfg(tau=0.9), seqs=[0, B - 1])
+
+
 def test_tbody_argument_errors():
     cfg = mi.config(0)
     ctx = mrp.MrpContext(cfg.d, cfg.V, cfg.M, cfg.L)

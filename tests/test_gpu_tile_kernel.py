@@ -65,3 +65,42 @@ def test_silu_epilogue_at_every_tile_height(M):
     rest = torch.ones_like(out[0], dtype=torch.bool)
     rest[idx_o] = False
     assert bool((out[:, rest] == 7.0).all())                      # rows past M are not written
+
+
+# Tiles of 192 and 256 weight rows x every height; 4 to 14 k steps of 32 (each length of the kernel's tail), one part or
+# several; rows and outputs that end inside a tile, an output narrower than one
+@pytest.mark.parametrize("M,R,K,nb,nv,ks", [
+    (1, 32, 128, 4, 4, 1), (128, 256, 192, 4, 4, 1), (129, 288, 320, 4, 3, 2), (250, 192, 1024, 4, 3, 8),
+    (160, 416, 576, 5, 3, 3), (75, 224, 320, 5, 4, 2), (192, 384, 448, 6, 3, 2), (190, 320, 512, 6, 4, 4),
+    (200, 192, 256, 7, 3, 2), (224, 512, 384, 7, 4, 2), (256, 96, 448, 8, 3, 1), (450, 544, 640, 8, 4, 4),
+])
+def test_two_plane_forms(M, R, K, nb, nv, ks):
+    lib = mrp.load_library()
+    launch = getattr(lib, "_ZN3mrp23launch_tiled_two_planesERKNS_13TiledGemmArgsEiiP12ihipStream_t")
+    nIb = max(-(-M // 256) * 8, -(-M // (32 * nb)) * nb)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + R)
+    x = torch.empty(M, K, device="cuda").normal_(0, 1, generator=gen)
+    w = torch.empty(R, K, dtype=torch.bfloat16, device="cuda").normal_(0, 0.05, generator=gen)
+    planes = torch.zeros(2, K // 16 * nIb * 512, dtype=torch.float16, device="cuda")
+    idx = _plane_index(M, K, nIb)
+    hi = x.half()
+    planes[0, idx], planes[1, idx] = hi, (x - hi.float()).half()
+    out = torch.full((ks * M * R + 64,), 7.0, device="cuda")
+    Wp = mrp.pack_weight(w, body=True)
+    a = _Args()
+    a.Wp, a.KBw, a.n_rb, a.nIb, a.M, a.R = Wp.data_ptr(), K // 16, R // 32, nIb, M, R
+    a.seg[0] = _Seg(planes.data_ptr(), planes.shape[1] // 8, K // 64, 2)
+    a.nseg, a.nMt, a.nVt, a.nKs, a.out = 1, -(-M // (32 * nb)), -(-R // (64 * nv)), ks, out.data_ptr()
+    assert launch(C.byref(a), nb, nv, C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    torch.cuda.synchronize()
+    got = out[:ks * M * R].view(ks, M, R).double()
+    xe, we = planes[0, idx].double() + planes[1, idx].double(), w.half().double()
+    kp = K // ks
+    for n in range(ks):
+        xs, ws = xe[:, n * kp:(n + 1) * kp], we[:, n * kp:(n + 1) * kp]
+        # two planes of K / 32 MFMAs of 32 products, each addition within 2^-24 of what was summed so far
+        bound = (2 * kp // 32 + 32) * 2.0 ** -24 * (xs.abs() @ ws.abs().t())
+        err = (got[n] - xs @ ws.t()).abs()
+        assert bool((err <= bound).all()), (n, float((err / bound).max()))
+    assert bool((out[ks * M * R:] == 7.0).all())                   # nothing past the last part
