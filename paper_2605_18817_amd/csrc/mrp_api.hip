@@ -732,7 +732,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             tg.nseg = 1;
             tg.nMt = tiled_row_tiles(M); tg.nVt = (V + 255) / 256;
             tg.nKs = 1;
-            tg.z = z; tg.pm = c->pm; tg.ps = c->ps; tg.pi = c->pi;
+            tg.z = z; tg.pm = c->pm; tg.ps = c->ps;
             HIP_TRY(c, launch_tiled_gemm(tg, EPI_LM, st));
             nT_lm = tg.nVt;
         }

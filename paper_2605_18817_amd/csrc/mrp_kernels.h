@@ -83,7 +83,6 @@ struct TiledGemmArgs {
     long plane_stride;
     float *z;            // EPI_LM: [M][R] in/out, partials [nVt][M]
     float *pm, *ps;
-    int *pi;
 };
 
 // Bits of a context's device error word (the MRP_FLAG_* values of include/mrp.h): an index the caller
@@ -321,7 +320,7 @@ struct SelectArgs {
     uint8_t *remasked;      // this state's slot [M] or nullptr
     int32_t *x_tok;         // [M] token recorded at reveal, or nullptr
     int remask_mode;        // 1: remask on the probability of the recorded token (needs z, x_tok)
-    const float *z;         // [M][V] updated logits (remask_mode 1)
+    const float *z;         // [M][V] updated logits (remask_mode 1; argmax of the tile kernel's winning tile)
     const uint16_t *E;      // embedding rows to gather for the next head (nullptr: skip)
     uint4 *xe;
     int nIb;

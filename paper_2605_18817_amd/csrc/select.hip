@@ -81,6 +81,7 @@ __global__ __launch_bounds__(256) void reduce_rows_kernel(const float *__restric
     }
 }
 
+constexpr int TILE_V = 256;      // vocabulary entries per tile of the tile kernel
 constexpr int MERGE_BATCH = 16;  // strides of 64 partial tiles fetched together (1024 tiles per round trip)
 
 __device__ __forceinline__ bool more_confident(const float *conf, int a, int b) {
@@ -115,11 +116,12 @@ __global__ __launch_bounds__(NT) void merge_select_kernel(const SelectArgs a) {
     }
 
     if (a.row_stride == 1 && a.slot_stride > 1) {
-        // Layout [tile][row] (the GEMM kernels that own whole row tiles write it): the sequence's L
+        // Layout [tile][row] (the GEMM kernel that owns whole row tiles writes it, without indices): the sequence's L
         // rows of one tile are contiguous.  Thread (row p, group grp) merges tiles grp, grp + NG, ...
         // in order, so a load instruction fetches whole 4 L-byte runs; the groups' results are then
         // merged per row, first inside each wavefront, then over the wavefronts in order.
         __shared__ Part g_part[NW][MAX_L];
+        __shared__ float s_max[MAX_L];
         int Lp = 1;
         while (Lp < L) Lp <<= 1;
         const int NG = NT / Lp, p = threadIdx.x % Lp, grp = threadIdx.x / Lp;
@@ -128,7 +130,6 @@ __global__ __launch_bounds__(NT) void merge_select_kernel(const SelectArgs a) {
             const size_t i = (size_t)b * L + p;
             for (int t0 = grp; t0 < a.nT; t0 += NG * 8) {
                 float m[8], sx[8];
-                int ix[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {   // eight tiles in flight
                     const int t = t0 + u * NG;
@@ -136,10 +137,9 @@ __global__ __launch_bounds__(NT) void merge_select_kernel(const SelectArgs a) {
                     const size_t o = (size_t)(ok ? t : 0) * a.slot_stride + i;
                     m[u] = ok ? a.pm[o] : -INFINITY;
                     sx[u] = ok ? a.ps[o] : 0.f;
-                    ix[u] = ok ? a.pi[o] : 0x7fffffff;
                 }
 #pragma unroll
-                for (int u = 0; u < 8; ++u) pt = part_merge(pt, Part{m[u], sx[u], ix[u]});
+                for (int u = 0; u < 8; ++u) pt = part_merge(pt, Part{m[u], sx[u], t0 + u * NG});
             }
         }
         for (int o = Lp; o < 64; o <<= 1) {      // (lanes o apart hold the same row)
@@ -159,8 +159,27 @@ __global__ __launch_bounds__(NT) void merge_select_kernel(const SelectArgs a) {
             const int i = b * L + q;
             const float conf = 1.0f / r.s;
             const float lse = r.m + logf(r.s);
-            a.tok[i] = r.i; a.conf[i] = conf; a.lse[i] = lse;
-            s_lse[q] = lse; s_conf[q] = conf; s_tok[q] = r.i;
+            a.conf[i] = conf; a.lse[i] = lse;
+            s_lse[q] = lse; s_conf[q] = conf; s_tok[q] = r.i; s_max[q] = r.m;
+        }
+        __syncthreads();
+        // the lowest entry of the winning tile that is the maximum: one wavefront per row, 4 of the tile's 256 entries per
+        // lane (a row of a single wavefront's lanes each; the tile kernel would spend 2 of its 11 vector instructions per
+        // entry on keeping it)
+        for (int q = wave; q < L; q += NW) {
+            const float mx = s_max[q];
+            const int i = b * L + q, v = s_tok[q] * TILE_V + 4 * lane;
+            int at = 0x7fffffff;
+            if (mx > -INFINITY) {
+                const float4 x = load4_row(a.z + (size_t)i * a.V, v, a.V, -INFINITY);
+                at = x.x == mx ? v : (x.y == mx ? v + 1 : (x.z == mx ? v + 2 : (x.w == mx ? v + 3 : at)));
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                const int other = __shfl_xor(at, off);
+                at = other < at ? other : at;
+            }
+            if (lane == 0) { a.tok[i] = at; s_tok[q] = at; }
         }
     } else {
     // one wavefront per row: merge the row's nT partials in a fixed order

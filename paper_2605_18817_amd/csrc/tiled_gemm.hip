@@ -33,8 +33,8 @@
 //
 // Epilogues: EPI_PARTIAL (fp32 tile to out[i][r]; part ks of a k split to out[ks][i][r]), EPI_SILU (SiLU of the
 // tile as the two fp16 activation planes of the next GEMM; no k split) and EPI_LM (the tile is added to the
-// logit state, which is stored back, and the per-row (max, sum-exp, argmax) partial of
-// the tile's 256 vocabulary entries is written; paper Section 3.2 / Algorithm 2
+// logit state, which is stored back, and the per-row (max, sum-exp) partial of
+// the tile's 256 vocabulary entries is written: the merge looks up which entry the maximum is; paper Section 3.2 / Algorithm 2
 // l <- l + delta).
 #include "mrp_kernels.h"
 
@@ -80,23 +80,20 @@ typedef __attribute__((address_space(3))) void *las_ptr;
 // flight for later steps are not drained.
 __device__ __forceinline__ void tg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// A value's other copies lie in lane ^ 16, lane ^ 32 and lane ^ 48 (the four lanes of a row of a 16 x 16 tile):
-// the exchanges swap every other 16 lanes / the two halves of two registers, here of two copies of the same one.
+// Maximum without the instruction per operand that the compiler puts ahead of fmaxf to quieten signalling NaNs
+__device__ __forceinline__ float max3(float x, float y, float z) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(y), "v"(z));
+    return r;
+}
+// The four lanes of a row of a 16 x 16 tile lie 16 apart.  The exchanges swap every other 16 lanes / the two halves of two
+// registers, here of two copies of the same one.
 template <class F>
-__device__ __forceinline__ int row_combine(int x, F f) {
-    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    x = f(a[0], a[1]);
-    const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    return f(b[0], b[1]);
-}
-__device__ __forceinline__ float row_max(float x) {
-    return __int_as_float(row_combine(__float_as_int(x), [](int p, int q) { return __float_as_int(fmaxf(__int_as_float(p), __int_as_float(q))); }));
-}
-__device__ __forceinline__ float row_sum(float x) {
-    return __int_as_float(row_combine(__float_as_int(x), [](int p, int q) { return __float_as_int(__int_as_float(p) + __int_as_float(q)); }));
-}
-__device__ __forceinline__ int row_min(int x) {
-    return row_combine(x, [](int p, int q) { return p < q ? p : q; });
+__device__ __forceinline__ float row_combine(float x, F f) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+    x = f(__int_as_float(a[0]), __int_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+    return f(__int_as_float(b[0]), __int_as_float(b[1]));
 }
 
 // REM = 2 + (k steps - 2) % 3: the k steps left for the straight-line tail after the unrolled loop (one form each: where
@@ -271,21 +268,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     constexpr int ZD = RAG ? 2 : 6;             // slice buffers: five (one) slices in flight ahead of the one added
     constexpr int ZE = RAG && NB == 8 ? 1 : 2;  // slices requested in the k loop
     f32x4 zc[ZD][8];
+    // The rows of the tile as a buffer of their own: a piece that lies past the matrix' last row, or (zoff) past the end of
+    // its row, reads zero and is not stored, without a branch for each piece.
     const int zv_lane = rw0 + 4 * lq;           // + 16 q
+    const int zrows = a.M - ib0 * 32 < 32 * NB ? a.M - ib0 * 32 : 32 * NB;
+    const __amdgpu_buffer_rsrc_t zbuf =
+        __builtin_amdgcn_make_buffer_rsrc(a.z + (size_t)ib0 * 32 * a.R, 0, (unsigned)zrows * (unsigned)a.R * 4u, 0x00020000);
+    unsigned zoff[4];
+    if constexpr (EPI == EPI_LM && !RAG) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) zoff[q] = zv_lane + 16 * q < a.R ? (unsigned)(ln * a.R + zv_lane + 16 * q) * 4u : 0xffffff00u;
+    }
+    auto zrow = [&](int ib, int hi) __attribute__((always_inline)) -> int { return (32 * ib + 16 * hi) * a.R * 4; };
     auto zpiece = [&](int ib, int pc) __attribute__((always_inline)) -> f32x4 {   // pc: 4 hi + q
-        int i = (ib0 + ib) * 32 + 16 * (pc >> 2) + ln;
-        int v = zv_lane + 16 * (pc & 3);
-        i = i < a.M ? i : a.M - 1;
         if constexpr (RAG) {
+            int i = (ib0 + ib) * 32 + 16 * (pc >> 2) + ln;
+            int v = zv_lane + 16 * (pc & 3);
+            i = i < a.M ? i : a.M - 1;
             // (a piece that crosses the end of its row takes in the start of the next one, or starts early where that
             //  would pass the end of the matrix: the epilogue does not use it)
             const int to_end = a.M - i < 4 ? (a.M - i) * a.R - 4 : a.R, v_max = to_end < a.R - 1 ? to_end : a.R - 1;
             v = v < v_max ? v : v_max;
             const float4 x = load4(a.z + ((long)i * a.R + v));
             return f32x4{x.x, x.y, x.z, x.w};
+        } else {
+            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(zbuf, zoff[pc & 3], zrow(ib, pc >> 2), 0));
         }
-        v = v < a.R - 4 ? v : a.R - 4;
-        return *reinterpret_cast<const f32x4 *>(a.z + (size_t)i * a.R + v);
     };
 
     // One k step.  A wave issues in order, and a memory request that finds the request queue full
@@ -446,9 +454,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         // per wave: 32 NB activation rows x 64 vocabulary entries.  The logit tile is added here, one
         // 32-row slice (32 registers) at a time; the row reduction over v runs in registers: the maximum of a row's 64
         // entries first (they lie in four lanes), then the sum of exponentials against it.
+        // (A lane's 256 entries cost 9.5 vector instructions each, an exponential counted as four, and a tile 5 of its
+        // 115 us. Before, with a branch for every piece and the index of the maximum kept: LM head of 4096 rows, d = 4096, 4250 us, now
+        // 4205; of 1024 rows 1125 / 1112; of 192 rows, V = 50257, d = 2048, 60.8 / 59.1. Non-temporal pieces: 4330.)
         float *red_m = reinterpret_cast<float *>(tg_stage0);       // [4 waves][256 rows] (the stages are dead)
         float *red_s = red_m + 1024;
-        int *red_i = reinterpret_cast<int *>(red_s + 1024);
+        const bool row_end = !RAG && rw0 + 64 > a.R;       // (uniform over the wave) the rows end among its entries
         // The first ZE slices were requested during the last two k steps; ZD - 1 slices are kept in flight
         // ahead of the one being added; the sum is formed in place in the fetched registers.
         auto zfetch = [&](int ib, f32x4 (&dst)[8]) __attribute__((always_inline)) {
@@ -490,42 +501,45 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                             }
                         }
                     } else {
-                        if (i < a.M && v < a.R) *reinterpret_cast<f32x4 *>(a.z + (size_t)i * a.R + v) = x4;
-                        if (v >= a.R) x4 = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x4), zbuf, zoff[q], zrow(ib, hi), 0);
                     }
-                    m = fmaxf(fmaxf(m, fmaxf(x4[0], x4[1])), fmaxf(x4[2], x4[3]));
                 }
-                m = row_max(m);
-                int at = 0x7fffffff;
+                if (row_end) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        asm volatile("" : "+v"(xs[4 * hi + q]));      // (kept a branch: as selects this would cost every tile)
+                        if (zv_lane + 16 * q >= a.R) xs[4 * hi + q] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 x4 = xs[4 * hi + q];
+                    m = max3(max3(m, x4[0], x4[1]), x4[2], x4[3]);
+                }
+                m = row_combine(m, [](float x, float y) { return max3(x, y, y); });
                 float sum = 0.f;
 #pragma unroll
-                for (int q = 3; q >= 0; --q) {
-                    const int v = rw0 + 16 * q + 4 * lq;
+                for (int q = 0; q < 4; ++q) {
                     const f32x4 x4 = xs[4 * hi + q];
-#pragma unroll
-                    for (int e = 3; e >= 0; --e) at = x4[e] == m ? v + e : at;      // (the lowest index of equal entries)
                     sum += (__expf(x4[0] - m) + __expf(x4[1] - m)) + (__expf(x4[2] - m) + __expf(x4[3] - m));
                 }
-                at = row_min(m > -INFINITY ? at : 0x7fffffff);
-                sum = row_sum(sum);
+                sum = row_combine(sum, [](float x, float y) { return x + y; });
                 if (lq == 0) {
                     const int row = 32 * ib + 16 * hi + lne;
                     red_m[wave * 256 + row] = m;
                     red_s[wave * 256 + row] = sum;
-                    red_i[wave * 256 + row] = at;
                 }
             }
         }
         __syncthreads();
         if (tid < 32 * NB) {
-            Part pt = {red_m[tid], red_s[tid], red_i[tid]};
+            Part pt = {red_m[tid], red_s[tid], 0};
 #pragma unroll
-            for (int w = 1; w < 4; ++w) pt = part_merge(pt, Part{red_m[w * 256 + tid], red_s[w * 256 + tid], red_i[w * 256 + tid]});
+            for (int w = 1; w < 4; ++w) pt = part_merge(pt, Part{red_m[w * 256 + tid], red_s[w * 256 + tid], 0});
             const int i = ib0 * 32 + tid;
             if (i < a.M) {
                 a.pm[(size_t)vt * a.M + i] = pt.m;
                 a.ps[(size_t)vt * a.M + i] = pt.s;
-                a.pi[(size_t)vt * a.M + i] = pt.i;
             }
         }
     }
@@ -550,7 +564,8 @@ hipError_t launch_nb(const TiledGemmArgs &a, int epi, int rem, hipStream_t st) {
     if (epi == EPI_PARTIAL) return launch_inst<EPI_PARTIAL, false, NB, 4, false>(a, rem, st);
     // (a row that is no whole number of pieces has its own form: the handling of its end costs registers, and with
     //  them four of the five logit slices in flight)
-    return a.R % 4 ? launch_inst<EPI_LM, true, NB, 4, false>(a, rem, st) : launch_inst<EPI_LM, false, NB, 4, false>(a, rem, st);
+    // (the other one's byte offsets inside a tile are 32 bits)
+    return a.R % 4 || a.R > 4000000 ? launch_inst<EPI_LM, true, NB, 4, false>(a, rem, st) : launch_inst<EPI_LM, false, NB, 4, false>(a, rem, st);
 }
 
 template <int NB>
