@@ -12,7 +12,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function",
-         "-parallel-jobs=8"]   # the sources side by side: 133 s one after the other, 68 s (tiled_gemm.hip alone) with 8 CPUs
+         "-parallel-jobs=8"]   # the sources side by side: 210 s one after the other, 60 s with 8 CPUs
 
 
 def sources():

@@ -259,6 +259,9 @@ hipError_t stream_gemm_configure();   // once per device
 int stream_gemm_it(int M);   // activation row blocks per workgroup for M rows
 
 hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st);
+// its EPI_LM forms for nb row blocks per tile; rem = 2 + (k steps - 2) % 3
+hipError_t launch_tiled_lm(const TiledGemmArgs &a, int nb, int rem, hipStream_t st);
+hipError_t launch_tiled_lm_halves(const TiledGemmArgs &a, int nb, int rem, hipStream_t st);
 // EPI_PARTIAL of one segment of two planes on tiles of 64 nv weight rows (nv: 3 or 4) and nb 32-row blocks (4 to 8) of
 // activation rows
 hipError_t launch_tiled_two_planes(const TiledGemmArgs &a, int nb, int nv, hipStream_t st);

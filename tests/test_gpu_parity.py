@@ -306,6 +306,24 @@ def test_lm_head_kernel_by_width_and_vocabulary(d, B, L, V, tiles):
     prob.close()
 
 
+@pytest.mark.parametrize("B,L,V", [
+    (9, 16, 32768), (9, 16, 33024),      # 144 rows, tiles of 5 row blocks: 128 tiles are halved (3 + 2 blocks), 129 are not
+    (24, 16, 16384), (24, 16, 16640),    # 384 rows, 6 row blocks: 2 x 64, 2 x 65 tiles
+    (25, 16, 16384), (25, 16, 16640),    # 400 rows, 7 row blocks (4 + 3; the last half is one row block)
+    (32, 16, 16384), (32, 16, 16640),    # 512 rows, 8 row blocks
+    (9, 16, 32767), (25, 16, 16383),     # the same where rows end inside a piece, halved
+    (9, 16, 33021), (24, 16, 16637), (25, 16, 16638), (32, 16, 16639),      # ... and whole
+    (33, 16, 22016),                     # 528 rows: 258 tiles, two of them left over and halved
+])
+def test_left_over_tiles(B, L, V):
+    """LM head on the tile kernel with its left-over tiles halved (up to 128 of them) or whole, at every height; first, middle
+    and last sequence compared, and no logit of the others is touched twice or missed."""
+    cfg = mi.straddling(mi.config(0, d=128, V=V, B=B, L=L, K=1))
+    assert B * L > 512 or lm_head_on_tiles(B * L, 128, V)
+    prob, g, o, stats = _free_run(cfg, mrp.RevealCfg(tau=2.0), seqs=[0, B // 2, B - 1])
+    prob.close()
+
+
 @pytest.mark.parametrize("d,B,L,features", [
     (1024, 4, 4, 16), (1024, 17, 1, 32),                       # 16 rows | 17
     (2048, 4, 4, 16), (2048, 17, 1, 16), (2048, 4, 16, 16),    # one half tile of rows; two, the second with one row; 64 rows
