@@ -186,6 +186,12 @@ bool mrp::mlp_on_tiles(int M, int d, int nCU, size_t part_rows) {
     return M > 512 || (M > 128 && 4 * tiles * tiled_ksplit(tiles, (d / 64) * (NSPLIT + 1), nCU, part_rows, M) >= 3 * nCU);
 }
 
+// The MLP head body of a sequence in one workgroup, where both weight matrices pass through one CU in less than the launches
+// of the general path take.  Measured per step of three heads, V = 4096, general / per sequence, B x L: d = 256 81 / 62 us at
+// 1 x 4, 89 / 69 at 16 x 4, 187 / 101 at 64 x 16, 314 / 163 at 256 x 16, 363 / 280 at 1000 x 4; d = 128 79 / 49 at 1 x 4, 275 / 137 at
+// 256 x 16.  (Wider: 1 MB of weights at d = 384 take longer than the launches.)
+bool mrp::mlp_per_sequence(int L, int d) { return (d == 128 || d == 256) && L <= 16; }
+
 // Form of the tile kernel for [M][R] partial sums of two activation planes over Kc columns: weight rows per tile, row
 // blocks and k parts, the fastest by what the forms were measured to take: a round of tiles about 6 us and, per k step,
 // 0.15 us and 10.1 ns for each of its 4 nv nb MFMAs per wave; a part's sums 2 x 4 bytes per entry at 4 TB/s.  Forms that
@@ -545,8 +551,9 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
     const int off = cfg->state_offset;
     // MLP body at small row counts: the first GEMM also reads the conditioning embeddings from the table
     // itself (no gathered copy is made) and applies the SiLU
-    const bool mlp_tiles = !layers && mlp_on_tiles(M, d, c->nCU, c->part_rows);
-    const bool fused = !layers && !mlp_tiles;
+    const bool tiny = !layers && mlp_per_sequence(L, d);
+    const bool mlp_tiles = !layers && !tiny && mlp_on_tiles(M, d, c->nCU, c->part_rows);
+    const bool fused = !layers && !tiny && !mlp_tiles;
 
     SelectArgs sa;
     memset(&sa, 0, sizeof(sa));
@@ -570,15 +577,16 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
         sa.tok = io->tok; sa.conf = io->conf; sa.lse = io->lse;
         sa.draft_pos = io->draft_pos; sa.draft_tok = io->draft_tok;
         sa.remasked = io->remasked;
-        sa.E = (K > 0 && !fused) ? Eb : nullptr;
-        HIP_TRY(c, launch_merge_select(sa, st));
-    } else if (K > 0 && !fused) {
+        sa.E = (K > 0 && !fused && !tiny) ? Eb : nullptr;
+        if (K == 0 || !tiny) HIP_TRY(c, launch_merge_select(sa, st));
+    } else if (K > 0 && !fused && !tiny) {
         HIP_TRY(c, launch_gather_e(Eb, io->cond_tok, c->XE, c->nIb, B, L, d, V, c->err_flag, st));
     }
     if (K == 0) return MRP_OK;
 
-    HIP_TRY(c, launch_init_hidden(static_cast<const uint16_t *>(h), h_run, c->XH, c->plane, c->nIb, M, d,
-                                  h != nullptr, st));
+    if (!tiny)
+        HIP_TRY(c, launch_init_hidden(static_cast<const uint16_t *>(h), h_run, c->XH, c->plane, c->nIb, M, d,
+                                      h != nullptr, st));
     int np_h = h ? 1 : NSPLIT;
     const int nkr_d = d / (16 * KSTEP);
 
@@ -593,7 +601,18 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
         int nks1 = 1, nks2 = 1;
         bool silu_done = false;   // the first GEMM's epilogue already wrote s = SiLU(a) as activation planes
         const float *resid = nullptr;   // transformer body: residual stream added to the last projection
-        if (fused) {
+        if (tiny) {
+            // the decision on the state before, the head body and the norm (state 0's decision too, where it was run)
+            HeadTinyArgs ta;
+            memset(&ta, 0, sizeof(ta));
+            ta.sel = sa; ta.decide = k > 1 || cfg->run_state0;
+            ta.W1p = static_cast<const uint4 *>(hd.W1_packed); ta.W2p = static_cast<const uint4 *>(hd.W2_packed);
+            ta.h = k == 1 ? static_cast<const uint16_t *>(h) : nullptr; ta.hrun = h_run;
+            ta.E = Eb; ta.gamma = static_cast<const uint16_t *>(hd.gamma); ta.cond_tok = io->cond_tok;
+            ta.eps = c->dims.rms_eps; ta.carry = cfg->carry_hidden != 0;
+            ta.Y = c->Y; ta.nIb = c->nIb; ta.L = L; ta.V = V; ta.err_flag = c->err_flag;
+            HIP_TRY(c, launch_head_tiny(ta, B, d, st));
+        } else if (fused) {
             // s = SiLU(W1 [h ; e]) with e read from the embedding table, then u = W2 s
             HeadFusedArgs fa;
             memset(&fa, 0, sizeof(fa));
@@ -694,7 +713,8 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
         }
         }
         // h_run += u ; y = bf16(RMSNorm(u) * gamma)
-        HIP_TRY(c, launch_norm(c->PART, nks2, resid, static_cast<const uint16_t *>(hd.gamma), c->dims.rms_eps, h_run,
+        if (!tiny)
+            HIP_TRY(c, launch_norm(c->PART, nks2, resid, static_cast<const uint16_t *>(hd.gamma), c->dims.rms_eps, h_run,
                                cfg->carry_hidden != 0, c->Y, c->XH, c->plane, c->nIb, M, d, st));
         if (cfg->carry_hidden) np_h = NSPLIT;
         // z += W_lm y, fused with the split-vocabulary (max, sum-exp, argmax) partials
@@ -749,8 +769,8 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
         sa.tok = io->tok + (size_t)k * M; sa.conf = io->conf + (size_t)k * M; sa.lse = io->lse + (size_t)k * M;
         sa.draft_pos = io->draft_pos + k; sa.draft_tok = io->draft_tok + k;
         sa.remasked = io->remasked ? io->remasked + (size_t)k * M : nullptr;
-        sa.E = (k < K && !fused) ? Eb : nullptr;
-        HIP_TRY(c, launch_merge_select(sa, st));
+        sa.E = (k < K && !fused && !tiny) ? Eb : nullptr;
+        if (k == K || !tiny) HIP_TRY(c, launch_merge_select(sa, st));
     }
     return MRP_OK;
 }

@@ -329,6 +329,25 @@ struct SelectArgs {
     int nIb;
     int *err_flag;          // device error word (may be nullptr)
 };
+// MLP head body of one sequence per workgroup for d = 128 or 256, blocks of at most 16 rows (head_tiny.hip)
+struct HeadTinyArgs {
+    SelectArgs sel;            // the state before this head
+    int decide;                // decide on it first (else its outcome is in cond_tok)
+    const uint4 *W1p, *W2p;    // packed fp16 weights
+    const uint16_t *h;         // bf16 hidden state to start from, or nullptr: hrun
+    float *hrun;
+    const uint16_t *E, *gamma;
+    const int32_t *cond_tok;
+    float eps;
+    bool carry;
+    uint4 *Y;                  // packed LM-head operand
+    int nIb, L, V;
+    int *err_flag;
+};
+hipError_t launch_head_tiny(const HeadTinyArgs &a, int B, int d, hipStream_t st);
+// Does the MLP head body run as one workgroup per sequence?
+bool mlp_per_sequence(int L, int d);
+
 hipError_t launch_reduce_rows(const float *z, int M, int V, float *pm, float *ps, int *pi, int *nT_out,
                               hipStream_t st);
 int reduce_rows_tiles(int V);

@@ -276,6 +276,8 @@ def test_row_counts_where_the_kernels_change(d, B, L, K):
     (2560, 12, 16, 1),   # 192 rows, a width whose parts leave the tile kernel's round empty: small-row kernels
     (2048, 64, 16, 1),   # 1024 rows: second GEMM on 128-row tiles
     (384, 48, 16, 2),    # 768 rows, a width that ends inside a tile
+    (384, 59, 13, 1),    # 767 rows: small-row kernels (24 row tiles)
+    (384, 257, 1, 1),    # nine row tiles: 64-feature tiles
 ])
 def test_head_body_on_tiles(d, B, L, K):
     """The MLP head body on both sides of the switch to the tile kernel below 768 rows, and its second GEMM's forms."""
@@ -304,6 +306,37 @@ def test_lm_head_kernel_by_width_and_vocabulary(d, B, L, V, tiles):
     cfg = mi.straddling(mi.config(0, d=d, V=V, B=B, L=L, K=1))
     prob, g, o, stats = _free_run(cfg, mrp.RevealCfg(tau=2.0), seqs=[0, B - 1])
     prob.close()
+
+
+@pytest.mark.parametrize("d,B,L", [
+    (128, 5, 16), (256, 3, 1), (256, 7, 11), (256, 4, 16),      # one workgroup per sequence
+    (256, 300, 4),                                              # more of them than CUs; partials tile by tile
+    (256, 3, 17), (384, 4, 16),                                 # a longer block, a wider model: the general path
+])
+def test_narrow_head_body(d, B, L):
+    """The head body as one workgroup per sequence (d of 128 or 256, blocks of up to 16 rows) and past its limits: three heads
+    with remasking, then one head that continues without a state 0 and without the hidden carry."""
+    cfg = mi.straddling(mi.config(0, d=d, V=4100, B=B, L=L, K=3))
+    rcfg = mrp.RevealCfg(tau=0.5, tau_remask=0.3)
+    prob, g, o, stats = _free_run(cfg, rcfg, seqs=list(range(0, B, max(1, B // 5))))
+    try:
+        s = o.snaps[1]
+        h = mi.hidden(cfg)
+        full = list(range(0, B, max(1, B // 5)))
+        io = mrp.StepIO(len(full), L, 1)
+        io.masked.copy_(torch.from_numpy(s.masked)); io.revealed_at.copy_(torch.from_numpy(s.revealed_at))
+        io.cond_tok.copy_(torch.from_numpy(s.cond_tok)); io.protect_pos.copy_(torch.from_numpy(s.protect_pos))
+        io.x_tok.copy_(torch.from_numpy(s.x_tok))
+        rows = np.concatenate([np.arange(b * L, (b + 1) * L) for b in full])
+        z_d = torch.from_numpy(s.z.astype(np.float32)).cuda()
+        r1 = mrp.RevealCfg(tau=0.5, tau_remask=0.3, fresh_block=0, state_offset=1, run_state0=0, carry_hidden=0)
+        io, hrun_d = gpu_chain(prob, len(full), 1, z_d, h[rows], r1, io=io, heads=prob.heads_d[1:2])
+        np.testing.assert_array_equal(hrun_d.cpu().numpy(), mi.bf16_bits_to_f64(h[rows]).astype(np.float32))   # not carried
+        o1 = oracle_chain(prob, s.z, mi.bf16_bits_to_f64(h[rows]), r1, 1, masked=s.masked, revealed_at=s.revealed_at,
+                          cond_tok=s.cond_tok, protect_pos=s.protect_pos, heads=prob.heads[1:2], x_tok=s.x_tok)
+        compare_chain(io_to_host(io), z_d.cpu().numpy(), hrun_d.cpu().numpy(), o1, list(range(len(full))), L, 1, r1)
+    finally:
+        prob.close()
 
 
 @pytest.mark.parametrize("B,L,V", [
