@@ -25,27 +25,8 @@ __global__ __launch_bounds__(256) void pack_weight_kernel(const uint16_t *__rest
     dst[ci] = to_f16 ? bf16x8_to_f16x8(v) : v;
 }
 
-// from_h: hrun <- fp32(h), plane 0 <- fp16(h).  else: planes <- split2(hrun).
-__global__ __launch_bounds__(256) void init_hidden_kernel(const uint16_t *__restrict__ h, float *__restrict__ hrun,
-                                                          uint4 *__restrict__ xh, long plane_stride, int nIb, int M,
-                                                          int d, bool from_h) {
-    int i, c8;
-    if (!plane_block_lane((size_t)blockIdx.x * 4 + (threadIdx.x >> 6), d >> 4, M, i, c8)) return;
-    const size_t dst = act_chunk_index(i, c8, nIb);
-    if (from_h) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(h + (size_t)i * d + 8 * c8);
-        float x[8];
-        unpack_bf16x8(v, x);
-        float4 *hp = reinterpret_cast<float4 *>(hrun + (size_t)i * d + 8 * c8);
-        hp[0] = make_float4(x[0], x[1], x[2], x[3]);
-        hp[1] = make_float4(x[4], x[5], x[6], x[7]);
-        xh[dst] = bf16x8_to_f16x8(v);
-    } else {
-        const float4 *hp = reinterpret_cast<const float4 *>(hrun + (size_t)i * d + 8 * c8);
-        const float4 a = hp[0], b = hp[1];
-        const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        split_store(x, xh, dst, plane_stride);
-    }
+__global__ __launch_bounds__(256) void init_hidden_kernel(const InitHiddenArgs a) {
+    init_hidden_unit(a, (size_t)blockIdx.x * 4 + (threadIdx.x >> 6));
 }
 
 __global__ __launch_bounds__(256) void gather_e_kernel(const uint16_t *__restrict__ E,
@@ -75,10 +56,10 @@ __global__ __launch_bounds__(256) void silu_split_kernel(const float *__restrict
     split_store(x, s_planes, act_chunk_index(i, c8, nIb), plane_stride);
 }
 
-constexpr int NORM_MAX_CHUNKS = 4;  // per thread: d <= 8 * 256 * 4 = 8192
-
 // One workgroup per row: u = sum of k-split partials, RMSNorm -> bf16 y (packed),
-// h_run += u and the split planes of the new h_run for the next head.
+// h_run += u and the split planes of the new h_run for the next head.  NC: 8-column chunks per thread (d <= 2048 NC).
+// What bounds it up to a few hundred rows is one round of loads, so that everything is requested before anything is used.
+template <int NC>
 __global__ __launch_bounds__(256) void norm_kernel(const float *__restrict__ part, int nKs,
                                                    const float *__restrict__ resid,
                                                    const uint16_t *__restrict__ gamma, float eps,
@@ -88,25 +69,38 @@ __global__ __launch_bounds__(256) void norm_kernel(const float *__restrict__ par
     const int i = xcd_row_of(blockIdx.x);
     if (i >= M) return;   // (uniform over the workgroup)
     const int C8 = d >> 3;
-    float u[NORM_MAX_CHUNKS][8];
-    float4 hv[NORM_MAX_CHUNKS][2];   // the row of h_run, requested with u (one round trip instead of two)
+    float u[NC][8];
+    float4 hv[NC][2], rv[NC][2];   // the row of h_run and of the residual stream
+    uint4 gv[NC];
     float ss = 0.f;
 #pragma unroll
-    for (int n = 0; n < NORM_MAX_CHUNKS; ++n) {
+    for (int n = 0; n < NC; ++n) {
         const int c8 = threadIdx.x + 256 * n;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) u[n][e] = 0.f;
-        hv[n][0] = hv[n][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+        hv[n][0] = hv[n][1] = rv[n][0] = rv[n][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+        gv[n] = make_uint4(0, 0, 0, 0);
         if (c8 < C8) {
             if (carry) {
                 const float4 *hp = reinterpret_cast<const float4 *>(hrun + (size_t)i * d + 8 * c8);
                 hv[n][0] = hp[0];
                 hv[n][1] = hp[1];
             }
-            sum_partials(part, (size_t)M * d, nKs, (size_t)i * d + 8 * c8, u[n]);
             if (resid) {   // transformer body: u = residual stream + last projection
                 const float4 *rp = reinterpret_cast<const float4 *>(resid + (size_t)i * d + 8 * c8);
-                const float4 a = rp[0], b = rp[1];
+                rv[n][0] = rp[0];
+                rv[n][1] = rp[1];
+            }
+            gv[n] = *reinterpret_cast<const uint4 *>(gamma + 8 * c8);
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+        const int c8 = threadIdx.x + 256 * n;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u[n][e] = 0.f;
+        if (c8 < C8) {
+            sum_partials(part, (size_t)M * d, nKs, (size_t)i * d + 8 * c8, u[n]);
+            if (resid) {
+                const float4 a = rv[n][0], b = rv[n][1];
                 u[n][0] += a.x; u[n][1] += a.y; u[n][2] += a.z; u[n][3] += a.w;
                 u[n][4] += b.x; u[n][5] += b.y; u[n][6] += b.z; u[n][7] += b.w;
             }
@@ -121,11 +115,11 @@ __global__ __launch_bounds__(256) void norm_kernel(const float *__restrict__ par
     ss = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
     const float inv = 1.0f / sqrtf(ss / (float)d + eps);
 #pragma unroll
-    for (int n = 0; n < NORM_MAX_CHUNKS; ++n) {
+    for (int n = 0; n < NC; ++n) {
         const int c8 = threadIdx.x + 256 * n;
         if (c8 < C8) {
             float g[8];
-            unpack_bf16x8(*reinterpret_cast<const uint4 *>(gamma + 8 * c8), g);
+            unpack_bf16x8(gv[n], g);
             uint16_t yb[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) yb[e] = f32_to_bf16_rne(u[n][e] * inv * g[e]);
@@ -145,8 +139,6 @@ __global__ __launch_bounds__(256) void norm_kernel(const float *__restrict__ par
 }
 
 inline unsigned blocks_for(size_t n) { return (unsigned)((n + 255) / 256); }
-// workgroups of 4 waves, one (k block, row block) unit per wave
-inline unsigned plane_blocks(int M, int cols) { return (unsigned)(((size_t)((M + 31) / 32) * (cols / 16) + 3) / 4); }
 // one workgroup per row, rows padded to whole XCD rounds of 32-row blocks
 inline unsigned xcd_row_blocks(int M) { return (unsigned)((M + 255) / 256 * 256); }
 
@@ -160,10 +152,8 @@ hipError_t launch_pack_weight(const uint16_t *src, int rows, int cols, uint4 *ds
     return hipGetLastError();
 }
 
-hipError_t launch_init_hidden(const uint16_t *h, float *hrun, uint4 *xh, long plane_stride, int nIb, int M,
-                              int d, bool from_h, hipStream_t st) {
-    hipLaunchKernelGGL(init_hidden_kernel, dim3(plane_blocks(M, d)), dim3(256), 0, st, h, hrun, xh,
-                       plane_stride, nIb, M, d, from_h);
+hipError_t launch_init_hidden(const InitHiddenArgs &a, hipStream_t st) {
+    hipLaunchKernelGGL(init_hidden_kernel, dim3(plane_blocks(a.M, a.d)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -182,7 +172,8 @@ hipError_t launch_silu_split(const float *part, int nKs, uint4 *s_planes, long p
 
 hipError_t launch_norm(const float *part, int nKs, const float *resid, const uint16_t *gamma, float eps, float *hrun,
                        bool carry, uint4 *y, uint4 *xh, long plane_stride, int nIb, int M, int d, hipStream_t st) {
-    hipLaunchKernelGGL(norm_kernel, dim3(xcd_row_blocks(M)), dim3(256), 0, st, part, nKs, resid, gamma, eps, hrun, carry, y, xh,
+    const auto k = d <= 2048 ? norm_kernel<1> : (d <= 4096 ? norm_kernel<2> : norm_kernel<4>);      // (d <= 8192)
+    hipLaunchKernelGGL(k, dim3(xcd_row_blocks(M)), dim3(256), 0, st, part, nKs, resid, gamma, eps, hrun, carry, y, xh,
                        plane_stride, nIb, M, d);
     return hipGetLastError();
 }

@@ -567,9 +567,11 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
     sa.x_tok = io->x_tok; sa.remask_mode = cfg->remask_mode; sa.z = z;
     sa.err_flag = c->err_flag;
 
+    const InitHiddenArgs init = {static_cast<const uint16_t *>(h), h_run, c->XH, c->plane, c->nIb, M, d, h != nullptr};
+    const bool with_init = K > 0 && !tiny;
     if (cfg->run_state0) {
         int nT0 = 0;
-        HIP_TRY(c, launch_reduce_rows(z, M, V, c->pm, c->ps, c->pi, &nT0, st));
+        HIP_TRY(c, launch_reduce_rows(z, M, V, c->pm, c->ps, c->pi, &nT0, with_init ? &init : nullptr, st));
         sa.nT = nT0;
         sa.slot_stride = 1; sa.row_stride = nT0;
         sa.state = off; sa.do_reveal = 1; sa.fresh = cfg->fresh_block; sa.write_protect = 1;
@@ -584,9 +586,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
     }
     if (K == 0) return MRP_OK;
 
-    if (!tiny)
-        HIP_TRY(c, launch_init_hidden(static_cast<const uint16_t *>(h), h_run, c->XH, c->plane, c->nIb, M, d,
-                                      h != nullptr, st));
+    if (with_init && !cfg->run_state0) HIP_TRY(c, launch_init_hidden(init, st));
     int np_h = h ? 1 : NSPLIT;
     const int nkr_d = d / (16 * KSTEP);
 

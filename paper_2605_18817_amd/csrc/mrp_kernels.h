@@ -225,32 +225,62 @@ __device__ __forceinline__ uint4 bf16x8_to_f16x8(const uint4 &u) {
 }
 
 // Sum over the k-split partial buffers of the 8 floats at `off` (same order for any batching:
-// ((p0 + p1) + p2) + ...).  Four splits are fetched at a time so their latencies overlap.
+// ((p0 + p1) + p2) + ...).  Eight splits, then four, are fetched at a time so their latencies overlap.
+template <int N>
+__device__ __forceinline__ void add_partials(const float *__restrict__ part, size_t split_stride, float (&x)[8]) {
+    float4 a[N], b[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const float4 *p = reinterpret_cast<const float4 *>(part + u * split_stride);
+        a[u] = p[0]; b[u] = p[1];
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        x[0] += a[u].x; x[1] += a[u].y; x[2] += a[u].z; x[3] += a[u].w;
+        x[4] += b[u].x; x[5] += b[u].y; x[6] += b[u].z; x[7] += b[u].w;
+    }
+}
 __device__ __forceinline__ void sum_partials(const float *__restrict__ part, size_t split_stride, int nKs, size_t off,
                                              float (&x)[8]) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e] = 0.f;
+    part += off;
     int ks = 0;
-    for (; ks + 4 <= nKs; ks += 4) {
-        float4 a[4], b[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float4 *p = reinterpret_cast<const float4 *>(part + (size_t)(ks + u) * split_stride + off);
-            a[u] = p[0]; b[u] = p[1];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            x[0] += a[u].x; x[1] += a[u].y; x[2] += a[u].z; x[3] += a[u].w;
-            x[4] += b[u].x; x[5] += b[u].y; x[6] += b[u].z; x[7] += b[u].w;
-        }
-    }
-    for (; ks < nKs; ++ks) {
-        const float4 *p = reinterpret_cast<const float4 *>(part + (size_t)ks * split_stride + off);
-        const float4 a = p[0], b = p[1];
-        x[0] += a.x; x[1] += a.y; x[2] += a.z; x[3] += a.w;
-        x[4] += b.x; x[5] += b.y; x[6] += b.z; x[7] += b.w;
+    for (; ks + 8 <= nKs; ks += 8) add_partials<8>(part + ks * split_stride, split_stride, x);
+    if (ks + 4 <= nKs) { add_partials<4>(part + ks * split_stride, split_stride, x); ks += 4; }
+    if (ks + 2 <= nKs) { add_partials<2>(part + ks * split_stride, split_stride, x); ks += 2; }
+    if (ks < nKs) add_partials<1>(part + ks * split_stride, split_stride, x);
+}
+
+// hrun <- fp32(h), plane 0 <- fp16(h) (from_h), or planes <- split2(hrun): one unit is a wave's 1 KiB plane block
+struct InitHiddenArgs {
+    const uint16_t *h;
+    float *hrun;
+    uint4 *xh;
+    long plane_stride;
+    int nIb, M, d;
+    bool from_h;
+};
+__device__ __forceinline__ void init_hidden_unit(const InitHiddenArgs &a, size_t unit) {
+    int i, c8;
+    if (!plane_block_lane(unit, a.d >> 4, a.M, i, c8)) return;
+    const size_t dst = act_chunk_index(i, c8, a.nIb);
+    float4 *hp = reinterpret_cast<float4 *>(a.hrun + (size_t)i * a.d + 8 * c8);
+    if (a.from_h) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(a.h + (size_t)i * a.d + 8 * c8);
+        float x[8];
+        unpack_bf16x8(v, x);
+        hp[0] = make_float4(x[0], x[1], x[2], x[3]);
+        hp[1] = make_float4(x[4], x[5], x[6], x[7]);
+        a.xh[dst] = bf16x8_to_f16x8(v);
+    } else {
+        const float4 p = hp[0], q = hp[1];
+        const float x[8] = {p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w};
+        split_store(x, a.xh, dst, a.plane_stride);
     }
 }
+// workgroups of 4 waves, one (k block, row block) unit per wave
+inline unsigned plane_blocks(int M, int cols) { return (unsigned)(((size_t)((M + 31) / 32) * (cols / 16) + 3) / 4); }
 
 // ---- host-side launchers (defined in the .hip files) ----
 hipError_t launch_stream_gemm(const StreamGemmArgs &a, hipStream_t st);
@@ -289,8 +319,7 @@ size_t lm_persist_lds_bytes();
 hipError_t lm_persist_configure();    // once per device
 
 hipError_t launch_pack_weight(const uint16_t *src, int rows, int cols, uint4 *dst, bool to_f16, hipStream_t st);
-hipError_t launch_init_hidden(const uint16_t *h, float *hrun, uint4 *xh, long plane_stride, int nIb,
-                              int M, int d, bool from_h, hipStream_t st);
+hipError_t launch_init_hidden(const InitHiddenArgs &a, hipStream_t st);
 hipError_t launch_gather_e(const uint16_t *E, const int32_t *cond_tok, uint4 *xe, int nIb, int B, int L,
                            int d, int V, int *err_flag, hipStream_t st);
 hipError_t launch_silu_split(const float *part, int nKs, uint4 *s_planes, long plane_stride, int nIb,
@@ -348,8 +377,9 @@ hipError_t launch_head_tiny(const HeadTinyArgs &a, int B, int d, hipStream_t st)
 // Does the MLP head body run as one workgroup per sequence?
 bool mlp_per_sequence(int L, int d);
 
+// `init` (or nullptr): the hidden state's planes in the same launch
 hipError_t launch_reduce_rows(const float *z, int M, int V, float *pm, float *ps, int *pi, int *nT_out,
-                              hipStream_t st);
+                              const InitHiddenArgs *init, hipStream_t st);
 int reduce_rows_tiles(int V);
 hipError_t launch_merge_select(const SelectArgs &a, hipStream_t st);
 hipError_t launch_commit(int B, int L, const int32_t *x_tok, int8_t *revealed_at, const uint8_t *masked,

@@ -33,12 +33,18 @@ __device__ __forceinline__ Part block_merge(Part p, float *sm, float *ss, int *s
     return p;
 }
 
+// Grid: the row tiles of z; past its M rows the units of `init` (its M is 0: none), which need nothing of z and would
+// otherwise be a launch of their own (5 us at 4 to 200 rows).
 __global__ __launch_bounds__(256) void reduce_rows_kernel(const float *__restrict__ z, int M, int V,
                                                           float *__restrict__ pm, float *__restrict__ ps,
-                                                          int *__restrict__ pi) {
+                                                          int *__restrict__ pi, const InitHiddenArgs init) {
     __shared__ float sm[4], ss[4];
     __shared__ int si[4];
     const int t = blockIdx.x, i = blockIdx.y;
+    if (i >= M) {
+        init_hidden_unit(init, ((size_t)(i - M) * gridDim.x + t) * 4 + (threadIdx.x >> 6));
+        return;
+    }
     const float *row = z + (size_t)i * V;
     const int v0 = t * RT;
     float x[32];
@@ -267,10 +273,20 @@ int reduce_rows_tiles(int V) { return (V + RT - 1) / RT; }
 int verify_chunks(int V) { return (V + RT - 1) / RT; }
 
 hipError_t launch_reduce_rows(const float *z, int M, int V, float *pm, float *ps, int *pi, int *nT_out,
-                              hipStream_t st) {
+                              const InitHiddenArgs *init, hipStream_t st) {
     const int nT = reduce_rows_tiles(V);
     *nT_out = nT;
-    hipLaunchKernelGGL(reduce_rows_kernel, dim3(nT, M), dim3(256), 0, st, z, M, V, pm, ps, pi);
+    InitHiddenArgs ia = {};
+    unsigned more = 0;      // grid rows for the hidden state
+    if (init) {
+        const unsigned rows = (plane_blocks(init->M, init->d) + nT - 1) / nT;
+        if (M + rows <= 65535) { more = rows; ia = *init; }
+        else {
+            const hipError_t e = launch_init_hidden(*init, st);
+            if (e != hipSuccess) return e;
+        }
+    }
+    hipLaunchKernelGGL(reduce_rows_kernel, dim3(nT, M + more), dim3(256), 0, st, z, M, V, pm, ps, pi, ia);
     return hipGetLastError();
 }
 

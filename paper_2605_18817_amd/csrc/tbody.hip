@@ -39,10 +39,10 @@ __global__ __launch_bounds__(256) void rope_table_kernel(const int32_t *__restri
     out[idx] = make_float2((float)cos(ang), (float)sin(ang));
 }
 
-constexpr int NORM_MAX_CHUNKS = 4;  // per thread: d <= 8 * 256 * 4 = 8192
-
 // One workgroup per row: x = (resid ? resid : 0) + sum of partials; stream <- x;
-// planes <- split2(RMSNorm(x) gain).
+// planes <- split2(RMSNorm(x) gain).  NC: 8-column chunks per thread (d <= 2048 NC); the residual row and the gain are
+// requested ahead of the partials.
+template <int NC>
 __global__ __launch_bounds__(256) void resid_norm_split_kernel(const float *__restrict__ part, int nKs,
                                                                const float *resid, float *stream,
                                                                const uint16_t *__restrict__ gain, float eps,
@@ -52,18 +52,33 @@ __global__ __launch_bounds__(256) void resid_norm_split_kernel(const float *__re
     const int i = xcd_row_of(blockIdx.x);
     if (i >= M) return;   // (uniform over the workgroup)
     const int C8 = d >> 3;
-    float x[NORM_MAX_CHUNKS][8];
+    float x[NC][8];
+    float4 rv[NC][2];
+    uint4 gv[NC];
     float ss = 0.f;
 #pragma unroll
-    for (int n = 0; n < NORM_MAX_CHUNKS; ++n) {
+    for (int n = 0; n < NC; ++n) {
+        const int c8 = threadIdx.x + 256 * n;
+        rv[n][0] = rv[n][1] = make_float4(0.f, 0.f, 0.f, 0.f);
+        gv[n] = make_uint4(0, 0, 0, 0);
+        if (c8 < C8) {
+            if (resid) {
+                const float4 *rp = reinterpret_cast<const float4 *>(resid + (size_t)i * d + 8 * c8);
+                rv[n][0] = rp[0];
+                rv[n][1] = rp[1];
+            }
+            gv[n] = *reinterpret_cast<const uint4 *>(gain + 8 * c8);
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
         const int c8 = threadIdx.x + 256 * n;
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[n][e] = 0.f;
         if (c8 < C8) {
             sum_partials(part, (size_t)M * d, nKs, (size_t)i * d + 8 * c8, x[n]);
             if (resid) {
-                const float4 *rp = reinterpret_cast<const float4 *>(resid + (size_t)i * d + 8 * c8);
-                const float4 a = rp[0], b = rp[1];
+                const float4 a = rv[n][0], b = rv[n][1];
                 x[n][0] += a.x; x[n][1] += a.y; x[n][2] += a.z; x[n][3] += a.w;
                 x[n][4] += b.x; x[n][5] += b.y; x[n][6] += b.z; x[n][7] += b.w;
             }
@@ -81,11 +96,11 @@ __global__ __launch_bounds__(256) void resid_norm_split_kernel(const float *__re
     ss = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
     const float inv = 1.0f / sqrtf(ss / (float)d + eps);
 #pragma unroll
-    for (int n = 0; n < NORM_MAX_CHUNKS; ++n) {
+    for (int n = 0; n < NC; ++n) {
         const int c8 = threadIdx.x + 256 * n;
         if (c8 < C8) {
             float g[8], y[8];
-            unpack_bf16x8(*reinterpret_cast<const uint4 *>(gain + 8 * c8), g);
+            unpack_bf16x8(gv[n], g);
 #pragma unroll
             for (int e = 0; e < 8; ++e) y[e] = x[n][e] * inv * g[e];
             split_store(y, planes, act_chunk_index(i, c8, nIb), plane_stride);
@@ -603,7 +618,8 @@ hipError_t launch_rope_table(const int32_t *prefix_len, int B, int L, int P_max,
 hipError_t launch_resid_norm_split(const float *part, int nKs, const float *resid, float *stream,
                                    const uint16_t *gain, float eps, uint4 *planes, long plane_stride, int nIb, int M,
                                    int d, hipStream_t st) {
-    hipLaunchKernelGGL(resid_norm_split_kernel, dim3((M + 255) / 256 * 256), dim3(256), 0, st, part, nKs, resid, stream, gain, eps,
+    const auto k = d <= 2048 ? resid_norm_split_kernel<1> : (d <= 4096 ? resid_norm_split_kernel<2> : resid_norm_split_kernel<4>);
+    hipLaunchKernelGGL(k, dim3((M + 255) / 256 * 256), dim3(256), 0, st, part, nKs, resid, stream, gain, eps,
                        planes, plane_stride, nIb, M, d);
     return hipGetLastError();
 }
