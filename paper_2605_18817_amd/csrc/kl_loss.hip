@@ -4,14 +4,13 @@
 //     dL_i / ds[i][v] = softmax(s[i])[v] - softmax(l_{t-1}[i])[v],
 // with teacher T = l_{t-1} and student S = l_t + delta_t given as fp32 [M][V].
 //
-// Both passes are memory streams.  Every (row, 8192-wide vocabulary tile) keeps the online partial
+// All of it is a memory stream.  Every (row, 8192-wide vocabulary tile) keeps the online partial
 //     (m_T, s_T = sum e^{T - m_T}, a_T = sum e^{T - m_T} (T - S),  m_S, s_S = sum e^{S - m_S})
 // of the forward pass, and a row's partials merge to
 //     L_i = a_T / s_T - (m_T + log s_T) + (m_S + log s_S).
-// No softmax is written.  The gradient reads both tensors once more and writes the difference of the two
-// softmaxes.  Algorithmic bytes: 8 M V forward, 4 M V for the gradient; its second read of the tensors comes
-// largely from the last-level cache where the rows are taken in groups (see launch_kl_loss): at 1024 rows, V = 151936,
-// 80 % of them in the mask, 2.6 GB leave the L2s in 425 us, 6.2 TB/s, where a large copy moves 4.7.
+// No softmax is written.  Algorithmic bytes: 8 M V forward, 4 M V for the gradient, which is the difference of the two
+// softmaxes: taken from the entries that the forward pass left in registers (kl_grad_kernel; 1024 rows of 151936: 1.87 GB in
+// 383 us, 4.9 TB/s, where a large copy moves 4.7), or at few rows from a second read.
 #include "mrp_kernels.h"
 
 namespace mrp {
@@ -67,12 +66,15 @@ struct KlArgs {
     const uint8_t *mask;
     int V, nT;
     float scale;
-    float *part;
+    float *part;                  // without a gradient: five arrays, `stride` apart
+    unsigned long long *words;    // with one: the same as 64-bit words, mark and value
     size_t stride;
     float *loss, *grad;
-    int p0, nP;      // rows p0 .. p0 + nP - 1: partials
-    int g0, nG;      // rows g0 .. g0 + nG - 1: loss and gradient (their partials are complete)
+    int M;
+    int nq;                       // counters that the one-pass form draws from (0: two passes)
 };
+
+constexpr int MAX_Q = 7;
 
 // The 32 entries of a tensor's row that a thread handles in tile t: eight 16-byte pieces, -inf past the row's end
 __device__ __forceinline__ void kl_fetch(const float *row, int v0, int V, float4 (&x)[8]) {
@@ -84,12 +86,8 @@ __device__ __forceinline__ float kl_at(const float4 (&x)[8], int n) {
     return (n & 3) == 0 ? q.x : ((n & 3) == 1 ? q.y : ((n & 3) == 2 ? q.z : q.w));
 }
 
-// partial of one KT-wide tile of one row
-__device__ __forceinline__ void kl_partial(const KlArgs &a, int t, int i, KlPart *sw) {
-    if (a.mask && !a.mask[i]) return;   // (uniform over the workgroup)
-    float4 xt[8], xs[8];
-    kl_fetch(a.T + (size_t)i * a.V, t * KT, a.V, xt);
-    kl_fetch(a.S + (size_t)i * a.V, t * KT, a.V, xs);
+// Partial of one KT-wide tile from its entries; valid in thread 0.  sw: one slot per wavefront
+__device__ __forceinline__ KlPart kl_tile(const float4 (&xt)[8], const float4 (&xs)[8], KlPart *sw) {
     KlPart p = kl_identity();
 #pragma unroll
     for (int n = 0; n < 32; ++n) { p.mT = fmaxf(p.mT, kl_at(xt, n)); p.mS = fmaxf(p.mS, kl_at(xs, n)); }
@@ -112,32 +110,33 @@ __device__ __forceinline__ void kl_partial(const KlArgs &a, int t, int i, KlPart
     if (threadIdx.x == 0) {
         p = sw[0];
         for (int w = 1; w < 4; ++w) p = kl_merge(p, sw[w]);
+    }
+    return p;
+}
+
+// loss alone: partials of one KT-wide tile of one row
+__global__ __launch_bounds__(256) void kl_partial_kernel(const KlArgs a) {
+    __shared__ KlPart sw[4];
+    const int t = blockIdx.x, i = blockIdx.y;
+    if (a.mask && !a.mask[i]) return;   // (uniform over the workgroup)
+    float4 xt[8], xs[8];
+    kl_fetch(a.T + (size_t)i * a.V, t * KT, a.V, xt);
+    kl_fetch(a.S + (size_t)i * a.V, t * KT, a.V, xs);
+    const KlPart p = kl_tile(xt, xs, sw);
+    if (threadIdx.x == 0) {
         const size_t o = (size_t)i * a.nT + t;
         a.part[o] = p.mT; a.part[a.stride + o] = p.sT; a.part[2 * a.stride + o] = p.aT;
         a.part[3 * a.stride + o] = p.mS; a.part[4 * a.stride + o] = p.sS;
     }
 }
 
-// gradient of one KT-wide tile of one row; tile 0 also writes the row's loss
-__device__ __forceinline__ void kl_gradient(const KlArgs &a, int t, int i) {
-    const bool on = !a.mask || a.mask[i];     // (uniform over the workgroup)
+// Gradient of one KT-wide tile of one row from its entries; zero where the row is not in the mask
+__device__ __forceinline__ void kl_write(const KlArgs &a, int t, int i, bool on, const float4 (&xt)[8], const float4 (&xs)[8],
+                                         float lT, float lS) {
     float *gr = a.grad + (size_t)i * a.V;
-    const int v0 = t * KT;
-    float4 xt[8], xs[8];
-    float lT = 0.f, lS = 0.f;
-    if (on) {
-        kl_fetch(a.T + (size_t)i * a.V, v0, a.V, xt);     // in flight while the row's partials are merged
-        kl_fetch(a.S + (size_t)i * a.V, v0, a.V, xs);
-        const KlPart p = kl_row(a.part, a.stride, a.nT, i);
-        lT = p.mT + logf(p.sT);
-        lS = p.mS + logf(p.sS);
-        if (t == 0 && threadIdx.x == 0) a.loss[i] = a.scale * (p.aT / p.sT - lT + lS);
-    } else if (t == 0 && threadIdx.x == 0) {
-        a.loss[i] = 0.f;
-    }
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
-        const int v = v0 + 4 * (threadIdx.x + 256 * n);
+        const int v = t * KT + 4 * (threadIdx.x + 256 * n);
         float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
         if (on) {
             g.x = a.scale * (__expf(xs[n].x - lS) - __expf(xt[n].x - lT));
@@ -146,7 +145,6 @@ __device__ __forceinline__ void kl_gradient(const KlArgs &a, int t, int i) {
             g.w = a.scale * (__expf(xs[n].w - lS) - __expf(xt[n].w - lT));
         }
         if (v + 4 <= a.V) {
-            // (not kept in the last-level cache, which the rows still to be read again need)
             const f32x4_any gv = {g.x, g.y, g.z, g.w};
             __builtin_nontemporal_store(gv, reinterpret_cast<f32x4_any *>(gr + v));
         } else if (v < a.V) {
@@ -157,15 +155,99 @@ __device__ __forceinline__ void kl_gradient(const KlArgs &a, int t, int i) {
     }
 }
 
-// One launch takes the partials of one group of rows and the gradient of the group before it, alternating while
-// both have rows left, so that the reads of the one run beside the writes of the other.
-__global__ __launch_bounds__(256) void kl_kernel(const KlArgs a) {
+// Loss and gradient in one pass over the tensors: a workgroup keeps its tile's entries in registers (64 per thread, four
+// workgroups per CU), publishes the tile's partial, waits for the other tiles of its row and writes the gradient from
+// what it holds.  A value and its mark travel in one 64-bit word, so nothing else has to be ordered; words and counters are
+// cleared by a launch before.
+//
+// The wait ends whatever order workgroups start in: which tile a workgroup takes is drawn from one of nq counters as it
+// starts, so of the rows of a counter at most one has tiles that nobody has drawn yet.  Rows that are all drawn need
+// nobody else and leave; the others hold at most nq (nT - 1) places, an eighth of the device (kl_counters).
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void kl_grad_kernel(const KlArgs a) {
     __shared__ KlPart sw[4];
-    const int t = blockIdx.x, y = blockIdx.y, both = 2 * (a.nP < a.nG ? a.nP : a.nG);
-    const bool part = y < both ? (y & 1) == 0 : a.nP > a.nG;
-    const int r = y < both ? y >> 1 : y - both / 2;
-    if (part) kl_partial(a, t, a.p0 + r, sw);
-    else kl_gradient(a, t, a.g0 + r);
+    __shared__ float s_lse[2];
+    __shared__ int s_draw;
+    const int lane = threadIdx.x & 63, q = blockIdx.x % a.nq;
+    if (threadIdx.x == 0)
+        s_draw = (int)__hip_atomic_fetch_add(a.words + 5 * a.stride + 16 * q, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int draw = __builtin_amdgcn_readfirstlane(s_draw), t = draw % a.nT, i = draw / a.nT * a.nq + q;
+    if (i >= a.M) return;                     // (uniform over the workgroup, as is what follows)
+    const bool on = !a.mask || a.mask[i];
+    float4 xt[8], xs[8];
+    float lT = 0.f, lS = 0.f;
+    if (on) {
+        kl_fetch(a.T + (size_t)i * a.V, t * KT, a.V, xt);
+        kl_fetch(a.S + (size_t)i * a.V, t * KT, a.V, xs);
+        const KlPart p = kl_tile(xt, xs, sw);
+        unsigned long long *words = a.words + (size_t)i * a.nT;
+        if (threadIdx.x == 0) {
+            const float v[5] = {p.mT, p.sT, p.aT, p.mS, p.sS};
+#pragma unroll
+            for (int n = 0; n < 5; ++n)
+                __hip_atomic_store(words + n * a.stride + t, (1ull << 32) | __float_as_uint(v[n]), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (threadIdx.x < 64) {      // the order of kl_row
+            KlPart r = kl_identity();
+            for (int u = lane; u < a.nT; u += 64) {
+                unsigned long long w[5];
+                bool all;
+                do {
+                    all = true;
+#pragma unroll
+                    for (int n = 0; n < 5; ++n) {
+                        w[n] = __hip_atomic_load(words + n * a.stride + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        all = all && (w[n] >> 32) != 0;
+                    }
+                    if (!all) __builtin_amdgcn_s_sleep(4);
+                } while (!all);
+                float v[5];
+#pragma unroll
+                for (int n = 0; n < 5; ++n) v[n] = __uint_as_float((unsigned)w[n]);
+                r = kl_merge(r, KlPart{v[0], v[1], v[2], v[3], v[4]});
+            }
+            r = kl_wave_merge(r);
+            if (lane == 0) {
+                const float qT = r.mT + logf(r.sT), qS = r.mS + logf(r.sS);
+                s_lse[0] = qT;
+                s_lse[1] = qS;
+                if (t == 0) a.loss[i] = a.scale * (r.aT / r.sT - qT + qS);
+            }
+        }
+        __syncthreads();
+        lT = s_lse[0];
+        lS = s_lse[1];
+    } else if (t == 0 && threadIdx.x == 0) {
+        a.loss[i] = 0.f;
+    }
+    kl_write(a, t, i, on, xt, xs, lT, lS);
+}
+
+// The same in two passes, the second after the partials' launch
+__global__ __launch_bounds__(256) void kl_second_kernel(const KlArgs a) {
+    const int t = blockIdx.x, i = blockIdx.y;
+    const bool on = !a.mask || a.mask[i];     // (uniform over the workgroup)
+    float4 xt[8], xs[8];
+    float lT = 0.f, lS = 0.f;
+    if (on) {
+        kl_fetch(a.T + (size_t)i * a.V, t * KT, a.V, xt);     // in flight while the row's partials are merged
+        kl_fetch(a.S + (size_t)i * a.V, t * KT, a.V, xs);
+        const KlPart p = kl_row(a.part, a.stride, a.nT, i);
+        lT = p.mT + logf(p.sT);
+        lS = p.mS + logf(p.sS);
+        if (t == 0 && threadIdx.x == 0) a.loss[i] = a.scale * (p.aT / p.sT - lT + lS);
+    } else if (t == 0 && threadIdx.x == 0) {
+        a.loss[i] = 0.f;
+    }
+    kl_write(a, t, i, on, xt, xs, lT, lS);
+}
+
+// the words' first n entries of each of the five arrays, and the counters
+__global__ __launch_bounds__(256) void kl_clear_kernel(unsigned long long *words, size_t stride, int n) {
+    const int o = blockIdx.x * 256 + threadIdx.x;
+    if (o < n && blockIdx.y < 5) words[blockIdx.y * stride + o] = 0;
+    if (o < MAX_Q && blockIdx.y == 5) words[5 * stride + 16 * o] = 0;
 }
 
 // loss alone: one wavefront per row
@@ -180,42 +262,45 @@ __global__ __launch_bounds__(256) void kl_finish_kernel(const KlArgs a, int M) {
     if ((threadIdx.x & 63) == 0) a.loss[i] = loss;
 }
 
-// Rows taken together when there is a gradient: a group's teacher and student rows are read for the partials and
-// once more, one launch later, for the gradient.  What is live in between, two tensors of two groups, has to fit the
-// 256 MB last-level cache; smaller groups only add launches.  Measured at 1024 rows, V = 151936: 503 us with groups of
-// 52 MB per tensor, 523 of 40, 542 of 30, 612 of 20, 601 of 80, 558 in one group (579 with a launch per pass and the
-// scalar merge between them); at 64 rows one group, 34 us.
-constexpr size_t GROUP_BYTES = (size_t)52 << 20;
-
 }  // namespace
 
 int kl_tiles(int V) { return (V + KT - 1) / KT; }
 
+size_t kl_part_bytes(size_t stride) { return (5 * stride + 16 * MAX_Q) * sizeof(unsigned long long); }
+
+// Counters for the gradient of M rows of nT tiles in one pass, 0 for two passes.  What waits (counters x (nT - 1) workgroups,
+// four to a CU) may hold an eighth of the device.  An odd number, so that every counter serves all eight XCDs and the rows
+// read at one time lie apart differently from time to time: 1024 rows of 151936 take 408 us with one counter, 402 with 2, 391 with 3, 438 with
+// 4, 387 with 5, 383 with 7, 502 with 8 (plain instead of non-temporal stores with 4: 453).
+// With fewer tiles than two rounds of resident workgroups the second pass reads from the caches and costs less than clearing
+// and drawing.  Measured, us, two passes (with the rows in groups that fit the last-level cache) / one: 496 / 383 at 1024 rows of
+// 151936, 991 / 753 at 2048, 93 / 71 at 300 with half of them masked out, 116 / 78 at 1024 of 32000; but with 4 counters
+// 35.0 / 35.7 at 64 of 151936 (1216 tiles), 12.8 / 14.1 at 16, 13.6 / 14.5 at 64 of 50257.
+int kl_counters(int M, int nT, int nCU) {
+    if ((long)M * nT < 8 * nCU) return 0;
+    for (int nq = MAX_Q; nq > 0; nq -= 2)
+        if (nq * (nT - 1) <= nCU / 2) return nq;
+    return 0;
+}
+
 hipError_t launch_kl_loss(int M, int V, const float *teacher, const float *student, const uint8_t *mask, float scale,
-                          float *part, size_t part_stride, float *loss_rows, float *grad, hipStream_t st) {
-    KlArgs a = {teacher, student, mask, V, kl_tiles(V), scale, part, part_stride, loss_rows, grad, 0, M, 0, 0};
-    if (!grad) {
-        hipLaunchKernelGGL(kl_kernel, dim3(a.nT, M), dim3(256), 0, st, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kl_finish_kernel, dim3((M + 3) / 4), dim3(256), 0, st, a, M);
-        return hipGetLastError();
-    }
-    const size_t bytes = (size_t)M * V * sizeof(float);
-    int groups = (int)((bytes + GROUP_BYTES / 2) / GROUP_BYTES);
-    groups = groups < 1 ? 1 : (groups > M ? M : groups);
-    int rows = (M + groups - 1) / groups;
-    if (groups > 1 && rows > 32767) rows = 32767;    // (grid limit: two groups in one launch)
-    for (int r0 = 0; r0 < M + rows; r0 += rows) {
-        a.g0 = a.p0; a.nG = r0 ? a.nP : 0;
-        a.p0 = r0;
-        a.nP = r0 >= M ? 0 : (M - r0 < rows ? M - r0 : rows);
-        if (a.nP + a.nG == 0) break;
-        hipLaunchKernelGGL(kl_kernel, dim3(a.nT, a.nP + a.nG), dim3(256), 0, st, a);
+                          float *part, size_t part_stride, float *loss_rows, float *grad, int nCU, hipStream_t st) {
+    const KlArgs a = {teacher, student, mask, V, kl_tiles(V), scale, part, reinterpret_cast<unsigned long long *>(part), part_stride,
+                      loss_rows, grad, M, grad ? kl_counters(M, kl_tiles(V), nCU) : 0};
+    if (a.nq) {
+        const int n = M * a.nT;
+        hipLaunchKernelGGL(kl_clear_kernel, dim3((n + 255) / 256, 6), dim3(256), 0, st, a.words, part_stride, n);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kl_grad_kernel, dim3((M + a.nq - 1) / a.nq * a.nq * a.nT), dim3(256), 0, st, a);
+        return hipGetLastError();
     }
-    return hipSuccess;
+    hipLaunchKernelGGL(kl_partial_kernel, dim3(a.nT, M), dim3(256), 0, st, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (grad) hipLaunchKernelGGL(kl_second_kernel, dim3(a.nT, M), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(kl_finish_kernel, dim3((M + 3) / 4), dim3(256), 0, st, a, M);
+    return hipGetLastError();
 }
 
 }  // namespace mrp

@@ -28,7 +28,7 @@ struct mrp_ctx {
     int *pi;
     float *vwm;
     int *vwi;
-    float *kl_part;            // KL loss: 5 partial arrays [max_rows * tiles]
+    float *kl_part;            // KL loss: 5 partial arrays [max_rows * tiles] of 64-bit words, and counters
     size_t kl_stride;
     double *rms_part;          // residual magnitudes: per-workgroup sums of squares
     int *err_flag;             // device error word (MRP_FLAG_* bits), read and cleared by mrp_poll_error
@@ -98,7 +98,7 @@ Layout make_layout(const mrp_dims *dm, int nCU) {
     l.off_vwm = take(vw * 4);
     l.off_vwi = take(vw * 4);
     l.kl_stride = (size_t)dm->max_rows * kl_tiles(dm->V);
-    l.off_klp = take(5 * l.kl_stride * 4);
+    l.off_klp = take(kl_part_bytes(l.kl_stride));
     l.off_rms = take(residual_rms_part_bytes());
     l.off_err = take(256);
     l.total = o;
@@ -410,7 +410,7 @@ int mrp_kl_loss(mrp_ctx *c, void *stream, int M, const float *teacher, const flo
         return fail(c, MRP_ERR_ALIGN, "mrp_kl_loss: tensors must be 16-byte aligned");
     if (M == 0) return MRP_OK;
     HIP_TRY(c, launch_kl_loss(M, c->dims.V, teacher, student, row_mask, scale, c->kl_part, c->kl_stride,
-                              loss_rows, grad, static_cast<hipStream_t>(stream)));
+                              loss_rows, grad, c->nCU, static_cast<hipStream_t>(stream)));
     return MRP_OK;
 }
 

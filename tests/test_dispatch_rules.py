@@ -87,3 +87,14 @@ def test_mlp_body_kernel_by_rows_and_width():
                 assert not on_tiles(M, d, 256, rows(M))
     assert all(on_tiles(M, 4096, 256, 4096) for M in (129, 144, 160, 256, 257, 512))
     assert not any(on_tiles(M, 2560, 256, 4096) for M in (129, 192, 384))
+
+
+def test_waiting_gradient_workgroups_leave_the_device_free():
+    counters = library_rule("_ZN3mrp11kl_countersEiii", C.c_int, *[C.c_int] * 3)
+    for nCU in (1, 8, 32, 256):
+        for nT in range(1, 300):
+            for M in (1, 16, 100, 1024, 65535):
+                nq = counters(M, nT, nCU)
+                assert nq in (0, 1, 3, 5, 7) and nq * (nT - 1) <= nCU // 2      # of 4 nCU resident workgroups
+                assert nq == 0 or M * nT >= 8 * nCU
+    assert counters(1024, 19, 256) == 7 and counters(64, 19, 256) == 0 and counters(1024, 33, 256) == 3

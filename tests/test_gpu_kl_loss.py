@@ -13,6 +13,8 @@ argument, i.e. < 4e-6 relative; sums of V such terms in a tree keep that relativ
          combination to < 1e-4 absolute:  |loss_gpu - loss_orc| <= 1e-4 + 1e-4 |loss_orc|.
   grad:  scale (q - p) with p, q <= 1:    |g_gpu - g_orc| <= scale (2e-5 (p + q) + 1e-12).
 """
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -21,6 +23,7 @@ from scipy.special import softmax
 import mrp_inputs as mi
 import oracle as orc
 import paper_2605_18817_amd as mrp
+from harness import library_rule
 
 pytestmark = pytest.mark.gpu
 
@@ -156,4 +159,30 @@ def test_kl_loss_over_groups_of_rows(V, M):
     bound = 0.5 * (2e-5 * (p.exp() + q.exp()) + 1e-12) * on       # as above; rows that are off: exactly zero
     assert bool(((grad[:M] - 0.5 * (q.exp() - p.exp()) * on).abs() <= bound).all())
     assert bool((grad[M] == 9.0).all())
+    ctx.close()
+
+
+@pytest.mark.parametrize("V,M", [(4096, 2048), (4096, 2049), (8193, 1024), (8193, 1023), (151936, 108), (151936, 107), (65537, 230),
+                                 (262147, 63)])     # both sides of 2048 tiles; 1, 2, 9, 19 and 33 tiles a row: 7 to 3 counters
+def test_gradient_in_one_pass_and_two(V, M):
+    """The one-pass form and the two-pass form give the bits of the forward pass for the loss, for any order of rows on and off,
+    in place, and again on the same context (its words are cleared)."""
+    nq = library_rule("_ZN3mrp11kl_countersEiii", C.c_int, *[C.c_int] * 3)(M, -(-V // 8192), 256)
+    assert (nq > 0) == (M * -(-V // 8192) >= 2048)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V + M)
+    t = torch.empty(M, V, device="cuda").normal_(0, 2, generator=g)
+    s = t + torch.empty(M, V, device="cuda").normal_(0, 0.5, generator=g)
+    p, q = torch.log_softmax(t.double(), 1), torch.log_softmax(s.double(), 1)
+    ctx = mrp.MrpContext(128, V, M, 1)
+    for mask in (None, (torch.rand(M, device="cuda", generator=g) < 0.5).to(torch.uint8)):
+        on = torch.ones(M, 1, device="cuda", dtype=torch.double) if mask is None else mask.double().unsqueeze(1)
+        loss, loss1 = torch.full((M,), 9.0, device="cuda"), torch.full((M,), 9.0, device="cuda")
+        ctx.kl_loss(M, t, s, mask, 0.5, loss1)
+        for grad in (torch.full((M, V), 9.0, device="cuda"), s.clone()):      # the second over the student's own logits
+            src = grad if bool((grad == s).all()) else s
+            ctx.kl_loss(M, t, src, mask, 0.5, loss, grad)
+            assert torch.equal(loss, loss1)
+            bound = 0.5 * (2e-5 * (p.exp() + q.exp()) + 1e-12) * on
+            assert bool(((grad - 0.5 * (q.exp() - p.exp()) * on).abs() <= bound).all())
     ctx.close()
