@@ -198,15 +198,14 @@ bool mrp::mlp_per_sequence(int L, int d) { return (d == 128 || d == 256) && L <=
 // follow from it (two-plane products, us): 24576 x 4096 at 384 rows as 256 tiles of 192 x 192 114 (256 x 192: 132, three
 // quarters of a round); 4096 x 4096 at 592 rows as 64 tiles of 256 x 160 x 4 parts 37 (256 x 224: 46), at 1024 rows 128 tiles of
 // 256 x 128 x 2 parts 53 (256 x 256 x 4 parts: 59).
-TileForm mrp::two_plane_form(int M, int R, int Kc, int nCU, size_t cap_rows) {
-    const int ib = (M + 31) / 32, nIb = (ib + 7) / 8 * 8, nsteps = Kc / 32;
-    TileForm best = {8, 4, 1};
+static TileForm cheapest_form(TileForm best, int M, int R, int nsteps, int nCU, size_t cap_rows, int nv_min, int nb_min, int ks_min) {
+    const int ib = (M + 31) / 32, nIb = (ib + 7) / 8 * 8;
     double best_cost = 1e300;
-    for (int nv = 4; nv >= 3; --nv)
-        for (int nb = 4; nb <= 8; ++nb) {
+    for (int nv = 4; nv >= nv_min; --nv)
+        for (int nb = nb_min; nb <= 8; ++nb) {
             const int nMt = (ib + nb - 1) / nb, tiles = nMt * ((R + 64 * nv - 1) / (64 * nv));
             if (nMt * nb > nIb) continue;      // (row blocks that the planes have)
-            for (int ks = 1; ks <= 16; ks *= 2) {
+            for (int ks = ks_min; ks <= 16; ks *= 2) {
                 if (nsteps % ks != 0 || nsteps / ks < MRP_TILED_MIN_STEPS || (size_t)ks * M > cap_rows) break;
                 const double rounds = (tiles * ks + nCU - 1) / nCU;
                 const double cost = rounds * (nsteps / ks * (0.15 + 0.0404 * nv * nb) + 6.0) + (ks - 1) * (double)M * R * 2e-6;
@@ -214,6 +213,18 @@ TileForm mrp::two_plane_form(int M, int R, int Kc, int nCU, size_t cap_rows) {
             }
         }
     return best;
+}
+TileForm mrp::two_plane_form(int M, int R, int Kc, int nCU, size_t cap_rows) {
+    return cheapest_form(TileForm{8, 4, 1}, M, R, Kc / 32, nCU, cap_rows, 3, 4, 1);
+}
+// The first GEMM of the head body, whose step is as long (64 columns of one plane).  It keeps the parts that tiled_ksplit
+// finds, or takes more: fewer would round more.  Shorter tiles where the CUs have room for more of them: step of three heads with
+// V = 4096, tiles for the fewest of them / by the rule, us: d = 4096 589 / 555 at 592 rows, 648 / 618 at 768, 925 / 845 at 1280;
+// d = 2048 358 / 336 at 768, 453 / 398 at 1280, 490 / 436 at 1600; d = 1024 256 / 242 at 768.
+TileForm mrp::partial_form(int M, int R, int nsteps, int nCU, size_t cap_rows) {
+    const int nb = tiled_row_blocks(M), ks = tiled_ksplit(tiled_row_tiles(M) * ((R + 255) / 256), nsteps, nCU, cap_rows, M);
+    const TileForm own = {nb, 4, ks};
+    return ks == 1 ? own : cheapest_form(own, M, R, nsteps, nCU, cap_rows, 4, 5, ks);
 }
 
 namespace {
@@ -637,15 +648,15 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
             tg.seg[0] = TiledSeg{c->XH, c->plane, d / 64, np_h};
             tg.seg[1] = TiledSeg{c->XE, 0, d / 64, 1};
             tg.nseg = 2;
-            tg.nMt = tiled_row_tiles(M); tg.nVt = (d + 255) / 256;
-            tg.nKs = fuse_parts ? fuse_parts
-                                : tiled_ksplit(tg.nMt * tg.nVt, (d / 64) * (np_h + 1), c->nCU, c->part_rows, M);
-            nks1 = tg.nKs;
+            const TileForm f = fuse_parts ? TileForm{tiled_row_blocks(M), 4, fuse_parts}
+                                          : partial_form(M, d, (d / 64) * (np_h + 1), c->nCU, c->part_rows);
+            tg.nMt = (M + 32 * f.nb - 1) / (32 * f.nb); tg.nVt = (d + 255) / 256;
+            tg.nKs = nks1 = f.ks;
             tg.out = fused_u;
             // a single k part of the MLP body: SiLU and the fp16 split sit in the tile epilogue
             silu_done = !layers && tg.nKs == 1;
             tg.planes = c->S; tg.plane_stride = c->plane;
-            HIP_TRY(c, launch_tiled_gemm(tg, silu_done ? EPI_SILU : EPI_PARTIAL, st));
+            HIP_TRY(c, silu_done ? launch_tiled_gemm(tg, EPI_SILU, st) : launch_tiled_partial(tg, f.nb, st));
         } else {
             memset(&g, 0, sizeof(g));
             g.Wp = static_cast<const uint4 *>(hd.W1_packed);

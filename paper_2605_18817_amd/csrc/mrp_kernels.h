@@ -292,6 +292,8 @@ hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st);
 // its EPI_LM forms for nb row blocks per tile; rem = 2 + (k steps - 2) % 3
 hipError_t launch_tiled_lm(const TiledGemmArgs &a, int nb, int rem, hipStream_t st);
 hipError_t launch_tiled_lm_halves(const TiledGemmArgs &a, int nb, int rem, hipStream_t st);
+// EPI_PARTIAL on tiles of 256 weight rows and nb 32-row blocks (5 to 8) of activation rows
+hipError_t launch_tiled_partial(const TiledGemmArgs &a, int nb, hipStream_t st);
 // EPI_PARTIAL of one segment of two planes on tiles of 64 nv weight rows (nv: 3 or 4) and nb 32-row blocks (4 to 8) of
 // activation rows
 hipError_t launch_tiled_two_planes(const TiledGemmArgs &a, int nb, int nv, hipStream_t st);
@@ -306,6 +308,8 @@ int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M);
 // Tile kernel for the partial sums of two planes: 32-row blocks per tile, weight rows per tile / 64, k parts
 struct TileForm { int nb, nv, ks; };
 TileForm two_plane_form(int M, int R, int Kc, int nCU, size_t cap_rows);
+// The same for `nsteps` k steps of any planes, on 256 weight rows (nv = 4)
+TileForm partial_form(int M, int R, int nsteps, int nCU, size_t cap_rows);
 // Are the MLP head body's GEMMs of M rows on the tile kernel (or on the small-row kernels)?
 bool mlp_on_tiles(int M, int d, int nCU, size_t part_rows);
 // Is the LM head of M rows on the tile kernel (or the persistent one)?

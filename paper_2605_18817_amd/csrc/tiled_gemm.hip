@@ -7,15 +7,6 @@ namespace mrp {
 namespace {
 
 template <int NB>
-hipError_t launch_nb(const TiledGemmArgs &a, int epi, int rem, hipStream_t st) {
-    if (epi == EPI_SILU) {
-        if constexpr (NB >= 7) return launch_inst<EPI_SILU, false, NB, 4, false>(a, rem, st);
-        else return hipErrorInvalidValue;      // (launch_tiled_gemm rounds up to 7)
-    }
-    return launch_inst<EPI_PARTIAL, false, NB, 4, false>(a, rem, st);
-}
-
-template <int NB>
 hipError_t launch_two_planes(const TiledGemmArgs &a, int nv, int rem, hipStream_t st) {
     return nv == 3 ? launch_inst<EPI_PARTIAL, false, NB, 3, true>(a, rem, st) : launch_inst<EPI_PARTIAL, false, NB, 4, true>(a, rem, st);
 }
@@ -62,10 +53,18 @@ hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st) {
         const int left = a.nMt * a.nVt % 256;
         return left > 0 && left <= 128 ? launch_tiled_lm_halves(a, nb, rem, st) : launch_tiled_lm(a, nb, rem, st);
     }
-    if (nb == 5) return launch_nb<5>(a, epi, rem, st);
-    if (nb == 6) return launch_nb<6>(a, epi, rem, st);
-    if (nb == 7) return launch_nb<7>(a, epi, rem, st);
-    return launch_nb<8>(a, epi, rem, st);
+    if (epi == EPI_SILU)
+        return nb == 7 ? launch_inst<EPI_SILU, false, 7, 4, false>(a, rem, st) : launch_inst<EPI_SILU, false, 8, 4, false>(a, rem, st);
+    return launch_tiled_partial(a, nb, st);
+}
+
+hipError_t launch_tiled_partial(const TiledGemmArgs &a, int nb, hipStream_t st) {
+    const int nsteps = part_steps(a, true), rem = 2 + (nsteps - 2) % 3;
+    if (nsteps == 0 || nb < 5 || nb > 8 || a.nMt != (a.M + 32 * nb - 1) / (32 * nb) || a.nMt * nb > a.nIb) return hipErrorInvalidValue;
+    if (nb == 5) return launch_inst<EPI_PARTIAL, false, 5, 4, false>(a, rem, st);
+    if (nb == 6) return launch_inst<EPI_PARTIAL, false, 6, 4, false>(a, rem, st);
+    if (nb == 7) return launch_inst<EPI_PARTIAL, false, 7, 4, false>(a, rem, st);
+    return launch_inst<EPI_PARTIAL, false, 8, 4, false>(a, rem, st);
 }
 
 hipError_t launch_tiled_two_planes(const TiledGemmArgs &a, int nb, int nv, hipStream_t st) {

@@ -76,6 +76,23 @@ def test_two_plane_forms_fit(nCU):
             == [(6, 3, 1), (5, 4, 4), (4, 4, 2), (8, 4, 1)]
 
 
+def test_first_body_gemm_keeps_its_parts_or_takes_more():
+    form = library_rule("_ZN3mrp12partial_formEiiiim", _TileForm, *[C.c_int] * 4, C.c_size_t)
+    ksplit = library_rule("_ZN3mrp12tiled_ksplitEiiimi", C.c_int, *[C.c_int] * 3, C.c_size_t, C.c_int)
+    blocks = library_rule("_ZN3mrp16tiled_row_blocksEi", C.c_int, C.c_int)
+    for nCU in (32, 256):
+        for M in [*range(129, 2000, 31), 592, 640, 768, 1024, 4096, 65535]:
+            for d in (128, 1024, 2048, 2176, 2560, 4096, 5120):
+                for nsteps in (d // 32, d // 64 * 3):
+                    f, cap = form(M, d, nsteps, nCU, max(M, 4096)), max(M, 4096)
+                    own = ksplit(-(-M // (32 * blocks(M))) * -(-d // 256), nsteps, nCU, cap, M)
+                    assert f.nv == 4 and 5 <= f.nb <= 8 and own <= f.ks <= 16 and f.ks * M <= cap and nsteps % f.ks == 0
+                    assert own > 1 or (f.nb, f.ks) == (blocks(M), 1)
+                    tiles = -(-M // (32 * f.nb))
+                    assert tiles * f.nb <= -(-M // 256) * 8 and tiles * f.nb * 32 >= M
+    assert [(f.nb, f.ks) for f in (form(592, 4096, 192, 256, 4096), form(768, 2048, 96, 256, 4096))] == [(5, 4), (6, 4)]
+
+
 def test_mlp_body_kernel_by_rows_and_width():
     on_tiles = library_rule("_ZN3mrp12mlp_on_tilesEiiim", C.c_bool, *[C.c_int] * 3, C.c_size_t)
     rows = lambda M: 16 * M if M <= 128 else 4096

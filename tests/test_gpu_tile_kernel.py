@@ -104,3 +104,37 @@ def test_two_plane_forms(M, R, K, nb, nv, ks):
         err = (got[n] - xs @ ws.t()).abs()
         assert bool((err <= bound).all()), (n, float((err / bound).max()))
     assert bool((out[ks * M * R:] == 7.0).all())                   # nothing past the last part
+
+
+def test_tile_height_does_not_change_partial_sums():
+    """The forms of 256 weight rows and one plane at a time: what a part adds up does not depend on the tile."""
+    lib = mrp.load_library()
+    launch = getattr(lib, "_ZN3mrp20launch_tiled_partialERKNS_13TiledGemmArgsEiP12ihipStream_t")
+    M, R, K, ks, nIb = 592, 288, 320, 3, 24
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    x = torch.empty(M, 2 * K, device="cuda").normal_(0, 1, generator=gen)
+    w = torch.empty(R, 2 * K, dtype=torch.bfloat16, device="cuda").normal_(0, 0.05, generator=gen)
+    planes = torch.zeros(3, K // 16 * nIb * 512, dtype=torch.float16, device="cuda")
+    idx = _plane_index(M, K, nIb)
+    hi = x[:, :K].half()
+    planes[0, idx], planes[1, idx], planes[2, idx] = hi, (x[:, :K] - hi.float()).half(), x[:, K:].half()
+    Wp = mrp.pack_weight(w, body=True)
+    xe = torch.cat([planes[0, idx].double() + planes[1, idx].double(), planes[2, idx].double()], 1)
+    outs = []
+    for nb in (5, 6, 7, 8):
+        out = torch.full((ks * M * R + 64,), 7.0, device="cuda")
+        a = _Args()
+        a.Wp, a.KBw, a.n_rb, a.nIb, a.M, a.R = Wp.data_ptr(), 2 * K // 16, R // 32, nIb, M, R
+        a.seg[0] = _Seg(planes.data_ptr(), planes.shape[1] // 8, K // 64, 2)
+        a.seg[1] = _Seg(planes[2].data_ptr(), 0, K // 64, 1)
+        a.nseg, a.nMt, a.nVt, a.nKs, a.out = 2, -(-M // (32 * nb)), -(-R // 256), ks, out.data_ptr()
+        assert launch(C.byref(a), nb, C.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        torch.cuda.synchronize()
+        assert bool((out[ks * M * R:] == 7.0).all())
+        outs.append(out[:ks * M * R].view(ks, M, R))
+        assert torch.equal(outs[0], outs[-1])
+    we = w.half().double()
+    # K / 32 MFMAs of 32 products for each of three planes, the parts' sums in 64 bits
+    bound = (3 * K // 32 + 32) * 2.0 ** -24 * (xe.abs() @ we.abs().t())
+    assert bool(((outs[0].double().sum(0) - xe @ we.t()).abs() <= bound).all())
