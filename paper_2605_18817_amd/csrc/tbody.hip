@@ -123,14 +123,14 @@ __global__ __launch_bounds__(256) void swiglu_split_kernel(const float *__restri
 }
 
 // ------------------------------------------------------------------------------------------------
-// Attention.  One workgroup (NW = 8 or 4 wavefronts) per (kv head g, sequence b), or several that share
+// Attention.  One workgroup of eight wavefronts per (kv head g, sequence b), or several that share
 // the pair's prefix: its Q = (nh / nkv) * L query
 // vectors (query qq = hrep * L + i: head g * rep + hrep, block row i) share the keys and values of
 // head g.
 //   * The block's own L keys and values (fp32, from the projection) are handled by the whole
 //     workgroup on the vector ALU.
-//   * The prefix cache is walked in chunks of 32 positions, chunk c by wavefront c % NW, and each
-//     wavefront runs its own online softmax over its chunks: no workgroup barrier inside the walk.
+//   * The prefix cache is walked in chunks of 32 positions, chunk c by wavefront c % 8 (with more than 32 queries by the two
+//     wavefronts c % 4 of the query blocks), and each wavefront runs its own online softmax over its chunks: no workgroup barrier inside the walk.
 //     Both contractions run on the matrix cores on the cache's bf16 values as they are, with the fp32
 //     operand of each (queries, probabilities) as three bf16 terms (x = a + b + c up to 2^-24 |x|):
 //       scores  S^T[key][q]  = K[key][:] . (q_a + q_b + q_c)[q][:]          A = keys,      B = query planes
@@ -141,6 +141,11 @@ __global__ __launch_bounds__(256) void swiglu_split_kernel(const float *__restri
 //     a chunk's value rows are parked in LDS as they are and the transposed fragments (a lane = one
 //     dimension, 8 positions) are read back with the transposing 64-bit LDS read, four positions at a time.
 //   * At the end the partial results per query (block, the wavefronts) are merged in a fixed order.
+// What bounds it: a CU takes in one workgroup's cache at 25 to 30 GB/s, so the longest prefix; below that the latency of the phases
+// before and after the walk.  Three heads of three layers, V = 4096, prefixes random up to 1024: 4096 wide, 24 x 16 rows (64
+// queries) 3566 -> 3242 us, of that the prologue's requests sent together instead of one after the other 165, two waves per
+// SIMD instead of one with both query blocks 45, the waves' sums merged side by side 110 with 256 positions or more;
+// 2048 wide, 32 x 4 rows (8 queries) 1183 -> 1147.  The kernel alone: 72.6 -> 45.8 us and 33.3 -> 29.5.
 struct AttnArgs {
     const float *qkv;        // partial sums [nKs][M][ldq] of the q | k | v projection
     size_t split_stride;
@@ -153,7 +158,7 @@ struct AttnArgs {
     long plane_stride;
     int nIb;
     // Few (kv head, sequence) pairs leave most CUs idle: then `ns` workgroups share a pair's prefix (workgroup sp
-    // of a pair walks chunks (j ns + sp) NW + wave; sp = 0 also takes the block's own rows), each writes its
+    // of a pair walks chunks (j ns + sp) WPB + slot; sp = 0 also takes the block's own rows), each writes its
     // partial (maximum, sum, value sum in units of P_SCALE relative to that maximum) and attn_merge_kernel
     // combines the ns partials in the order sp = 0, 1, ...
     int ns;
@@ -168,19 +173,6 @@ constexpr int CK = 32;                 // prefix positions per chunk
 constexpr int SCOLS = 20;              // score columns of the block phase (16 + padding)
 constexpr int QROW = HD + 4;           // padded fp32 query / merged-output row in LDS: a wave's 32 rows at one column spread over the banks
 constexpr int KBROW = HD + 4;          // padded fp32 block-key row in LDS: the 16 keys of a score pass fall into different banks
-
-// sum over the k splits of one projection output, in split order; eight loads in flight at a time
-__device__ __forceinline__ float sum_col(const AttnArgs &a, size_t off) {
-    float x = 0.f;
-    for (int k0 = 0; k0 < a.nKs; k0 += 8) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = (k0 + u < a.nKs) ? a.qkv[(size_t)(k0 + u) * a.split_stride + off] : 0.f;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x += v[u];
-    }
-    return x;
-}
 
 __device__ __forceinline__ f32x16 mma_bf16(const uint4 &x, const uint4 &y, const f32x16 &c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, y), c, 0, 0, 0);
@@ -204,19 +196,28 @@ typedef __attribute__((address_space(3))) s16x4 *lds_s16x4_ptr;
 // row of a 32 x 32 accumulator tile held in element r of a lane of half-wave `half`
 __device__ __forceinline__ int acc_row(int r, int half) { return 8 * (r >> 2) + 4 * half + (r & 3); }
 
-// LDS carve-up of the attention kernel (NQ query slots); offsets in bytes
+// LDS carve-up of the attention kernel (NQ query slots, WPB waves to a block of 32 of them); offsets in bytes.  With two
+// query blocks the waves' value chunks lie where the block phase's tensors were; the waves' value sums take the place of everything
+// but the maxima and sums.
 template <int NQ, int NW>
 struct AttnLds {
-    static constexpr size_t qs = 0;                                                // float [NQ][HD] (later: merged output)
+    static constexpr int WPB = NW * 32 / NQ;
+    static constexpr size_t qs = 0;                                                // float [NQ][QROW]
     static constexpr size_t kb = qs + sizeof(float) * NQ * QROW;                   // float [LB][KBROW]
     static constexpr size_t vb = kb + sizeof(float) * LB * KBROW;                  // float [LB][HD]
     static constexpr size_t S = vb + sizeof(float) * LB * HD;                      // float [NQ][SCOLS]
-    static constexpr size_t stat = S + sizeof(float) * NQ * SCOLS;                 // float [4][NQ] block max / sum, merged sum / max
-    static constexpr size_t wstat = stat + sizeof(float) * 4 * NQ;                 // float [2][NW][NQ] per-wave max / sum
-    static constexpr size_t qp = wstat + sizeof(float) * 2 * NW * NQ;              // bf16 [NTERM][NQ][KROW]
-    static constexpr size_t vch = qp + sizeof(uint16_t) * NTERM * NQ * KROW;       // bf16 [NW][CK][VROW] per-wave value chunk
-    static constexpr size_t total = vch + sizeof(uint16_t) * NW * CK * VROW;
+    static constexpr size_t block_end = S + sizeof(float) * NQ * SCOLS;
+    static constexpr size_t vch = NQ > 32 ? 0 : block_end;                         // bf16 [NW][CK][VROW] per-wave value chunk
+    static constexpr size_t vch_end = vch + sizeof(uint16_t) * NW * CK * VROW;
+    static constexpr size_t qp = vch_end > block_end ? vch_end : block_end;        // bf16 [NTERM][NQ][KROW]
+    static constexpr size_t walk_end = qp + sizeof(uint16_t) * NTERM * NQ * KROW;
+    static constexpr size_t os = 0;                                                // float [WPB][NQ][QROW] the waves' value sums; the first becomes the result
+    static constexpr size_t os_end = os + sizeof(float) * WPB * NQ * QROW;
+    static constexpr size_t stat = walk_end > os_end ? walk_end : os_end;          // float [4][NQ] block max / sum, merged sum / max
+    static constexpr size_t wstat = stat + sizeof(float) * 4 * NQ;                 // float [2][WPB][NQ] per-wave max / sum
+    static constexpr size_t total = wstat + sizeof(float) * 2 * WPB * NQ;
 };
+static_assert(AttnLds<64, 8>::total <= 160 * 1024 && AttnLds<32, 8>::total <= 160 * 1024, "one workgroup's LDS");
 
 // softmax of the block phase: S[qq][0 .. 16) holds raw scores (-inf = no key) and is replaced by
 // exp(score - max); 256 / NQ adjacent lanes share a query.
@@ -239,11 +240,11 @@ __device__ __forceinline__ void softmax_block(float (*S)[SCOLS], float *blk_m, f
     if (part == 0) { blk_m[qq] = mx; blk_l[qq] = sum; }
 }
 
-// NQB: blocks of 32 query slots (1 or 2); NW: wavefronts (8 = two per SIMD, with the next chunk's
-// requests left to the other wave to hide; 4 = one per SIMD, each requesting one chunk ahead)
+// NQB: blocks of 32 query slots (1 or 2); NW: wavefronts, two per SIMD, so that one's softmax runs beside the other's matrix
+// instructions.  With two query blocks a wave has one of them, and every chunk is read by two waves.
 template <int NQB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
-    constexpr int NQ = 32 * NQB, NT = 64 * NW;
+    constexpr int NQ = 32 * NQB, NT = 64 * NW, WPB = NW / NQB;
     using Lds = AttnLds<NQ, NW>;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     float (*qs)[QROW] = reinterpret_cast<float (*)[QROW]>(smem_raw + Lds::qs);   // rotated, scaled queries (fp32)
@@ -254,20 +255,21 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
     float *blk_l = blk_m + NQ;
     float *tot_l = blk_l + NQ;
     float *tot_m = tot_l + NQ;
-    float (*w_m)[NQ] = reinterpret_cast<float (*)[NQ]>(smem_raw + Lds::wstat);    // [NW] per-wave running max
-    float (*w_l)[NQ] = w_m + NW;                                                  // [NW] per-wave running sum
+    float (*w_m)[NQ] = reinterpret_cast<float (*)[NQ]>(smem_raw + Lds::wstat);    // [WPB] per-wave running max
+    float (*w_l)[NQ] = w_m + WPB;                                                 // [WPB] per-wave running sum
     uint16_t (*qp)[NQ][KROW] = reinterpret_cast<uint16_t (*)[NQ][KROW]>(smem_raw + Lds::qp);   // [NTERM] query planes
     uint16_t (*vch)[CK][VROW] = reinterpret_cast<uint16_t (*)[CK][VROW]>(smem_raw + Lds::vch); // [NW] value chunks
 
     const int g = blockIdx.x, b = blockIdx.y, sp = blockIdx.z, ns = a.ns, tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, half = lane >> 5;
+    const int slot = wave % WPB, qb = wave / WPB;      // chunks slot, slot + WPB, ...; queries 32 qb .. 32 qb + 31
     const int L = a.L, rep = a.nh / a.nkv, Q = rep * L;
     const int qd = a.nh * HD, kvd = a.nkv * HD;
     int P = a.prefix_len[b];
     P = P < 0 ? 0 : (P > a.P_max ? a.P_max : P);
     const float scale = 0.08838834764831845f;   // 1 / sqrt(128)
     const int nchunks = (P + CK - 1) / CK;
-    const int c_first = sp * NW, c_step = NW * ns;    // this workgroup's chunks: c_first + wave + j c_step
+    const int c_first = sp * WPB, c_step = WPB * ns;  // this workgroup's chunks: c_first + slot + j c_step
     float *po = a.po + ((size_t)(b * a.nkv + g) * ns + sp) * NQ * HD;
     float *pml = a.pml + ((size_t)(b * a.nkv + g) * ns + sp) * NQ * 2;
     if (sp > 0 && c_first >= nchunks) {     // nothing of the prefix falls to this workgroup: an empty partial
@@ -303,55 +305,123 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
             }
         }
     };
-    if (c_first + wave < nchunks) { request_k(c_first + wave); request_v(c_first + wave); }
+    if (c_first + slot < nchunks) { request_k(c_first + slot); request_v(c_first + slot); }
 
-    // ---- prologue: the block's q (rotated, scaled; fp32 and as two fp16 planes), k (rotated) and v
-    for (int idx = tid; idx < NQ * (HD / 2); idx += NT) {
-        const int qq = idx / (HD / 2), j = idx % (HD / 2);
-        float r0 = 0.f, r1 = 0.f;
-        if (qq < Q) {
-            const int hrep = qq / L, i = qq % L, row = b * L + i;
-            const size_t off = (size_t)row * a.ldq + (size_t)(g * rep + hrep) * HD;
-            const float x0 = sum_col(a, off + j), x1 = sum_col(a, off + j + HD / 2);
-            const float2 cs = a.rope[(size_t)row * (HD / 2) + j];
-            r0 = (x0 * cs.x - x1 * cs.y) * scale;
-            r1 = (x1 * cs.x + x0 * cs.y) * scale;
-        }
-        qs[qq][j] = r0;
-        qs[qq][j + HD / 2] = r1;
-        uint32_t t0[NTERM], t1[NTERM];
-        split3(r0, t0);
-        split3(r1, t1);
+    // ---- prologue: the block's q (rotated, scaled; fp32 and as bf16 terms), k (rotated) and v.  Four columns (of q and k: and
+    // the four that rotate with them) are an item; a thread requests those of all its items, then of the next k parts.
+    constexpr int QI = NQ * (HD / 8) / NT, VI = LB * (HD / 4) / NT, UB = QI == 1 ? 4 : 2;
+    static_assert(LB * (HD / 8) <= NT, "one key item per thread");
+    const int jq = 4 * (tid & 15), ik = tid >> 4;     // columns jq .. and HD / 2 + jq .. of query items (tid + n NT) / 16 and of key row ik
+    const bool has_k = sp == 0 && ik < L;
+    const float *qsrc[QI], *ksrc, *vsrc[VI];
+    float4 cs[QI + 1][2];                             // (cos, sin) of columns jq, jq + 1 and jq + 2, jq + 3
 #pragma unroll
-        for (int t = 0; t < NTERM; ++t) {
-            qp[t][qq][j] = (uint16_t)(t0[t] >> 16);
-            qp[t][qq][j + HD / 2] = (uint16_t)(t1[t] >> 16);
+    for (int n = 0; n <= QI; ++n) {
+        const int qq = n < QI ? ik + n * (NT / 16) : 0, hrep = qq / L, i = n < QI ? qq - hrep * L : (ik < L ? ik : 0);
+        const int row = b * L + i;
+        const size_t off = (size_t)row * a.ldq + jq;
+        if (n < QI) qsrc[n] = a.qkv + off + (size_t)(g * rep + (qq < Q ? hrep : 0)) * HD;
+        else ksrc = a.qkv + off + qd + (size_t)g * HD;
+        const float4 *r = reinterpret_cast<const float4 *>(a.rope + (size_t)row * (HD / 2) + jq);
+        cs[n][0] = r[0]; cs[n][1] = r[1];
+    }
+#pragma unroll
+    for (int n = 0; n < VI; ++n) {
+        const int i = (tid + n * NT) / (HD / 4);
+        vsrc[n] = a.qkv + (size_t)(b * L + (i < L ? i : 0)) * a.ldq + qd + kvd + (size_t)g * HD + 4 * (tid % (HD / 4));
+    }
+    const auto add4 = [](float4 &x, const float4 &y) __attribute__((always_inline)) { x.x += y.x; x.y += y.y; x.z += y.z; x.w += y.w; };
+    float4 xq[QI][2], xk[2], xv[VI];
+    {
+        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int n = 0; n < QI; ++n) xq[n][0] = xq[n][1] = zero;
+        xk[0] = xk[1] = zero;
+#pragma unroll
+        for (int n = 0; n < VI; ++n) xv[n] = zero;
+        for (int k0 = 0; k0 < a.nKs; k0 += UB) {
+            float4 tq[UB][QI][2], tk[UB][2], tv[UB][VI];
+#pragma unroll
+            for (int u = 0; u < UB; ++u) {
+                // (a part that is not there: the last one again, not added)
+                const size_t so = (size_t)(k0 + u < a.nKs ? k0 + u : a.nKs - 1) * a.split_stride;
+#pragma unroll
+                for (int n = 0; n < QI; ++n)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) tq[u][n][h] = *reinterpret_cast<const float4 *>(qsrc[n] + so + h * (HD / 2));
+                if (sp == 0) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) tk[u][h] = *reinterpret_cast<const float4 *>(ksrc + so + h * (HD / 2));
+#pragma unroll
+                    for (int n = 0; n < VI; ++n) tv[u][n] = *reinterpret_cast<const float4 *>(vsrc[n] + so);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < UB; ++u) {
+                if (k0 + u >= a.nKs) break;
+#pragma unroll
+                for (int n = 0; n < QI; ++n)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) add4(xq[n][h], tq[u][n][h]);
+                if (sp == 0) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) add4(xk[h], tk[u][h]);
+#pragma unroll
+                    for (int n = 0; n < VI; ++n) add4(xv[n], tv[u][n]);
+                }
+            }
         }
     }
-    if (sp == 0) {    // (uniform over the workgroup) the block's own keys and values
-        for (int idx = tid; idx < L * (HD / 2); idx += NT) {
-            const int i = idx / (HD / 2), j = idx % (HD / 2), row = b * L + i;
-            const size_t off = (size_t)row * a.ldq + qd + (size_t)g * HD;
-            const float x0 = sum_col(a, off + j), x1 = sum_col(a, off + j + HD / 2);
-            const float2 cs = a.rope[(size_t)row * (HD / 2) + j];
-            kb[i][j] = x0 * cs.x - x1 * cs.y;
-            kb[i][j + HD / 2] = x1 * cs.x + x0 * cs.y;
+    // (x0, x1) of a column pair rotated by (cos, sin)
+    const auto rotate = [](const float4 (&x)[2], const float4 (&r)[2], float (&lo)[4], float (&hi)[4]) __attribute__((always_inline)) {
+        const float x0[4] = {x[0].x, x[0].y, x[0].z, x[0].w}, x1[4] = {x[1].x, x[1].y, x[1].z, x[1].w};
+        const float co[4] = {r[0].x, r[0].z, r[1].x, r[1].z}, si[4] = {r[0].y, r[0].w, r[1].y, r[1].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            lo[e] = x0[e] * co[e] - x1[e] * si[e];
+            hi[e] = x1[e] * co[e] + x0[e] * si[e];
         }
-        for (int idx = tid; idx < L * HD; idx += NT) {
-            const int i = idx / HD, e = idx % HD, row = b * L + i;
-            vb[i][e] = sum_col(a, (size_t)row * a.ldq + qd + kvd + (size_t)g * HD + e);
+    };
+#pragma unroll
+    for (int n = 0; n < QI; ++n) {
+        const int qq = ik + n * (NT / 16);
+        float r[2][4];
+        rotate(xq[n], cs[n], r[0], r[1]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            uint32_t t[4][NTERM];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                r[h][e] = qq < Q ? r[h][e] * scale : 0.f;
+                split3(r[h][e], t[e]);
+            }
+            *reinterpret_cast<float4 *>(&qs[qq][jq + h * (HD / 2)]) = make_float4(r[h][0], r[h][1], r[h][2], r[h][3]);
+#pragma unroll
+            for (int m = 0; m < NTERM; ++m)
+                *reinterpret_cast<uint2 *>(&qp[m][qq][jq + h * (HD / 2)]) = make_uint2(pair_bf16(t[0][m], t[1][m]), pair_bf16(t[2][m], t[3][m]));
         }
     }
+    if (has_k) {
+        float r[2][4];
+        rotate(xk, cs[QI], r[0], r[1]);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) *reinterpret_cast<float4 *>(&kb[ik][jq + h * (HD / 2)]) = make_float4(r[h][0], r[h][1], r[h][2], r[h][3]);
+    }
+    if (sp == 0)      // (uniform over the workgroup)
+#pragma unroll
+        for (int n = 0; n < VI; ++n) {
+            const int i = (tid + n * NT) / (HD / 4);
+            if (i < L) *reinterpret_cast<float4 *>(&vb[i][4 * (tid % (HD / 4))]) = xv[n];
+        }
     __syncthreads();
 
     // ---- the block's own rows (fp32 keys and values, vector ALU); absent keys -inf.  The value sum is
-    // held in accumulator layout: wave w owns dimensions 32 w .. 32 w + 31, element r of a lane is
-    // o[query 32 qb + lane % 32][dimension 32 w + acc_row(r, half)], in units of P_SCALE.
-    f32x16 o_blk[NQB];
+    // held in accumulator layout: wave w owns dimensions 32 (w % 4) .. + 31 of query block w / 4, element r of a lane is
+    // o[query 32 (w / 4) + lane % 32][dimension 32 (w % 4) + acc_row(r, half)], in units of P_SCALE.
+    const int bqb = wave >> 2, bdb = wave & 3;
+    f32x16 o_blk;
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o_blk[qb][r] = 0.f;
+    for (int r = 0; r < 16; ++r) o_blk[r] = 0.f;
     if (sp == 0) {
         for (int qq = tid >> 4; qq < NQ; qq += NT / 16) {
             const int key = tid & 15;
@@ -370,42 +440,36 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
         __syncthreads();
         softmax_block<NQ, NT>(S, blk_m, blk_l);
         __syncthreads();
-        for (int k = 0; k < L && wave < 4; ++k) {   // (waves 0 .. 3 own the 4 x 32 dimensions of the block's partial)
+        for (int k = 0; k < L && bqb < NQB; ++k) {
+            const float pk = S[32 * bqb + l32][k] * P_SCALE;
 #pragma unroll
-            for (int qb = 0; qb < NQB; ++qb) {
-                const float pk = S[32 * qb + l32][k] * P_SCALE;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float4 v = *reinterpret_cast<const float4 *>(&vb[k][32 * wave + 8 * j + 4 * half]);
-                    o_blk[qb][4 * j + 0] += pk * v.x; o_blk[qb][4 * j + 1] += pk * v.y;
-                    o_blk[qb][4 * j + 2] += pk * v.z; o_blk[qb][4 * j + 3] += pk * v.w;
-                }
+            for (int j = 0; j < 4; ++j) {
+                const float4 v = *reinterpret_cast<const float4 *>(&vb[k][32 * bdb + 8 * j + 4 * half]);
+                o_blk[4 * j + 0] += pk * v.x; o_blk[4 * j + 1] += pk * v.y;
+                o_blk[4 * j + 2] += pk * v.z; o_blk[4 * j + 3] += pk * v.w;
             }
         }
     } else {          // the block's rows belong to the pair's first workgroup
         for (int q = tid; q < NQ; q += NT) { blk_m[q] = -INFINITY; blk_l[q] = 0.f; }
     }
 
+    if constexpr (NQB > 1) __syncthreads();     // the value chunks take the place of what the block phase read
+
     // ---- this wave's chunks of the prefix: running max / sum per query (both half-waves hold the
     // same copy) and the value sum for ALL 128 dimensions (4 blocks of 32), in units of P_SCALE
-    float run_m[NQB], run_l[NQB];
-    f32x16 o_acc[NQB][4];
+    float run_m = -INFINITY, run_l = 0.f;
+    f32x16 o_acc[4];
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) {
-        run_m[qb] = -INFINITY;
-        run_l[qb] = 0.f;
+    for (int db = 0; db < 4; ++db)
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o_acc[qb][db][r] = 0.f;
-    }
+        for (int r = 0; r < 16; ++r) o_acc[db][r] = 0.f;
     // LDS addresses of this lane's transposing reads: the 16 lanes of a group fetch 4 rows x 16 dimensions
     // (lane s of the group: row s / 4, dimensions 4 (s % 4) ..) and lane L of the group receives the 4 rows'
     // values of dimension L.  Groups 0, 1 serve half-wave 0 (dimensions 0 .. 15 and 16 .. 31 of a block of 32),
     // groups 2, 3 half-wave 1, whose accumulator rows start 4 positions further.
     const int gq = lane >> 4, gs = lane & 15;
     const uint16_t *vt_base = &vch[wave][4 * half + (gs >> 2)][16 * (gq & 1) + 4 * (gs & 3)];
-    for (int c = c_first + wave; c < nchunks; c += c_step) {
+    for (int c = c_first + slot; c < nchunks; c += c_step) {
         __builtin_amdgcn_wave_barrier();   // (the previous chunk's value reads come before these writes)
 #pragma unroll
         for (int n = 0; n < CK * HD / 8 / 64; ++n)
@@ -413,56 +477,53 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
         __builtin_amdgcn_wave_barrier();
         if (c + c_step < nchunks) request_v(c + c_step);   // (the value registers are free again)
 
-        uint4 pf[NQB][2][NTERM];          // probabilities: [k step of the value product][term]
+        // scores of the chunk's 32 keys for this lane's query
+        f32x16 sc;
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) {
-            // scores of the chunk's 32 keys for this lane's query
-            f32x16 sc;
+        for (int r = 0; r < 16; ++r) sc[r] = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+        for (int ks = 0; ks < HD / 16; ++ks) {
+            const int col = 16 * ks + 8 * half;
 #pragma unroll
-            for (int ks = 0; ks < HD / 16; ++ks) {
-                const int col = 16 * ks + 8 * half;
-#pragma unroll
-                for (int t = 0; t < NTERM; ++t)
-                    sc = mma_bf16(kreg[ks], *reinterpret_cast<const uint4 *>(&qp[t][32 * qb + l32][col]), sc);
-            }
-            if (qb == NQB - 1 && c + c_step < nchunks) request_k(c + c_step);   // (the key registers are free again)
-            float cmax = -INFINITY;
-            if ((c + 1) * CK > P) {     // (uniform) the prefix's last chunk: absent positions score -inf
-#pragma unroll
-                for (int r = 0; r < 16; ++r) sc[r] = (c * CK + acc_row(r, half) < P) ? sc[r] : -INFINITY;
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) cmax = fmaxf(cmax, sc[r]);
-            cmax = fmaxf(cmax, __shfl_xor(cmax, 32));   // finite: a chunk holds at least one key
-            const float m_new = fmaxf(run_m[qb], cmax);
-            const float f = (run_m[qb] == -INFINITY) ? 0.f : __expf(run_m[qb] - m_new);
-            float csum = 0.f;
-            uint32_t pt[16][NTERM];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float pr = __expf(sc[r] - m_new);   // exp(-inf) = 0 for absent keys
-                csum += pr;
-                split3(pr, pt[r]);
-            }
-            csum += __shfl_xor(csum, 32);
-            run_l[qb] = run_l[qb] * f + csum;
-            run_m[qb] = m_new;
-            if (__any(f != 1.0f)) {   // (uniform over the wave: once the maxima have settled nothing is rescaled)
-#pragma unroll
-                for (int db = 0; db < 4; ++db)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) o_acc[qb][db][r] *= f;
-            }
-            // the lane's 16 probabilities are its B fragments: k step s holds accumulator rows 8 s .. 8 s + 7
-#pragma unroll
-            for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-                for (int t = 0; t < NTERM; ++t)
-                    pf[qb][s2][t] = make_uint4(pair_bf16(pt[8 * s2][t], pt[8 * s2 + 1][t]), pair_bf16(pt[8 * s2 + 2][t], pt[8 * s2 + 3][t]),
-                                               pair_bf16(pt[8 * s2 + 4][t], pt[8 * s2 + 5][t]), pair_bf16(pt[8 * s2 + 6][t], pt[8 * s2 + 7][t]));
+            for (int t = 0; t < NTERM; ++t)
+                sc = mma_bf16(kreg[ks], *reinterpret_cast<const uint4 *>(&qp[t][32 * qb + l32][col]), sc);
         }
+        if (c + c_step < nchunks) request_k(c + c_step);   // (the key registers are free again)
+        float cmax = -INFINITY;
+        if ((c + 1) * CK > P) {     // (uniform) the prefix's last chunk: absent positions score -inf
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sc[r] = (c * CK + acc_row(r, half) < P) ? sc[r] : -INFINITY;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) cmax = fmaxf(cmax, sc[r]);
+        cmax = fmaxf(cmax, __shfl_xor(cmax, 32));   // finite: a chunk holds at least one key
+        const float m_new = fmaxf(run_m, cmax);
+        const float f = (run_m == -INFINITY) ? 0.f : __expf(run_m - m_new);
+        float csum = 0.f;
+        uint32_t pt[16][NTERM];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float pr = __expf(sc[r] - m_new);   // exp(-inf) = 0 for absent keys
+            csum += pr;
+            split3(pr, pt[r]);
+        }
+        csum += __shfl_xor(csum, 32);
+        run_l = run_l * f + csum;
+        run_m = m_new;
+        if (__any(f != 1.0f)) {   // (uniform over the wave: once the maxima have settled nothing is rescaled)
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o_acc[db][r] *= f;
+        }
+        // the lane's 16 probabilities are its B fragments: k step s holds accumulator rows 8 s .. 8 s + 7
+        uint4 pf[2][NTERM];               // [k step of the value product][term]
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+            for (int t = 0; t < NTERM; ++t)
+                pf[s2][t] = make_uint4(pair_bf16(pt[8 * s2][t], pt[8 * s2 + 1][t]), pair_bf16(pt[8 * s2 + 2][t], pt[8 * s2 + 3][t]),
+                                       pair_bf16(pt[8 * s2 + 4][t], pt[8 * s2 + 5][t]), pair_bf16(pt[8 * s2 + 6][t], pt[8 * s2 + 7][t]));
         // values: V^T fragments in the same key order (k step s, element e <-> accumulator row 8 s + e =
         // chunk row 16 s + 8 (e / 4) + 4 half + e % 4): two transposing reads of four rows each
 #pragma unroll
@@ -474,68 +535,61 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
                 const uint2 w0 = __builtin_bit_cast(uint2, v0), w1 = __builtin_bit_cast(uint2, v1);
                 const uint4 vf = make_uint4(w0.x, w0.y, w1.x, w1.y);
 #pragma unroll
-                for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-                    for (int t = 0; t < NTERM; ++t) o_acc[qb][db] = mma_bf16(vf, pf[qb][s2][t], o_acc[qb][db]);
+                for (int t = 0; t < NTERM; ++t) o_acc[db] = mma_bf16(vf, pf[s2][t], o_acc[db]);
             }
         }
     }
 
     // ---- merge the partial results per query in a fixed order: block, then the waves
-    if (half == 0) {
+    // Every wave leaves its sums in LDS; then wave w adds up those of its 32 x 32 piece of the block's partial.  (One wave after
+    // the other on one copy took 0.9 us each.)
+    __syncthreads();   // every wave is done with its value chunk and the queries
+    float (*os)[NQ][QROW] = reinterpret_cast<float (*)[NQ][QROW]>(smem_raw + Lds::os);
+    if (half == 0) { w_m[slot][32 * qb + l32] = run_m; w_l[slot][32 * qb + l32] = run_l; }
+    if (c_first + slot < nchunks) {
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) { w_m[wave][32 * qb + l32] = run_m[qb]; w_l[wave][32 * qb + l32] = run_l[qb]; }
-    }
-    __syncthreads();   // (also: every wave is done with the fp32 queries, whose buffer takes the merged output)
-    float f_blk[NQB], f_own[NQB];
+        for (int db = 0; db < 4; ++db)
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) {
-        const int q = 32 * qb + l32;
-        float m_tot = blk_m[q];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) m_tot = fmaxf(m_tot, w_m[w][q]);
-        f_blk[qb] = (blk_m[q] == -INFINITY) ? 0.f : __expf(blk_m[q] - m_tot);   // (m_tot is finite: some wave had a chunk)
-        float l_tot = blk_l[q] * f_blk[qb];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const float fw = (w_m[w][q] == -INFINITY) ? 0.f : __expf(w_m[w][q] - m_tot);
-            l_tot += w_l[w][q] * fw;
-            if (w == wave) f_own[qb] = fw;
-        }
-        if (wave == 0 && half == 0) { tot_l[q] = l_tot; tot_m[q] = m_tot; }
-        if (wave < 4) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)   // the block's partial: this wave's 32 dimensions
-                *reinterpret_cast<float4 *>(&qs[q][32 * wave + 8 * j + 4 * half]) =
-                    make_float4(o_blk[qb][4 * j] * f_blk[qb], o_blk[qb][4 * j + 1] * f_blk[qb],
-                                o_blk[qb][4 * j + 2] * f_blk[qb], o_blk[qb][4 * j + 3] * f_blk[qb]);
-        }
+            for (int j = 0; j < 4; ++j)
+                *reinterpret_cast<float4 *>(&os[slot][32 * qb + l32][32 * db + 8 * j + 4 * half]) =
+                    make_float4(o_acc[db][4 * j], o_acc[db][4 * j + 1], o_acc[db][4 * j + 2], o_acc[db][4 * j + 3]);
     }
     __syncthreads();
-    for (int w = 0; w < NW && c_first + w < nchunks; ++w) {   // (uniform over the workgroup)
-        if (wave == w) {
+    if (bqb < NQB) {
+        const int q = 32 * bqb + l32;
+        float m_tot = blk_m[q];
 #pragma unroll
-            for (int qb = 0; qb < NQB; ++qb)
+        for (int w = 0; w < WPB; ++w) m_tot = fmaxf(m_tot, w_m[w][q]);
+        const float f_blk = (blk_m[q] == -INFINITY) ? 0.f : __expf(blk_m[q] - m_tot);   // (m_tot is finite: some wave had a chunk)
+        float l_tot = blk_l[q] * f_blk;
 #pragma unroll
-                for (int db = 0; db < 4; ++db)
+        for (int r = 0; r < 16; ++r) o_blk[r] *= f_blk;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        float4 *dst = reinterpret_cast<float4 *>(&qs[32 * qb + l32][32 * db + 8 * j + 4 * half]);
-                        float4 v = *dst;
-                        v.x += o_acc[qb][db][4 * j] * f_own[qb]; v.y += o_acc[qb][db][4 * j + 1] * f_own[qb];
-                        v.z += o_acc[qb][db][4 * j + 2] * f_own[qb]; v.w += o_acc[qb][db][4 * j + 3] * f_own[qb];
-                        *dst = v;
-                    }
+        for (int w = 0; w < WPB; ++w) {
+            if (c_first + w >= nchunks) break;      // (uniform)
+            const float fw = (w_m[w][q] == -INFINITY) ? 0.f : __expf(w_m[w][q] - m_tot);
+            l_tot += w_l[w][q] * fw;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float4 v = *reinterpret_cast<const float4 *>(&os[w][q][32 * bdb + 8 * j + 4 * half]);
+                o_blk[4 * j + 0] += v.x * fw; o_blk[4 * j + 1] += v.y * fw;
+                o_blk[4 * j + 2] += v.z * fw; o_blk[4 * j + 3] += v.w * fw;
+            }
         }
-        __syncthreads();
+        if (bdb == 0 && half == 0) { tot_l[q] = l_tot; tot_m[q] = m_tot; }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)      // (the piece of the first wave's sums that only this wave reads)
+            *reinterpret_cast<float4 *>(&os[0][q][32 * bdb + 8 * j + 4 * half]) =
+                make_float4(o_blk[4 * j], o_blk[4 * j + 1], o_blk[4 * j + 2], o_blk[4 * j + 3]);
     }
+    __syncthreads();
 
     if (ns > 1) {     // this workgroup's partial; attn_merge_kernel finishes
         for (int idx = tid; idx < Q * (HD / 4); idx += NT) {
             const int qq = idx / (HD / 4), c = idx % (HD / 4);
-            *reinterpret_cast<float4 *>(po + (size_t)qq * HD + 4 * c) = *reinterpret_cast<const float4 *>(&qs[qq][4 * c]);
+            *reinterpret_cast<float4 *>(po + (size_t)qq * HD + 4 * c) = *reinterpret_cast<const float4 *>(&os[0][qq][4 * c]);
         }
-        for (int q = tid; q < Q; q += NT) { pml[2 * q] = tot_m[q]; pml[2 * q + 1] = tot_l[q]; }
+        for (int qq = tid; qq < Q; qq += NT) { pml[2 * qq] = tot_m[qq]; pml[2 * qq + 1] = tot_l[qq]; }
         return;
     }
     // ---- normalise and write the activation planes
@@ -545,7 +599,7 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
         const float inv = 1.0f / (tot_l[qq] * P_SCALE);
         float x[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = qs[qq][8 * c + e] * inv;
+        for (int e = 0; e < 8; ++e) x[e] = os[0][qq][8 * c + e] * inv;
         split_store(x, a.o_planes, act_chunk_index(row, (g * rep + hrep) * (HD / 8) + c, a.nIb), a.plane_stride);
     }
 }
@@ -600,7 +654,7 @@ hipError_t attn_launch_one(const AttnArgs &a, int B, hipStream_t st) {
 
 hipError_t tbody_configure() {
     hipError_t e = attn_configure_one<1, 8>();
-    if (e == hipSuccess) e = attn_configure_one<2, 4>();
+    if (e == hipSuccess) e = attn_configure_one<2, 8>();
     return e;
 }
 
@@ -661,7 +715,7 @@ hipError_t launch_attention(const float *qkv, int nKs, int M, int B, int L, int 
     a.po = scratch;
     a.pml = scratch + (size_t)ATTN_SPLIT_PAIRS * 64 * HD;
     if (Q <= 32) return attn_launch_one<1, 8>(a, B, st);
-    return attn_launch_one<2, 4>(a, B, st);
+    return attn_launch_one<2, 8>(a, B, st);
 }
 
 }  // namespace mrp

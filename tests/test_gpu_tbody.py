@@ -2,6 +2,8 @@
 projection and the shared LM head) against the fp64 oracle, free-running over all K heads, under
 the same parity rule as the MLP body (tests/harness.py).  Weights, prefix caches and prefix lengths
 come from the seeded generators; prefix lengths include 0 and the cache capacity."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -9,7 +11,7 @@ import torch
 import mrp_inputs as mi
 import oracle as orc
 import paper_2605_18817_amd as mrp
-from harness import compare_chain, dev_bits, io_to_host, oracle_chain
+from harness import compare_chain, dev_bits, io_to_host, library_rule, oracle_chain
 
 pytestmark = pytest.mark.gpu
 
@@ -210,3 +212,65 @@ def test_tbody_argument_errors():
         assert ctx.tbody_create(1, 2, 1, 256, 16, check=False) != 0
     finally:
         ctx.close()
+
+
+# Query slots 1, 8, 31 .. 33 and 64 (one block of 32 and two); k parts 1, 2, 3, 5 and 16 (batches of four or two); every prefix of the
+# list in one launch: none, one position, whole and broken chunks, more than one round of chunks; 1, 2 and 4 workgroups per pair
+@pytest.mark.parametrize("nh,nkv,L,nKs,P_max,split", [
+    (1, 1, 1, 1, 300, 2), (4, 2, 4, 3, 1024, 4), (31, 1, 1, 2, 1024, 4), (64, 32, 16, 5, 300, 1), (33, 1, 1, 16, 700, 4),
+    (8, 2, 16, 1, 1024, 4), (16, 4, 11, 2, 300, 2), (12, 12, 16, 4, 300, 1)])
+def test_attention_kernel(nh, nkv, L, nKs, P_max, split):
+    prefixes = [0, P_max, 1, 31, 32, 33, 127, 128, 129, 255, 256, 257]
+    prefixes = prefixes[:6] if nkv == 32 else prefixes
+    B, rep = len(prefixes), nh // nkv
+    M, nIb, ldq = B * L, -(-B * L // 256) * 8, (nh + 2 * nkv) * 128
+    i = C.c_int
+    assert library_rule("_ZN3mrp15attention_splitEiiii", i, i, i, i, i)(B, nkv, rep * L, P_max) == split
+    g = torch.Generator(device="cuda")
+    g.manual_seed(nh * 100 + L)
+    part = torch.empty(nKs, M, ldq, device="cuda").normal_(0, nKs ** -0.5, generator=g)
+    ang = torch.empty(M, 64, device="cuda").uniform_(0, 6.283, generator=g)
+    rope = torch.stack([ang.cos(), ang.sin()], 2).contiguous()
+    kc, vc = [torch.empty(B, P_max, nkv, 128, device="cuda").normal_(0, 1, generator=g).bfloat16() for _ in range(2)]
+    for b, P in enumerate(prefixes):        # what lies past a prefix need not be finite
+        kc[b, P:], vc[b, P:] = float("nan"), float("inf")
+    plen = torch.tensor(prefixes, dtype=torch.int32, device="cuda")
+    scratch = torch.full((256 * 64 * 130,), float("nan"), device="cuda")
+    planes = torch.full((2, nh * 8 * nIb * 512), 7.0, dtype=torch.float16, device="cuda")
+    launch = library_rule("_ZN3mrp16launch_attentionEPKfiiiiiiPK15HIP_vector_typeIfLj2EEPKtS7_PKiiPS2_IjLj4EEliPfP12ihipStream_t",
+                          i, C.c_void_p, i, i, i, i, i, i, *[C.c_void_p] * 4, i, C.c_void_p, C.c_long, i, C.c_void_p, C.c_void_p)
+    assert launch(part.data_ptr(), nKs, M, B, L, nh, nkv, rope.data_ptr(), kc.data_ptr(), vc.data_ptr(), plen.data_ptr(), P_max,
+                  planes.data_ptr(), planes.shape[1] // 8, nIb, scratch.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    r, c = torch.arange(M, device="cuda").unsqueeze(1), torch.arange(nh * 128, device="cuda").unsqueeze(0)
+    idx = (((c >> 4) * nIb + (r >> 5)) * 64 + (r & 31) + 32 * ((c >> 3) & 1)) * 8 + (c & 7)
+    got = (planes[0][idx].double() + planes[1][idx].double()).view(B, L, nh, 128)
+
+    x = part.double().sum(0).view(B, L, nh + 2 * nkv, 128)
+    size = part.abs().double().sum(0).view(B, L, nh + 2 * nkv, 128)      # what the parts' sum rounds against
+    co, si = rope[..., 0].double().view(B, L, 1, 64), rope[..., 1].double().view(B, L, 1, 64)
+    turn = lambda t: torch.cat([t[..., :64] * co - t[..., 64:] * si, t[..., 64:] * co + t[..., :64] * si], 3)
+    reach = lambda t: torch.cat([t[..., :64] * co.abs() + t[..., 64:] * si.abs(), t[..., 64:] * co.abs() + t[..., :64] * si.abs()], 3)
+    q, k, v = turn(x[:, :, :nh]) * 128 ** -0.5, turn(x[:, :, nh:nh + nkv]), x[:, :, nh + nkv:]
+    aq, ak = reach(size[:, :, :nh]) * 128 ** -0.5, reach(size[:, :, nh:nh + nkv])
+    e = 2.0 ** -24
+    for b, P in enumerate(prefixes):
+        for h in range(nkv):
+            heads = slice(h * rep, (h + 1) * rep)
+            keys = torch.cat([kc[b, :P, h].double(), k[b, :, h]])
+            vals = torch.cat([vc[b, :P, h].double(), v[b, :, h]])
+            akeys = torch.cat([kc[b, :P, h].double().abs(), ak[b, :, h]])
+            avals = torch.cat([vc[b, :P, h].double().abs(), size[b, :, nh + nkv + h]])
+            s = q[b, :, heads].reshape(-1, 128) @ keys.t()
+            p = torch.softmax(s, 1)
+            ref = p @ vals
+            # A score: the parts' sums and the rotation (nKs + 4 roundings of each operand), then at most 128 x 3 additions.  The
+            # output: its weights off by that score error and by the exponentials' own (some ulp of scores' size, merged over
+            # partials), T + 16 additions, 2^-22 for its two 16-bit halves.
+            ds = (2 * (nKs + 4) + 400) * e * (aq[b, :, heads].reshape(-1, 128) @ akeys.t()).amax(1, keepdim=True) + 8 * e * s.abs().amax(1, keepdim=True)
+            bound = (2 * ds + (keys.shape[0] + 64) * e) * (p @ avals) + 4 * e * ref.abs() + 2.0 ** -24
+            err = (got[b, :, heads].reshape(-1, 128) - ref).abs()
+            assert bool((err <= bound).all()), (P, h, float((err / bound).max()))
+    rest = torch.ones_like(planes[0], dtype=torch.bool)
+    rest[idx] = False
+    assert bool((planes[:, rest] == 7.0).all())
