@@ -1,4 +1,4 @@
-// The MLP body of an MRP head at a small number of activation rows (below 768) (paper Section 3.2 and
+// The MLP body of an MRP head at a small number of activation rows (below the tile kernel's range) (paper Section 3.2 and
 // Algorithm 2, inner loop: u = W2 SiLU(W1 [h ; e])) as two launches with no
 // partial sums in memory: each GEMM reduces its k split inside the workgroup
 // through LDS, the first reads the conditioning embedding straight from the

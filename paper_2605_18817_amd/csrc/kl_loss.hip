@@ -72,6 +72,7 @@ struct KlArgs {
     float *loss, *grad;
     int M;
     int nq;                       // counters that the one-pass form draws from (0: two passes)
+    int spin;                     // looks at a word before its tile is taken as one that nobody has room for
 };
 
 constexpr int MAX_Q = 7;
@@ -86,23 +87,18 @@ __device__ __forceinline__ float kl_at(const float4 (&x)[8], int n) {
     return (n & 3) == 0 ? q.x : ((n & 3) == 1 ? q.y : ((n & 3) == 2 ? q.z : q.w));
 }
 
-// Partial of one KT-wide tile from its entries; valid in thread 0.  sw: one slot per wavefront
-__device__ __forceinline__ KlPart kl_tile(const float4 (&xt)[8], const float4 (&xs)[8], KlPart *sw) {
-    KlPart p = kl_identity();
-#pragma unroll
-    for (int n = 0; n < 32; ++n) { p.mT = fmaxf(p.mT, kl_at(xt, n)); p.mS = fmaxf(p.mS, kl_at(xs, n)); }
-    if (p.mT > -INFINITY) {
-#pragma unroll
-        for (int n = 0; n < 32; ++n) {
-            const float vt = kl_at(xt, n), vs = kl_at(xs, n);
-            if (vt > -INFINITY) {   // (padding past V is -inf in both tensors: skip, T - S would be NaN)
-                const float e = __expf(vt - p.mT);
-                p.sT += e;
-                p.aT += e * (vt - vs);
-                p.sS += __expf(vs - p.mS);
-            }
-        }
+__device__ __forceinline__ void kl_max(KlPart &p, float vt, float vs) { p.mT = fmaxf(p.mT, vt); p.mS = fmaxf(p.mS, vs); }
+__device__ __forceinline__ void kl_add(KlPart &p, float vt, float vs) {
+    if (vt > -INFINITY) {       // (padding past V is -inf in both tensors: skip, T - S would be NaN)
+        const float e = __expf(vt - p.mT);
+        p.sT += e;
+        p.aT += e * (vt - vs);
+        p.sS += __expf(vs - p.mS);
     }
+}
+
+// The workgroup's partial from its threads'; valid in thread 0.  sw: one slot per wavefront
+__device__ __forceinline__ KlPart kl_join(KlPart p, KlPart *sw) {
     p = kl_wave_merge(p);
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) sw[wave] = p;
@@ -112,6 +108,34 @@ __device__ __forceinline__ KlPart kl_tile(const float4 (&xt)[8], const float4 (&
         for (int w = 1; w < 4; ++w) p = kl_merge(p, sw[w]);
     }
     return p;
+}
+
+// Partial of one KT-wide tile from its entries; valid in thread 0
+__device__ __forceinline__ KlPart kl_tile(const float4 (&xt)[8], const float4 (&xs)[8], KlPart *sw) {
+    KlPart p = kl_identity();
+#pragma unroll
+    for (int n = 0; n < 32; ++n) kl_max(p, kl_at(xt, n), kl_at(xs, n));
+    if (p.mT > -INFINITY) {
+#pragma unroll
+        for (int n = 0; n < 32; ++n) kl_add(p, kl_at(xt, n), kl_at(xs, n));
+    }
+    return kl_join(p, sw);
+}
+
+// The same from memory, four entries at a time in the same order (few registers: the caller holds another tile)
+__device__ __forceinline__ KlPart kl_tile_again(const float *T, const float *S, int v0, int V, KlPart *sw) {
+    KlPart p = kl_identity();
+#pragma clang loop unroll(disable)
+    for (int n = 0; n < 16; ++n) {
+        const int v = v0 + 4 * (threadIdx.x + 256 * (n & 7));
+        const float4 x = load4_row(T, v, V, -INFINITY), y = load4_row(S, v, V, -INFINITY);
+        if (n < 8) {
+            kl_max(p, x.x, y.x); kl_max(p, x.y, y.y); kl_max(p, x.z, y.z); kl_max(p, x.w, y.w);
+        } else if (p.mT > -INFINITY) {
+            kl_add(p, x.x, y.x); kl_add(p, x.y, y.y); kl_add(p, x.z, y.z); kl_add(p, x.w, y.w);
+        }
+    }
+    return kl_join(p, sw);
 }
 
 // loss alone: partials of one KT-wide tile of one row
@@ -160,13 +184,16 @@ __device__ __forceinline__ void kl_write(const KlArgs &a, int t, int i, bool on,
 // what it holds.  A value and its mark travel in one 64-bit word, so nothing else has to be ordered; words and counters are
 // cleared by a launch before.
 //
-// The wait ends whatever order workgroups start in: which tile a workgroup takes is drawn from one of nq counters as it
-// starts, so of the rows of a counter at most one has tiles that nobody has drawn yet.  Rows that are all drawn need
-// nobody else and leave; the others hold at most nq (nT - 1) places, an eighth of the device (kl_counters).
+// Which tile a workgroup takes is drawn from one of nq counters as it starts, so of the rows of a counter at most one has tiles
+// that nobody has drawn yet.  Rows that are all drawn need nobody else and leave; the others hold at most nq (nT - 1) places, an
+// eighth of the device (kl_counters).  The wait ends with fewer places, too (a stream limited to some CUs, a device shared
+// with kernels that stay): after `spin` looks the workgroup takes the missing partial itself, with the same bits.
+// It offers what it found only in words that are still empty: a tile may be overwritten with its gradient (a gradient in the
+// place of the logits) once all its words are there, so what was read too late is not taken.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void kl_grad_kernel(const KlArgs a) {
     __shared__ KlPart sw[4];
     __shared__ float s_lse[2];
-    __shared__ int s_draw;
+    __shared__ int s_draw, s_missing;
     const int lane = threadIdx.x & 63, q = blockIdx.x % a.nq;
     if (threadIdx.x == 0)
         s_draw = (int)__hip_atomic_fetch_add(a.words + 5 * a.stride + 16 * q, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -179,8 +206,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     if (on) {
         kl_fetch(a.T + (size_t)i * a.V, t * KT, a.V, xt);
         kl_fetch(a.S + (size_t)i * a.V, t * KT, a.V, xs);
-        const KlPart p = kl_tile(xt, xs, sw);
         unsigned long long *words = a.words + (size_t)i * a.nT;
+        const KlPart p = kl_tile(xt, xs, sw);
         if (threadIdx.x == 0) {
             const float v[5] = {p.mT, p.sT, p.aT, p.mS, p.sS};
 #pragma unroll
@@ -188,34 +215,56 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                 __hip_atomic_store(words + n * a.stride + t, (1ull << 32) | __float_as_uint(v[n]), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         }
-        if (threadIdx.x < 64) {      // the order of kl_row
-            KlPart r = kl_identity();
-            for (int u = lane; u < a.nT; u += 64) {
-                unsigned long long w[5];
-                bool all;
-                do {
-                    all = true;
+        for (;;) {
+            if (threadIdx.x < 64) {      // the order of kl_row
+                KlPart r = kl_identity();
+                int missing = -1;
+                for (int u = lane; u < a.nT; u += 64) {
+                    unsigned long long w[5];
+                    bool all;
+                    int looks = 0;
+                    do {
+                        all = true;
 #pragma unroll
-                    for (int n = 0; n < 5; ++n) {
-                        w[n] = __hip_atomic_load(words + n * a.stride + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        all = all && (w[n] >> 32) != 0;
+                        for (int n = 0; n < 5; ++n) {
+                            w[n] = __hip_atomic_load(words + n * a.stride + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            all = all && (w[n] >> 32) != 0;
+                        }
+                        if (!all) __builtin_amdgcn_s_sleep(4);
+                    } while (!all && ++looks < a.spin);
+                    if (!all) missing = u;
+                    float v[5];
+#pragma unroll
+                    for (int n = 0; n < 5; ++n) v[n] = __uint_as_float((unsigned)w[n]);
+                    r = kl_merge(r, KlPart{v[0], v[1], v[2], v[3], v[4]});
+                }
+                const unsigned long long who = __ballot(missing >= 0);
+                const int first = who ? __shfl(missing, __ffsll(who) - 1) : -1;
+                r = kl_wave_merge(r);
+                if (lane == 0) {
+                    s_missing = first;
+                    if (first < 0) {
+                        const float qT = r.mT + logf(r.sT), qS = r.mS + logf(r.sS);
+                        s_lse[0] = qT;
+                        s_lse[1] = qS;
+                        if (t == 0) a.loss[i] = a.scale * (r.aT / r.sT - qT + qS);
                     }
-                    if (!all) __builtin_amdgcn_s_sleep(4);
-                } while (!all);
-                float v[5];
-#pragma unroll
-                for (int n = 0; n < 5; ++n) v[n] = __uint_as_float((unsigned)w[n]);
-                r = kl_merge(r, KlPart{v[0], v[1], v[2], v[3], v[4]});
+                }
             }
-            r = kl_wave_merge(r);
-            if (lane == 0) {
-                const float qT = r.mT + logf(r.sT), qS = r.mS + logf(r.sS);
-                s_lse[0] = qT;
-                s_lse[1] = qS;
-                if (t == 0) a.loss[i] = a.scale * (r.aT / r.sT - qT + qS);
+            __syncthreads();
+            const int take = __builtin_amdgcn_readfirstlane(s_missing);     // (uniform over the workgroup)
+            if (take < 0) break;
+            const KlPart p2 = kl_tile_again(a.T + (size_t)i * a.V, a.S + (size_t)i * a.V, take * KT, a.V, sw);
+            if (threadIdx.x == 0) {
+                const float v[5] = {p2.mT, p2.sT, p2.aT, p2.mS, p2.sS};
+#pragma unroll
+                for (int n = 0; n < 5; ++n) {
+                    unsigned long long none = 0;
+                    __hip_atomic_compare_exchange_strong(words + n * a.stride + take, &none, (1ull << 32) | __float_as_uint(v[n]),
+                                                         __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
         }
-        __syncthreads();
         lT = s_lse[0];
         lS = s_lse[1];
     } else if (t == 0 && threadIdx.x == 0) {
@@ -284,9 +333,9 @@ int kl_counters(int M, int nT, int nCU) {
 }
 
 hipError_t launch_kl_loss(int M, int V, const float *teacher, const float *student, const uint8_t *mask, float scale,
-                          float *part, size_t part_stride, float *loss_rows, float *grad, int nCU, hipStream_t st) {
+                          float *part, size_t part_stride, float *loss_rows, float *grad, int nCU, int spin, hipStream_t st) {
     const KlArgs a = {teacher, student, mask, V, kl_tiles(V), scale, part, reinterpret_cast<unsigned long long *>(part), part_stride,
-                      loss_rows, grad, M, grad ? kl_counters(M, kl_tiles(V), nCU) : 0};
+                      loss_rows, grad, M, grad ? kl_counters(M, kl_tiles(V), nCU) : 0, spin};
     if (a.nq) {
         const int n = M * a.nT;
         hipLaunchKernelGGL(kl_clear_kernel, dim3((n + 255) / 256, 6), dim3(256), 0, st, a.words, part_stride, n);

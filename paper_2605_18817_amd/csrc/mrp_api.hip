@@ -421,7 +421,7 @@ int mrp_kl_loss(mrp_ctx *c, void *stream, int M, const float *teacher, const flo
         return fail(c, MRP_ERR_ALIGN, "mrp_kl_loss: tensors must be 16-byte aligned");
     if (M == 0) return MRP_OK;
     HIP_TRY(c, launch_kl_loss(M, c->dims.V, teacher, student, row_mask, scale, c->kl_part, c->kl_stride,
-                              loss_rows, grad, c->nCU, static_cast<hipStream_t>(stream)));
+                              loss_rows, grad, c->nCU, KL_SPIN, static_cast<hipStream_t>(stream)));
     return MRP_OK;
 }
 

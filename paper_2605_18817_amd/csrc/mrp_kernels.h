@@ -458,7 +458,8 @@ int residual_rms_workgroups(int n_blocks, int S, long ntiles, int nCU);
 
 int kl_tiles(int V);
 hipError_t launch_kl_loss(int M, int V, const float *teacher, const float *student, const uint8_t *mask, float scale,
-                          float *part, size_t part_stride, float *loss_rows, float *grad, int nCU, hipStream_t st);
+                          float *part, size_t part_stride, float *loss_rows, float *grad, int nCU, int spin, hipStream_t st);
+constexpr int KL_SPIN = 1 << 13;      // looks of about a microsecond each: far beyond any wait with the device to oneself
 size_t kl_part_bytes(size_t stride);
 int kl_counters(int M, int nT, int nCU);
 

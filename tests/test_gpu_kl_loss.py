@@ -186,3 +186,26 @@ def test_gradient_in_one_pass_and_two(V, M):
             bound = 0.5 * (2e-5 * (p.exp() + q.exp()) + 1e-12) * on
             assert bool(((grad - 0.5 * (q.exp() - p.exp()) * on).abs() <= bound).all())
     ctx.close()
+
+
+@pytest.mark.parametrize("V,M", [(151936, 108), (8193, 1024)])
+def test_one_pass_without_waiting(V, M):
+    """A workgroup that finds its row's other partials missing takes them itself: with no patience at all, the same bits, also
+    over the student's own logits."""
+    launch = library_rule("_ZN3mrp14launch_kl_lossEiiPKfS1_PKhfPfmS4_S4_iiP12ihipStream_t", C.c_int, C.c_int, C.c_int, *[C.c_void_p] * 3,
+                          C.c_float, C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_void_p)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V)
+    t = torch.empty(M, V, device="cuda").normal_(0, 2, generator=g)
+    s = t + torch.empty(M, V, device="cuda").normal_(0, 0.5, generator=g)
+    n = M * -(-V // 8192)
+    words = torch.zeros(5 * n + 16 * 7, dtype=torch.int64, device="cuda")
+    loss, want, grad = [torch.full((M,), 9.0, device="cuda") for _ in range(2)] + [torch.empty_like(s)]
+    ctx = mrp.MrpContext(128, V, M, 1)
+    ctx.kl_loss(M, t, s, None, 0.5, want, grad)
+    ctx.close()
+    for out in (torch.full_like(s, 9.0), s):
+        assert launch(M, V, t.data_ptr(), s.data_ptr(), None, 0.5, words.data_ptr(), n, loss.data_ptr(), out.data_ptr(), 256, 0,
+                      torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(loss, want) and torch.equal(out, grad)
