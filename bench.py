@@ -86,15 +86,12 @@ def bench_kl_loss(args, np, torch, mi, mrp) -> dict:
     loss = torch.empty((M,), dtype=torch.float32, device="cuda")
     grad = torch.empty((M, V), dtype=torch.float32, device="cuda")
     elapsed, ev = _time_steps(torch, lambda: ctx.kl_loss(M, t_d, s_d, m_d, 1.0 / M, loss, grad), args.warmup, args.steps)
-    # Both tensors of the rows in the mask once, the gradient of all rows once (zeros outside the mask).  The kernel reads
-    # the rows in the mask a second time, for the gradient; that is its own doing and counts for nothing here.
+    # Both tensors of the rows in the mask once, the gradient of all rows once (zeros outside the mask).
     byt = (8.0 * mask.mean() + 4.0) * M * V
     ach = byt / (ev / args.steps) / 1e9
     roof = {"bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBS,
-            # (the counters of profiles/kl_loss_pmc.txt sit between the L2s and the last-level cache, which answers part of
-            #  the second read: no measure of HBM bytes)
             "traffic": None,
-            "kernel": "kl_kernel (partials of a group of rows, gradient of the one before)",
+            "kernel": "kl_grad_kernel (a tile stays in registers from its partial to its gradient)",
             "kernel_ms": 1e3 * ev / args.steps}
     cpu = None
     if not args.skip_cpu_baseline:
