@@ -124,13 +124,13 @@ __global__ __launch_bounds__(256) void swiglu_split_kernel(const float *__restri
 
 // ------------------------------------------------------------------------------------------------
 // Attention.  One workgroup of eight wavefronts per (kv head g, sequence b), or several that share
-// the pair's prefix: its Q = (nh / nkv) * L query
-// vectors (query qq = hrep * L + i: head g * rep + hrep, block row i) share the keys and values of
-// head g.
+// the pair's prefix: its Q = (nh / nkv) * L query vectors (query qq = hrep * L + i: head g * rep + hrep, block row i)
+// share the keys and values of head g.
 //   * The block's own L keys and values (fp32, from the projection) are handled by the whole
 //     workgroup on the vector ALU.
 //   * The prefix cache is walked in chunks of 32 positions, chunk c by wavefront c % 8 (with more than 32 queries by the two
-//     wavefronts c % 4 of the query blocks), and each wavefront runs its own online softmax over its chunks: no workgroup barrier inside the walk.
+//     wavefronts c % 4 of the query blocks), and each wavefront runs its own online softmax over its chunks: no
+//     workgroup barrier inside the walk.
 //     Both contractions run on the matrix cores on the cache's bf16 values as they are, with the fp32
 //     operand of each (queries, probabilities) as three bf16 terms (x = a + b + c up to 2^-24 |x|):
 //       scores  S^T[key][q]  = K[key][:] . (q_a + q_b + q_c)[q][:]          A = keys,      B = query planes
@@ -141,11 +141,12 @@ __global__ __launch_bounds__(256) void swiglu_split_kernel(const float *__restri
 //     a chunk's value rows are parked in LDS as they are and the transposed fragments (a lane = one
 //     dimension, 8 positions) are read back with the transposing 64-bit LDS read, four positions at a time.
 //   * At the end the partial results per query (block, the wavefronts) are merged in a fixed order.
-// What bounds it: a CU takes in one workgroup's cache at 25 to 30 GB/s, so the longest prefix; below that the latency of the phases
-// before and after the walk.  Three heads of three layers, V = 4096, prefixes random up to 1024: 4096 wide, 24 x 16 rows (64
-// queries) 3566 -> 3242 us, of that the prologue's requests sent together instead of one after the other 165, two waves per
-// SIMD instead of one with both query blocks 45, the waves' sums merged side by side 110 with 256 positions or more;
-// 2048 wide, 32 x 4 rows (8 queries) 1183 -> 1147.  The kernel alone: 72.6 -> 45.8 us and 33.3 -> 29.5.
+// What bounds it: the longest prefix, 0.6 to 0.8 us per chunk on its CU (requests, LDS, softmax and matrix instructions of a wave follow each
+// other; cache rows side by side in memory or 2 KB apart take the same); with every prefix at 1024 and few queries HBM (134 MB in 28 us); below
+// that the latency of the phases before and after the walk, 7 to 10 us.  A step of three heads of three layers, V = 151936, prefixes
+// random up to 1024: 4096 wide, 24 x 16 rows (64 queries) 4841 -> 4619 us, of that the prologue's requests sent together instead
+// of one after the other 165, two waves per SIMD instead of one with both query blocks 45, the waves' sums merged side by side
+// 10; 2048 wide, 32 x 4 rows (8 queries) 1617 -> 1584, by the merge.  The kernel alone: 72.6 -> 45.8 us and 33.3 -> 29.5.
 struct AttnArgs {
     const float *qkv;        // partial sums [nKs][M][ldq] of the q | k | v projection
     size_t split_stride;
