@@ -255,18 +255,21 @@ __device__ __forceinline__ void tile_body(const TiledGemmArgs &a, int vt, int ib
     constexpr int ZD = RAG ? 2 : (NB < 5 ? NB + 1 : 6);     // slice buffers: five (one) slices in flight ahead of the one added
     constexpr int ZE = RAG && NB == 8 ? 1 : 2;  // slices requested in the k loop
     f32x4 zc[ZD][8];
-    // The rows of the tile as a buffer of their own: a piece that lies past the matrix' last row, or (zoff) past the end of
-    // its row, reads zero and is not stored, without a branch for each piece.
+    // Every 16 rows of the tile as a buffer of their own, with as many of them as lie inside row_lim: a piece past those, or
+    // (zoff) past the end of its row, reads zero and is not stored, without a branch for each piece.  The rows stand in the
+    // buffer's base and its size: a scalar offset is no part of what a raw buffer's bounds check compares.
     const int zv_lane = rw0 + 4 * lq;           // + 16 q
-    const int zrows = row_lim - ib0 * 32 < 32 * NB ? row_lim - ib0 * 32 : 32 * NB;
-    const __amdgpu_buffer_rsrc_t zbuf =
-        __builtin_amdgcn_make_buffer_rsrc(a.z + (size_t)ib0 * 32 * a.R, 0, (unsigned)zrows * (unsigned)a.R * 4u, 0x00020000);
+    float *const ztile = a.z + (size_t)ib0 * 32 * a.R;
+    const size_t zgroup = (size_t)16 * a.R;
+    auto zbuf = [&](int ib, int hi) __attribute__((always_inline)) -> __amdgpu_buffer_rsrc_t {
+        const int g = 2 * ib + hi, left = row_lim - ib0 * 32 - 16 * g, rows = left < 16 ? left : 16;
+        return __builtin_amdgcn_make_buffer_rsrc(ztile + g * zgroup, 0, left > 0 ? (unsigned)rows * (unsigned)a.R * 4u : 0u, 0x00020000);
+    };
     unsigned zoff[4];
     if constexpr (EPI == EPI_LM && !RAG) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) zoff[q] = zv_lane + 16 * q < a.R ? (unsigned)(ln * a.R + zv_lane + 16 * q) * 4u : 0xffffff00u;
     }
-    auto zrow = [&](int ib, int hi) __attribute__((always_inline)) -> int { return (32 * ib + 16 * hi) * a.R * 4; };
     auto zpiece = [&](int ib, int pc) __attribute__((always_inline)) -> f32x4 {   // pc: 4 hi + q
         if constexpr (RAG) {
             int i = (ib0 + ib) * 32 + 16 * (pc >> 2) + ln;
@@ -279,7 +282,7 @@ __device__ __forceinline__ void tile_body(const TiledGemmArgs &a, int vt, int ib
             const float4 x = load4(a.z + ((long)i * a.R + v));
             return f32x4{x.x, x.y, x.z, x.w};
         } else {
-            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(zbuf, zoff[pc & 3], zrow(ib, pc >> 2), 0));
+            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(zbuf(ib, pc >> 2), zoff[pc & 3], 0, 0));
         }
     };
 
@@ -488,7 +491,7 @@ __device__ __forceinline__ void tile_body(const TiledGemmArgs &a, int vt, int ib
                             }
                         }
                     } else {
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x4), zbuf, zoff[q], zrow(ib, hi), 0);
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x4), zbuf(ib, hi), zoff[q], 0, 0);
                     }
                 }
                 if (row_end) {
@@ -576,10 +579,10 @@ hipError_t launch_inst(const TiledGemmArgs &a, int rem, hipStream_t st) {
 }
 
 // EPI_LM: a row that is no whole number of pieces has its own form (the handling of its end costs registers, and with
-// them four of the five logit slices in flight; the other one's byte offsets inside a tile are 32 bits)
+// them four of the five logit slices in flight; the other one's byte offsets inside 16 rows are 32 bits)
 template <int NB, bool HALVES>
 hipError_t launch_lm_nb(const TiledGemmArgs &a, int rem, hipStream_t st) {
-    return a.R % 4 || a.R > 4000000 ? launch_inst<EPI_LM, true, NB, 4, false, HALVES>(a, rem, st)
+    return a.R % 4 || a.R > (1 << 26) - 64 ? launch_inst<EPI_LM, true, NB, 4, false, HALVES>(a, rem, st)
                                     : launch_inst<EPI_LM, false, NB, 4, false, HALVES>(a, rem, st);
 }
 template <bool HALVES>

@@ -350,11 +350,62 @@ def test_narrow_head_body(d, B, L):
 ])
 def test_left_over_tiles(B, L, V):
     """LM head on the tile kernel with its left-over tiles halved (up to 128 of them) or whole, at every height; first, middle
-    and last sequence compared, and no logit of the others is touched twice or missed."""
+    and last sequence compared (every logit of the others, and what lies behind them: below)."""
     cfg = mi.straddling(mi.config(0, d=128, V=V, B=B, L=L, K=1))
     assert B * L > 512 or lm_head_on_tiles(B * L, 128, V)
     prob, g, o, stats = _free_run(cfg, mrp.RevealCfg(tau=2.0), seqs=[0, B // 2, B - 1])
     prob.close()
+
+
+@pytest.mark.parametrize("B,L,V", [
+    (37, 16, 16640), (37, 16, 8192),     # 592 rows: the last of three 224-row tiles holds 144, five 16-row groups lie past them; halved
+    (33, 16, 22016), (33, 16, 16640),    # 528 rows: 144 of 192; halved
+    (25, 16, 16384), (25, 16, 16644),    # 400 rows: 176 of 224, halved at 128 rows of a tile; whole, the rows end inside a tile
+    (18, 16, 16384), (18, 16, 16640),    # 288 rows: 128 of 160
+    (129, 1, 33024), (577, 1, 16640),    # one row in the first group past a whole number of groups; of three 224-row tiles
+    (513, 1, 8192), (153, 2, 16388),     # one row in a half; 306 rows: 146 of 160
+    (24, 16, 16384), (32, 16, 16640),    # whole tiles only
+    (25, 16, 16383), (153, 2, 16641),    # rows that start on any 4-byte boundary
+    (65, 2, 4200004),                    # byte offsets of a tile beyond 32 bits
+])
+def test_every_logit_once_and_nothing_behind_them(B, L, V):
+    """The tile kernel's tiles that hold fewer rows than they are high, after a larger batch on the same context (the LM head's
+    operand rows past the batch are then not zero): every logit against the same sequences in batches of at most 128 rows,
+    which the persistent kernel takes, and a guard of a whole tile's rows behind the matrix."""
+    d, M, more = 128, B * L, 256 // L
+    assert M > 512 or lm_head_on_tiles(M, d, V)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + V)
+    normal = lambda *s, std, dtype=torch.bfloat16: torch.empty(s, dtype=dtype, device="cuda").normal_(0, std, generator=gen)
+    E, W = normal(V, d, std=0.02), normal(V, d, std=0.02)
+    Wp = mrp.pack_weight(W)
+    head = [mrp.Head(mrp.pack_weight(normal(d, 2 * d, std=0.05), body=True), mrp.pack_weight(normal(d, d, std=0.05), body=True),
+                     torch.ones(d, dtype=torch.bfloat16, device="cuda"))]
+    h, z0 = normal((B + more) * L, d, std=1.0), normal(M, V, std=2.0, dtype=torch.float32)
+    rcfg = mrp.RevealCfg(tau=2.0)
+
+    def run(ctx, z, first, n):
+        hrun = torch.zeros(n * L, d, device="cuda")
+        ctx.chain_step(n, 1, h[first * L:(first + n) * L], hrun, E, Wp, head, z, rcfg, mrp.StepIO(n, L, 1))
+        torch.cuda.synchronize()
+
+    ctx = mrp.MrpContext(d, V, (B + more) * L, L)
+    run(ctx, torch.zeros((B + more) * L, V, device="cuda"), 0, B + more)
+    flat = torch.full(((M + 256) * V,), 7.0, device="cuda")
+    z = flat[:M * V].view(M, V)
+    z.copy_(z0)
+    run(ctx, z, 0, B)
+    assert bool((flat[M * V:] == 7.0).all())
+    # two orders of summing 128 products, at most 128 roundings each; |w . y| <= |w| |y| with |y| = sqrt(d) from the norm
+    w_norm = float(W.float().norm(dim=1).max())
+    for b0 in range(0, B, 128 // L):
+        n, rows = min(128 // L, B - b0), slice(b0 * L, (b0 + min(128 // L, B - b0)) * L)
+        ref = z0[rows].clone()
+        run(ctx, ref, b0, n)
+        assert bool(((ref - z0[rows]).abs().amax(1) > 0.05).all())        # (the head adds something to every row)
+        bound = 2 * 128 * 2.0 ** -24 * w_norm * 1.01 * d ** 0.5 + 2.0 ** -23 * ref.abs()
+        assert bool(((z[rows] - ref).abs() <= bound).all()), b0
+    ctx.close()
 
 
 @pytest.mark.parametrize("d,B,L,features", [

@@ -1,7 +1,7 @@
-"""The tile kernel issues its matrix instructions as inline assembly, so the compiler does not keep the distances that
-their operands and results need.  This reads the assembly of the built library (no GPU): an accumulator is touched by
+"""What the tile kernel relies on, read from the assembly of the built library (no GPU).  Its matrix instructions are inline
+assembly, so the compiler does not keep the distances that their operands and results need: an accumulator is touched by
 nothing but the next MFMA on it until every pass of the last one is over, and an operand is not written by a vector
-instruction right ahead."""
+instruction right ahead.  And its logit pieces rely on the bounds check of their buffers."""
 import re
 import shutil
 import subprocess
@@ -80,18 +80,33 @@ def _faults(ins):
     return found
 
 
-def test_matrix_instructions_keep_their_distances(tmp_path):
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
     if OBJDUMP is None:
         pytest.skip("no llvm-objdump")
     hip_build.build(force=False)
-    lib = tmp_path / "lib.so"
+    folder = tmp_path_factory.mktemp("lib")
+    lib = folder / "lib.so"
     shutil.copy(hip_build.LIB, lib)
-    subprocess.run([OBJDUMP, "--offloading", str(lib)], check=True, stdout=subprocess.DEVNULL, cwd=tmp_path)
-    kernels = {}
-    for image in sorted(tmp_path.glob("lib.so.*gfx950*")):
+    subprocess.run([OBJDUMP, "--offloading", str(lib)], check=True, stdout=subprocess.DEVNULL, cwd=folder)
+    found = {}
+    for image in sorted(folder.glob("lib.so.*gfx950*")):
         text = subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", str(image)], check=True, stdout=subprocess.PIPE, text=True).stdout
-        kernels.update(_kernels(text, "tiled_gemm_kernel"))
-    assert len(kernels) >= 60
+        found.update(_kernels(text, "tiled_gemm_kernel"))
+    assert len(found) >= 60
+    return found
+
+
+def test_matrix_instructions_keep_their_distances(kernels):
     for name, ins in kernels.items():
         assert sum(op.startswith("v_mfma") for _, op, _ in ins) >= 200, name
         assert not _faults(ins), (name, _faults(ins)[:4])
+
+
+def test_buffer_bounds_see_the_whole_offset(kernels):
+    """A raw buffer's bounds check compares the lane's offset with the buffer's size; a scalar offset comes on top of it
+    unchecked.  So rows that are not there have to be missing from the buffer's size, and the scalar offset is zero."""
+    pieces = [(name, op, ops) for name, ins in kernels.items() for _, op, ops in ins if op.startswith("buffer_")]
+    assert len(pieces) >= 2000
+    wrong = [p for p in pieces if p[2][3].split() != ["0", "offen"]]
+    assert not wrong, (len(wrong), wrong[:3])
