@@ -182,8 +182,11 @@ int mrp::small_tile_blocks(int R, int Kc, int M, int nCU) {
 // (Error of u against 64 bits at 384 rows, d = 4096: 3.46e-7 / 3.08e-7 of its norm.)
 bool mrp::mlp_on_tiles(int M, int d, int nCU, size_t part_rows) {
     if (M >= 768 || d <= 2048) return M >= 768;
+    if (M <= 128 || M > 512) return M > 512;
+    // (k parts for one and for two planes of the hidden state: no fewer than the small-row kernels' eight waves)
     const int tiles = tiled_row_tiles(M) * ((d + 255) / 256);
-    return M > 512 || (M > 128 && 4 * tiles * tiled_ksplit(tiles, (d / 64) * (NSPLIT + 1), nCU, part_rows, M) >= 3 * nCU);
+    const int one = tiled_ksplit(tiles, (d / 64) * 2, nCU, part_rows, M), two = tiled_ksplit(tiles, (d / 64) * (NSPLIT + 1), nCU, part_rows, M);
+    return one >= 8 && two >= 8 && 4 * tiles * two >= 3 * nCU && two_plane_form(M, d, d, nCU, part_rows, 0).ks > 0;
 }
 
 // The MLP head body of a sequence in one workgroup, where both weight matrices pass through one CU in less than the launches
@@ -195,18 +198,22 @@ bool mrp::mlp_per_sequence(int L, int d) { return (d == 128 || d == 256) && L <=
 // Form of the tile kernel for [M][R] partial sums of two activation planes over Kc columns: weight rows per tile, row
 // blocks and k parts, the fastest by what the forms were measured to take: a round of tiles about 6 us and, per k step,
 // 0.15 us and 10.1 ns for each of its 4 nv nb MFMAs per wave; a part's sums 2 x 4 bytes per entry at 4 TB/s.  Forms that
-// follow from it (two-plane products, us): 24576 x 4096 at 384 rows as 256 tiles of 192 x 192 114 (256 x 192: 132, three
+// follow from it (two-plane products, us): 24576 x 4096 at 384 rows in one part as 256 tiles of 192 x 192 114 (256 x 192: 132, three
 // quarters of a round); 4096 x 4096 at 592 rows as 64 tiles of 256 x 160 x 4 parts 37 (256 x 224: 46), at 1024 rows 128 tiles of
 // 256 x 128 x 2 parts 53 (256 x 256 x 4 parts: 59).
-static TileForm cheapest_form(TileForm best, int M, int R, int nsteps, int nCU, size_t cap_rows, int nv_min, int nb_min, int ks_min) {
+// The parts are at least ks_plain where one sum takes both planes, and ks_apart where the low plane has a sum of its own
+// (0: not such a form); ks = 0: there is none.
+static TileForm cheapest_form(int M, int R, int nsteps, int nCU, size_t cap_rows, int nv_min, int nb_min, int ks_plain, int ks_apart) {
     const int ib = (M + 31) / 32, nIb = (ib + 7) / 8 * 8;
+    TileForm best = {0, 0, 0};
     double best_cost = 1e300;
     for (int nv = 4; nv >= nv_min; --nv)
         for (int nb = nb_min; nb <= 8; ++nb) {
             const int nMt = (ib + nb - 1) / nb, tiles = nMt * ((R + 64 * nv - 1) / (64 * nv));
-            if (nMt * nb > nIb) continue;      // (row blocks that the planes have)
+            const int ks_min = ks_apart > 0 && tiled_low_apart(nv, nb) ? ks_apart : ks_plain;
+            if (nMt * nb > nIb || ks_min == 0) continue;      // (row blocks that the planes have)
             for (int ks = ks_min; ks <= 16; ks *= 2) {
-                if (nsteps % ks != 0 || nsteps / ks < MRP_TILED_MIN_STEPS || (size_t)ks * M > cap_rows) break;
+                if (nsteps % ks != 0 || (ks > 1 && nsteps / ks < MRP_TILED_MIN_STEPS) || (size_t)ks * M > cap_rows) break;
                 const double rounds = (tiles * ks + nCU - 1) / nCU;
                 const double cost = rounds * (nsteps / ks * (0.15 + 0.0404 * nv * nb) + 6.0) + (ks - 1) * (double)M * R * 2e-6;
                 if (cost < best_cost) { best_cost = cost; best = TileForm{nb, nv, ks}; }
@@ -214,8 +221,17 @@ static TileForm cheapest_form(TileForm best, int M, int R, int nsteps, int nCU, 
         }
     return best;
 }
-TileForm mrp::two_plane_form(int M, int R, int Kc, int nCU, size_t cap_rows) {
-    return cheapest_form(TileForm{8, 4, 1}, M, R, Kc / 32, nCU, cap_rows, 3, 4, 1);
+// What a form may round is what the kernel in whose place it stands does (error of a product against 64 bits, of its norm,
+// normal operands, k = 4096: tiles with one sum for both planes 5.8e-7 / 4.1 / 3.0 / 2.2 in 1 / 2 / 4 / 8 parts, with a sum for
+// the low plane 4.1 / 2.9 / 2.1 / 1.6; wide kernel 2.96 / 2.14 / 1.61 / 1.29, small-row kernels 2.2; 1024 to 12288 alike, in
+// proportion to the root).  So a plain form keeps the parts that tiled_ksplit finds, one with the low plane apart half of them; in
+// the place of `wide` parts of the wide kernel it is twice as many with the low plane apart (16 in the place of 8 would be
+// 3 to 5 % further off), in that of the eight waves of the small-row kernels (`wide` = 0) four.  (24576 x 4096 at 384 rows in two
+// parts instead of one: step of three heads of three layers 4646 -> 4786 us.)
+TileForm mrp::two_plane_form(int M, int R, int Kc, int nCU, size_t cap_rows, int wide) {
+    if (wide >= 0) return wide > 4 ? TileForm{0, 0, 0} : cheapest_form(M, R, Kc / 32, nCU, cap_rows, 3, 4, 0, wide ? 2 * wide : 4);
+    const int ks = tiled_ksplit(tiled_row_tiles(M) * ((R + 255) / 256), Kc / 32, nCU, cap_rows, M);
+    return cheapest_form(M, R, Kc / 32, nCU, cap_rows, 3, 4, ks, ks > 1 ? ks / 2 : 1);
 }
 // The first GEMM of the head body, whose step is as long (64 columns of one plane).  It keeps the parts that tiled_ksplit
 // finds, or takes more: fewer would round more.  Shorter tiles where the CUs have room for more of them: step of three heads with
@@ -223,8 +239,7 @@ TileForm mrp::two_plane_form(int M, int R, int Kc, int nCU, size_t cap_rows) {
 // d = 2048 358 / 336 at 768, 453 / 398 at 1280, 490 / 436 at 1600; d = 1024 256 / 242 at 768.
 TileForm mrp::partial_form(int M, int R, int nsteps, int nCU, size_t cap_rows) {
     const int nb = tiled_row_blocks(M), ks = tiled_ksplit(tiled_row_tiles(M) * ((R + 255) / 256), nsteps, nCU, cap_rows, M);
-    const TileForm own = {nb, 4, ks};
-    return ks == 1 ? own : cheapest_form(own, M, R, nsteps, nCU, cap_rows, 4, 5, ks);
+    return ks == 1 ? TileForm{nb, 4, 1} : cheapest_form(M, R, nsteps, nCU, cap_rows, 4, 5, ks, 0);
 }
 
 namespace {
@@ -235,41 +250,47 @@ int small_tile_features(int nf) { return nf == 0 ? 16 : 32 * nf; }
 // of k splits written (1 for the tiled kernel) or -1 after a launch error (*err set).
 int gemm_partial(mrp_ctx *c, hipStream_t st, const void *Wp, int R, int Kc, const uint4 *act, long plane_stride,
                  int nplanes, int M, float *out, size_t out_floats, hipError_t *err) {
+    const bool body_tiles = body_on_tiles(M, Kc) && R % 256 == 0;
+    const size_t cap_rows = out_floats / (size_t)R;
+    // 65 .. 512 rows: the wide kernel's 64-feature x 128-row tiles with k split over workgroups.
+    // 128-feature tiles halve the activation bytes a CU pulls in per output; they pay once there are enough of
+    // them (measured at 128 rows, d = 2048: the 12288-feature gate/up projection, 96 tiles, 26.5 -> 24 us; with 32
+    // or 16 tiles, the qkv and o / down projections, the step is 2 - 5 % slower)
+    const int nrg = (M + 127) / 128, nf = (R % 128 == 0 && (R / 128) * nrg >= 96) ? 4 : 2, nft = R / (32 * nf);
+    const int ks = small_rows_kernel(M, Kc) && M > 64 && R % 64 == 0 && nplanes <= 2
+        ? wide_gemm_ksplit(nft * nrg, Kc / 16, c->nCU, cap_rows, M, nf) : 0;      // (0: not that kernel)
     // On the tile kernel where the body is, and from 65 rows for weights of 20 M entries and more (measured at 96 to 512
     // rows, wide / tile kernel with what the consumer takes longer to add up the parts: 25 M entries 23 to 55 us / 21 to 39,
     // 101 M 64 to 204 / 54 to 158; but 17 M 18 to 37 / 19 to 37, 8 M 11 to 23 / 13 to 23).
-    if (nplanes == 2 && R % 32 == 0 && Kc % 64 == 0 &&
-        ((body_on_tiles(M, Kc) && R % 256 == 0) || (M > 64 && (size_t)R * Kc >= 20000000))) {
-        const TileForm f = two_plane_form(M, R, Kc, c->nCU, out_floats / (size_t)R);
-        TiledGemmArgs tg;
-        memset(&tg, 0, sizeof(tg));
-        tg.Wp = static_cast<const uint4 *>(Wp);
-        tg.KBw = Kc / 16; tg.n_rb = R / 32; tg.nIb = c->nIb; tg.M = M; tg.R = R;
-        tg.seg[0] = TiledSeg{act, plane_stride, Kc / 64, nplanes};
-        tg.nseg = 1;
-        tg.nKs = f.ks;
-        tg.nMt = (M + 32 * f.nb - 1) / (32 * f.nb); tg.nVt = (R + 64 * f.nv - 1) / (64 * f.nv);
-        tg.out = out;
-        *err = launch_tiled_two_planes(tg, f.nb, f.nv, st);
-        return *err == hipSuccess ? tg.nKs : -1;
-    }
-    if (small_rows_kernel(M, Kc) && M > 64 && R % 64 == 0 && nplanes <= 2) {
-        // 65 .. 512 rows: 64-feature x 128-row tiles with k split over workgroups
-        const int nrg = (M + 127) / 128;
-        // 128-feature tiles halve the activation bytes a CU pulls in per output; they pay once there are enough of
-        // them (measured at 128 rows, d = 2048: the 12288-feature gate/up projection, 96 tiles, 26.5 -> 24 us; with 32
-        // or 16 tiles, the qkv and o / down projections, the step is 2 - 5 % slower)
-        const int nf = (R % 128 == 0 && (R / 128) * nrg >= 96) ? 4 : 2;
-        const int nft = R / (32 * nf);
-        const int ks = wide_gemm_ksplit(nft * nrg, Kc / 16, c->nCU, out_floats / (size_t)R, M, nf);
-        if (ks > 0) {
-            WideGemmArgs wg;
-            wg.Wp = static_cast<const uint4 *>(Wp); wg.X = act; wg.plane = plane_stride; wg.nplanes = nplanes;
-            wg.out = out; wg.nIb = c->nIb; wg.M = M; wg.R = R; wg.Kc = Kc; wg.nKs = ks; wg.nft = nft; wg.nrg = nrg;
-            wg.nf = nf;
-            *err = launch_wide_gemm(wg, st);
-            return *err == hipSuccess ? ks : -1;
+    if (nplanes == 2 && R % 32 == 0 && Kc % 64 == 0 && (body_tiles || (M > 64 && (size_t)R * Kc >= 20000000))) {
+        int wide = body_tiles ? -1 : ks;
+        if (!body_tiles && !small_rows_kernel(M, Kc)) {      // in the place of the streaming kernel's parts, a sum each
+            const int streamed = pick_ksplit(R / WG_ROWS, ((M + 31) / 32 + stream_gemm_it(M) - 1) / stream_gemm_it(M),
+                                             Kc / (16 * KSTEP), cap_rows, M);
+            for (wide = 1; 4 * wide < streamed;) wide *= 2;
         }
+        const TileForm f = two_plane_form(M, R, Kc, c->nCU, cap_rows, wide);
+        if (f.ks > 0) {
+            TiledGemmArgs tg;
+            memset(&tg, 0, sizeof(tg));
+            tg.Wp = static_cast<const uint4 *>(Wp);
+            tg.KBw = Kc / 16; tg.n_rb = R / 32; tg.nIb = c->nIb; tg.M = M; tg.R = R;
+            tg.seg[0] = TiledSeg{act, plane_stride, Kc / 64, nplanes};
+            tg.nseg = 1;
+            tg.nKs = f.ks;
+            tg.nMt = (M + 32 * f.nb - 1) / (32 * f.nb); tg.nVt = (R + 64 * f.nv - 1) / (64 * f.nv);
+            tg.out = out;
+            *err = launch_tiled_two_planes(tg, f.nb, f.nv, st);
+            return *err == hipSuccess ? tg.nKs : -1;
+        }
+    }
+    if (ks > 0) {
+        WideGemmArgs wg;
+        wg.Wp = static_cast<const uint4 *>(Wp); wg.X = act; wg.plane = plane_stride; wg.nplanes = nplanes;
+        wg.out = out; wg.nIb = c->nIb; wg.M = M; wg.R = R; wg.Kc = Kc; wg.nKs = ks; wg.nft = nft; wg.nrg = nrg;
+        wg.nf = nf;
+        *err = launch_wide_gemm(wg, st);
+        return *err == hipSuccess ? ks : -1;
     }
     if (small_rows_kernel(M, Kc) && R % 32 == 0 && Kc % 128 == 0 && nplanes <= 2) {
         SmallGemmArgs sg;
@@ -712,7 +733,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
         // u = W2 s
         TiledGemmArgs tg;
         memset(&tg, 0, sizeof(tg));
-        const TileForm f = two_plane_form(M, d, d, c->nCU, c->part_rows);
+        const TileForm f = two_plane_form(M, d, d, c->nCU, c->part_rows, M > 512 ? -1 : 0);
         tg.Wp = static_cast<const uint4 *>(hd.W2_packed);
         tg.KBw = d / 16; tg.n_rb = d / 32; tg.nIb = c->nIb; tg.M = M; tg.R = d;
         tg.seg[0] = TiledSeg{c->S, c->plane, d / 64, NSPLIT};

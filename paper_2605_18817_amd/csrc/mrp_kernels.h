@@ -307,7 +307,10 @@ int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M);
 // ---- which kernel (mrp_api.hip) ----
 // Tile kernel for the partial sums of two planes: 32-row blocks per tile, weight rows per tile / 64, k parts
 struct TileForm { int nb, nv, ks; };
-TileForm two_plane_form(int M, int R, int Kc, int nCU, size_t cap_rows);
+// Do those forms keep a sum of its own for the low plane?  (What the registers have room for.)
+constexpr bool tiled_low_apart(int nv, int nb) { return nv * nb <= 18; }
+// in the place of `wide` k parts of the wide kernel (0: the small-row kernels, -1: the tile kernel's one plane after the other)
+TileForm two_plane_form(int M, int R, int Kc, int nCU, size_t cap_rows, int wide);
 // The same for `nsteps` k steps of any planes, on 256 weight rows (nv = 4)
 TileForm partial_form(int M, int R, int nsteps, int nCU, size_t cap_rows);
 // Are the MLP head body's GEMMs of M rows on the tile kernel (or on the small-row kernels)?

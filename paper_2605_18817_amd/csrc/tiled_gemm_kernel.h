@@ -222,7 +222,7 @@ __device__ __forceinline__ void tile_body(const TiledGemmArgs &a, int vt, int ib
             }
     // Two planes on short tiles leave registers for a sum of its own for the low plane: its products (2^-11 of the high
     // plane's) would round the high plane's sum as often again.
-    constexpr bool LO = P2 && NV * NB <= 18;
+    constexpr bool LO = P2 && tiled_low_apart(NV, NB);
     f32x4 low[LO ? NV : 1][LO ? NB : 1][2];
     if constexpr (LO) {
 #pragma unroll

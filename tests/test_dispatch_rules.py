@@ -59,21 +59,34 @@ class _TileForm(C.Structure):
 
 
 @pytest.mark.parametrize("nCU", [32, 256])
-def test_two_plane_forms_fit(nCU):
-    form = library_rule("_ZN3mrp14two_plane_formEiiiim", _TileForm, *[C.c_int] * 4, C.c_size_t)
+def test_two_plane_forms_fit_and_sum_no_longer(nCU):
+    form = library_rule("_ZN3mrp14two_plane_formEiiiimi", _TileForm, *[C.c_int] * 4, C.c_size_t, C.c_int)
+    ksplit = library_rule("_ZN3mrp12tiled_ksplitEiiimi", C.c_int, *[C.c_int] * 3, C.c_size_t, C.c_int)
+    blocks = library_rule("_ZN3mrp16tiled_row_blocksEi", C.c_int, C.c_int)
     for M in [*range(1, 70), 96, 128, 129, 160, 192, 193, 250, 384, 400, 512, 513, 592, 767, 768, 1000, 1024, 4096, 65535]:
         for R, K in [(32, 64), (32, 128), (128, 128), (4096, 4096), (6144, 4096), (24576, 4096), (4096, 12288), (12288, 2048),
                      (2176, 2176), (131072, 128), (2304, 8192)]:
             for cap in (M, 4 * M, 16 * M, max(M, 4096)):
-                f = form(M, R, K, nCU, cap)
-                tiles = -(-M // (32 * f.nb))
-                assert 4 <= f.nb <= 8 and f.nv in (3, 4) and 1 <= f.ks <= 16 and f.ks * M <= cap
-                assert tiles * f.nb <= -(-M // 256) * 8 and tiles * f.nb * 32 >= M      # row blocks that the planes hold
-                assert K // 32 % f.ks == 0 and K // 32 // f.ks >= min(4, K // 32)       # whole parts of four k steps at least
+                for wide in (-1, 0, 1, 2, 4, 8):     # in the place of the one-plane tiles, the small-row kernels, the wide kernel's parts
+                    f = form(M, R, K, nCU, cap, wide)
+                    if f.ks == 0:                    # (another kernel's: never where the tile kernel is the only one)
+                        assert wide >= 0
+                        continue
+                    tiles = -(-M // (32 * f.nb))
+                    assert 4 <= f.nb <= 8 and f.nv in (3, 4) and 1 <= f.ks <= 16 and f.ks * M <= cap
+                    assert tiles * f.nb <= -(-M // 256) * 8 and tiles * f.nb * 32 >= M  # row blocks that the planes hold
+                    assert K // 32 % f.ks == 0 and K // 32 // f.ks >= min(4, K // 32)   # whole parts of four k steps at least
+                    apart = f.nv * f.nb <= 18        # a sum of its own for the low plane: as good as twice the parts
+                    if wide < 0:
+                        own = ksplit(-(-M // (32 * blocks(M))) * -(-R // 256), K // 32, nCU, cap, M)
+                        assert f.ks * (2 if apart else 1) >= own
+                    else:
+                        assert wide < 8 and apart and f.ks >= (2 * wide or 4)
     if nCU == 256:                                   # the sizes it was measured at
-        assert [(f.nb, f.nv, f.ks) for f in (form(384, 24576, 4096, 256, 1 << 20), form(592, 4096, 4096, 256, 4096),
-                                             form(1024, 4096, 4096, 256, 4096), form(4096, 4096, 4096, 256, 4096))] \
-            == [(6, 3, 1), (5, 4, 4), (4, 4, 2), (8, 4, 1)]
+        assert [(f.nb, f.nv, f.ks) for f in (form(384, 24576, 4096, 256, 4096, 1), form(128, 12288, 2048, 256, 2048, 2),
+                                             form(592, 4096, 4096, 256, 4096, -1), form(1024, 4096, 4096, 256, 4096, -1),
+                                             form(4096, 4096, 4096, 256, 4096, -1), form(384, 4096, 4096, 256, 4096, 0))] \
+            == [(6, 3, 2), (4, 3, 4), (5, 4, 4), (4, 4, 2), (8, 4, 1), (4, 4, 4)]
 
 
 def test_first_body_gemm_keeps_its_parts_or_takes_more():
@@ -95,6 +108,8 @@ def test_first_body_gemm_keeps_its_parts_or_takes_more():
 
 def test_mlp_body_kernel_by_rows_and_width():
     on_tiles = library_rule("_ZN3mrp12mlp_on_tilesEiiim", C.c_bool, *[C.c_int] * 3, C.c_size_t)
+    ksplit = library_rule("_ZN3mrp12tiled_ksplitEiiimi", C.c_int, *[C.c_int] * 3, C.c_size_t, C.c_int)
+    blocks = library_rule("_ZN3mrp16tiled_row_blocksEi", C.c_int, C.c_int)
     rows = lambda M: 16 * M if M <= 128 else 4096
     for M in range(1, 800):
         for d in range(128, 8193, 128):
@@ -102,6 +117,9 @@ def test_mlp_body_kernel_by_rows_and_width():
                 assert on_tiles(M, d, 256, rows(M))
             elif M <= 128 or d <= 2048:
                 assert not on_tiles(M, d, 256, rows(M))
+            elif on_tiles(M, d, 256, rows(M)):       # 129 to 512 rows: k parts of the first GEMM, for one and for two planes
+                parts = [ksplit(-(-M // (32 * blocks(M))) * -(-d // 256), d // 64 * n, 256, rows(M), M) for n in (2, 3)]
+                assert min(parts) >= 8, (M, d)       # (the small-row kernels have eight waves)
     assert all(on_tiles(M, 4096, 256, 4096) for M in (129, 144, 160, 256, 257, 512))
     assert not any(on_tiles(M, 2560, 256, 4096) for M in (129, 192, 384))
 

@@ -138,3 +138,66 @@ def test_tile_height_does_not_change_partial_sums():
     # K / 32 MFMAs of 32 products for each of three planes, the parts' sums in 64 bits
     bound = (3 * K // 32 + 32) * 2.0 ** -24 * (xe.abs() @ we.abs().t())
     assert bool(((outs[0].double().sum(0) - xe @ we.t()).abs() <= bound).all())
+
+
+class _Wide(C.Structure):
+    _fields_ = ([("Wp", C.c_void_p), ("X", C.c_void_p), ("plane", C.c_long), ("nplanes", C.c_int), ("out", C.c_void_p)]
+                + [(n, C.c_int) for n in ("nIb", "M", "R", "Kc", "nKs", "nft", "nrg", "nf")])
+
+
+class _Small(C.Structure):
+    _fields_ = ([("Wp", C.c_void_p), ("X", C.c_void_p), ("plane", C.c_long), ("nplanes", C.c_int), ("out", C.c_void_p)]
+                + [(n, C.c_int) for n in ("nIb", "M", "R", "Kc", "nf", "nct", "nrt")])
+
+
+@pytest.mark.parametrize("K", [1024, 2560, 4096, 12288])
+def test_two_planes_are_no_further_from_64_bits(K):
+    """A two-plane form that sums as long as the rule allows, and the kernel in whose place it stands, on the same product
+    (a root mean square over 256 x 512 sums, of which each kernel's rounding is a fixed property): the wide kernel with
+    1, 2 and 4 parts, the small-row kernels, the one-plane tiles with 1 to 8 parts."""
+    lib = mrp.load_library()
+    two = getattr(lib, "_ZN3mrp23launch_tiled_two_planesERKNS_13TiledGemmArgsEiiP12ihipStream_t")
+    one = getattr(lib, "_ZN3mrp20launch_tiled_partialERKNS_13TiledGemmArgsEiP12ihipStream_t")
+    wide = getattr(lib, "_ZN3mrp16launch_wide_gemmERKNS_12WideGemmArgsEP12ihipStream_t")
+    small = getattr(lib, "_ZN3mrp17launch_small_gemmERKNS_13SmallGemmArgsEP12ihipStream_t")
+    M, R, nIb = 256, 512, 8
+    st = C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    x = torch.empty(M, K, device="cuda").normal_(0, 1, generator=gen)
+    w = torch.empty(R, K, dtype=torch.bfloat16, device="cuda").normal_(0, 0.02, generator=gen)
+    planes = torch.zeros(2, K // 16 * nIb * 512, dtype=torch.float16, device="cuda")
+    idx = _plane_index(M, K, nIb)
+    hi = x.half()
+    planes[0, idx], planes[1, idx] = hi, (x - hi.float()).half()
+    Wp = mrp.pack_weight(w, body=True)
+    exact = (planes[0, idx].double() + planes[1, idx].double()) @ w.half().double().t()
+    out = torch.empty(8 * M * R, device="cuda")
+    src = (Wp.data_ptr(), planes.data_ptr(), planes.shape[1] // 8, 2, out.data_ptr())
+
+    def tiles(launch, ks, nb, *nv):
+        a = _Args()
+        a.Wp, a.KBw, a.n_rb, a.nIb, a.M, a.R = Wp.data_ptr(), K // 16, R // 32, nIb, M, R
+        a.seg[0] = _Seg(planes.data_ptr(), planes.shape[1] // 8, K // 64, 2)
+        a.nseg, a.nMt, a.nVt, a.nKs, a.out = 1, -(-M // (32 * nb)), -(-R // (64 * (nv or (4,))[0])), ks, out.data_ptr()
+        return launch(C.byref(a), nb, *nv, st)
+
+    def error(rc, ks):
+        assert rc == 0
+        torch.cuda.synchronize()
+        parts = out[:ks * M * R].view(ks, M, R)
+        total = parts[0].clone()
+        for p in parts[1:]:                                        # as the consumers add them
+            total += p
+        return float((total.double() - exact).norm() / exact.norm())
+
+    apart = {ks: error(tiles(two, ks, 4, nv), ks) for ks, nv in ((1, 4), (2, 3), (4, 4), (8, 3)) if K // 32 % ks == 0}
+    both = {ks: error(tiles(two, ks, 8, 4), ks) for ks in (1, 2, 4, 8)}
+    own = {ks: error(tiles(one, ks, 8), ks) for ks in (1, 2, 4, 8)}
+    for ks in (1, 2, 4):
+        if K // 16 % (ks * 16) == 0:
+            assert apart[2 * ks] <= error(wide(C.byref(_Wide(*src, nIb, M, R, K, ks, R // 64, M // 128, 2)), st), ks), ks
+        assert apart[ks] <= own[2 * ks], ks
+    assert apart[4] <= error(small(C.byref(_Small(*src, nIb, M, R, K, 1, R // 32, M // 32)), st), 1)
+    # (one sum for both planes adds the same products in another order: at most 1 % apart either way)
+    assert all(both[ks] <= 1.01 * own[ks] for ks in both), (both, own)
