@@ -191,9 +191,20 @@ bool mrp::mlp_on_tiles(int M, int d, int nCU, size_t part_rows) {
 
 // The MLP head body of a sequence in one workgroup, where both weight matrices pass through one CU in less than the launches
 // of the general path take.  Measured per step of three heads, V = 4096, general / per sequence, B x L: d = 256 81 / 62 us at
-// 1 x 4, 89 / 69 at 16 x 4, 187 / 101 at 64 x 16, 314 / 163 at 256 x 16, 363 / 280 at 1000 x 4; d = 128 79 / 49 at 1 x 4, 275 / 137 at
+// 1 x 4, 89 / 69 at 16 x 4, 187 / 101 at 64 x 16, 305 / 158 at 256 x 16, 355 / 266 at 1000 x 4; d = 128 79 / 49 at 1 x 4, 266 / 135 at
 // 256 x 16.  (Wider: 1 MB of weights at d = 384 take longer than the launches.)
-bool mrp::mlp_per_sequence(int L, int d) { return (d == 128 || d == 256) && L <= 16; }
+// Every sequence pulls the weights and computes 16 rows, so short blocks in large numbers are the general path's, whose
+// time goes with the rows: d = 256 236 / 209 at 1024 x 1, 240 / 249 at 1200 x 1, 578 / 707 at 4096 x 1; 373 / 324 at 1500 x 2, 480 / 483
+// at 2200 x 2, 688 / 810 at 4096 x 2; 488 / 468 at 2000 x 3, 653 / 699 at 3000 x 3; 541 / 519 at 2000 x 4, 1034 / 1080 at 4000 x 4; 824 /
+// 734 at 2300 x 6, 2668 / 2795 at 8192 x 6; 3263 / 3178 at 8000 x 8, 2949 / 2588 at 4000 x 16; d = 128 299 / 223 at 1400 x 1, 538 / 551 at 4096 x 1,
+// 519 / 490 at 3000 x 2, 737 / 726 at 4000 x 3, 1782 / 1835 at 8000 x 4, 2346 / 2292 at 8192 x 6.  One row each at d = 256 is a third
+// round of workgroups from 513, while the general path is the small-row kernels' up to 767: 129 / 129 at 512, 136 / 153 at 513, 151 /
+// 170 at 767, 211 / 202 at 769.
+bool mrp::mlp_per_sequence(int B, int L, int d) {
+    if ((d != 128 && d != 256) || L > 16) return false;
+    if (d == 256 && L == 1) return B <= 512 || (B >= 768 && B <= 1024);
+    return L >= 8 || B <= 768 * L * (256 / d);
+}
 
 // Form of the tile kernel for [M][R] partial sums of two activation planes over Kc columns: weight rows per tile, row
 // blocks and k parts, the fastest by what the forms were measured to take: a round of tiles about 6 us and, per k step,
@@ -583,7 +594,7 @@ static int chain_impl(mrp_ctx *c, void *stream, int B, int K, const void *h, flo
     const int off = cfg->state_offset;
     // MLP body at small row counts: the first GEMM also reads the conditioning embeddings from the table
     // itself (no gathered copy is made) and applies the SiLU
-    const bool tiny = !layers && mlp_per_sequence(L, d);
+    const bool tiny = !layers && mlp_per_sequence(B, L, d);
     const bool mlp_tiles = !layers && !tiny && mlp_on_tiles(M, d, c->nCU, c->part_rows);
     const bool fused = !layers && !tiny && !mlp_tiles;
 

@@ -381,8 +381,8 @@ struct HeadTinyArgs {
     int *err_flag;
 };
 hipError_t launch_head_tiny(const HeadTinyArgs &a, int B, int d, hipStream_t st);
-// Does the MLP head body run as one workgroup per sequence?
-bool mlp_per_sequence(int L, int d);
+// Does the MLP head body of B sequences run as one workgroup per sequence?
+bool mlp_per_sequence(int B, int L, int d);
 
 // `init` (or nullptr): the hidden state's planes in the same launch
 hipError_t launch_reduce_rows(const float *z, int M, int V, float *pm, float *ps, int *pi, int *nT_out,

@@ -124,6 +124,20 @@ def test_mlp_body_kernel_by_rows_and_width():
     assert not any(on_tiles(M, 2560, 256, 4096) for M in (129, 192, 384))
 
 
+def test_head_body_per_sequence_only_where_it_is_ahead():
+    rule = library_rule("_ZN3mrp16mlp_per_sequenceEiii", C.c_bool, *[C.c_int] * 3)
+    for d in range(128, 1025, 128):
+        for L in range(1, 65):
+            for B in (1, 3, 256, 4096, 65535 // L):
+                assert not (rule(B, L, d) and (d > 256 or L > 16))
+    ahead = {256: [(1, 1), (512, 1), (768, 1), (1024, 1), (256, 2), (1500, 2), (2000, 3), (2000, 4), (2300, 6), (8000, 8), (4000, 16)],
+             128: [(1, 1), (1400, 1), (3000, 2), (4000, 3), (4000, 4), (8192, 6), (8000, 8), (4000, 16)]}
+    behind = {256: [(513, 1), (767, 1), (1200, 1), (4096, 1), (2600, 2), (4096, 2), (3000, 3), (4000, 4), (8192, 6)],
+              128: [(4096, 1), (8000, 3), (8000, 4)]}          # B x L as measured
+    assert all(rule(B, L, d) for d in ahead for B, L in ahead[d])
+    assert not any(rule(B, L, d) for d in behind for B, L in behind[d])
+
+
 def test_waiting_gradient_workgroups_leave_the_device_free():
     counters = library_rule("_ZN3mrp11kl_countersEiii", C.c_int, *[C.c_int] * 3)
     for nCU in (1, 8, 32, 256):

@@ -311,7 +311,9 @@ def test_lm_head_kernel_by_width_and_vocabulary(d, B, L, V, tiles):
 @pytest.mark.parametrize("d,B,L", [
     (128, 5, 16), (256, 3, 1), (256, 7, 11), (256, 4, 16),      # one workgroup per sequence
     (256, 300, 4),                                              # more of them than CUs; partials tile by tile
-    (256, 3, 17), (384, 4, 16),                                 # a longer block, a wider model: the general path
+    (256, 512, 1), (256, 513, 1),                               # blocks of one row: two rounds of workgroups, past them the general path
+    (128, 1537, 1), (256, 1540, 2),                             # more short blocks than it pays for
+    (256, 3, 17), (384, 4, 16),                                 # a longer block, a wider model
 ])
 def test_narrow_head_body(d, B, L):
     """The head body as one workgroup per sequence (d of 128 or 256, blocks of up to 16 rows) and past its limits: three heads
