@@ -10,7 +10,8 @@
 //     L_i = a_T / s_T - (m_T + log s_T) + (m_S + log s_S).
 // No softmax is written.  Algorithmic bytes: 8 M V forward, 4 M V for the gradient, which is the difference of the two
 // softmaxes: taken from the entries that the forward pass left in registers (kl_grad_kernel; 1024 rows of 151936: 1.87 GB in
-// 383 us, 4.9 TB/s, where a large copy moves 4.7), or at few rows from a second read.
+// 383 us, 4.9 TB/s, where a large copy moves 4.7), or from a second read: at few rows, and where a row's tiles are too many
+// for the places that may wait.
 #include "mrp_kernels.h"
 
 namespace mrp {
@@ -73,6 +74,8 @@ struct KlArgs {
     int M;
     int nq;                       // counters that the one-pass form draws from (0: two passes)
     int spin;                     // looks at a word before its tile is taken as one that nobody has room for
+    int p0, nP;                   // two passes: rows p0 .. p0 + nP - 1: partials
+    int g0, nG;                   // rows g0 .. g0 + nG - 1: loss and gradient (their partials are complete)
 };
 
 constexpr int MAX_Q = 7;
@@ -138,10 +141,8 @@ __device__ __forceinline__ KlPart kl_tile_again(const float *T, const float *S, 
     return kl_join(p, sw);
 }
 
-// loss alone: partials of one KT-wide tile of one row
-__global__ __launch_bounds__(256) void kl_partial_kernel(const KlArgs a) {
-    __shared__ KlPart sw[4];
-    const int t = blockIdx.x, i = blockIdx.y;
+// partials of one KT-wide tile of one row
+__device__ __forceinline__ void kl_partial(const KlArgs &a, int t, int i, KlPart *sw) {
     if (a.mask && !a.mask[i]) return;   // (uniform over the workgroup)
     float4 xt[8], xs[8];
     kl_fetch(a.T + (size_t)i * a.V, t * KT, a.V, xt);
@@ -152,6 +153,10 @@ __global__ __launch_bounds__(256) void kl_partial_kernel(const KlArgs a) {
         a.part[o] = p.mT; a.part[a.stride + o] = p.sT; a.part[2 * a.stride + o] = p.aT;
         a.part[3 * a.stride + o] = p.mS; a.part[4 * a.stride + o] = p.sS;
     }
+}
+__global__ __launch_bounds__(256) void kl_partial_kernel(const KlArgs a) {      // loss alone
+    __shared__ KlPart sw[4];
+    kl_partial(a, blockIdx.x, blockIdx.y, sw);
 }
 
 // Gradient of one KT-wide tile of one row from its entries; zero where the row is not in the mask
@@ -273,9 +278,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     kl_write(a, t, i, on, xt, xs, lT, lS);
 }
 
-// The same in two passes, the second after the partials' launch
-__global__ __launch_bounds__(256) void kl_second_kernel(const KlArgs a) {
-    const int t = blockIdx.x, i = blockIdx.y;
+// The same from a second read; tile 0 also writes the row's loss
+__device__ __forceinline__ void kl_second(const KlArgs &a, int t, int i) {
     const bool on = !a.mask || a.mask[i];     // (uniform over the workgroup)
     float4 xt[8], xs[8];
     float lT = 0.f, lS = 0.f;
@@ -292,23 +296,15 @@ __global__ __launch_bounds__(256) void kl_second_kernel(const KlArgs a) {
     kl_write(a, t, i, on, xt, xs, lT, lS);
 }
 
-// the words' first n entries of each of the five arrays, and the counters
-__global__ __launch_bounds__(256) void kl_clear_kernel(unsigned long long *words, size_t stride, int n) {
-    const int o = blockIdx.x * 256 + threadIdx.x;
-    if (o < n && blockIdx.y < 5) words[blockIdx.y * stride + o] = 0;
-    if (o < MAX_Q && blockIdx.y == 5) words[5 * stride + 16 * o] = 0;
-}
-
-// loss alone: one wavefront per row
-__global__ __launch_bounds__(256) void kl_finish_kernel(const KlArgs a, int M) {
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= M) return;
-    float loss = 0.f;
-    if (!a.mask || a.mask[i]) {
-        const KlPart p = kl_row(a.part, a.stride, a.nT, i);
-        loss = a.scale * (p.aT / p.sT - (p.mT + logf(p.sT)) + (p.mS + logf(p.sS)));
-    }
-    if ((threadIdx.x & 63) == 0) a.loss[i] = loss;
+// Two passes: one launch takes the partials of one group of rows and the gradient of the group before it, alternating
+// while both have rows left, so that the reads of the one run beside the writes of the other.
+__global__ __launch_bounds__(256) void kl_two_pass_kernel(const KlArgs a) {
+    __shared__ KlPart sw[4];
+    const int t = blockIdx.x, y = blockIdx.y, both = 2 * (a.nP < a.nG ? a.nP : a.nG);
+    const bool part = y < both ? (y & 1) == 0 : a.nP > a.nG;
+    const int r = y < both ? y >> 1 : y - both / 2;
+    if (part) kl_partial(a, t, a.p0 + r, sw);
+    else kl_second(a, t, a.g0 + r);
 }
 
 }  // namespace
@@ -332,10 +328,41 @@ int kl_counters(int M, int nT, int nCU) {
     return 0;
 }
 
+// Rows taken together in two passes: a group's rows are read for the partials and once more, one launch later, for the
+// gradient.  What is live in between, two tensors of two groups, has to fit the 256 MB last-level cache; smaller groups
+// only add launches.  Measured, us, in one group / in groups of 52 MB per tensor: 533 / 495 at 128 rows of 1.2 M (560 with 32 MB, 518
+// with 40, 501 with 64), 901 / 848 at 128 of 2 M, 1059 / 1029 at 100 of 3 M (4 rows a group); but 887 / 908 at 64 of 4 M, 869 / 951 at
+// 32 of 8 M.
+int kl_group_rows(int M, int V) {
+    constexpr size_t GROUP_BYTES = (size_t)52 << 20;
+    const size_t row_bytes = V * sizeof(float), fit = GROUP_BYTES / row_bytes;
+    const int rows = fit < 4 || M * row_bytes < GROUP_BYTES * 3 / 2 ? M : (int)fit;
+    return rows < M && rows > 32767 ? 32767 : rows;      // (grid limit: two groups in one launch)
+}
+
+// the words' first n entries of each of the five arrays, and the counters
+__global__ __launch_bounds__(256) void kl_clear_kernel(unsigned long long *words, size_t stride, int n) {
+    const int o = blockIdx.x * 256 + threadIdx.x;
+    if (o < n && blockIdx.y < 5) words[blockIdx.y * stride + o] = 0;
+    if (o < MAX_Q && blockIdx.y == 5) words[5 * stride + 16 * o] = 0;
+}
+
+// loss alone: one wavefront per row
+__global__ __launch_bounds__(256) void kl_finish_kernel(const KlArgs a, int M) {
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= M) return;
+    float loss = 0.f;
+    if (!a.mask || a.mask[i]) {
+        const KlPart p = kl_row(a.part, a.stride, a.nT, i);
+        loss = a.scale * (p.aT / p.sT - (p.mT + logf(p.sT)) + (p.mS + logf(p.sS)));
+    }
+    if ((threadIdx.x & 63) == 0) a.loss[i] = loss;
+}
+
 hipError_t launch_kl_loss(int M, int V, const float *teacher, const float *student, const uint8_t *mask, float scale,
                           float *part, size_t part_stride, float *loss_rows, float *grad, int nCU, int spin, hipStream_t st) {
     const KlArgs a = {teacher, student, mask, V, kl_tiles(V), scale, part, reinterpret_cast<unsigned long long *>(part), part_stride,
-                      loss_rows, grad, M, grad ? kl_counters(M, kl_tiles(V), nCU) : 0, spin};
+                      loss_rows, grad, M, grad ? kl_counters(M, kl_tiles(V), nCU) : 0, spin, 0, 0, 0, 0};
     if (a.nq) {
         const int n = M * a.nT;
         hipLaunchKernelGGL(kl_clear_kernel, dim3((n + 255) / 256, 6), dim3(256), 0, st, a.words, part_stride, n);
@@ -344,11 +371,24 @@ hipError_t launch_kl_loss(int M, int V, const float *teacher, const float *stude
         hipLaunchKernelGGL(kl_grad_kernel, dim3((M + a.nq - 1) / a.nq * a.nq * a.nT), dim3(256), 0, st, a);
         return hipGetLastError();
     }
+    if (grad) {
+        KlArgs b = a;
+        const int rows = kl_group_rows(M, V);
+        for (int r0 = 0; r0 < M + rows; r0 += rows) {
+            b.g0 = b.p0; b.nG = b.nP;
+            b.p0 = r0;
+            b.nP = r0 >= M ? 0 : (M - r0 < rows ? M - r0 : rows);
+            if (b.nP + b.nG == 0) break;
+            hipLaunchKernelGGL(kl_two_pass_kernel, dim3(b.nT, b.nP + b.nG), dim3(256), 0, st, b);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     hipLaunchKernelGGL(kl_partial_kernel, dim3(a.nT, M), dim3(256), 0, st, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (grad) hipLaunchKernelGGL(kl_second_kernel, dim3(a.nT, M), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(kl_finish_kernel, dim3((M + 3) / 4), dim3(256), 0, st, a, M);
+    hipLaunchKernelGGL(kl_finish_kernel, dim3((M + 3) / 4), dim3(256), 0, st, a, M);
     return hipGetLastError();
 }
 

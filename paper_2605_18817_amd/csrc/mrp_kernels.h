@@ -465,5 +465,6 @@ hipError_t launch_kl_loss(int M, int V, const float *teacher, const float *stude
 constexpr int KL_SPIN = 1 << 13;      // looks of about a microsecond each: far beyond any wait with the device to oneself
 size_t kl_part_bytes(size_t stride);
 int kl_counters(int M, int nT, int nCU);
+int kl_group_rows(int M, int V);       // rows that two passes take together
 
 }  // namespace mrp

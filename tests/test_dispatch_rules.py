@@ -147,3 +147,16 @@ def test_waiting_gradient_workgroups_leave_the_device_free():
                 assert nq in (0, 1, 3, 5, 7) and nq * (nT - 1) <= nCU // 2      # of 4 nCU resident workgroups
                 assert nq == 0 or M * nT >= 8 * nCU
     assert counters(1024, 19, 256) == 7 and counters(64, 19, 256) == 0 and counters(1024, 33, 256) == 3
+
+
+def test_two_pass_gradient_takes_rows_that_the_cache_holds():
+    rows = library_rule("_ZN3mrp13kl_group_rowsEii", C.c_int, C.c_int, C.c_int)
+    for V in (1, 100, 4096, 50257, 151936, 1100000, 3000000, 3500000, 4000000, 67000000):
+        for M in (1, 2, 16, 89, 128, 135, 1024, 32768, 65535):
+            r, row = rows(M, V), 4 * V
+            assert 1 <= r <= M
+            if r < M:                                # two tensors of two groups in 256 MB, no fewer than four rows a group
+                assert 4 * r * row <= 256 << 20 and r >= 4 and 2 * r <= 65535
+            else:
+                assert row > (13 << 20) or M * row < 78 << 20
+    assert [rows(128, 1200000), rows(100, 3000000), rows(64, 4000000), rows(1024, 151936), rows(16, 151936)] == [11, 4, 64, 89, 16]

@@ -139,7 +139,7 @@ def test_kl_loss_full_size_sampled_rows():
         ctx.close()
 
 
-@pytest.mark.parametrize("V,M", [(151936, 391), (50257, 403), (50257, 259)])   # several groups of rows, uneven; one group
+@pytest.mark.parametrize("V,M", [(151936, 391), (50257, 403), (50257, 259)])   # one pass, rows dealt unevenly over the counters; two passes
 def test_kl_loss_over_groups_of_rows(V, M):
     g = torch.Generator(device="cuda")
     g.manual_seed(V + M)
@@ -188,16 +188,25 @@ def test_gradient_in_one_pass_and_two(V, M):
     ctx.close()
 
 
+def _launch():
+    """The loss with a number of CUs and of looks of its own (the library's: the stream's CUs)."""
+    return library_rule("_ZN3mrp14launch_kl_lossEiiPKfS1_PKhfPfmS4_S4_iiP12ihipStream_t", C.c_int, C.c_int, C.c_int, *[C.c_void_p] * 3,
+                        C.c_float, C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_void_p)
+
+
+def _tensors(V, M):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V)
+    t = torch.empty(M, V, device="cuda").normal_(0, 2, generator=g)
+    return t, t + torch.empty(M, V, device="cuda").normal_(0, 0.5, generator=g)
+
+
 @pytest.mark.parametrize("V,M", [(151936, 108), (8193, 1024)])
 def test_one_pass_without_waiting(V, M):
     """A workgroup that finds its row's other partials missing takes them itself: with no patience at all, the same bits, also
     over the student's own logits."""
-    launch = library_rule("_ZN3mrp14launch_kl_lossEiiPKfS1_PKhfPfmS4_S4_iiP12ihipStream_t", C.c_int, C.c_int, C.c_int, *[C.c_void_p] * 3,
-                          C.c_float, C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p, C.c_int, C.c_int, C.c_void_p)
-    g = torch.Generator(device="cuda")
-    g.manual_seed(V)
-    t = torch.empty(M, V, device="cuda").normal_(0, 2, generator=g)
-    s = t + torch.empty(M, V, device="cuda").normal_(0, 0.5, generator=g)
+    launch = _launch()
+    t, s = _tensors(V, M)
     n = M * -(-V // 8192)
     words = torch.zeros(5 * n + 16 * 7, dtype=torch.int64, device="cuda")
     loss, want, grad = [torch.full((M,), 9.0, device="cuda") for _ in range(2)] + [torch.empty_like(s)]
@@ -209,3 +218,31 @@ def test_one_pass_without_waiting(V, M):
                       torch.cuda.current_stream().cuda_stream) == 0
         torch.cuda.synchronize()
         assert torch.equal(loss, want) and torch.equal(out, grad)
+
+
+@pytest.mark.parametrize("V,M", [(151936, 391), (151936, 135), (151936, 134), (1100000, 40), (4000000, 17)])
+def test_two_passes_over_groups_of_rows(V, M):
+    """Rows whose tiles are too many for the places that may wait (32 CUs; a vocabulary above a million on any number) take two
+    passes, in groups of rows from one and a half of them on (135 rows of 151936), with the bits of the forward pass for
+    the loss, also in place and with rows off."""
+    nCU = 32 if V < 1000000 else 256
+    assert library_rule("_ZN3mrp11kl_countersEiii", C.c_int, *[C.c_int] * 3)(M, -(-V // 8192), nCU) == 0
+    launch = _launch()
+    t, s = _tensors(V, M)
+    n = M * -(-V // 8192)
+    words = torch.zeros(5 * n + 16 * 7, dtype=torch.int64, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    mask = (torch.arange(M, device="cuda") % 5 != 2).to(torch.uint8)
+    loss, want = torch.full((M,), 9.0, device="cuda"), torch.full((M,), 9.0, device="cuda")
+    assert launch(M, V, t.data_ptr(), s.data_ptr(), mask.data_ptr(), 0.5, words.data_ptr(), n, want.data_ptr(), None, nCU, 9, st) == 0
+    lt, ls = torch.logsumexp(t.double(), 1, keepdim=True), torch.logsumexp(s.double(), 1, keepdim=True)
+    s0 = s.clone()
+    for out in (torch.full((M + 1, V), 9.0, device="cuda")[:M], s):
+        assert launch(M, V, t.data_ptr(), s.data_ptr(), mask.data_ptr(), 0.5, words.data_ptr(), n, loss.data_ptr(), out.data_ptr(),
+                      nCU, 9, st) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(loss, want)
+        for i in range(M):
+            p, q = (t[i].double() - lt[i]).exp(), (s0[i].double() - ls[i]).exp()
+            bound = 0.5 * (2e-5 * (p + q) + 1e-12)                # as above; rows that are off: exactly zero
+            assert bool(((out[i] - 0.5 * (q - p) * float(mask[i])).abs() <= bound * float(mask[i])).all()), i
