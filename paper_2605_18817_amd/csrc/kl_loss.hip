@@ -191,8 +191,10 @@ __device__ __forceinline__ void kl_write(const KlArgs &a, int t, int i, bool on,
 //
 // Which tile a workgroup takes is drawn from one of nq counters as it starts, so of the rows of a counter at most one has tiles
 // that nobody has drawn yet.  Rows that are all drawn need nobody else and leave; the others hold at most nq (nT - 1) places, an
-// eighth of the device (kl_counters).  The wait ends with fewer places, too (a stream limited to some CUs, a device shared
-// with kernels that stay): after `spin` looks the workgroup takes the missing partial itself, with the same bits.
+// eighth of the device (kl_counters).  The wait ends with fewer places, too (a device shared with kernels that stay, a
+// graph replayed on a stream of fewer CUs): after `spin` looks the workgroup takes the missing partial itself, with the same
+// bits, and from then on does not wait for others of the row.  (512 rows of 151936 on a device that has 32 places left: 16 ms with
+// 128 looks, 24 with 512; 1050 with 8192 for each partial that is missing.  Two passes, which a stream of 8 CUs takes, 2.9.)
 // It offers what it found only in words that are still empty: a tile may be overwritten with its gradient (a gradient in the
 // place of the logits) once all its words are there, so what was read too late is not taken.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void kl_grad_kernel(const KlArgs a) {
@@ -220,7 +222,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                 __hip_atomic_store(words + n * a.stride + t, (1ull << 32) | __float_as_uint(v[n]), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         }
-        for (;;) {
+        for (int patience = a.spin;; patience = 0) {
             if (threadIdx.x < 64) {      // the order of kl_row
                 KlPart r = kl_identity();
                 int missing = -1;
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
                             all = all && (w[n] >> 32) != 0;
                         }
                         if (!all) __builtin_amdgcn_s_sleep(4);
-                    } while (!all && ++looks < a.spin);
+                    } while (!all && ++looks < patience);
                     if (!all) missing = u;
                     float v[5];
 #pragma unroll
@@ -321,8 +323,11 @@ size_t kl_part_bytes(size_t stride) { return (5 * stride + 16 * MAX_Q) * sizeof(
 // and drawing.  Measured, us, two passes (with the rows in groups that fit the last-level cache) / one: 496 / 383 at 1024 rows of
 // 151936, 991 / 753 at 2048, 93 / 71 at 300 with half of them masked out, 116 / 78 at 1024 of 32000; but with 4 counters
 // 35.0 / 35.7 at 64 of 151936 (1216 tiles), 12.8 / 14.1 at 16, 13.6 / 14.5 at 64 of 50257.
+// Fewer CUs (a stream limited to some of them, a partition) don't draw what the memory gives, and the second read is the
+// caches' for longer: two passes / one on 64 CUs 95 / 124 at 128 of 151936, 453 / 499 at 512, 156 / 174 at 1024 of 32000; on 128 CUs 68 / 76,
+// 285 / 284, 122 / 105.
 int kl_counters(int M, int nT, int nCU) {
-    if ((long)M * nT < 8 * nCU) return 0;
+    if (nCU < 128 || (long)M * nT * nCU < 2048 * 256) return 0;
     for (int nq = MAX_Q; nq > 0; nq -= 2)
         if (nq * (nT - 1) <= nCU / 2) return nq;
     return 0;

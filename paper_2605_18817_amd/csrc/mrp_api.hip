@@ -174,6 +174,18 @@ int mrp::small_tile_blocks(int R, int Kc, int M, int nCU) {
     return (R % 64 == 0 && (R / 32) * nrt > nCU && nrt >= 6) ? 2 : 1;
 }
 
+// Compute units that the stream's work may run on
+int mrp::stream_cus(hipStream_t st, int nCU) {
+    uint32_t mask[64] = {};
+    if (hipExtStreamGetCUMask(st, 64, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return nCU;
+    }
+    int n = 0;
+    for (uint32_t m : mask) n += __builtin_popcount(m);
+    return n > 0 && n < nCU ? n : nCU;
+}
+
 // The MLP head body's GEMMs on the tile kernel: from 768 rows, for d > 2048 from 513, and there from 129 where the
 // first GEMM's tiles and k parts find three quarters of the CUs (d = 4096, but not 2560, whose 40 k steps of a plane split
 // into 8 parts).  Measured per step of three heads with V = 4096, small-row kernels / tile kernel: d = 4096 485 / 426 us at
@@ -452,8 +464,9 @@ int mrp_kl_loss(mrp_ctx *c, void *stream, int M, const float *teacher, const flo
     if (c->dims.V % 4 == 0 && (!aligned16(teacher) || !aligned16(student) || (grad && !aligned16(grad))))
         return fail(c, MRP_ERR_ALIGN, "mrp_kl_loss: tensors must be 16-byte aligned");
     if (M == 0) return MRP_OK;
+    const hipStream_t st = static_cast<hipStream_t>(stream);
     HIP_TRY(c, launch_kl_loss(M, c->dims.V, teacher, student, row_mask, scale, c->kl_part, c->kl_stride,
-                              loss_rows, grad, c->nCU, KL_SPIN, static_cast<hipStream_t>(stream)));
+                              loss_rows, grad, grad ? stream_cus(st, c->nCU) : c->nCU, KL_SPIN, st));
     return MRP_OK;
 }
 

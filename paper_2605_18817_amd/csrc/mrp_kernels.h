@@ -462,9 +462,10 @@ int residual_rms_workgroups(int n_blocks, int S, long ntiles, int nCU);
 int kl_tiles(int V);
 hipError_t launch_kl_loss(int M, int V, const float *teacher, const float *student, const uint8_t *mask, float scale,
                           float *part, size_t part_stride, float *loss_rows, float *grad, int nCU, int spin, hipStream_t st);
-constexpr int KL_SPIN = 1 << 13;      // looks of about a microsecond each: far beyond any wait with the device to oneself
+constexpr int KL_SPIN = 128;          // looks of about half a microsecond: the tiles of a row that has the device are some 20 us apart
 size_t kl_part_bytes(size_t stride);
 int kl_counters(int M, int nT, int nCU);
+int stream_cus(hipStream_t st, int nCU);      // compute units that the stream's work may run on (mrp_api.hip)
 int kl_group_rows(int M, int V);       // rows that two passes take together
 
 }  // namespace mrp

@@ -140,13 +140,14 @@ def test_head_body_per_sequence_only_where_it_is_ahead():
 
 def test_waiting_gradient_workgroups_leave_the_device_free():
     counters = library_rule("_ZN3mrp11kl_countersEiii", C.c_int, *[C.c_int] * 3)
-    for nCU in (1, 8, 32, 256):
+    for nCU in (1, 8, 32, 64, 127, 128, 256):
         for nT in range(1, 300):
             for M in (1, 16, 100, 1024, 65535):
                 nq = counters(M, nT, nCU)
                 assert nq in (0, 1, 3, 5, 7) and nq * (nT - 1) <= nCU // 2      # of 4 nCU resident workgroups
-                assert nq == 0 or M * nT >= 8 * nCU
+                assert nq == 0 or (nCU >= 128 and M * nT * nCU >= 2048 * 256)
     assert counters(1024, 19, 256) == 7 and counters(64, 19, 256) == 0 and counters(1024, 33, 256) == 3
+    assert counters(128, 19, 128) == 0 and counters(512, 19, 128) == 3 and counters(1024, 4, 64) == 0   # (where it was measured)
 
 
 def test_two_pass_gradient_takes_rows_that_the_cache_holds():

@@ -246,3 +246,41 @@ def test_two_passes_over_groups_of_rows(V, M):
             p, q = (t[i].double() - lt[i]).exp(), (s0[i].double() - ls[i]).exp()
             bound = 0.5 * (2e-5 * (p + q) + 1e-12)                # as above; rows that are off: exactly zero
             assert bool(((out[i] - 0.5 * (q - p) * float(mask[i])).abs() <= bound * float(mask[i])).all()), i
+
+
+@pytest.mark.parametrize("cus", [8, 128, 192])
+def test_stream_of_few_compute_units(cus):
+    """On a stream limited to some CUs the library counts those: two passes below 128."""
+    V, M = 50257, 1024
+    torch.zeros(1, device="cuda")
+    hip = C.CDLL(next(ln.split()[-1] for ln in open("/proc/self/maps") if "libamdhip64" in ln))
+    words = (C.c_uint32 * 8)(*[(1 << max(0, min(32, cus - 32 * i))) - 1 for i in range(8)])
+    handle = C.c_void_p()
+    assert hip.hipExtStreamCreateWithCUMask(C.byref(handle), C.c_uint32(8), words) == 0
+    count = library_rule("_ZN3mrp10stream_cusEP12ihipStream_ti", C.c_int, C.c_void_p, C.c_int)
+    assert count(handle, 256) == cus and count(None, 256) == 256
+    t, s = _tensors(V, M)
+    out = [(torch.full((M,), 9.0, device="cuda"), torch.full((M, V), 9.0, device="cuda")) for _ in range(2)]
+    ctx = mrp.MrpContext(128, V, M, 1)
+    ctx.kl_loss(M, t, s, None, 0.5, *out[0])
+    torch.cuda.synchronize()
+    stream = torch.cuda.ExternalStream(handle.value)
+    with torch.cuda.stream(stream):
+        ctx.kl_loss(M, t, s, None, 0.5, *out[1])
+    stream.synchronize()
+    lt, ls = torch.logsumexp(t.double(), 1, keepdim=True), torch.logsumexp(s.double(), 1, keepdim=True)
+    p, q = (t.double() - lt).exp(), (s.double() - ls).exp()
+    for loss, grad in out:
+        assert torch.equal(loss, out[0][0])
+        assert bool(((grad - 0.5 * (q - p)).abs() <= 0.5 * (2e-5 * (p + q) + 1e-12)).all())     # as above
+    graph = torch.cuda.CUDAGraph()                                 # the stream is asked for its CUs under capture, too
+    with torch.cuda.graph(graph):
+        ctx.kl_loss(M, t, s, None, 0.5, *out[1])
+    for _ in range(3):
+        out[1][1].fill_(9.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    ctx.close()
+    del stream
+    assert hip.hipStreamDestroy(handle) == 0
