@@ -64,7 +64,7 @@ struct LmPersistArgs {
     int *pi;
 };
 
-// LDS-tiled GEMM (256 x 256 tiles) for many activation rows
+// LDS-tiled GEMM (tiles of up to 256 x 256) for many activation rows
 struct TiledSeg {
     const uint4 *base;   // activation planes of this K segment
     long plane_stride;
@@ -76,7 +76,7 @@ struct TiledGemmArgs {
     int KBw, n_rb, nIb, M, R;
     TiledSeg seg[2];
     int nseg;
-    int nMt, nVt;        // tiles along activation rows (tiled_row_tiles(M)) / weight rows
+    int nMt, nVt;        // tiles along activation rows / weight rows, of the height and width launched
     int nKs;             // k parts (EPI_PARTIAL only: part ks writes out[ks][M][R]; 1 for EPI_LM)
     float *out;          // EPI_PARTIAL: [nKs][M][R]
     uint4 *planes;       // EPI_SILU: the NSPLIT fp16 planes [R / 16][nIb][64] of SiLU(X W^T), plane_stride apart
@@ -288,7 +288,7 @@ size_t stream_gemm_lds_bytes(int it);
 hipError_t stream_gemm_configure();   // once per device
 int stream_gemm_it(int M);   // activation row blocks per workgroup for M rows
 
-hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st);
+hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st);      // EPI_LM, EPI_SILU
 // its EPI_LM forms for nb row blocks per tile; rem = 2 + (k steps - 2) % 3
 hipError_t launch_tiled_lm(const TiledGemmArgs &a, int nb, int rem, hipStream_t st);
 hipError_t launch_tiled_lm_halves(const TiledGemmArgs &a, int nb, int rem, hipStream_t st);

@@ -41,8 +41,8 @@ int tiled_ksplit(int tiles, int nsteps, int nCU, size_t cap_rows, int M) {
 }
 
 hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st) {
-    const int nsteps = part_steps(a, epi == EPI_PARTIAL), rem = 2 + (nsteps - 2) % 3;
-    if (nsteps == 0) return hipErrorInvalidValue;
+    const int nsteps = part_steps(a, false), rem = 2 + (nsteps - 2) % 3;
+    if (nsteps == 0 || (epi != EPI_LM && epi != EPI_SILU)) return hipErrorInvalidValue;
     int nb = tiled_row_blocks(a.M);
     // EPI_SILU has instances of 7 and 8 row blocks only: on 256 CUs an unsplit k comes with 768 rows and more, which make
     // no shorter tiles.  With fewer CUs (a partition of the device) it comes with fewer rows, too; those are as many
@@ -53,9 +53,7 @@ hipError_t launch_tiled_gemm(const TiledGemmArgs &a, int epi, hipStream_t st) {
         const int left = a.nMt * a.nVt % 256;
         return left > 0 && left <= 128 ? launch_tiled_lm_halves(a, nb, rem, st) : launch_tiled_lm(a, nb, rem, st);
     }
-    if (epi == EPI_SILU)
-        return nb == 7 ? launch_inst<EPI_SILU, false, 7, 4, false>(a, rem, st) : launch_inst<EPI_SILU, false, 8, 4, false>(a, rem, st);
-    return launch_tiled_partial(a, nb, st);
+    return nb == 7 ? launch_inst<EPI_SILU, false, 7, 4, false>(a, rem, st) : launch_inst<EPI_SILU, false, 8, 4, false>(a, rem, st);
 }
 
 hipError_t launch_tiled_partial(const TiledGemmArgs &a, int nb, hipStream_t st) {

@@ -21,7 +21,7 @@ class _Args(C.Structure):
     _fields_ = ([("Wp", C.c_void_p)] + [(n, C.c_int) for n in ("KBw", "n_rb", "nIb", "M", "R")] + [("seg", _Seg * 2)]
                 + [(n, C.c_int) for n in ("nseg", "nMt", "nVt", "nKs")]
                 + [("out", C.c_void_p), ("planes", C.c_void_p), ("plane_stride", C.c_long)]
-                + [(n, C.c_void_p) for n in ("z", "pm", "ps", "pi")])
+                + [(n, C.c_void_p) for n in ("z", "pm", "ps")])
 
 
 def _plane_index(rows, cols, nIb):
