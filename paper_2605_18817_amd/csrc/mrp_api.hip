@@ -134,8 +134,7 @@ int pick_ksplit(int nVt, int nMg, int G, size_t part_rows, int M) {
 
 // Which GEMM kernel the transformer body's projections take for M rows and operands of width Kc (below; the MLP body:
 // mlp_on_tiles).  The 256 x 256 tile kernel (with its k split when the tiles are few) from 768 rows, for wide
-// operands from 513; below, the kernels that reduce their k split inside the workgroup (no partial sums in
-// memory) or the wide ones.
+// operands from 513; below, what gemm_partial finds.
 bool body_on_tiles(int M, int Kc) { return M >= 768 || (Kc > 2048 && M > 512); }
 bool small_rows_kernel(int M, int Kc) { return !body_on_tiles(M, Kc); }
 
@@ -270,15 +269,17 @@ namespace {
 int small_tile_features(int nf) { return nf == 0 ? 16 : 32 * nf; }
 
 // out[ks][M][R] = partial sums of W [R][Kc] (packed) times the activation planes; returns the number
-// of k splits written (1 for the tiled kernel) or -1 after a launch error (*err set).
+// of k parts written or -1 after a launch error (*err set).
 int gemm_partial(mrp_ctx *c, hipStream_t st, const void *Wp, int R, int Kc, const uint4 *act, long plane_stride,
                  int nplanes, int M, float *out, size_t out_floats, hipError_t *err) {
     const bool body_tiles = body_on_tiles(M, Kc) && R % 256 == 0;
     const size_t cap_rows = out_floats / (size_t)R;
     // 65 .. 512 rows: the wide kernel's 64-feature x 128-row tiles with k split over workgroups.
     // 128-feature tiles halve the activation bytes a CU pulls in per output; they pay once there are enough of
-    // them (measured at 128 rows, d = 2048: the 12288-feature gate/up projection, 96 tiles, 26.5 -> 24 us; with 32
-    // or 16 tiles, the qkv and o / down projections, the step is 2 - 5 % slower)
+    // them (measured with 64 / 128 features, what the consumer adds up included: 4096 x 4096 39.1 / 31.8 us at 384 rows, 96
+    // tiles, and 40.7 / 37.0 at 512, 8192 x 2048 24.4 / 24.3 at 256 and 40.4 / 30.4 at 384, 6144 x 1024 12.5 / 15.9 at 256, 96 tiles,
+    // but 22.8 / 17.9 at 384, 144; with 32 or 16 tiles, the qkv and o / down projections at 128 rows, d = 2048, the step is 2 - 5 %
+    // slower)
     const int nrg = (M + 127) / 128, nf = (R % 128 == 0 && (R / 128) * nrg >= 96) ? 4 : 2, nft = R / (32 * nf);
     const int ks = small_rows_kernel(M, Kc) && M > 64 && R % 64 == 0 && nplanes <= 2
         ? wide_gemm_ksplit(nft * nrg, Kc / 16, c->nCU, cap_rows, M, nf) : 0;      // (0: not that kernel)

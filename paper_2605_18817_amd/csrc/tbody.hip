@@ -146,7 +146,8 @@ __global__ __launch_bounds__(256) void swiglu_split_kernel(const float *__restri
 // that the latency of the phases before and after the walk, 7 to 10 us.  A step of three heads of three layers, V = 151936, prefixes
 // random up to 1024: 4096 wide, 24 x 16 rows (64 queries) 4841 -> 4619 us, of that the prologue's requests sent together instead
 // of one after the other 165, two waves per SIMD instead of one with both query blocks 45, the waves' sums merged side by side
-// 10; 2048 wide, 32 x 4 rows (8 queries) 1617 -> 1584, by the merge.  The kernel alone: 72.6 -> 45.8 us and 33.3 -> 29.5.
+// 10; 2048 wide, 32 x 4 rows (8 queries) 1617 -> 1584, by the merge.  The kernel's part of a launch in these steps: 69 -> 47 us and
+// 33 -> 29.5.
 struct AttnArgs {
     const float *qkv;        // partial sums [nKs][M][ldq] of the q | k | v projection
     size_t split_stride;
@@ -471,8 +472,10 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnArgs a) {
     const int gq = lane >> 4, gs = lane & 15;
     const uint16_t *vt_base = &vch[wave][4 * half + (gs >> 2)][16 * (gq & 1) + 4 * (gs & 3)];
     // Of the two waves on a SIMD the second goes first where both could: they leave step, and one's LDS reads and softmax run beside
-    // the other's matrix instructions (32 x 8 pairs, 8 queries, random prefixes:
-    // 27.0 -> 25.8 us; 64 queries 40.5 -> 40.3).
+    // the other's matrix instructions (launched alone over and over, random prefixes: 32 x 8 pairs, 8 queries
+    // 27.0 -> 25.8 us; 64 queries 40.5 -> 40.3. Steps of three heads of three layers, five runs of each within 0.1 %: 128 rows of
+    // d = 2048 1566 -> 1558 us, 1024 rows 2775 -> 2764, 512 rows of d = 1024 1105 -> 1093; 64 rows of d = 4096, prefixes shared by four
+    // workgroups, 2069 -> 2074).
     if (wave & 4) __builtin_amdgcn_s_setprio(1);
     for (int c = c_first + slot; c < nchunks; c += c_step) {
         __builtin_amdgcn_wave_barrier();   // (the previous chunk's value reads come before these writes)

@@ -1,9 +1,9 @@
 // Tiled MFMA GEMM (bf16 operands for the LM head, fp16 for the head body) for many activation rows (the MFMA-bound regime of the MRP
 // chain):  out[i][r] (+)= sum_k W[r][k] * X[i][k]  with output tiles of up to 256 x 256.
 //
-// A workgroup of four wavefronts computes a tile of 256 weight rows x 256 activation rows (160, 192 or
-// 224 where M rows fall into as many tiles of that height);
-// each wave owns 64 weight rows x all activation rows as 4 x 16 (10, 12, 14) MFMA 16x16x32 tiles (up to
+// A workgroup of four wavefronts computes a tile of 256 weight rows x 160 to 256 activation rows (LM head: as few 32-row
+// blocks as M rows need in that many tiles; halved tiles 96 or 128; two planes 192 or 256 x 128 to 256);
+// each wave owns 64 (48) weight rows x all activation rows as 4 (3) x 6 to 16 MFMA 16x16x32 tiles (up to
 // 256 fp32 accumulators).  The weight fragments go from the packed layout straight into MFMA
 // operand registers (the same 1 KiB blocks of 32 rows x 16 k, a fragment of 16 rows x 32 k being four 256-byte
 // runs of two of them); no two waves load the same fragment.  The activation operand arrives in LDS by LDS-direct
@@ -11,21 +11,22 @@
 // the MFMA "A" operand, so a lane's accumulators of a sub-tile are 4 consecutive outputs of one activation row.
 //
 // What limits this kernel: the chip's power and the memory requests of a k step.  With zero weights the LM head of
-// 4096 rows (d = 4096, V = 151936) takes 3.71 ms, with random ones 4.28 ms: the clock falls under the load.  So it
+// 4096 rows (d = 4096, V = 151936) took 3.71 ms, with random ones 4.28 ms: the clock falls under the load.  So it
 // takes the MFMA that costs the least per product: a loop of LDS fragment reads and MFMAs reaches 1.73 PFLOP/s on random
 // data with 32x32x16 (which passes its accumulators through the core twice as often) and 1.93 with 16x16x32 (2.45 both
 // on zeros).  Without its epilogue that LM head takes 3.64 ms (1.4 PFLOP/s; without the k loop's memory requests
 // 2.84 ms, without its LDS reads as well 2.55 ms): the layout is the one with the fewest request bytes (64 KiB per
 // step), operands are requested two steps ahead, and the requests are spread between the MFMAs.
-// Per head, 32x32x16 / now: 4.66 / 4.27 ms at 4096 rows, 1.22 / 1.12 at 1024, 0.78 / 0.72 at 592, 0.50 / 0.475 at 384
-// (d = 4096); of that the MFMA shape 4 %, one wait for the LDS reads per phase 1.5 %, the place of the barrier 1.5 %, the order of
+// Per head, 32x32x16 / now, epilogue and halved tiles included: 4.69 / 4.23 ms at 4096 rows, 1.23 / 1.11 at 1024, 0.78 / 0.73 at
+// 592 (d = 4096); of that the MFMA shape 4 %, one wait for the LDS reads per phase 1.5 %, the place of the barrier 1.5 %, the order of
 // the MFMAs 0.7 %.
 //
 // The head body's activations are two fp16 planes.  Where all of an operand is (P2), a k step is 32 k of both planes,
 // so that a weight fragment is requested once for both (48 KiB of requests per step instead of 64), and the tiles
 // come in more sizes (192 or 256 weight rows, 128 to 256 activation rows): with few tiles what counts is how many CUs
 // they leave idle.  At 384 rows, d = 4096 (us, the wide GEMM kernel / 256 x 192 tiles with the planes one after the other /
-// now): 24576 x 4096 187 / 146 / 114 - 123, 6144 x 4096 52 / 45 / 36 - 40, 4096 x 12288 78 / 62 / 60 - 63.
+// in the parts that keep the wide kernel's rounding): 24576 x 4096 187 / 146 / 121, 6144 x 4096 52 / 45 / 36, 4096 x 12288 78 /
+// 62 / 69.
 //
 // Workgroups are ordered so that the 32 CUs of one XCD work at the same time on a
 // block of 4 (activation) x 8 (weight) tiles and share its operand slices in that
@@ -540,8 +541,8 @@ __device__ __forceinline__ void tile_body(const TiledGemmArgs &a, int vt, int ib
 // k parts of a split follow each other, so that few tiles still spread over all XCDs.)
 // HALVES: left-over tiles that fill at most half a turn are dealt out as halves of their rows, so that the last round
 // takes half as long (a form of its own: with both bodies in one kernel the whole tiles are up to 2.7 % slower). LM head,
-// whole / halved, us: d = 4096, V = 151936: 329 / 315 at 192 rows, 371 / 352 at 256, 1092 / 1070 at 1024 (9.3 turns),
-// 4135 / 4105 at 4096 (37.1); d = 2048: 222 / 210 at 256; V = 8192, d = 4096: 91 / 64 at 512 (64 tiles); V = 32000, d = 1024: 27.4 / 22
+// whole / halved, us: d = 4096, V = 151936: 338 / 326 at 192 rows, 378 / 357 at 256, 1128 / 1112 at 1024 (9.3 turns),
+// 4261 / 4232 at 4096 (37.1); d = 2048: 222 / 210 at 256; V = 8192, d = 4096: 94 / 65 at 512 (64 tiles); V = 32000, d = 1024: 27.4 / 22
 // at 144 (125 tiles).
 template <int EPI, int REM, bool RAG, int NB, int NV, bool P2, bool HALVES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void tiled_gemm_kernel(

@@ -1,6 +1,6 @@
 // Partial-sum GEMM for 65 .. 512 activation rows with wide tiles:  out[ks][i][r] = sum over k part ks of
 // W[r][k] X[i][k]  (the projections of the transformer head body, paper Section 3.2, at the row counts of a
-// draft step, for weights of less than 20 M entries: larger ones are on the tile kernel).
+// draft step, for weights of less than 20 M entries: larger ones are on the tile kernel where that finds as many parts).
 //
 // With 32 x 32 tiles every workgroup re-reads its rows' activation planes (fp32 activations are two fp16
 // planes, so 4 bytes per element against the weights' 2), and what the CUs pull out of the L2s is several times
