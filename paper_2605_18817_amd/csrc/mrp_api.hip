@@ -187,17 +187,19 @@ int mrp::stream_cus(hipStream_t st, int nCU) {
 
 // The MLP head body's GEMMs on the tile kernel: from 768 rows, for d > 2048 from 513, and there from 129 where the
 // first GEMM's tiles and k parts find three quarters of the CUs (d = 4096, but not 2560, whose 40 k steps of a plane split
-// into 8 parts).  Measured per step of three heads with V = 4096, small-row kernels / tile kernel: d = 4096 485 / 426 us at
-// 144 rows, 549 / 491 at 192, 552 / 521 at 256, 608 / 485 at 320, 658 / 531 at 384, 832 / 638 at 512; d = 2560 285 / 354 at 192,
+// into 8 parts), all of them where those are 16 parts, which are as much to add up as to compute.  Measured per step of three
+// heads with V = 4096, small-row kernels / tile kernel: d = 4096 424 / 369 us at 144 rows, 537 / 486 at 192, 538 / 527 at 256, 542 /
+// 430 at 320, 564 / 446 at 384, 713 / 530 at 512; d = 6144 765 / 602 at 144, 903 / 726 at 256; d = 3584 463 / 391 at 336; d = 3072
+// 258 / 278 at 144, 386 / 411 at 256 (16 parts), but 313 / 310 at 272, 395 / 346 at 384 (8); d = 2560 285 / 354 at 192,
 // 346 / 370 at 384; d = 2048 284 / 298 at 288, 306 / 326 at 384, 346 / 377 at 512, 394 / 391 at 640; d = 1024 237 / 284 at 640.
-// (Error of u against 64 bits at 384 rows, d = 4096: 3.46e-7 / 3.08e-7 of its norm.)
+// (Error of u against 64 bits at 384 rows, d = 4096, three heads: 5.06e-7 / 4.67e-7 of its norm.)
 bool mrp::mlp_on_tiles(int M, int d, int nCU, size_t part_rows) {
     if (M >= 768 || d <= 2048) return M >= 768;
     if (M <= 128 || M > 512) return M > 512;
     // (k parts for one and for two planes of the hidden state: no fewer than the small-row kernels' eight waves)
     const int tiles = tiled_row_tiles(M) * ((d + 255) / 256);
     const int one = tiled_ksplit(tiles, (d / 64) * 2, nCU, part_rows, M), two = tiled_ksplit(tiles, (d / 64) * (NSPLIT + 1), nCU, part_rows, M);
-    return one >= 8 && two >= 8 && 4 * tiles * two >= 3 * nCU && two_plane_form(M, d, d, nCU, part_rows, 0).ks > 0;
+    return one >= 8 && two >= 8 && 4 * tiles * two >= (two > 8 ? 4 : 3) * nCU && two_plane_form(M, d, d, nCU, part_rows, 0).ks > 0;
 }
 
 // The MLP head body of a sequence in one workgroup, where both weight matrices pass through one CU in less than the launches

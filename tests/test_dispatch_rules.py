@@ -122,6 +122,7 @@ def test_mlp_body_kernel_by_rows_and_width():
                 assert min(parts) >= 8, (M, d)       # (the small-row kernels have eight waves)
     assert all(on_tiles(M, 4096, 256, 4096) for M in (129, 144, 160, 256, 257, 512))
     assert not any(on_tiles(M, 2560, 256, 4096) for M in (129, 192, 384))
+    assert not any(on_tiles(M, 3072, 256, 4096) for M in (129, 144, 256)) and all(on_tiles(M, 3072, 256, 4096) for M in (257, 384, 512))
 
 
 def test_head_body_per_sequence_only_where_it_is_ahead():
