@@ -1,6 +1,7 @@
-"""The tile kernel's SiLU epilogue through its own launcher: with all the CUs of a whole device the library splits k at
-the row counts whose tiles are shorter than seven row blocks, so no chain step reaches this epilogue there; on a partition
-of the device, with fewer CUs, it does."""
+"""The tile kernel's forms through their own launchers: the SiLU epilogue (with all the CUs of a whole device the library
+splits k at the row counts whose tiles are shorter than seven row blocks, so no chain step reaches this epilogue there; on
+a partition of the device, with fewer CUs, it does), the partial sums at every tile size, and their error beside that of
+the kernels in whose place they stand."""
 import ctypes as C
 
 import pytest
@@ -99,8 +100,9 @@ def test_two_plane_forms(M, R, K, nb, nv, ks):
     kp = K // ks
     for n in range(ks):
         xs, ws = xe[:, n * kp:(n + 1) * kp], we[:, n * kp:(n + 1) * kp]
-        # two planes of K / 32 MFMAs of 32 products, each addition within 2^-24 of what was summed so far
-        bound = (2 * kp // 32 + 32) * 2.0 ** -24 * (xs.abs() @ ws.abs().t())
+        # two planes of K / 32 MFMAs of twice 16 products (the bits are those of the 16-wide instruction), each addition
+        # within 2^-24 of what was summed so far
+        bound = (2 * kp // 16 + 32) * 2.0 ** -24 * (xs.abs() @ ws.abs().t())
         err = (got[n] - xs @ ws.t()).abs()
         assert bool((err <= bound).all()), (n, float((err / bound).max()))
     assert bool((out[ks * M * R:] == 7.0).all())                   # nothing past the last part
@@ -135,8 +137,8 @@ def test_tile_height_does_not_change_partial_sums():
         outs.append(out[:ks * M * R].view(ks, M, R))
         assert torch.equal(outs[0], outs[-1])
     we = w.half().double()
-    # K / 32 MFMAs of 32 products for each of three planes, the parts' sums in 64 bits
-    bound = (3 * K // 32 + 32) * 2.0 ** -24 * (xe.abs() @ we.abs().t())
+    # K / 32 MFMAs of twice 16 products for each of three planes, the parts' sums in 64 bits
+    bound = (3 * K // 16 + 32) * 2.0 ** -24 * (xe.abs() @ we.abs().t())
     assert bool(((outs[0].double().sum(0) - xe @ we.t()).abs() <= bound).all())
 
 
